@@ -33,8 +33,9 @@ HBM_PEAK_GBPS = 8000.0     # MI355X HBM3E, published peak
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16, published peak
 
 
-def algorithmic_bytes(w, tabs):
-    """Bytes the method itself must move (per kernel class and per pipeline launch)."""
+def algorithmic_bytes(w, tabs, one_pass=False):
+    """Bytes the method itself must move (per kernel class and per pipeline launch).  one_pass: pack and regather read a
+    row once and store it to both of its places, so the R rows of STAGE are not read back."""
     row = w.row_bytes
     T, k, E, S, tp = w.tokens, w.top_k, w.experts, w.slices, w.tp
     pos = tabs["pos_final"]
@@ -54,7 +55,9 @@ def algorithmic_bytes(w, tabs):
         "pack_s": [(int(alive_s[j]) + int(rows_s[j])) * row for j in range(S)],
         "regather_s": [2 * int(rows_s[j]) * row for j in range(S)],
     }
-    out["total"] = (alive + T + 4 * R) * row + idx_bytes
+    out["place"] = (alive + 2 * R) * row + 2 * T * k * 4
+    out["plan_place"] = (alive + 2 * R) * row + out["plan"]
+    out["total"] = (alive + T + (3 if one_pass else 4) * R) * row + idx_bytes
     return out
 
 
@@ -142,14 +145,16 @@ def measure(args, w, steps, warmup, full):
             return (time.perf_counter() - c0) * 1e3 / n
 
     tabs = m.read_tables(cfg, b.ws)
-    ab = algorithmic_bytes(w, tabs)
+    ab = algorithmic_bytes(w, tabs, one_pass=mode < 0)
     if w.padded:
         pad_bytes = (tabs["final_rows"] - ab["R"]) * ab["row"]      # zero-filled by the regather of slice 0
         ab["total"] += pad_bytes
         ab["regather_s"][0] += pad_bytes
-        ab["regather"] += pad_bytes
+        for name in ("regather", "place", "plan_place"):
+            ab[name] += pad_bytes
     if mirror:
-        ab["total"] += 2 * ab["R"] * ab["row"]
+        ab["total"] += (1 if mode < 0 else 2) * ab["R"] * ab["row"]
+        ab["return"] = (2 * ab["R"] + w.tokens) * ab["row"] + 2 * w.tokens * w.top_k * 4
         ab["unregather_s"] = ab["regather_s"]
         ab["combine_s"] = [ab["regather_s"][j] // 2 + (w.tokens // w.slices) * ab["row"] for j in range(w.slices)]
     if gate:
@@ -202,7 +207,8 @@ def measure(args, w, steps, warmup, full):
             seq += [("regather", reg_g[0])]
             for gi in range(1, G):
                 seq += [("pack", pack_g[gi]), ("regather", reg_g[gi])]
-        per_launch = {"combine": ab["combine"], "gate": ab.get("gate")}
+        per_launch = {"combine": ab["combine"], "gate": ab.get("gate"), "place": ab["place"], "plan_place": ab["plan_place"],
+                      "return": ab.get("return")}
         for kname in ("pack", "regather", "pack_regather", "plan_pack"):
             vals = [v for n_, v in seq if n_ == kname]
             per_launch[kname] = sum(vals) / len(vals) if vals else None
@@ -211,7 +217,7 @@ def measure(args, w, steps, warmup, full):
             per_launch["regather"] = ab["regather_s"][S - 1]
             if S > 1:
                 per_launch["pack_regather"] = sum(ab["pack_s"][j] + ab["regather_s"][j - 1] for j in range(1, S)) / (S - 1)
-        if mirror:
+        if mirror and "return" not in kernels:
             # the return pipeline: fetch and combine per launch group, as two kernels or co-scheduled; the group
             # count follows from the launches seen (groups are even)
             n_uc = round(kernels["unregather_combine"]["launches_per_step"]) if "unregather_combine" in kernels else 0
@@ -228,7 +234,7 @@ def measure(args, w, steps, warmup, full):
                 per_launch["unregather"] = sum(un_g) / len(un_g)
                 per_launch["combine"] = sum(cb_g) / len(cb_g)
         movers = [kname for kname in ("pack", "regather", "pack_regather", "combine", "plan_pack", "unregather",
-                                      "unregather_combine", "gate") if kname in kernels]
+                                      "unregather_combine", "gate", "place", "plan_place", "return") if kname in kernels]
         dom = max(movers, key=lambda kname: kernels[kname]["us_per_step"])
         achieved = per_launch[dom] / (kernels[dom]["avg_us"] * 1e-6) / 1e9
         # HBM-side bytes per launch of that kernel from rocprofv3 counters (profiles/traffic.json, written by
@@ -266,7 +272,8 @@ def measure(args, w, steps, warmup, full):
                 v[kk] = round(v[kk], 3)
         res["roofline"] = roofline
         res["kernels"] = kernels
-        res["pipeline"] = {"realisation": pmode, "first_launch_slices": first, "slices_per_launch": spg, "plan_fused_with_first_pack": fused}
+        one = "place" in kernels or "plan_place" in kernels
+        res["pipeline"] = {"realisation": "one pass", "plan_fused": "plan_place" in kernels} if one else {"realisation": pmode, "first_launch_slices": first, "slices_per_launch": spg, "plan_fused_with_first_pack": fused}
 
     if args.calib_copy_mib > 0:
         nbytes = args.calib_copy_mib << 20

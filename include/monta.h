@@ -217,19 +217,19 @@ int monta_allgather_regather(const monta_cfg *cfg, const void *stage, void *gath
                              int schedule, void *stream);
 
 /* The slice pipeline (the paper's multi-stream schedule, section "AllToAll
- * performance", Implementation): regather(j) runs after pack(j) and overlaps
- * pack(j+1); everything has finished, in stream order, when the call's work on
- * `stream` completes.  Equivalent to calling monta_dispatch and monta_regather
- * for j = 0..S-1.  How the overlap is realised is chosen by
- * monta_set_pipeline_mode(). */
+ * performance", Implementation).  Equivalent to calling monta_dispatch and
+ * monta_regather for j = 0..S-1: STAGE and FINAL hold the same bytes, and everything
+ * has finished, in stream order, when the call's work on `stream` completes.  By
+ * default every row is read once and stored to both places in one pass; how the two
+ * passes overlap where they are kept apart is chosen by monta_set_pipeline_mode(). */
 int monta_dispatch_regather(const monta_cfg *cfg, const void *x, void *stage, void *final_,
                             const void *ws, void *stream);
 
 /* monta_route followed by monta_dispatch_regather, as one call.  Same results and
- * same tables.  In pipeline mode 1, for shapes whose histogram table is small, the
- * kernel that finishes the plan also packs slice 0 (those workgroups derive their
- * rows themselves), so the first pack does not wait for the plan; otherwise the
- * call is exactly the two calls in sequence. */
+ * same tables.  By default, and in pipeline mode 1, for shapes whose histogram table is
+ * small the kernel that finishes the plan also moves rows (all of them by default, slice
+ * 0 in mode 1; those workgroups derive their rows themselves), so the first row does not
+ * wait for the plan; otherwise the call is exactly the two calls in sequence. */
 int monta_route_dispatch_regather(const monta_cfg *cfg, const float *logits, const void *x, int32_t *topk_idx,
                                   float *gates, void *stage, void *final_, void *ws, void *stream);
 
@@ -249,7 +249,7 @@ int monta_combine(const monta_cfg *cfg, const void *y, const float *gates, void 
  * workspace.  The caller still passes every input and output: logits [T][E], x [T][H], topk_idx / gates [T][k],
  * stage / final_ [max_rows][H], out [T][H], all device pointers as in the calls above; results are bit-identical
  * to those calls.  Calls no hipMalloc / hipFree and creates no stream or event: pipeline mode 0 is replaced by
- * the size-chosen mode, and with event profiling enabled the call is refused (MONTA_ERR_INVALID).  Problems
+ * the default mode, and with event profiling enabled the call is refused (MONTA_ERR_INVALID).  Problems
  * whose tables (monta_ws_layout.ws_bytes) exceed 16 MiB are refused with MONTA_ERR_TOO_LARGE before any GPU
  * work; the five named workloads need at most 8.2 MiB.  Every call on one GPU shares that GPU's array: the
  * counters in it are cleared by a small kernel at the start of each call, the tables are overwritten, and two
@@ -275,8 +275,9 @@ int monta_combine_staged(const monta_cfg *cfg, const void *y_stage, const float 
 
 /* The return pipeline on one stream.  With pipeline mode 0 or 1, launch j fetches slice j back and, in disjoint
  * workgroups of the same grid, combines the tokens of slice j-1 (S+1 launches); with mode 2, fetch and combine of
- * every slice are two plain kernels; the default (-1) groups consecutive slices as the forward pipeline does
- * (groups of up to 256 MiB, two plain kernels per group once a group is that large or the problem is one group). */
+ * every slice are two plain kernels.  The default (-1) does both in one pass, each row of y read once, stored to its
+ * row of y_stage and added; where the memory of y, y_stage and out overlaps it keeps them apart and groups consecutive
+ * slices (groups of up to 256 MiB, two plain kernels per group once a group is that large or the problem is one group). */
 int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage, const float *gates, void *out,
                              const void *ws, void *stream);
 
@@ -286,20 +287,23 @@ int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage,
  *   1  one stream, co-scheduled grids: launch j does regather(j-1) and pack(j) in
  *      disjoint workgroups of one grid (S+1 launches, no events);
  *   2  one stream, strictly serial pack(0), regather(0), pack(1), ...
- *  -1  (default) chosen per call from the sizes, as the paper's planner picks its chunk count from
- *      the traffic: consecutive slices are grouped into one launch until a launch's share of STAGE
+ *  -1  (default) no separate passes: one launch reads every token row once and stores it to its rows
+ *      of STAGE and of FINAL, so STAGE is not read back.  Where FINAL shares memory with x the passes
+ *      stay apart, in a realisation chosen from the sizes, as the paper's planner picks its chunk count
+ *      from the traffic: consecutive slices are grouped into one launch until a launch's share of STAGE
  *      reaches 256 MiB; the groups run as in 1 while their copies are short, as in 2 once a group
  *      moves 192 MiB or more.  A problem that fits one group runs in three launches: plan + pack of
  *      the first slices (about one round of workgroups), pack of the rest co-scheduled with the
  *      regather of the first, regather of the rest.
  * With 0, 1 or 2 every launch covers exactly one slice.  STAGE keeps its [slice][tp rank][expert]
- * layout in every case; only the launch grouping differs.
+ * layout in every case; only the launches differ.
  * Returns MONTA_ERR_INVALID for other values.  Process-wide. */
 int monta_set_pipeline_mode(int mode);
 int monta_get_pipeline_mode(void);
-/* Host only: what monta_route_dispatch_regather would do for cfg under the current switch: the realisation
- * (0, 1 or 2), the slices the first launch covers, the slices each later launch covers, and whether the kernel
- * that finishes the plan also packs the first launch's slices.  Benchmarks use it to attribute bytes to launches. */
+/* Host only: how the two passes are launched for cfg, under the current switch, where they are kept apart: the
+ * realisation (0, 1 or 2), the slices the first launch covers, the slices each later launch covers, and whether the
+ * kernel that finishes the plan also packs the first launch's slices.  Benchmarks that set a mode use it to attribute
+ * bytes to launches; the default mode's single pass has nothing to group. */
 int monta_pipeline_query(const monta_cfg *cfg, int32_t *mode, int32_t *first_slices, int32_t *slices_per_launch,
                          int32_t *plan_fused);
 
@@ -351,7 +355,10 @@ enum monta_kernel_id {
     MONTA_K_GATE = 11,      /* gate projection                                */
     MONTA_K_EXPERT = 12,    /* expert layer (grouped GEMM)                    */
     MONTA_K_ALLGATHER_REGATHER = 13, /* co-scheduled grid of the pipelined two-pass order */
-    MONTA_K_COUNT = 14
+    MONTA_K_PLACE = 14,     /* pack and regather in one pass                  */
+    MONTA_K_PLAN_PLACE = 15, /* the same with the plan tables finished in the same grid */
+    MONTA_K_RETURN = 16,    /* the mirrored return path in one pass           */
+    MONTA_K_COUNT = 17
 };
 int monta_profile_enable(int on);
 int monta_profile_reset(void);

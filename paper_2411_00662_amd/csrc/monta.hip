@@ -615,8 +615,9 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     return MONTA_OK;
 }
 
-// How one call runs the slice pipeline: the realisation (0, 1 or 2) and how many consecutive slices one launch
-// covers.  An explicit mode keeps one slice per launch.  The default (-1) chooses from the sizes, as the paper's
+// How one call runs the two passes of the slice pipeline where they are kept apart (single_pass() says when they are not):
+// the realisation (0, 1 or 2) and how many consecutive slices one launch covers.  An explicit mode keeps one slice per
+// launch.  The default (-1) chooses from the sizes, as the paper's
 // planner chooses its chunk count from the traffic (section "Network-traffic-aware"): measured on MI355X,
 //  - a launch boundary costs a few microseconds of idle memory system, so slices that move only tens of
 //    megabytes are grouped until a launch's share of STAGE reaches 256 MiB (the size of the memory-side cache:
@@ -639,6 +640,74 @@ bool plan_pack_shape_ok(const Geometry &g)
     const int rows_per_wg = kMoverThreads / s.lpr;
     return s.fast_plan && (int64_t)s.num_blocks * s.E <= 2048 && s.Tu % s.TB == 0 && rows_per_wg <= s.TB &&
            kMoverThreads >= s.TB;
+}
+
+// Do the bytes [a, a + na) and [b, b + nb) share any?
+bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
+{
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa < pb + (uintptr_t)nb && pb < pa + (uintptr_t)na;
+}
+
+// By default the dispatch runs in one pass (place_kernel): each row is read once and stored to its rows in STAGE and in
+// FINAL.  An explicit pipeline mode asks for the two passes, and they are kept where FINAL shares memory with x: rows of x
+// still to be read would be overwritten.
+bool single_pass(const Geometry &g, const void *x, const void *final_)
+{
+    return g.modes.pipeline < 0 && !overlap(x, (int64_t)g.s.T * g.row_bytes, final_, g.max_rows * g.row_bytes);
+}
+
+// Cache policy of the single pass: nothing reads STAGE again, so its stores stream; x and FINAL stay cacheable (the combine
+// or the experts read FINAL next).  Measured against the other seven choices, step of 8192 x 8 KiB rows, top-2: 90 us
+// against 94-120, of 8192 x 16 KiB, top-1: 106 against 107-139; beyond the memory-side cache the choice moves 1-3 %.
+Shape place_shape(const Geometry &g)
+{
+    Shape s = g.s;
+    if (g.modes.cache < 0) s.cache = NT_PACK_ST;
+    return s;
+}
+
+int launch_place(const Geometry &g, const PlanPtrs &p, const void *x, void *stage, void *final_, hipStream_t st)
+{
+    const Shape s = place_shape(g);
+    ProfScope ps(MONTA_K_PLACE, st);
+    const dim3 grid(mover_grid(s, s.T)), block(kMoverThreads);
+    const u32x4 *xv = static_cast<const u32x4 *>(x);
+    u32x4 *sv = static_cast<u32x4 *>(stage), *fv = static_cast<u32x4 *>(final_);
+    if (s.lpr >= kWave) hipLaunchKernelGGL(place_kernel<true>, grid, block, 0, st, xv, sv, fv, p, s);
+    else hipLaunchKernelGGL(place_kernel<false>, grid, block, 0, st, xv, sv, fv, p, s);
+    HIP_TRY(hipGetLastError());
+    return MONTA_OK;
+}
+
+// Tokens per workgroup of plan_place_kernel, 0 if the kernel does not fit the shape.  The tokens of a workgroup must
+// belong to one route workgroup, and the histogram table must be small enough to be reduced by every workgroup; one round
+// of resident workgroups does that once each, more rows per workgroup keep it at one round.
+int plan_place_span(const Geometry &g)
+{
+    const Shape &s = g.s;
+    if (!s.fast_plan || (int64_t)s.num_blocks * s.E > 2048) return 0;
+    auto fits = [&](int span) { return span <= s.TB && s.TB % span == 0 && (s.Tu % span == 0 || s.U == 1); };
+    int span = kMoverThreads / s.lpr;
+    if (!fits(span)) return 0;
+    while ((s.T + span - 1) / span > kResidentMoverWgs && fits(2 * span)) span *= 2;
+    return span;
+}
+
+int launch_plan_place(const Geometry &g, const PlanPtrs &p, int span, const int32_t *topk_idx, const void *x, void *stage,
+                      void *final_, hipStream_t st)
+{
+    const Shape s = place_shape(g);
+    ProfScope ps(MONTA_K_PLAN_PLACE, st);
+    const dim3 grid(s.num_blocks + (s.T + span - 1) / span), block(kMoverThreads);
+    const u32x4 *xv = static_cast<const u32x4 *>(x);
+    u32x4 *sv = static_cast<u32x4 *>(stage), *fv = static_cast<u32x4 *>(final_);
+    if (s.lpr >= kWave)
+        hipLaunchKernelGGL(plan_place_kernel<true>, grid, block, 0, st, topk_idx, xv, sv, fv, p, s, span, s.num_blocks);
+    else
+        hipLaunchKernelGGL(plan_place_kernel<false>, grid, block, 0, st, topk_idx, xv, sv, fv, p, s, span, s.num_blocks);
+    HIP_TRY(hipGetLastError());
+    return MONTA_OK;
 }
 
 PipePlan pipeline_plan(const Geometry &g)
@@ -728,6 +797,7 @@ int pipeline_impl(const Geometry &g, const PipePlan &pp, const void *x, void *st
 
 int dispatch_regather_impl(const Geometry &g, const void *x, void *stage, void *final_, const void *ws, hipStream_t st)
 {
+    if (single_pass(g, x, final_)) return launch_place(g, plan_ptrs(g, ws), x, stage, final_, st);
     return pipeline_impl(g, pipeline_plan(g), x, stage, final_, ws, false, st);
 }
 
@@ -743,6 +813,15 @@ int route_dispatch_regather_impl(const Geometry &g, const float *logits, const v
 {
     int rc = MONTA_OK;
     const Shape &s = g.s;
+    if (single_pass(g, x, final_)) {
+        const PlanPtrs p = plan_ptrs(g, ws);
+        if (const int span = plan_place_span(g)) {
+            if ((rc = launch_route(g, p, logits, topk_idx, gates, st))) return rc;
+            return launch_plan_place(g, p, span, topk_idx, x, stage, final_, st);
+        }
+        if ((rc = route_impl(g, logits, topk_idx, gates, ws, st))) return rc;
+        return launch_place(g, p, x, stage, final_, st);
+    }
     const PipePlan pp = pipeline_plan(g);
     const int rows_per_wg = kMoverThreads / s.lpr;
     if (!plan_pack_fused(g, pp)) {
@@ -1151,6 +1230,37 @@ int launch_unregather_combine(const Geometry &g, const PlanPtrs &p, int dtype, c
     return MONTA_OK;
 }
 
+int launch_return(const Geometry &g, const PlanPtrs &p, int dtype, const void *y, void *y_stage, const float *gates,
+                  void *out, hipStream_t st)
+{
+    Shape s = g.s;
+    // y_stage and out are not read again here; y streams only where it does not fit the memory-side cache anyway (8192
+    // tokens, top-2, 8 KiB rows: 49.9 us with y cacheable, 64.7 streamed; 65536 tokens of 14 KiB, top-8: 1417 and 1394)
+    if (g.modes.cache < 0) {
+        const int64_t touched = ((int64_t)s.T + 2 * g.max_rows) * g.row_bytes;
+        s.cache = NT_REG_ST | NT_COMB_ST | (touched > (1024ll << 20) ? NT_REG_LD : 0);
+    }
+    const bool wide = s.vpr > 2 * s.lpr, pf = s.k >= 3 && s.k <= s.lpr;       // as in monta_combine
+    const u32x4 *yv = static_cast<const u32x4 *>(y);
+    u32x4 *sv = static_cast<u32x4 *>(y_stage), *ov = static_cast<u32x4 *>(out);
+    const dim3 grid(mover_grid(s, s.T)), block(kMoverThreads);
+    ProfScope ps(MONTA_K_RETURN, st);
+    auto launch = [&](auto bf, auto nv, auto pfc) {
+        hipLaunchKernelGGL((return_kernel<decltype(bf)::value, decltype(nv)::value, decltype(pfc)::value>), grid, block, 0, st,
+                           yv, sv, gates, ov, p, s);
+    };
+    auto by_form = [&](auto bf) {
+        using two = std::integral_constant<int, 2>;
+        using four = std::integral_constant<int, 4>;
+        if (pf) { if (wide) launch(bf, four{}, std::true_type{}); else launch(bf, two{}, std::true_type{}); }
+        else { if (wide) launch(bf, four{}, std::false_type{}); else launch(bf, two{}, std::false_type{}); }
+    };
+    if (dtype == MONTA_BF16) by_form(std::true_type{});
+    else by_form(std::false_type{});
+    HIP_TRY(hipGetLastError());
+    return MONTA_OK;
+}
+
 int check_staged_combine(const monta_cfg *cfg, Geometry *g, const void *y_stage, const float *gates, void *out,
                          const void *ws)
 {
@@ -1190,6 +1300,10 @@ int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage,
     const Shape &s = g.s;
     const PlanPtrs p = plan_ptrs(g, ws);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int64_t y_bytes = g.max_rows * g.row_bytes, out_bytes = (int64_t)s.T * g.row_bytes;
+    if (g.modes.pipeline < 0 && !overlap(y, y_bytes, y_stage, y_bytes) && !overlap(y, y_bytes, out, out_bytes) &&
+        !overlap(y_stage, y_bytes, out, out_bytes))
+        return launch_return(g, p, cfg->dtype, y, y_stage, gates, out, st);
     const int per_slice = s.tp * s.Tu;
     // Launch grouping as in the forward pipeline, by the same measurements: with an explicit pipeline mode launch j
     // fetches slice j back and, in disjoint workgroups of the same grid, combines the tokens of slice j-1; by

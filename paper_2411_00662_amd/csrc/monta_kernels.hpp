@@ -92,6 +92,16 @@ __device__ __forceinline__ void with_policy(bool ntl, bool nts, F f)
     }
 }
 
+// The same for the three streams of the single-pass dispatch.
+template <typename F>
+__device__ __forceinline__ void with_policy3(bool ntl, bool nts, bool ntf, F f)
+{
+    with_policy(ntl, nts, [&](auto l, auto st) {
+        if (ntf) f(l, st, std::true_type{});
+        else f(l, st, std::false_type{});
+    });
+}
+
 // ------------------------------------------------------------ route + plan
 
 // Row stride (floats) of the logits tile in LDS.  A wave holds 64 / L tokens with L lanes each, lane (token, sub)
@@ -725,26 +735,33 @@ __device__ __forceinline__ void regather_rows_t(u32x4 *stage, u32x4 *fin, const 
 
 // Capacity-padded layout: zero-fills the padding rows [e*C + kept[e], (e+1)*C) of every expert.  Padding row i
 // (0 <= i < E*C - R) belongs to the expert found by bisection over pad_before[e] = e*C - kept_prefix[e].
-__device__ __forceinline__ void pad_rows(u32x4 *__restrict__ fin, const PlanPtrs &p, const Shape &s, int wg, int nwg)
+// kept_prefix and kept: the plan tables, or the same values rebuilt in LDS.
+__device__ __forceinline__ void pad_rows(u32x4 *__restrict__ fin, const int32_t *kept_prefix, const int32_t *kept, int R,
+                                         const Shape &s, int wg, int nwg)
 {
     const int lpr = s.lpr, vpr = s.vpr, E = s.E, C = s.C;
     const int rows_per_wg = kMoverThreads / lpr;
     const int sub = threadIdx.x / lpr, lane = threadIdx.x - sub * lpr;
-    int total = E * C - p.kept_prefix[E];
+    int total = E * C - R;
     if (total > s.max_rows) total = s.max_rows;
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = wg * rows_per_wg + sub; i < total; i += nwg * rows_per_wg) {
         int lo = 0, hi = E - 1;                      // largest e with pad_before[e] <= i
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (mid * C - p.kept_prefix[mid] <= i) lo = mid;
+            if (mid * C - kept_prefix[mid] <= i) lo = mid;
             else hi = mid - 1;
         }
-        const int row = lo * C + p.kept[lo] + (i - (lo * C - p.kept_prefix[lo]));
+        const int row = lo * C + min(kept[lo], C) + (i - (lo * C - kept_prefix[lo]));
         if ((unsigned)row >= (unsigned)s.max_rows || row >= (lo + 1) * C) continue;
         u32x4 *dst = fin + (size_t)row * vpr;
         for (int v = lane; v < vpr; v += lpr) st16<true>(dst + v, zero);
     }
+}
+
+__device__ __forceinline__ void pad_rows(u32x4 *__restrict__ fin, const PlanPtrs &p, const Shape &s, int wg, int nwg)
+{
+    pad_rows(fin, p.kept_prefix, p.kept, p.kept_prefix[s.E], s, wg, nwg);
 }
 
 __device__ __forceinline__ void regather_rows(const u32x4 *__restrict__ stage, u32x4 *__restrict__ fin,
@@ -826,6 +843,177 @@ __global__ __launch_bounds__(kMoverThreads) void plan_pack_kernel(const int32_t 
     with_policy(s.cache & NT_PACK_LD, s.cache & NT_PACK_ST, [&](auto l, auto st) {
         pack_rows_selfplan_t<decltype(l)::value, decltype(st)::value>(bp, x, stage, topk_idx, p, s, t0, nt,
                                                                       bid - n_plan);
+    });
+}
+
+// ---- pack and re-gather in one pass
+//
+// A kept pair's row has two places, one in STAGE and one in FINAL, and both are known once the plan is: each token row
+// is read once and stored to all of them, instead of being packed into STAGE and read back from there.  Of the
+// (alive + R) + 2R rows that the two passes move, alive + 2R are left.  STAGE and FINAL end up as the two passes leave
+// them.
+
+// One row, with the rows its choices go to held by the first k lanes of its lane group (my_ps, my_pf; bit j of `kept`:
+// choice j is kept), so that no lane waits for a table between two stores.  WAVE: a row is shared by whole waves, the
+// destinations are then uniform and live in scalar registers.  `val` is the row's first pass, already requested.
+template <bool WAVE, bool NTL, bool NTS, bool NTF>
+__device__ __forceinline__ void place_row(const u32x4 *__restrict__ src, u32x4 *__restrict__ stage, u32x4 *__restrict__ fin,
+                                          const Shape &s, int lane, int gbase, unsigned int kept, int my_ps, int my_pf,
+                                          u32x4 (&val)[kVecInFlight])
+{
+    const int lpr = s.lpr, vpr = s.vpr;
+    if (WAVE) kept = __builtin_amdgcn_readfirstlane(kept);
+    for (int vbase = 0; vbase < vpr; vbase += lpr * kVecInFlight) {
+        const int v0 = vbase + lane;
+        if (vbase != 0) {
+#pragma unroll
+            for (int q = 0; q < kVecInFlight; ++q)
+                if (v0 + q * lpr < vpr) val[q] = ld16<NTL>(src + v0 + q * lpr);
+        }
+        for (unsigned int rem = kept; rem; rem &= rem - 1) {
+            const int j = __builtin_ctz(rem);
+            int ps, pf;
+            if (WAVE) {
+                ps = __builtin_amdgcn_readlane(my_ps, j);
+                pf = __builtin_amdgcn_readlane(my_pf, j);
+            } else {
+                ps = __shfl(my_ps, gbase + j, kWave);
+                pf = __shfl(my_pf, gbase + j, kWave);
+            }
+            u32x4 *ds = stage + (size_t)ps * vpr, *df = fin + (size_t)pf * vpr;
+#pragma unroll
+            for (int q = 0; q < kVecInFlight; ++q)
+                if (v0 + q * lpr < vpr) st16<NTS>(ds + v0 + q * lpr, val[q]);
+#pragma unroll
+            for (int q = 0; q < kVecInFlight; ++q)
+                if (v0 + q * lpr < vpr) st16<NTF>(df + v0 + q * lpr, val[q]);
+        }
+    }
+}
+
+// Tokens [t0, t0+nt), the rows of their choices taken from the plan tables.
+template <bool WAVE, bool NTL, bool NTS, bool NTF>
+__device__ __forceinline__ void place_rows_t(const u32x4 *__restrict__ x, u32x4 *__restrict__ stage, u32x4 *__restrict__ fin,
+                                             const PlanPtrs &p, const Shape &s, int t0, int nt, int wg, int nwg)
+{
+    const int lpr = s.lpr, vpr = s.vpr, k = s.k;
+    const int rows_per_wg = kMoverThreads / lpr;
+    const int sub = threadIdx.x / lpr, lane = threadIdx.x - sub * lpr;
+    const int wl = threadIdx.x & (kWave - 1);
+    const int gbase = lpr >= kWave ? 0 : (wl & ~(lpr - 1)), gl = wl - gbase;
+    const unsigned int kmask = k >= 32 ? 0xffffffffu : ((1u << k) - 1u);
+    for (int i = wg * rows_per_wg + sub; i < nt; i += nwg * rows_per_wg) {
+        const int t = t0 + i;
+        const u32x4 *src = x + (size_t)t * vpr;
+        // the row's first pass and the table entries are requested together; the row of a token whose choices were all
+        // dropped is read in vain
+        u32x4 val[kVecInFlight];
+#pragma unroll
+        for (int q = 0; q < kVecInFlight; ++q)
+            if (lane + q * lpr < vpr) val[q] = ld16<NTL>(src + lane + q * lpr);
+        const size_t pair = (size_t)t * k;
+        if (WAVE || k <= lpr) {
+            int ps = -1, pf = -1;
+            if (gl < k) {
+                ps = p.pos_stage[pair + gl];
+                pf = p.pos_final[pair + gl];
+            }
+            const bool ok = (unsigned)ps < (unsigned)s.max_rows && (unsigned)pf < (unsigned)s.max_rows;
+            const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
+            place_row<WAVE, NTL, NTS, NTF>(src, stage, fin, s, lane, gbase, kept, ps, pf, val);
+        } else {
+            // fewer lanes per row than choices (rows of at most 256 bytes): one choice after the other
+            for (int j = 0; j < k; ++j) {
+                const int ps = p.pos_stage[pair + j], pf = p.pos_final[pair + j];
+                if ((unsigned)ps >= (unsigned)s.max_rows || (unsigned)pf >= (unsigned)s.max_rows) continue;
+                if (lane < vpr) {           // lpr < 32 lanes hold the whole row in their first vectors
+                    st16<NTS>(stage + (size_t)ps * vpr + lane, val[0]);
+                    st16<NTF>(fin + (size_t)pf * vpr + lane, val[0]);
+                }
+            }
+        }
+    }
+}
+
+template <bool WAVE>
+__global__ __launch_bounds__(kMoverThreads) void place_kernel(const u32x4 *__restrict__ x, u32x4 *__restrict__ stage,
+                                                              u32x4 *__restrict__ fin, PlanPtrs p, Shape s)
+{
+    with_policy3(s.cache & NT_PACK_LD, s.cache & NT_PACK_ST, s.cache & NT_REG_ST, [&](auto l, auto st, auto f) {
+        place_rows_t<WAVE, decltype(l)::value, decltype(st)::value, decltype(f)::value>(x, stage, fin, p, s, 0, s.T,
+                                                                                       blockIdx.x, gridDim.x);
+    });
+    if (s.padded) pad_rows(fin, p, s, blockIdx.x, gridDim.x);
+}
+
+// The same ahead of the plan tables: the first n_plan workgroups finish the plan, each of the others rebuilds the scans
+// for the one route workgroup its `span` consecutive tokens belong to (the host checks the shape) and derives the rows of
+// their choices itself.  One rebuild serves all rows of a workgroup, and the first row and its routing are on their way
+// while it runs.
+template <bool WAVE, bool NTL, bool NTS, bool NTF>
+__device__ __forceinline__ void place_rows_selfplan_t(BlockPlan &bp, const u32x4 *__restrict__ x, u32x4 *__restrict__ stage,
+                                                      u32x4 *__restrict__ fin, const int32_t *__restrict__ topk_idx,
+                                                      const PlanPtrs &p, const Shape &s, int span, int wg, int nwg)
+{
+    const int lpr = s.lpr, vpr = s.vpr, k = s.k;
+    const int rows_per_wg = kMoverThreads / lpr;
+    const int sub = threadIdx.x / lpr, lane = threadIdx.x - sub * lpr;
+    const int wl = threadIdx.x & (kWave - 1);
+    const int gbase = lpr >= kWave ? 0 : (wl & ~(lpr - 1)), gl = wl - gbase;
+    const unsigned int kmask = k >= 32 ? 0xffffffffu : ((1u << k) - 1u);
+    const int t_first = wg * span, t_end = min(t_first + span, s.T);
+    const int u = t_first / s.Tu;
+    const int b = u * s.bpu + (t_first - u * s.Tu) / s.TB;
+    u32x4 val[kVecInFlight];
+    int e = 0, lr = 0;
+    auto request = [&](int t) {
+        const u32x4 *src = x + (size_t)t * vpr;
+#pragma unroll
+        for (int q = 0; q < kVecInFlight; ++q)
+            if (lane + q * lpr < vpr) val[q] = ld16<NTL>(src + lane + q * lpr);
+        if (gl < k) {
+            e = topk_idx[(size_t)t * k + gl];
+            lr = p.local_rank[(size_t)t * k + gl];
+        }
+    };
+    if (t_first + sub < t_end) request(t_first + sub);
+    block_plan(bp, b, p, s);
+    for (int t = t_first + sub; t < t_end; t += rows_per_wg) {
+        if (t != t_first + sub) request(t);
+        if (WAVE || k <= lpr) {
+            int ps = -1, pf = -1;
+            const bool ok = gl < k && place_pair(bp, s, e, lr, pf, ps);
+            const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
+            place_row<WAVE, NTL, NTS, NTF>(x + (size_t)t * vpr, stage, fin, s, lane, gbase, kept, ps, pf, val);
+        } else {
+            for (int j = 0; j < k; ++j) {
+                int ps, pf;
+                if (!place_pair(bp, s, topk_idx[(size_t)t * k + j], p.local_rank[(size_t)t * k + j], pf, ps)) continue;
+                if (lane < vpr) {
+                    st16<NTS>(stage + (size_t)ps * vpr + lane, val[0]);
+                    st16<NTF>(fin + (size_t)pf * vpr + lane, val[0]);
+                }
+            }
+        }
+    }
+    if (s.padded) pad_rows(fin, bp.kpre, bp.total, bp.R, s, wg, nwg);
+}
+
+template <bool WAVE>
+__global__ __launch_bounds__(kMoverThreads) void plan_place_kernel(const int32_t *__restrict__ topk_idx,
+                                                                   const u32x4 *__restrict__ x, u32x4 *__restrict__ stage,
+                                                                   u32x4 *__restrict__ fin, PlanPtrs p, Shape s, int span,
+                                                                   int n_plan)
+{
+    __shared__ BlockPlan bp;
+    const int bid = blockIdx.x;
+    if (bid < n_plan) {
+        plan_positions_block(bp, bid, topk_idx, p, s);
+        return;
+    }
+    with_policy3(s.cache & NT_PACK_LD, s.cache & NT_PACK_ST, s.cache & NT_REG_ST, [&](auto l, auto st, auto f) {
+        place_rows_selfplan_t<WAVE, decltype(l)::value, decltype(st)::value, decltype(f)::value>(
+            bp, x, stage, fin, topk_idx, p, s, span, bid - n_plan, gridDim.x - n_plan);
     });
 }
 
@@ -911,10 +1099,14 @@ __device__ __forceinline__ unsigned int f64_to_bf16_rne(double d)
 // still holds them.  A dropped pair is skipped; a token with no kept pair writes zeros.
 // `pos_table` is pos_final (y in FINAL layout) or pos_stage (y in the unit-major layout of the mirrored
 // return path); tokens [t0, t0+nt) are combined by workgroups wg of nwg.
-template <bool BF16, int NV, bool NTL, bool NTS>
+// KEEP: the mirrored return path in one pass: each row read from y is also stored, unchanged, to its place in the
+// unit-major layout (keep, rows from keep_table; non-temporal if NTK) before it is added.
+template <bool BF16, int NV, bool NTL, bool NTS, bool KEEP = false, bool NTK = false>
 __device__ __forceinline__ void combine_rows_t(const u32x4 *__restrict__ y, const float *__restrict__ gates,
                                                u32x4 *__restrict__ out, const int32_t *__restrict__ pos_table,
-                                               const Shape &s, int t0, int nt, int wg, int nwg)
+                                               const Shape &s, int t0, int nt, int wg, int nwg,
+                                               u32x4 *__restrict__ keep = nullptr,
+                                               const int32_t *__restrict__ keep_table = nullptr)
 {
     constexpr int NF = BF16 ? 8 : 4;            // accumulators per vector
     const int lpr = s.lpr, vpr = s.vpr, k = s.k;
@@ -940,6 +1132,14 @@ __device__ __forceinline__ void combine_rows_t(const u32x4 *__restrict__ y, cons
 #pragma unroll
                 for (int q = 0; q < NV; ++q)
                     if (v0 + q * lpr < vpr) val[q] = ld16<NTL>(src + v0 + q * lpr);
+                if (KEEP) {
+                    const int pk = keep_table[(size_t)t * k + j];
+                    if ((unsigned)pk < (unsigned)s.max_rows) {
+#pragma unroll
+                        for (int q = 0; q < NV; ++q)
+                            if (v0 + q * lpr < vpr) st16<NTK>(keep + (size_t)pk * vpr + v0 + q * lpr, val[q]);
+                    }
+                }
 #pragma unroll
                 for (int q = 0; q < NV; ++q) {
                     if (v0 + q * lpr < vpr) {
@@ -980,10 +1180,12 @@ __device__ __forceinline__ void combine_rows_t(const u32x4 *__restrict__ y, cons
 // the next kept choice is requested before the current one is added, so two rows' loads are in flight per
 // lane and the fp64 arithmetic runs under them.  Needs k <= lanes per row (the host checks).  Same order of
 // additions, same result.
-template <bool BF16, int NV, bool NTL, bool NTS>
+template <bool BF16, int NV, bool NTL, bool NTS, bool KEEP = false, bool NTK = false>
 __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, const float *__restrict__ gates,
                                                   u32x4 *__restrict__ out, const int32_t *__restrict__ pos_table,
-                                                  const Shape &s, int t0, int nt, int wg, int nwg)
+                                                  const Shape &s, int t0, int nt, int wg, int nwg,
+                                                  u32x4 *__restrict__ keep = nullptr,
+                                                  const int32_t *__restrict__ keep_table = nullptr)
 {
     constexpr int NF = BF16 ? 8 : 4;            // accumulators per vector
     const int lpr = s.lpr, vpr = s.vpr, k = s.k;
@@ -996,11 +1198,12 @@ __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, c
     for (int i = wg * rows_per_wg + sub; i < nt; i += nwg * rows_per_wg) {
         const int t = t0 + nt - 1 - i;
         u32x4 *dst = out + (size_t)t * vpr;
-        int my_pos = -1;
+        int my_pos = -1, my_keep = -1;
         float my_g = 0.f;
         if (gl < k) {
             my_pos = pos_table[(size_t)t * k + gl];
             my_g = gates[(size_t)t * k + gl];
+            if (KEEP) my_keep = keep_table[(size_t)t * k + gl];
         }
         const unsigned long long valid = __ballot((unsigned)my_pos < (unsigned)s.max_rows);
         const unsigned int kept = (unsigned int)(valid >> gbase) & kmask;      // bit j: choice j of this token is kept
@@ -1016,11 +1219,13 @@ __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, c
             unsigned int rem = kept;
             u32x4 cur[NV];
             float g_cur = 0.f;
+            int k_cur = -1;
             bool have = rem != 0;
             if (have) {
                 const int j = __builtin_ctz(rem);
                 rem &= rem - 1;
                 const int pf = __shfl(my_pos, gbase + j, kWave);
+                if (KEEP) k_cur = __shfl(my_keep, gbase + j, kWave);
                 g_cur = __shfl(my_g, gbase + j, kWave);
                 const u32x4 *src = y + (size_t)pf * vpr;
 #pragma unroll
@@ -1030,11 +1235,13 @@ __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, c
             while (have) {
                 u32x4 nxt[NV];
                 float g_nxt = 0.f;
+                int k_nxt = -1;
                 const bool have_nxt = rem != 0;
                 if (have_nxt) {
                     const int j = __builtin_ctz(rem);
                     rem &= rem - 1;
                     const int pf = __shfl(my_pos, gbase + j, kWave);
+                    if (KEEP) k_nxt = __shfl(my_keep, gbase + j, kWave);
                     g_nxt = __shfl(my_g, gbase + j, kWave);
                     const u32x4 *src = y + (size_t)pf * vpr;
 #pragma unroll
@@ -1042,6 +1249,11 @@ __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, c
                         if (v0 + q * lpr < vpr) nxt[q] = ld16<NTL>(src + v0 + q * lpr);
                 }
                 const double gj = (double)g_cur;
+                if (KEEP && (unsigned)k_cur < (unsigned)s.max_rows) {
+#pragma unroll
+                    for (int q = 0; q < NV; ++q)
+                        if (v0 + q * lpr < vpr) st16<NTK>(keep + (size_t)k_cur * vpr + v0 + q * lpr, cur[q]);
+                }
 #pragma unroll
                 for (int q = 0; q < NV; ++q) {
                     if (v0 + q * lpr < vpr) {
@@ -1059,6 +1271,7 @@ __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, c
 #pragma unroll
                 for (int q = 0; q < NV; ++q) cur[q] = nxt[q];
                 g_cur = g_nxt;
+                k_cur = k_nxt;
                 have = have_nxt;
             }
 #pragma unroll
@@ -1205,6 +1418,25 @@ __global__ __launch_bounds__(kMoverThreads) void unregather_combine_kernel(const
                                                                                   nt, idx, n_comb_wg);
         });
     }
+}
+
+// The whole return path in one pass: for every token the rows of its kept choices are read from y once, stored to their
+// places in the unit-major layout and added up, instead of being fetched into that layout and read back from there
+// (2R + T rows instead of 3R + T).  Same rows, same order of additions.  PF as above.
+template <bool BF16, int NV, bool PF>
+__global__ __launch_bounds__(kMoverThreads) void return_kernel(const u32x4 *__restrict__ y, u32x4 *__restrict__ y_stage,
+                                                               const float *__restrict__ gates, u32x4 *__restrict__ out,
+                                                               PlanPtrs p, Shape s)
+{
+    with_policy3(s.cache & NT_REG_LD, s.cache & NT_COMB_ST, s.cache & NT_REG_ST, [&](auto l, auto st, auto kp) {
+        constexpr bool NTL = decltype(l)::value, NTS = decltype(st)::value, NTK = decltype(kp)::value;
+        if (PF)
+            combine_rows_pf_t<BF16, NV, NTL, NTS, true, NTK>(y, gates, out, p.pos_final, s, 0, s.T, blockIdx.x, gridDim.x,
+                                                             y_stage, p.pos_stage);
+        else
+            combine_rows_t<BF16, NV, NTL, NTS, true, NTK>(y, gates, out, p.pos_final, s, 0, s.T, blockIdx.x, gridDim.x,
+                                                          y_stage, p.pos_stage);
+    });
 }
 
 // --------------------------------------------------------- gate projection

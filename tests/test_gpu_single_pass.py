@@ -1,0 +1,95 @@
+"""GPU parity of the single-pass dispatch and return path (the library's default).
+
+Each token row is read once and stored to its rows of STAGE and of FINAL; on the way back each row of y is read once,
+stored to its row of y_stage and added.  Bar: every table, STAGE, FINAL (canary intact above R), y_stage and out are
+bit for bit what the two passes give (pipeline mode 2, itself held against the oracle elsewhere), and STAGE / FINAL are
+the oracle's.  The shapes sit on the edges of the kernels: fewer lanes per row than choices, rows shared by part of a
+wave, by one wave, by whole workgroups and by more than one pass; workgroups of several rows; token counts that no
+group of rows divides; the padded layout; tables too large for a workgroup to rebuild.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import BF16, FP32, Workload, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    Workload("row16", 640, 8, BF16, 32, 20, 4, 2, 2, 0.5, zipf_s=0.8),              # 1 lane a row, 20 choices
+    Workload("row128", 96, 64, BF16, 16, 12, 4, 1, 1, 0.0),                         # 8 lanes a row, 12 choices
+    Workload("row272", 330, 136, BF16, 5, 3, 5, 2, 3, 0.7, zipf_s=0.8),             # 17 vectors on 32 lanes
+    Workload("row1k", 4096, 256, FP32, 8, 2, 4, 2, 4, 1.25, zipf_s=0.5),            # a wave a row, four rows a workgroup
+    Workload("row1040", 777, 260, FP32, 7, 7, 7, 7, 3, 0.9, zipf_s=0.8, renorm=0),  # 65 vectors: 128 lanes a row
+    Workload("row16k", 520, 8192, BF16, 8, 2, 8, 1, 1, 0.6, zipf_s=1.0),            # exactly one pass of a workgroup
+    Workload("row32k", 65, 8196, FP32, 4, 2, 2, 1, 5, 0.8, zipf_s=0.5),             # three passes, the last one vector
+    Workload("one", 1, 4096, BF16, 8, 2, 8, 1, 1, 0.0),
+    Workload("odd", 37, 2048, BF16, 8, 2, 8, 1, 1, 0.0),
+    Workload("rounds", 12288, 1024, BF16, 4, 2, 4, 1, 3, 0.9, zipf_s=0.5),          # more than one round: rows per workgroup
+    Workload("wide", 2048, 128, BF16, 64, 8, 8, 4, 8, 0.5, zipf_s=1.2),             # table too large to rebuild per workgroup
+    Workload("padded", 600, 264, BF16, 7, 3, 7, 5, 2, 0.5, zipf_s=0.8, padded=1),
+    Workload("padded16", 512, 4096, BF16, 8, 2, 8, 1, 1, 2.0, padded=1),
+]
+
+
+@pytest.fixture(scope="module")
+def m():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_00662_amd as mod
+    mod.binding.lib()
+    return mod
+
+
+def run(m, w, mode, fused, logits, x):
+    import torch
+    cfg = m.make_cfg(w.tokens, w.hidden, w.dtype, w.experts, w.top_k, w.ep, w.tp, w.slices, w.capacity_factor, w.renorm, w.padded)
+    b = m.alloc_buffers(cfg, logits, x, canary=0xA5)
+    y_stage = b.stage.clone()
+    m.monta_set_pipeline_mode(mode)
+    if fused:
+        m.monta_route_dispatch_regather(cfg, b.logits, b.x, b.topk_idx, b.gates, b.stage, b.final, b.ws)
+    else:
+        m.monta_route(cfg, b.logits, b.topk_idx, b.gates, b.ws)
+        m.monta_dispatch_regather(cfg, b.x, b.stage, b.final, b.ws)
+    m.monta_unregather_combine(cfg, b.final, y_stage, b.gates, b.out, b.ws)
+    torch.cuda.synchronize()
+    return cfg, b, y_stage, m.read_tables(cfg, b.ws)
+
+
+def same_bytes(a, b):
+    import torch
+    return torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("w", SHAPES, ids=lambda w: w.name)
+def test_single_pass_equals_two_passes(m, w):
+    from paper_2411_00662_amd import buffers as bufs
+    logits, x = make_inputs(w)
+    cfg, b2, ys2, t2 = run(m, w, 2, False, logits, x)
+    ref = oracle.forward(logits, x, k=w.top_k, ep=w.ep, tp=w.tp, S=w.slices, cf=w.capacity_factor, renorm=w.renorm, padded=w.padded)
+    for fused in (False, True):
+        _, b, ys, t = run(m, w, -1, fused, logits, x)
+        R = t["R"]
+        for name in ("counts", "kept", "offsets", "n", "stage_off", "unit_base", "send_rows", "unit_rows", "pos_final", "pos_stage"):
+            assert np.array_equal(t[name], t2[name]), name
+        assert np.array_equal(t["row_map"][:R], t2["row_map"][:R]) and t["alive"] == t2["alive"]
+        for name in ("stage", "final", "out", "gates", "topk_idx"):
+            assert same_bytes(getattr(b, name), getattr(b2, name)), name
+        assert same_bytes(ys, ys2)
+        assert np.array_equal(bufs.to_host_act(cfg, b.stage, R), ref.stage[:R])
+        assert np.array_equal(bufs.to_host_act(cfg, b.final, t["final_rows"]), ref.final[:t["final_rows"]])
+
+
+def test_final_in_the_memory_of_x(m):
+    """FINAL may reuse the memory of x where the whole of x is packed first (one slice): the passes are then kept apart."""
+    import torch
+    w = Workload("alias", 1024, 512, BF16, 8, 2, 4, 2, 1, 0.0)
+    logits, x = make_inputs(w)
+    cfg, want, _, _ = run(m, w, 2, False, logits, x)
+    b = m.alloc_buffers(cfg, logits, x, canary=0xA5)
+    b.final[:w.tokens] = b.x
+    m.monta_route_dispatch_regather(cfg, b.logits, b.final, b.topk_idx, b.gates, b.stage, b.final, b.ws)
+    torch.cuda.synchronize()
+    assert same_bytes(b.final, want.final) and same_bytes(b.stage, want.stage)
