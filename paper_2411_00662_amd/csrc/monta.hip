@@ -490,29 +490,28 @@ int launch_gate_small_any(const u32x4 *x, const u32x4 *w, float *logits, int64_t
 }
 
 template <bool RAGGED_LAST>
-int launch_expert_dtl_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, unsigned grid, hipStream_t st)
+int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, unsigned grid, hipStream_t st)
 {
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_dtl_kernel<RAGGED_LAST>), kDtlLdsBytes, lds_opt_in)) return rc;
-    hipLaunchKernelGGL(expert_dtl_kernel<RAGGED_LAST>, dim3(grid), dim3(kDtlThreads), kDtlLdsBytes, st,
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_big_kernel<RAGGED_LAST>), kBigLdsBytes, lds_opt_in)) return rc;
+    hipLaunchKernelGGL(expert_big_kernel<RAGGED_LAST>, dim3(grid), dim3(kBigThreads), kBigLdsBytes, st,
                        static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
                        static_cast<unsigned short *>(y), a);
     return MONTA_OK;
 }
 
-int launch_expert_dtl(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, hipStream_t st)
+int launch_expert_big(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, hipStream_t st)
 {
-    const int64_t row_tiles = (rows_bound + kDtlBM - 1) / kDtlBM + a.E;      // each expert may end in a ragged tile
-    const int64_t nct = (a.N + kDtlBN - 1) / kDtlBN;
+    const int64_t row_tiles = (rows_bound + kBigBM - 1) / kBigBM + a.E;      // each expert may end in a ragged tile
+    const int64_t nct = (a.N + kBigBN - 1) / kBigBN;
     // whole blocks of 256 workgroups: the kernel hands out tile numbers in such blocks, 32 per XCD
     const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    a.reserved = 0;
-    // The segments' ragged last tiles go to the end of the numbering (and skip their empty blocks) only when there
-    // are few of them, at most one round of 256 workgroups: measured on MI355X, 2-2.5 % faster with 8 and with 2
-    // experts, 2.4 % slower with 64 experts of 28 column tiles, whose ragged tiles then lose their panel's L2 reuse.
-    if ((int64_t)a.E * nct <= 256) return launch_expert_dtl_t<true>(x_final, w_exp, y, a, (unsigned)grid, st);
-    return launch_expert_dtl_t<false>(x_final, w_exp, y, a, (unsigned)grid, st);
+    // The segments' ragged last tiles go to the end of the numbering only when there are few of them, at most one round
+    // of 256 workgroups: measured on MI355X, eight segments of about 2048 rows 464 us against 480 with the ragged tiles in
+    // place; 64 segments of 191 rows, where every tile is ragged, 448 against 440.
+    if ((int64_t)a.E * nct <= 256) return launch_expert_big_t<true>(x_final, w_exp, y, a, (unsigned)grid, st);
+    return launch_expert_big_t<false>(x_final, w_exp, y, a, (unsigned)grid, st);
 }
 
 template <int BM, int BN, int WM, int WN>
@@ -527,7 +526,6 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
     constexpr int64_t block = 32 * G::kWgsPerCu * kXcds;            // the kernel numbers its tiles in such blocks
     const int64_t grid8 = (row_tiles * nct + block - 1) / block * block;
     if (grid8 > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    a.reserved = 0;
     hipLaunchKernelGGL((expert_bf16_kernel<BM, BN, WM, WN>), dim3((unsigned)grid8), dim3(G::kThreads), G::kLdsBytes, st,
                        static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
                        static_cast<unsigned short *>(y), a);
@@ -598,15 +596,20 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     int64_t rows_bound = slice < 0 ? (int64_t)s.max_rows : std::min<int64_t>(s.max_rows, (int64_t)(s.T / s.S) * s.k);
     ProfScope ps(MONTA_K_EXPERT, st);
     if (cfg->dtype == MONTA_BF16) {
-        // whole 64-element steps and segments long enough for 256-row tiles: the direct-to-LDS kernel
-        if (cfg->hidden % 64 == 0 && rows_bound / s.E >= 256)
-            rc = launch_expert_dtl(x_final, w_exp, y, a, rows_bound, st);
+        // Whole 64-element steps and segments long enough for the tiles of 256 rows: the direct-to-LDS kernel.  The choice
+        // looks at the whole problem, not at the slice: the kernels add in different orders, and a row's result must not
+        // depend on which launch computed it.
+        // Measured, old kernel against new: 8 experts of 4096 x 4096, 96 / 191 / 400 / 2048 rows each 153 / 143 / 134 / 555
+        // against 94 / 104 / 121 / 466 us; 64 experts of 7168 x 2048, 96 / 128 / 191 rows 348 / 564 / 580 against 391 / 406
+        // / 440 us, where the weights' trip from memory bounds both and two workgroups per CU hide it better.
+        const int64_t kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
+        if (cfg->hidden % 64 == 0 && cfg->hidden <= kBigMaxHidden && kept_bound / s.E >= 96)
+            rc = launch_expert_big(x_final, w_exp, y, a, rows_bound, st);
         else
             rc = launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
         if (rc) return rc;
     } else {
-        a.reserved = 0;
-        const int64_t blocks = ((int64_t)s.max_rows * out_features + 255) / 256;
+            const int64_t blocks = ((int64_t)s.max_rows * out_features + 255) / 256;
         if (blocks > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(expert_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, static_cast<const float *>(x_final),
                            static_cast<const float *>(w_exp), static_cast<float *>(y), a);

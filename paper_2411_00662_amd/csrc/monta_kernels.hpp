@@ -1890,7 +1890,6 @@ struct ExpertArgs {
     const int32_t *hi_base; // [E] one past its last row is hi_base[e] + hi_len[e] ...
     const int32_t *hi_len;  // [E] ... or hi_base[e] alone if this is nullptr
     int32_t E, H, N, max_rows;
-    int32_t reserved;       // unused
 };
 
 // The expert whose tiles include logical tile number L, found without walking the experts one by one (a walk costs
@@ -2073,79 +2072,96 @@ __global__ __launch_bounds__(64 * WM * WN, (64 * WM * WN <= 256 ? 2 : 1)) void e
         }
 }
 
-// The same contraction with direct-to-LDS loads (global_load_lds_dwordx4: 64 lanes x 16 bytes land in 1 KiB of
-// LDS that the instruction addresses, lane i at byte 16*i, without passing through registers).  That frees the
-// registers the staged tile occupied, so 8 waves can hold a 256 x 256 tile of y (a wave 128 x 64), which halves
-// the L2 traffic per flop, and a step needs one barrier instead of two: the next step's tile streams into the other
-// of two LDS buffers while the MFMAs run.  Rows are 128 bytes in LDS without padding; the 16-byte piece c of row r
-// sits at position c ^ ((r / 2) % 8).  A fragment read has 16 lanes (16 consecutive rows, one piece each) share the
-// 64 banks: two rows fill them, so the pieces must differ among the even rows and among the odd rows, which r / 2
-// gives; c ^ (r % 8) makes rows r and r + 8 collide (measured with ds_read_b128 alone: 113 against 220 bytes per
-// clock and CU).  Since the LDS position of a lane's data is fixed by the instruction, the swizzle is applied on the
-// global side (lane i of a chunk of 8 rows fetches piece (i % 8) ^ ((row / 2) % 8) of tile row `row` = chunk * 8 +
-// i / 8).  Needs H to be a multiple of 64 (a tail step cannot be zero-filled on this path); rows past a segment's
-// end are fetched from its last row and their results are not stored.
-// Measured on MI355X (16384 x 4096 x 4096, one expert, bursts of 20 launches): 590-610 us against 715-740 us for the
-// register-staged kernel; with clocks settled over thousands of launches a stand-alone copy of this loop takes
-// 460-477 us.  A segment's ragged last tile costs a full tile's time (skipping the MFMAs of its empty 32-row blocks
-// was measured and does not pay).
-constexpr int kDtlBM = 256, kDtlBN = 256, kDtlWM = 2, kDtlWN = 4, kDtlThreads = 64 * kDtlWM * kDtlWN;
-constexpr int kDtlStageBytes = (kDtlBM + kDtlBN) * 128;
-constexpr int kDtlLdsBytes = 2 * kDtlStageBytes;
+// The same contraction with direct-to-LDS loads, for long segments: a 256 x 256 tile of y per workgroup of 4 waves, one
+// per SIMD, each 128 x 128 = 8 x 8 tiles of the 16x16x32 MFMA (256 accumulator registers; the other 256 hold two sets of
+// fragments).  What bounds such a kernel is the matrix pipe, provided that everything else fits beside it:
+//  - LDS reads.  A wave tile of 128 x 128 reads a third less per flop than 128 x 64 (128 KiB per step of 64 elements
+//    against 192), and the fragments of the next 32-element slice are read while the present one is multiplied, one read
+//    per four MFMAs, so no MFMA waits for the LDS.
+//  - Register moves.  Left to itself the compiler rotates the accumulators through copies (about one per MFMA); the MFMA
+//    is therefore written with its accumulator tied in place, and the order of reads, loads and MFMAs is pinned.
+//  - Loads.  A step's tile (256 rows of x, 256 of w, 128 bytes each) goes straight to one of two LDS buffers while the
+//    other is read; the buffer is free once its second slice has been read, so the loads of stage s+2 are issued under the
+//    second slice of stage s and have until the end of the first slice of stage s+1.  That covers an L2 hit but no miss:
+//    each workgroup also touches, one stage ahead, one line per row of its share of the tiles it shares with the other
+//    workgroups on its XCD (its own eighth of a weight tile, its quarter of an x tile), so that misses are taken early.
+// Rows are 128 bytes in LDS without padding; the 16-byte piece c of row r sits at position c ^ ((r / 2) % 8): a fragment
+// read has 16 lanes (16 consecutive rows, one piece each) share the 64 banks, two rows fill them, so the pieces must
+// differ among the even rows and among the odd rows.  The LDS position of a lane's data is fixed by the instruction, so
+// the swizzle is applied on the global side.  Buffer descriptors end at the segment's last row and at the last output
+// feature: rows past them arrive as zeros and cost no traffic.  Needs H to be a multiple of 64.
+// The weight rows are the MFMA's A operand, so that a lane ends up with four consecutive features of a row: 8-byte stores.
+// Measured on MI355X, random normal inputs, bursts of 300 launches: 16384 x 4096 x 4096 in one segment 477-495 us with the
+// 8-wave kernel this one replaced (128 x 64 per wave, 32x32x16 MFMA, fragment reads scheduled by the compiler), 376-380
+// now (1.45 PFLOP/s; without any loads 329, a library GEMM 348-356); two segments of 4096 x 8192 x 8192 958-981 -> 743
+// (805 without the early touch); eight uneven segments of about 2048 rows (4.3 rounds of workgroups) 553 -> 448.  What
+// bounds it now: the matrix pipe at the clock the chip holds under this load, and the last round of a launch.
+constexpr int kBigBM = 256, kBigBN = 256, kBigThreads = 256;
+constexpr int kBigStageBytes = (kBigBM + kBigBN) * 128;
+constexpr int kBigLdsBytes = 2 * kBigStageBytes + 2048;           // two stages, and 512 bytes per wave for the early touches
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+typedef __attribute__((address_space(3))) void lds_void;
+constexpr uint32_t kOutOfRange = 0x80000000u;                      // a lane offset past every descriptor: no access
+constexpr int kBigMaxHidden = 1 << 20;                             // a tile's 256 rows end far below it
+
+// four fp32 -> four bf16, nearest-even, as 8 bytes
+__device__ __forceinline__ uint2 pack_bf16x4(f32x4 v)
+{
+    uint2 o;
+    o.x = f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16);
+    o.y = f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16);
+    return o;
+}
 
 // A ragged tile of at most 64 rows, the kind a launch's last round is made of: so little arithmetic per step that the
-// step is as long as its loads take to arrive.  Compact stages of 64 + 256 rows (40 KiB), three of them, the loads of
-// two steps in flight: half the time per step of the two-stage loop.  Eight waves, each all 64 rows x 32 columns.
-// Every wave issues the same number of loads per step (rows past the segment's end repeat its last row), because the
-// wait for a stage counts the younger loads.  The barrier is the bare instruction behind a wait for the LDS reads: the
-// compiler's own barrier would wait for every outstanding load, the next stages' included.
-__device__ __forceinline__ void expert_dtl_small_rows(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
-                                                      unsigned short *__restrict__ y, const ExpertArgs &a, int e,
-                                                      int row0, int row_end, int col0, unsigned char *lds)
+// step is as long as its loads take to arrive.  Compact stages of 64 + 256 rows (40 KiB), three of them, the loads of two
+// steps in flight.  Four waves, each all 64 rows x 64 columns.  Every wave issues the same number of loads per step,
+// because the wait for a stage counts the younger loads.  The barrier is the bare instruction behind a wait for the LDS
+// reads: the compiler's own barrier would wait for every outstanding load, the next stages' included.
+__device__ __forceinline__ void expert_small_rows(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, unsigned short *__restrict__ y,
+                                                  const ExpertArgs &a, int row0, int row_end, int col0, unsigned char *lds)
 {
-    constexpr int XR = 64, WR = 256, STG = (XR + WR) * 128, NST = 3, CPW = (XR + WR) / 8 / 8;   // 5 chunks per wave
-    static_assert(NST * STG <= kDtlLdsBytes && XR % 16 == 0, "expert_dtl_small_rows: stages must fit the kernel's LDS");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 31, g = lane >> 5;
-    const int cpr = a.H / 8, nsteps = a.H / 64;
+    constexpr int XR = 64, WR = 256, STG = (XR + WR) * 128, NST = 3, CX = XR / 8 / 4, CW = WR / 8 / 4;   // chunks per wave
+    static_assert(NST * STG <= kBigLdsBytes, "expert_small_rows: stages must fit the kernel's LDS");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 15, g = lane >> 4;
+    const int nsteps = a.H / 64;
+    const uint32_t rowb = (uint32_t)a.H * 2;
     const int lr = lane >> 3;
-    const u32x4 *src[CPW];
+    // row of the lane in chunk c: 8 c + lane / 8, so (row / 2) % 8 = (4 c + lr / 2) % 8
+    auto offset = [&](int c) { return (uint32_t)(c * 8 + lr) * rowb + (((lane & 7) ^ ((4 * c + (lr >> 1)) & 7)) * 16); };
+    uint32_t ox[CX], ow[CW];
 #pragma unroll
-    for (int q = 0; q < CPW; ++q) {
-        const int trow = (wave * CPW + q) * 8 + lr;                // 0 .. 319
-        const int lc = (lane & 7) ^ ((trow >> 1) & 7);
-        if (trow < XR) {
-            const int r = row0 + trow;
-            src[q] = x + (int64_t)(r < row_end ? r : row_end - 1) * cpr + lc;
-        } else {
-            const int n = col0 + trow - XR;
-            src[q] = w + ((int64_t)e * a.N + (n < a.N ? n : a.N - 1)) * cpr + lc;
-        }
-    }
+    for (int q = 0; q < CX; ++q) ox[q] = offset(wave * CX + q);
+#pragma unroll
+    for (int q = 0; q < CW; ++q) ow[q] = offset(wave * CW + q);
     auto issue = [&](int step, int slot) {
+        unsigned char *base = lds + slot * STG;
 #pragma unroll
-        for (int q = 0; q < CPW; ++q)
-            __builtin_amdgcn_global_load_lds(
-                (const void __attribute__((address_space(1))) *)(src[q] + step * 8),
-                (void __attribute__((address_space(3))) *)(lds + slot * STG + (wave * CPW + q) * 1024), 16, 0, 0);
+        for (int q = 0; q < CX; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * CX + q) * 1024), 16, ox[q], step * 128, 0, 0);
+#pragma unroll
+        for (int q = 0; q < CW; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * CW + q) * 1024), 16, ow[q],
+                                                     step * 128, 0, 0);
     };
-    f32x16 acc[2];
+    f32x4 acc[4][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-    const unsigned char *pa = lds + (size_t)m * 128;
-    const unsigned char *pb = lds + (size_t)(XR + wave * 32 + m) * 128;
-    int koff[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) koff[ks] = ((2 * ks + g) ^ ((m >> 1) & 7)) * 16;
-    const int nb = row_end - row0 > 32 ? 2 : 1;                    // 32-row blocks with rows of the segment
+        for (int j = 0; j < 4; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const unsigned char *px = lds + m * 128, *pw = lds + (XR + wave * 64 + m) * 128;
+    const int nb = (row_end - row0 + 15) / 16;                     // 16-row blocks with rows of the segment
 
     issue(0, 0);
     if (nsteps > 1) issue(1, 1);
     int slot = 0;
     for (int step = 0; step < nsteps; ++step) {
-        // stage `step` has landed once at most the CPW loads of stage step+1 are outstanding (loads finish in order)
-        if (step + 1 < nsteps) __builtin_amdgcn_s_waitcnt(0x0f70 | CPW);
+        // stage `step` has landed once at most the loads of stage step+1 are outstanding (loads finish in order)
+        if (step + 1 < nsteps) __builtin_amdgcn_s_waitcnt(0x0f70 | (CX + CW));
         else __builtin_amdgcn_s_waitcnt(0x0f70);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): this wave's reads of the previous stage
@@ -2154,38 +2170,42 @@ __device__ __forceinline__ void expert_dtl_small_rows(const u32x4 *__restrict__ 
         if (step + 2 < nsteps) issue(step + 2, slot == 0 ? 2 : slot - 1);   // the slot of stage step-1, free now
         const int buf = slot * STG;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8 fb = *reinterpret_cast<const bf16x8 *>(pb + buf + koff[ks]);
-            const bf16x8 fa0 = *reinterpret_cast<const bf16x8 *>(pa + buf + koff[ks]);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa0, fb, acc[0], 0, 0, 0);
-            if (nb > 1) {
-                const bf16x8 fa1 = *reinterpret_cast<const bf16x8 *>(pa + buf + 32 * 128 + koff[ks]);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa1, fb, acc[1], 0, 0, 0);
-            }
+        for (int ks = 0; ks < 2; ++ks) {
+            const int ko = ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
+            bf16x8 fw[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(pw + buf + ko + j * 2048);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (i < nb) {
+                    const bf16x8 fx = *reinterpret_cast<const bf16x8 *>(px + buf + ko + i * 2048);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fx, acc[i][j], 0, 0, 0);
+                }
         }
         slot = slot == 2 ? 0 : slot + 1;
     }
-    const int n = col0 + wave * 32 + m;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i) {
+        const int r = row0 + i * 16 + m;
+        if (r < row_end) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = row0 + i * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
-            if (r < row_end && n < a.N) y[(int64_t)r * a.N + n] = (unsigned short)f32_to_bf16_rne(acc[i][v]);
+            for (int j = 0; j < 4; ++j) {
+                const int n = col0 + wave * 64 + j * 16 + 4 * g;
+                if (n < a.N) *reinterpret_cast<uint2 *>(y + (int64_t)r * a.N + n) = pack_bf16x4(acc[i][j]);
+            }
         }
+    }
 }
 
-
 template <bool RAGGED_LAST>
-__global__ __launch_bounds__(kDtlThreads) void expert_dtl_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
-                                                                 unsigned short *__restrict__ y, ExpertArgs a)
+__global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
+                                                                    unsigned short *__restrict__ y, ExpertArgs a)
 {
-    constexpr int BM = kDtlBM, BN = kDtlBN, WM = kDtlWM, WN = kDtlWN, WAVES = WM * WN;
-    constexpr int CPW = (BM + BN) / 8 / WAVES;                     // 1 KiB chunks (8 tile rows) per wave and step
-    constexpr int MT = BM / WM / 32, NT = BN / WN / 32;
-    static_assert((BM + BN) % (8 * WAVES) == 0 && BM % 16 == 0, "expert_dtl_kernel: chunks must divide among the waves");
-    extern __shared__ __align__(16) unsigned char dtl_lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 31, g = lane >> 5;
+#if defined(__HIP_DEVICE_COMPILE__)         // the matrix instruction is written out: nothing for the host pass to parse
+    constexpr int BM = kBigBM, BN = kBigBN, P = 8;                 // P: row tiles of a panel
+    extern __shared__ __align__(16) unsigned char big_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cpr = a.H / 8, nsteps = a.H / 64;
     const int nct = (a.N + BN - 1) / BN;
 
@@ -2198,26 +2218,29 @@ __global__ __launch_bounds__(kDtlThreads) void expert_dtl_kernel(const u32x4 *__
     int64_t L = (j / 32) * (32 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 32 + j % 32;
     // With RAGGED_LAST the whole tiles of all experts are numbered first and the ragged last tiles of the segments
     // after them, the one with the most rows first: a launch rarely fills its last round of workgroups, and this way
-    // that round consists of the tiles that cost least (their empty 32-row blocks are skipped below).  The price: a
-    // ragged tile no longer shares its weight tile's trip through the L2 with the other row tiles of its panel, so
-    // the host asks for it only when the ragged tiles are few (at most one round of workgroups).
+    // that round consists of the tiles that cost least.  The price: a ragged tile no longer shares its weight tile's
+    // trip through the L2 with the other row tiles of its panel, so the host asks for it only when the ragged tiles are
+    // few (at most one round of workgroups).
     int64_t whole = 0;
     const ExpertTileHit hit = RAGGED_LAST ? find_expert_tile<BM, true>(a, nct, L, lane, &whole)
                                           : find_expert_tile<BM, false>(a, nct, L, lane);
-    int e = hit.e;
-    int row0 = 0, row_end = 0, ct = 0;
+    int e = hit.e, row0 = 0, row_end = 0, ct = 0;
+    int sharers = 1, share = 0;                                    // row tiles side by side on one weight tile; which of them
     if (e < a.E) {
-        constexpr int P = 8;                                       // row tiles of a panel (4..32 measure alike)
         const int tiles = hit.tiles, full = tiles / P;             // whole panels
         int rt;
         if (hit.L < (int64_t)full * P * nct) {
             const int p = (int)(hit.L / (P * nct)), rem = (int)(hit.L % (P * nct));
             ct = rem / P;
-            rt = p * P + rem % P;
+            share = rem % P;
+            rt = p * P + share;
+            sharers = P;
         } else {
             const int rem = (int)(hit.L - (int64_t)full * P * nct), pr = tiles - full * P;
             ct = rem / pr;
-            rt = full * P + rem % pr;
+            share = rem % pr;
+            rt = full * P + share;
+            sharers = pr;
         }
         row0 = hit.lo + rt * BM;
         row_end = hit.hi < a.max_rows ? hit.hi : a.max_rows;
@@ -2225,7 +2248,7 @@ __global__ __launch_bounds__(kDtlThreads) void expert_dtl_kernel(const u32x4 *__
         // ragged tiles: position L / nct in the order (rows in the ragged tile, descending; expert, ascending).  The
         // tile buffers are not in use yet, so their first bytes serve as the scratch of the ranking (E <= 256).
         const int64_t Lr = L - whole;
-        int *scr = reinterpret_cast<int *>(dtl_lds);
+        int *scr = reinterpret_cast<int *>(big_lds);
         int my_rem = 0;
         if (tid < a.E) {
             const int lo = a.lo[tid], hi = a.hi_base[tid] + (a.hi_len ? a.hi_len[tid] : 0);
@@ -2253,124 +2276,155 @@ __global__ __launch_bounds__(kDtlThreads) void expert_dtl_kernel(const u32x4 *__
             row_end = hi < a.max_rows ? hi : a.max_rows;
         }
     }
-    if (e == a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup (uniform for the workgroup)
+    // the same for the whole workgroup: into scalar registers
+    e = __builtin_amdgcn_readfirstlane(e);
+    row0 = __builtin_amdgcn_readfirstlane(row0);
+    row_end = __builtin_amdgcn_readfirstlane(row_end);
+    sharers = __builtin_amdgcn_readfirstlane(sharers);
+    share = __builtin_amdgcn_readfirstlane(share);
+    ct = __builtin_amdgcn_readfirstlane(ct);
+    if (e >= a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup
     const int col0 = ct * BN;
-    if (RAGGED_LAST && row_end - row0 <= 64) {                     // a short ragged tile: the three-stage loop
-        expert_dtl_small_rows(x, w, y, a, e, row0, row_end, col0, dtl_lds);
+    const uint32_t rowb = (uint32_t)a.H * 2;
+    const int xr = min(row_end - row0, BM), wr = min(a.N - col0, BN);
+    const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
+    const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
+    if (xr <= 64) {                                                // the loop for tiles with little arithmetic
+        expert_small_rows(rx, rw, y, a, row0, row_end, col0, big_lds);
         return;
     }
 
-    // source of this lane in each of its wave's chunks: tile row chunk*8 + lane/8, piece (lane%8) ^ ((row/2)%8)
-    // (BM is a multiple of 16, so the rows of the weight tile swizzle like rows 0.. of their own)
+    // A step's tile is 32 + 32 chunks of 8 rows (1 KiB); this wave fetches chunks 8 wave .. 8 wave + 7 of x and of w.
     const int lr = lane >> 3;
-    const u32x4 *src[CPW];
-    unsigned skip = 0;                      // chunks of 8 rows of x wholly past the segment's end: never fetched
+    uint32_t off[8];
 #pragma unroll
-    for (int q = 0; q < CPW; ++q) {
-        const int trow = (wave * CPW + q) * 8 + lr;
-        const int lc = (lane & 7) ^ ((trow >> 1) & 7);
-        if (RAGGED_LAST && (wave * CPW + q) * 8 < BM && row0 + (wave * CPW + q) * 8 >= row_end) skip |= 1u << q;
-        if (trow < BM) {
-            const int r = row0 + trow;
-            src[q] = x + (int64_t)(r < row_end ? r : row_end - 1) * cpr + lc;
-        } else {
-            const int n = col0 + trow - BM;
-            src[q] = w + ((int64_t)e * a.N + (n < a.N ? n : a.N - 1)) * cpr + lc;
-        }
+    for (int q = 0; q < 8; ++q) {
+        const int trow = (wave * 8 + q) * 8 + lr;
+        off[q] = (uint32_t)trow * rowb + (((lane & 7) ^ ((trow >> 1) & 7)) * 16);
     }
-    auto issue = [&](int step, int buf) {
-        if (skip == 0) {
-#pragma unroll
-            for (int q = 0; q < CPW; ++q)
-                __builtin_amdgcn_global_load_lds(
-                    (const void __attribute__((address_space(1))) *)(src[q] + step * 8),
-                    (void __attribute__((address_space(3))) *)(dtl_lds + buf * kDtlStageBytes + (wave * CPW + q) * 1024), 16, 0, 0);
-        } else {
-#pragma unroll
-            for (int q = 0; q < CPW; ++q)
-                if (!((skip >> q) & 1u))
-                    __builtin_amdgcn_global_load_lds(
-                        (const void __attribute__((address_space(1))) *)(src[q] + step * 8),
-                        (void __attribute__((address_space(3))) *)(dtl_lds + buf * kDtlStageBytes + (wave * CPW + q) * 1024), 16, 0, 0);
-        }
+    auto issue = [&](int q, bool is_w, int step, int buf) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            is_w ? rw : rx, (lds_void *)(big_lds + buf * kBigStageBytes + (is_w ? BM * 128 : 0) + (wave * 8 + q) * 1024), 16,
+            off[q], step * 128, 0, 0);
+    };
+    const uint32_t touch_w = lane * sharers / 64 == share ? (uint32_t)(wave * 64 + lane) * rowb : kOutOfRange;
+    const uint32_t touch_x = lane < 16 ? (uint32_t)((ct & 3) * 64 + wave * 16 + lane) * rowb : kOutOfRange;
+    auto touch = [&](int step) {
+        const int so = min(step, nsteps - 1) * 128;
+        lds_void *sink = (lds_void *)(big_lds + 2 * kBigStageBytes + wave * 512);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sink, 4, touch_w, so, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, sink, 4, touch_x, so, 0, 0);
     };
 
-    f32x16 acc[MT][NT];
+    // The waves form a 2 x 2 grid.  In a ragged tile the rows are split evenly between the two row halves: nb 16-row
+    // blocks each.
+    const int m = lane & 15, g = lane >> 4, wm = wave >> 1, wn = wave & 1;
+    const int nb = (xr + 31) / 32;
+    const int wrow = wm * nb * 16;
+    f32x4 acc[8][8];                                               // [16-row block of x][16 output features]
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int n = 0; n < 8; ++n) acc[i][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const unsigned char *px = big_lds + (wrow + m) * 128, *pw = big_lds + (BM + wn * 128 + m) * 128;
+    const int k0 = (g ^ ((m >> 1) & 7)) * 16, k1 = ((4 + g) ^ ((m >> 1) & 7)) * 16;      // this lane's piece, slice 0 and 1
+    bf16x8 fx[2][8], fw[2][8];
+    auto read_w = [&](int set, int i, int buf, int ko) {
+        fw[set][i] = *reinterpret_cast<const bf16x8 *>(pw + buf * kBigStageBytes + ko + i * 2048);
+    };
+    auto read_x = [&](int set, int i, int buf, int ko) {
+        fx[set][i] = *reinterpret_cast<const bf16x8 *>(px + buf * kBigStageBytes + ko + i * 2048);
+    };
+    // no instruction near it reads the accumulator: the next MFMA on the same one is a whole slice away, and the epilogue
+    // waits first
+    auto mma = [&](int set, int i, int n) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][n]) : "v"(fw[set][n]), "v"(fx[set][i]));
+    };
+    auto barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // One slice: 64 MFMAs on fragment set `set`; between them the 16 reads of the other set (buffer `buf`, piece offset ko)
+    // and, if LOADS, the 16 loads of stage `step` into buffer `to`.
+    auto slice = [&](int set, int buf, int ko, bool loads, int step, int to) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int wm = wave / WN, wn = wave % WN;
-    const unsigned char *pa = dtl_lds + (size_t)(wm * (BM / WM) + m) * 128;
-    const unsigned char *pb = dtl_lds + (size_t)(BM + wn * (BN / WN) + m) * 128;
-    int koff[kExpBK / 16];                                         // byte offset of this lane's fragment piece per k-slice
+        for (int q = 0; q < 16; ++q) {
+            if (q < 8) read_w(set ^ 1, q, buf, ko);
+            else read_x(set ^ 1, q - 8, buf, ko);
+            mma(set, q / 2, (q & 1) * 4 + 0);
+            mma(set, q / 2, (q & 1) * 4 + 1);
+            if (loads) issue(q / 2, q & 1, step, to);
+            mma(set, q / 2, (q & 1) * 4 + 2);
+            mma(set, q / 2, (q & 1) * 4 + 3);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // the same for a ragged tile: only the wave's nb blocks with rows are multiplied
+    auto slice_ragged = [&](int set, int buf, int ko, bool loads, int step, int to) {
 #pragma unroll
-    for (int ks = 0; ks < kExpBK / 16; ++ks) koff[ks] = ((2 * ks + g) ^ ((m >> 1) & 7)) * 16;   // 32-row blocks: (row/2)%8 = (m/2)%8
-
-    // 32-row blocks of this wave that hold rows of the segment (all MT of them except in a ragged tile)
-    int nb = MT;
-    if (RAGGED_LAST) {
-        nb = (row_end - row0 - wm * (BM / WM) + 31) / 32;
-        nb = nb < 0 ? 0 : (nb > MT ? MT : nb);
-    }
-
-    issue(0, 0);
-    for (int step = 0; step < nsteps; ++step) {
-        // s_waitcnt vmcnt(0) (expcnt and lgkmcnt left at their maxima): this step's tile has landed in LDS
-        __builtin_amdgcn_s_waitcnt(0x0f70);
-        __syncthreads();                                           // ... for every wave, and the other buffer is free
-        if (step + 1 < nsteps) issue(step + 1, (step + 1) & 1);    // streams in during the MFMAs
-        const int buf = (step & 1) * kDtlStageBytes;
-        if (nb == MT) {
-#pragma unroll
-            for (int ks = 0; ks < kExpBK / 16; ++ks) {
-                bf16x8 fa[MT], fb[NT];
-#pragma unroll
-                for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const bf16x8 *>(pa + buf + i * 32 * 128 + koff[ks]);
-#pragma unroll
-                for (int j = 0; j < NT; ++j) fb[j] = *reinterpret_cast<const bf16x8 *>(pb + buf + j * 32 * 128 + koff[ks]);
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 8; ++i) {
+            read_w(set ^ 1, i, buf, ko);
+            read_x(set ^ 1, i, buf, ko);
+            if (loads) {
+                issue(i, true, step, to);
+                issue(i, false, step, to);
             }
-        } else if (nb > 0) {
-            // ragged tile: blocks past the segment's end are not multiplied (uniform per wave); the fragment reads stay
-            // as they are, so that the loop keeps the shape of the one above (what they fetch there is never used)
+            __builtin_amdgcn_sched_barrier(0);
+            if (i < nb) {
 #pragma unroll
-            for (int ks = 0; ks < kExpBK / 16; ++ks) {
-                bf16x8 fa[MT], fb[NT];
+                for (int n = 0; n < 8; ++n) mma(set, i, n);
+            }
+        }
+    };
+    auto run = [&](auto slice_fn) {
+        for (int s = 0; s < nsteps; ++s) {
+            const int buf = s & 1;
+            slice_fn(0, buf, k1, false, 0, 0);
+            // vmcnt(2) lgkmcnt(0): stage s+1 is in LDS (only the two early touches are younger), and this wave has read
+            // all of stage s
+            __builtin_amdgcn_s_waitcnt(0x0072);
+            barrier();
+            // past the end the last stage is fetched again, into the buffer that is not read any more
+            slice_fn(1, buf ^ 1, k0, true, min(s + 2, nsteps - 1), buf);
+            touch(s + 3);
+        }
+    };
 #pragma unroll
-                for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const bf16x8 *>(pa + buf + i * 32 * 128 + koff[ks]);
+    for (int q = 0; q < 16; ++q) issue(q / 2, q & 1, 0, 0);
 #pragma unroll
-                for (int j = 0; j < NT; ++j) fb[j] = *reinterpret_cast<const bf16x8 *>(pb + buf + j * 32 * 128 + koff[ks]);
+    for (int q = 0; q < 16; ++q) issue(q / 2, q & 1, min(1, nsteps - 1), 1);
+    __builtin_amdgcn_s_waitcnt(0x4f70);                            // vmcnt(16): stage 0
+    touch(2);
+    barrier();
 #pragma unroll
-                for (int i = 0; i < MT; ++i)
-                    if (i < nb) {
+    for (int i = 0; i < 8; ++i) {
+        read_w(0, i, 0, k0);
+        read_x(0, i, 0, k0);
+    }
+    if (nb == 8) run(slice);
+    else run(slice_ragged);
+    asm volatile("s_nop 15\n\ts_nop 15");                          // the last MFMAs' results
+    __builtin_amdgcn_sched_barrier(0);
+
+    // acc[i][n][v]: row 16 i + m of the wave's rows, output feature 16 n + 4 g + v of its columns
 #pragma unroll
-                        for (int j = 0; j < NT; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-                    }
+    for (int i = 0; i < 8; ++i) {
+        const int r = row0 + wrow + i * 16 + m;
+        if (i < nb && r < row_end) {
+#pragma unroll
+            for (int n = 0; n < 8; ++n) {
+                const int c = col0 + wn * 128 + n * 16 + 4 * g;
+                if (c < a.N) *reinterpret_cast<uint2 *>(y + (int64_t)r * a.N + c) = pack_bf16x4(acc[i][n]);
             }
         }
     }
-
-    // accumulator element v of a lane: row (v/4)*8 + g*4 + v%4, column m of the 32 x 32 tile
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int n = col0 + wn * (BN / WN) + j * 32 + m;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = row0 + wm * (BM / WM) + i * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
-                if (r < row_end && n < a.N) y[(int64_t)r * a.N + n] = (unsigned short)f32_to_bf16_rne(acc[i][j][v]);
-            }
-        }
+#else
+    (void)x;
+    (void)w;
+    (void)y;
+    (void)a;
+#endif
 }
 
 // fp32 activations (small test shapes only): one thread per output element, fp32 fused multiply-adds

@@ -1,0 +1,55 @@
+"""Expert layer with segment sizes on the edges of its kernels' tiles, fixed by the logits (top-1, one expert per token
+run).  Small-integer inputs: every partial sum is an integer below 2^24, so any order of additions gives the oracle's
+value and the comparison is exact."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from workloads import BF16, FP32, Workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def m():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_00662_amd as mod
+    mod.binding.lib()
+    return mod
+
+
+def check(m, sizes, H, N, dtype):
+    import torch
+    from paper_2411_00662_amd import buffers as bufs
+    T, E = sum(sizes), len(sizes)
+    w = Workload("tiles", T, H, dtype, E, 1, 1, 1, 1, 0.0)
+    rng = np.random.default_rng(T + H + N)
+    logits = rng.uniform(-0.25, 0.25, size=(T, E)).astype(np.float32)
+    logits[np.arange(T), np.repeat(np.arange(E), sizes)] += 4.0
+    to_act = (lambda a: a) if dtype == FP32 else workloads.f32_to_bf16_bits
+    x = to_act(rng.integers(-4, 5, size=(T, H)).astype(np.float32))
+    we = to_act(rng.integers(-4, 5, size=(E, N, H)).astype(np.float32))
+    cfg = m.make_cfg(T, H, dtype, E, 1, 1, 1, 1, 0.0)
+    b = m.alloc_buffers(cfg, logits, x)
+    m.monta_route_dispatch_regather(cfg, b.logits, b.x, b.topk_idx, b.gates, b.stage, b.final, b.ws)
+    y = torch.empty((T + 1, N), dtype=b.final.dtype, device="cuda:0")
+    y.view(torch.uint8).fill_(0x5A)
+    m.monta_expert_linear(cfg, b.final, bufs.to_device_act(cfg, we.reshape(E * N, H)), N, y[:T], b.ws)
+    torch.cuda.synchronize()
+    got = bufs.to_host_act(cfg, y)
+    ref = oracle.forward(logits, x, k=1, ep=1, tp=1, S=1, cf=0.0)
+    assert [int(v) for v in ref.plan.kept] == list(sizes)
+    lo, hi = oracle.expert_ranges(ref.plan, 1, 1)
+    np.testing.assert_array_equal(got[:T], oracle.expert(ref.final, we, lo, hi))
+    assert np.all(got[T].view(np.uint8) == 0x5A)
+
+
+# rows of a ragged tile around its 32-row steps (two halves of 16-row blocks), around the 64 rows of the short loop and
+# around whole tiles; columns of one lane group, of one and of two tiles, and so many that the ragged tiles stay in place
+@pytest.mark.parametrize("H", [64, 128, 192])
+@pytest.mark.parametrize("N", [8, 248, 264, 6664])
+def test_long_segments(m, H, N):
+    check(m, [65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 321, 64], H, N, BF16)
