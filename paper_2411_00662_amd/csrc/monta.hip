@@ -514,6 +514,42 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, const Exp
     return launch_expert_big_t<false>(x_final, w_exp, y, a, (unsigned)grid, st);
 }
 
+template <int XR, int WR, int NST>
+int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, hipStream_t st)
+{
+    using G = ShortTile<XR, WR, NST>;
+    static LdsOptIn lds_opt_in;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST>), G::kLdsBytes, lds_opt_in)) return rc;
+    const int64_t row_tiles = rows_bound / XR + std::min<int64_t>(a.E, rows_bound);
+    const int64_t nct = (a.N + WR - 1) / WR;
+    const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
+    if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((expert_short_kernel<XR, WR, NST>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st,
+                       static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
+                       static_cast<unsigned short *>(y), a);
+    return MONTA_OK;
+}
+
+// Which tile: with r rows per expert, a kernel of R x C tiles has about experts * (r / R + 1/2) * N / C of them, and a
+// launch that leaves CUs idle is slower with large tiles than with small ones.  Measured on MI355X (us for tiles of 32 x 64,
+// 64 x 128, 256 x 256):
+//   8 experts, 4096 x 4096:   r = 16: 41, 41, 73   32: 53, 42, 75   96: 84, 59, 92   128: 105, 101, 97   256: -, 144, 113
+//   2 experts, 8192 x 8192:   r = 16: 40, 75, 108  48: 57, 79, 119  128: 110, 102, 168   256: -, 177, 215   512: -, 261, 219
+//   64 experts, 2048 x 2048:  r = 16: 98, 113, 125  48: 129, 118, 132  64: 149, 128, 134  128: 224, 175, 156
+//   64 experts, 7168 x 2048:  r = 16: 311, 312, 310  64: 511, 388, 389  96: 620, 438, 395
+//   8 experts, 1024 x 1024:   r = 128: 10, 14, 28   512: -, 28, 37   1024: -, 43, 37
+// So a tile is taken where most experts fit one of its rows' tiles, or where its tiles number at most 2.5 per CU.
+int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
+                        int64_t kept_bound, hipStream_t st)
+{
+    const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
+    auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
+    constexpr int64_t kFewTiles = 640;
+    if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
+    if (r <= 56 || tiles(64, 128) <= kFewTiles) return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
+    return launch_expert_big(x_final, w_exp, y, a, rows_bound, st);
+}
+
 template <int BM, int BN, int WM, int WN>
 int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, hipStream_t st)
 {
@@ -596,15 +632,11 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     int64_t rows_bound = slice < 0 ? (int64_t)s.max_rows : std::min<int64_t>(s.max_rows, (int64_t)(s.T / s.S) * s.k);
     ProfScope ps(MONTA_K_EXPERT, st);
     if (cfg->dtype == MONTA_BF16) {
-        // Whole 64-element steps and segments long enough for the tiles of 256 rows: the direct-to-LDS kernel.  The choice
-        // looks at the whole problem, not at the slice: the kernels add in different orders, and a row's result must not
-        // depend on which launch computed it.
-        // Measured, old kernel against new: 8 experts of 4096 x 4096, 96 / 191 / 400 / 2048 rows each 153 / 143 / 134 / 555
-        // against 94 / 104 / 121 / 466 us; 64 experts of 7168 x 2048, 96 / 128 / 191 rows 348 / 564 / 580 against 391 / 406
-        // / 440 us, where the weights' trip from memory bounds both and two workgroups per CU hide it better.
+        // The direct-to-LDS kernels take whole 64-element steps.  The choice of tile looks at the whole problem, not at the
+        // slice, so that a slice runs as the whole would.
         const int64_t kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
-        if (cfg->hidden % 64 == 0 && cfg->hidden <= kBigMaxHidden && kept_bound / s.E >= 96)
-            rc = launch_expert_big(x_final, w_exp, y, a, rows_bound, st);
+        if (cfg->hidden % 64 == 0 && cfg->hidden <= kBigMaxHidden)
+            rc = launch_expert_tiled(x_final, w_exp, y, a, rows_bound, kept_bound, st);
         else
             rc = launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
         if (rc) return rc;

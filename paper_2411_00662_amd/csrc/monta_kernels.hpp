@@ -2117,85 +2117,125 @@ __device__ __forceinline__ uint2 pack_bf16x4(f32x4 v)
     return o;
 }
 
-// A ragged tile of at most 64 rows, the kind a launch's last round is made of: so little arithmetic per step that the
-// step is as long as its loads take to arrive.  Compact stages of 64 + 256 rows (40 KiB), three of them, the loads of two
-// steps in flight.  Four waves, each all 64 rows x 64 columns.  Every wave issues the same number of loads per step,
-// because the wait for a stage counts the younger loads.  The barrier is the bare instruction behind a wait for the LDS
-// reads: the compiler's own barrier would wait for every outstanding load, the next stages' included.
-__device__ __forceinline__ void expert_small_rows(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, unsigned short *__restrict__ y,
+// A tile of at most XR rows x WR output features: so little arithmetic per step that the step is as long as its loads take
+// to arrive, so what counts is how many bytes are on their way.  Compact stages of XR + WR rows, NST of them, the loads of
+// NST - 1 steps in flight.  Four waves, each all rows x WR / 4 columns.  Every wave issues the same number of loads per step,
+// also past the end (out of range: no traffic), because the wait for a stage counts the younger loads.  The barrier is the
+// bare instruction behind a wait for the LDS reads: the compiler's own barrier would wait for every outstanding load, the
+// next stages' included.
+template <int XR, int WR, int NST>
+struct ShortTile {
+    static constexpr int kStageBytes = (XR + WR) * 128, kLdsBytes = NST * kStageBytes;
+    static constexpr int kCX = XR / 32, kCW = WR / 32, kLoads = kCX + kCW;       // 8-row chunks per wave and step
+    static constexpr int kYounger = (NST - 2) * kLoads;                         // loads issued after those of the stage waited for
+    static constexpr int kWait = 0x0f70 | (kYounger & 15) | ((kYounger >> 4) << 14);        // s_waitcnt vmcnt(kYounger)
+    static_assert(XR % 32 == 0 && WR % 64 == 0 && NST >= 3 && kYounger < 64, "short tile: shape");
+};
+
+template <int XR, int WR, int NST>
+__device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, unsigned short *__restrict__ y,
                                                   const ExpertArgs &a, int row0, int row_end, int col0, unsigned char *lds)
 {
-    constexpr int XR = 64, WR = 256, STG = (XR + WR) * 128, NST = 3, CX = XR / 8 / 4, CW = WR / 8 / 4;   // chunks per wave
-    static_assert(NST * STG <= kBigLdsBytes, "expert_small_rows: stages must fit the kernel's LDS");
+    using G = ShortTile<XR, WR, NST>;
+    constexpr int RB = XR / 16, CB = WR / 64;                      // 16-row blocks, 16-column blocks of a wave
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 15, g = lane >> 4;
     const int nsteps = a.H / 64;
     const uint32_t rowb = (uint32_t)a.H * 2;
     const int lr = lane >> 3;
     // row of the lane in chunk c: 8 c + lane / 8, so (row / 2) % 8 = (4 c + lr / 2) % 8
     auto offset = [&](int c) { return (uint32_t)(c * 8 + lr) * rowb + (((lane & 7) ^ ((4 * c + (lr >> 1)) & 7)) * 16); };
-    uint32_t ox[CX], ow[CW];
+    uint32_t ox[G::kCX], ow[G::kCW];
 #pragma unroll
-    for (int q = 0; q < CX; ++q) ox[q] = offset(wave * CX + q);
+    for (int q = 0; q < G::kCX; ++q) ox[q] = offset(wave * G::kCX + q);
 #pragma unroll
-    for (int q = 0; q < CW; ++q) ow[q] = offset(wave * CW + q);
+    for (int q = 0; q < G::kCW; ++q) ow[q] = offset(wave * G::kCW + q);
     auto issue = [&](int step, int slot) {
-        unsigned char *base = lds + slot * STG;
+        unsigned char *base = lds + slot * G::kStageBytes;
+        const uint32_t past = step < nsteps ? 0u : kOutOfRange;
 #pragma unroll
-        for (int q = 0; q < CX; ++q)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * CX + q) * 1024), 16, ox[q], step * 128, 0, 0);
+        for (int q = 0; q < G::kCW; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * G::kCW + q) * 1024), 16, ow[q] | past,
+                                                     step * 128, 0, 0);
 #pragma unroll
-        for (int q = 0; q < CW; ++q)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * CW + q) * 1024), 16, ow[q],
+        for (int q = 0; q < G::kCX; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * G::kCX + q) * 1024), 16, ox[q] | past,
                                                      step * 128, 0, 0);
     };
-    f32x4 acc[4][4];
+    f32x4 acc[RB][CB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const unsigned char *px = lds + m * 128, *pw = lds + (XR + wave * 64 + m) * 128;
+        for (int j = 0; j < CB; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const unsigned char *px = lds + m * 128, *pw = lds + (XR + wave * (WR / 4) + m) * 128;
     const int nb = (row_end - row0 + 15) / 16;                     // 16-row blocks with rows of the segment
 
-    issue(0, 0);
-    if (nsteps > 1) issue(1, 1);
+#pragma unroll
+    for (int q = 0; q < NST - 1; ++q) issue(q, q);
     int slot = 0;
     for (int step = 0; step < nsteps; ++step) {
-        // stage `step` has landed once at most the loads of stage step+1 are outstanding (loads finish in order)
-        if (step + 1 < nsteps) __builtin_amdgcn_s_waitcnt(0x0f70 | (CX + CW));
-        else __builtin_amdgcn_s_waitcnt(0x0f70);
+        __builtin_amdgcn_s_waitcnt(G::kWait);                      // stage `step` has landed (loads finish in order)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): this wave's reads of the previous stage
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (step + 2 < nsteps) issue(step + 2, slot == 0 ? 2 : slot - 1);   // the slot of stage step-1, free now
-        const int buf = slot * STG;
+        issue(step + NST - 1, slot == 0 ? NST - 1 : slot - 1);     // the slot of stage step-1, free now
+        const int buf = slot * G::kStageBytes;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const int ko = ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
-            bf16x8 fw[4];
+            bf16x8 fw[CB];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(pw + buf + ko + j * 2048);
+            for (int j = 0; j < CB; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(pw + buf + ko + j * 2048);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < RB; ++i)
                 if (i < nb) {
                     const bf16x8 fx = *reinterpret_cast<const bf16x8 *>(px + buf + ko + i * 2048);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fx, acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fx, acc[i][j], 0, 0, 0);
                 }
         }
-        slot = slot == 2 ? 0 : slot + 1;
+        slot = slot == NST - 1 ? 0 : slot + 1;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RB; ++i) {
         const int r = row0 + i * 16 + m;
         if (r < row_end) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int n = col0 + wave * 64 + j * 16 + 4 * g;
+            for (int j = 0; j < CB; ++j) {
+                const int n = col0 + wave * (WR / 4) + j * 16 + 4 * g;
                 if (n < a.N) *reinterpret_cast<uint2 *>(y + (int64_t)r * a.N + n) = pack_bf16x4(acc[i][j]);
             }
         }
     }
+}
+
+// Few rows per expert (a decoding step): every weight is read once for a handful of rows, and the layer lasts as long as
+// the weights take to arrive from memory.  Two workgroups per CU, 128 KiB of loads in flight per CU.  Measured on MI355X,
+// register-staged 128 x 256 tiles before, now (floor: the weights at 6.4 TB/s): 8 experts of 4096 x 4096, 16 rows each 138 ->
+// 41 us (42); 64 of 7168 x 2048, 16 rows 314 -> 311 us (294); 64 of 2048 x 2048 133 -> 98 us (84).  Streaming the weights
+// straight into registers in the MFMA's layout (16 rows x 64 bytes per load) was measured too: 61, 434 and 121 us.
+template <int XR, int WR, int NST>
+__global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
+                                                              unsigned short *__restrict__ y, ExpertArgs a)
+{
+    extern __shared__ __align__(16) unsigned char short_lds[];
+    const int lane = threadIdx.x & 63;
+    const int cpr = a.H / 8, nct = (a.N + WR - 1) / WR;
+    // numbers are dealt to the XCDs in blocks of 32, row tiles fastest: row tiles of one weight tile meet in one L2
+    const int64_t j = blockIdx.x / kXcds;
+    const int64_t L = (j / 32) * (32 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 32 + j % 32;
+    const ExpertTileHit hit = find_expert_tile<XR>(a, nct, L, lane);
+    const int e = __builtin_amdgcn_readfirstlane(hit.e);
+    if (e >= a.E) return;                                          // surplus workgroup
+    const int ct = __builtin_amdgcn_readfirstlane((int)(hit.L / hit.tiles));
+    const int row0 = __builtin_amdgcn_readfirstlane(hit.lo + (int)(hit.L % hit.tiles) * XR);
+    const int seg_end = __builtin_amdgcn_readfirstlane(hit.hi < a.max_rows ? hit.hi : a.max_rows);
+    if (row0 < 0 || row0 >= seg_end) return;
+    const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
+    const uint32_t rowb = (uint32_t)a.H * 2;
+    expert_short_tile<XR, WR, NST>(make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb),
+                                   make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb), y, a,
+                                   row0, row_end, col0, short_lds);
 }
 
 template <bool RAGGED_LAST>
@@ -2290,7 +2330,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= 64) {                                                // the loop for tiles with little arithmetic
-        expert_small_rows(rx, rw, y, a, row0, row_end, col0, big_lds);
+        static_assert(ShortTile<64, 256, 3>::kLdsBytes <= kBigLdsBytes, "short tile: stages must fit the kernel's LDS");
+        expert_short_tile<64, 256, 3>(rx, rw, y, a, row0, row_end, col0, big_lds);
         return;
     }
 

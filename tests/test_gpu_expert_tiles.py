@@ -53,3 +53,17 @@ def check(m, sizes, H, N, dtype):
 @pytest.mark.parametrize("N", [8, 248, 264, 6664])
 def test_long_segments(m, H, N):
     check(m, [65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 321, 64], H, N, BF16)
+
+
+# few rows per expert: row counts around the 16-row blocks and past one tile, hidden sizes of fewer steps than waves and
+# of several turns of the registers in flight, columns of one lane group and of several workgroups
+@pytest.mark.parametrize("sizes", [[1], [1, 0, 2, 0], [16, 1, 7], [17, 33, 4, 31, 0, 15], [64, 65, 20, 1, 129, 40]], ids=str)
+@pytest.mark.parametrize("H,N", [(64, 8), (192, 72), (256, 520), (2176, 40), (4096, 264)])
+def test_few_rows(m, sizes, H, N):
+    check(m, sizes, H, N, BF16)
+
+
+def test_few_rows_many_columns(m):
+    """More column tiles than one round of workgroups; segments of several row tiles."""
+    check(m, [5, 30, 1, 12], 128, 8200, BF16)
+    check(m, [5, 30, 1, 12], 128, 4104, BF16)
