@@ -641,10 +641,11 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
             rc = launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
         if (rc) return rc;
     } else {
-            const int64_t blocks = ((int64_t)s.max_rows * out_features + 255) / 256;
-        if (blocks > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL(expert_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, static_cast<const float *>(x_final),
-                           static_cast<const float *>(w_exp), static_cast<float *>(y), a);
+            const int64_t row_tiles = rows_bound / kF32Tile + s.E, nct = (out_features + kF32Tile - 1) / kF32Tile;
+        const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
+        if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+        hipLaunchKernelGGL(expert_f32_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const u32x4 *>(x_final),
+                           static_cast<const u32x4 *>(w_exp), static_cast<float *>(y), a);
     }
     HIP_TRY(hipGetLastError());
     return MONTA_OK;

@@ -67,3 +67,11 @@ def test_few_rows_many_columns(m):
     """More column tiles than one round of workgroups; segments of several row tiles."""
     check(m, [5, 30, 1, 12], 128, 8200, BF16)
     check(m, [5, 30, 1, 12], 128, 4104, BF16)
+
+
+# 64 x 64 tiles of fp32: rows and columns on both sides of the 32-row halves and of the tile, hidden sizes that are not
+# whole 32-element steps
+@pytest.mark.parametrize("H", [4, 32, 36, 100])
+@pytest.mark.parametrize("N", [4, 32, 64, 132])
+def test_fp32_tiles(m, H, N):
+    check(m, [1, 31, 32, 33, 0, 64, 65, 130], H, N, FP32)
