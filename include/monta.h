@@ -308,11 +308,10 @@ int monta_pipeline_query(const monta_cfg *cfg, int32_t *mode, int32_t *first_sli
                          int32_t *plan_fused);
 
 /* How monta_route builds the plan tables.  -1 (default): when the per-workgroup
- * histogram table is small (num_blocks * experts <= 65536) every workgroup of the
- * positions kernel rebuilds the scans it needs from that table (no serial tail);
- * otherwise, and always with mode 0, the last route workgroup to finish does the
- * scans once (ticket counter) and a separate kernel finishes the positions.  Both
- * produce identical tables.  Process-wide. */
+ * histogram table is small (num_blocks * experts <= 4096) every workgroup of the
+ * positions kernel rebuilds the scans it needs from that table; otherwise, and always
+ * with mode 0, a kernel of its own scans the table first.  Both produce identical
+ * tables.  Process-wide. */
 int monta_set_plan_mode(int mode);
 int monta_get_plan_mode(void);
 

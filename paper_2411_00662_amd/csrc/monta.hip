@@ -23,7 +23,7 @@ using namespace monta;
 
 thread_local int g_last_hip = 0;
 std::atomic<int> g_pipeline_mode{-1};  // -1: chosen from the bytes one slice moves
-std::atomic<int> g_plan_mode{-1};      // -1: per-workgroup rebuild when the histogram table is small; 0: always ticketed scan
+std::atomic<int> g_plan_mode{-1};      // -1: per-workgroup rebuild when the histogram table is small; 0: always the scan kernel
 std::atomic<int> g_cache_policy{-1};   // -1: chosen from the working-set size
 
 // The process-wide switches as one entry point saw them when it was called: every decision of that call, and of
@@ -54,6 +54,10 @@ int pow2ceil(int v)
 }
 
 constexpr size_t kRouteLdsBudget = 120 * 1024;
+constexpr int64_t kFewRouteBlocks = 128;
+// Routing and plan with 8192 counters: 73 us if every workgroup reduces them and only 32 workgroups run it (2048 tokens, 256
+// experts), 35 if a kernel scans them; with 256 workgroups 35 and 37.  At 2048 counters the launch costs more than it saves.
+constexpr int64_t kRebuildMax = 4096;
 
 struct Geometry {
     Shape s;
@@ -62,7 +66,7 @@ struct Geometry {
     int64_t row_bytes;
     size_t route_lds;
     int route_threads;   // workgroup size of the route kernel: TB * lanes per token
-    int plan_threads;    // workgroup size of the positions kernels: one lane per token
+    int64_t blocks_by_lds;   // route workgroups if only the LDS limited their tokens
 };
 
 // Per-expert capacity: C = min(T, ceil(cf*T*k/E)), cf = 0 meaning "no drop".
@@ -129,15 +133,20 @@ int validate(const monta_cfg *c, Geometry *g)
     int TB = 256;
     while (TB > 32 && (route_lds_bytes(TB, s.E, s.k) > kRouteLdsBudget || TB / 2 >= s.Tu)) TB >>= 1;
     if (route_lds_bytes(TB, s.E, s.k) > kRouteLdsBudget) return MONTA_ERR_UNSUPPORTED;
+    // ... and no more than leaves every second CU a workgroup (down to one wave of tokens): 8192 tokens, 64 experts, top-8:
+    // 28.5 us for routing and plan in workgroups of 256 tokens, 24.2 in 64; 16384 tokens, 32 experts: 19.1 and 18.2
+    auto blocks = [&](int tb) { return (int64_t)((s.Tu + tb - 1) / tb) * U; };
+    g->blocks_by_lds = blocks(TB);
+    while (TB > kWave && blocks(TB) < kFewRouteBlocks) TB >>= 1;
     s.TB = TB;
     s.bpu = (s.Tu + TB - 1) / TB;
     const int64_t nb = (int64_t)s.bpu * U;
     if (nb * s.E > 0x7fffffffLL) return MONTA_ERR_UNSUPPORTED;
     s.num_blocks = (int32_t)nb;
-    // the per-workgroup rebuild of the scans reads num_blocks*E counters in every workgroup
-    s.fast_plan = (g->modes.plan != 0 && nb * s.E <= 65536) ? 1 : 0;
+    // the per-workgroup rebuild of the scans reads num_blocks*E counters in every workgroup; a larger table is scanned by a
+    // kernel of its own
+    s.fast_plan = (g->modes.plan != 0 && nb * s.E <= kRebuildMax) ? 1 : 0;
     g->route_lds = route_lds_bytes(TB, s.E, s.k);
-    g->plan_threads = TB < kWave ? kWave : TB;
     const int rl = route_lanes_per_token(TB, s.E);
     s.rl = rl;
     g->route_threads = TB * rl < kWave ? kWave : TB * rl;
@@ -571,12 +580,33 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
 int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int32_t *topk_idx, float *gates,
                  hipStream_t st)
 {
-    static LdsOptIn lds_opt_in;
-    if (g.route_lds > 48 * 1024)
-        if (int rc = opt_in_lds(reinterpret_cast<const void *>(route_plan_kernel), (int)kRouteLdsBudget, lds_opt_in)) return rc;
-    ProfScope ps(MONTA_K_ROUTE, st);
-    hipLaunchKernelGGL(route_plan_kernel, dim3(g.s.num_blocks), dim3(g.route_threads), g.route_lds, st, logits,
-                       topk_idx, gates, p, g.s);
+    // a lane's elements in four groups: of 2, 4 or 8
+    const int per_lane = (g.s.E + g.s.rl - 1) / g.s.rl;
+    auto launch = [&](auto lc, auto gs) -> int {
+        constexpr int L = decltype(lc)::value, GS = decltype(gs)::value;
+        static LdsOptIn lds_opt_in;
+        if (g.route_lds > 48 * 1024)
+            if (int rc = opt_in_lds(reinterpret_cast<const void *>(route_plan_kernel<L, GS>), (int)kRouteLdsBudget, lds_opt_in))
+                return rc;
+        ProfScope ps(MONTA_K_ROUTE, st);
+        hipLaunchKernelGGL((route_plan_kernel<L, GS>), dim3(g.s.num_blocks), dim3(g.route_threads), g.route_lds, st, logits,
+                           topk_idx, gates, p, g.s);
+        HIP_TRY(hipGetLastError());
+        return MONTA_OK;
+    };
+    auto with_groups = [&](auto lc) -> int {
+        if (per_lane <= 8) return launch(lc, std::integral_constant<int, 2>{});
+        if (per_lane <= 16) return launch(lc, std::integral_constant<int, 4>{});
+        return launch(lc, std::integral_constant<int, 8>{});
+    };
+    int rc;
+    if (g.s.rl == 1) rc = with_groups(std::integral_constant<int, 1>{});
+    else if (g.s.rl == 2) rc = with_groups(std::integral_constant<int, 2>{});
+    else if (g.s.rl == 4) rc = with_groups(std::integral_constant<int, 4>{});
+    else rc = with_groups(std::integral_constant<int, 8>{});
+    if (rc || g.s.fast_plan) return rc;
+    ProfScope ps(MONTA_K_POSITIONS, st);
+    hipLaunchKernelGGL(block_scan_kernel, dim3((g.s.E + kWave - 1) / kWave), dim3(kScanWaves * kWave), 0, st, p, g.s);
     HIP_TRY(hipGetLastError());
     return MONTA_OK;
 }
@@ -716,13 +746,18 @@ int launch_place(const Geometry &g, const PlanPtrs &p, const void *x, void *stag
     return MONTA_OK;
 }
 
-// Tokens per workgroup of plan_place_kernel, 0 if the kernel does not fit the shape.  The tokens of a workgroup must
-// belong to one route workgroup, and the histogram table must be small enough to be reduced by every workgroup; one round
-// of resident workgroups does that once each, more rows per workgroup keep it at one round.
+// Tokens per workgroup of plan_place_kernel, 0 if the shape is better served (or only served) by the plan and the rows in
+// kernels of their own.  The tokens of a workgroup must belong to one route workgroup; one round of resident workgroups
+// rebuilds the plan once each, more rows per workgroup keep it at one round.
 int plan_place_span(const Geometry &g)
 {
     const Shape &s = g.s;
-    if (!s.fast_plan || (int64_t)s.num_blocks * s.E > 2048) return 0;
+    // A table that every workgroup reduces must be small.  Where the scans are there already the rows' own time decides: a
+    // launch less is worth it for short jobs (2048 tokens x 2 KiB, top-8 of 256: 45.6 -> 39.9 us; 32768 x 512 B, 285 MB: 92.6
+    // -> 85.9), long ones run better in the plain kernel (8192 x 4 KiB, 570 MB: 113.6 -> 116.3).
+    if (s.fast_plan ? (int64_t)s.num_blocks * s.E > 2048
+                    : ((int64_t)s.T + 2 * slice_rows_bound(g, s.S)) * g.row_bytes > (320ll << 20))
+        return 0;
     auto fits = [&](int span) { return span <= s.TB && s.TB % span == 0 && (s.Tu % span == 0 || s.U == 1); };
     int span = kMoverThreads / s.lpr;
     if (!fits(span)) return 0;
@@ -776,10 +811,7 @@ int route_impl(const Geometry &g, const float *logits, int32_t *topk_idx, float 
     PlanPtrs p = plan_ptrs(g, ws);
     if (int rc = launch_route(g, p, logits, topk_idx, gates, st)) return rc;
     ProfScope ps(MONTA_K_POSITIONS, st);
-    if (s.fast_plan)
-        hipLaunchKernelGGL(plan_positions_kernel, dim3(s.num_blocks), dim3(g.plan_threads), 0, st, topk_idx, p, s);
-    else
-        hipLaunchKernelGGL(positions_kernel, dim3((s.T + 255) / 256), dim3(256), 0, st, topk_idx, p, s);
+    hipLaunchKernelGGL(plan_positions_kernel, dim3(s.num_blocks), dim3(kPlanThreads), 0, st, topk_idx, p, s);
     HIP_TRY(hipGetLastError());
     return MONTA_OK;
 }
@@ -1389,7 +1421,9 @@ int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage,
 // kernels.
 
 constexpr size_t kStaticScratchBytes = 16u << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// fewer than 256 route workgroups where there could be fewer than 128 (validate), two tables, at most 256 experts
+constexpr size_t kStaticFinerBytes = 512u << 10;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticFinerBytes];
 
 namespace {
 
@@ -1427,7 +1461,10 @@ int monta_route_dispatch_combine_static(const monta_cfg *cfg, const float *logit
     if (stage == final_ || final_ == out || stage == out || x == out) return MONTA_ERR_INVALID;
     monta_ws_layout L;
     fill_layout(g, &L);
-    if ((size_t)L.ws_bytes > kStaticScratchBytes) return MONTA_ERR_TOO_LARGE;
+    // the limit is on the tables as they are with as few route workgroups as fit: what the finer histograms of small
+    // problems add does not count against it
+    const int64_t finer = 2 * (align_up((int64_t)g.s.num_blocks * g.s.E * 4, 256) - align_up(g.blocks_by_lds * g.s.E * 4, 256));
+    if ((size_t)(L.ws_bytes - finer) > kStaticScratchBytes || finer > (int64_t)kStaticFinerBytes) return MONTA_ERR_TOO_LARGE;
     // event profiling creates events per launch and the two-stream pipeline creates a stream: neither belongs
     // in a call that must not allocate
     if (g_prof_on.load()) return MONTA_ERR_INVALID;

@@ -24,7 +24,7 @@ constexpr int kMoverThreads = 256;   // threads per workgroup of the row movers
 constexpr int kVecInFlight = 4;      // 16-byte loads issued by a lane before its first store
 
 // meta[] slots (int32)
-enum { META_R = 0, META_ALIVE = 1, META_C = 2, META_DONE = 3, META_FINAL_ROWS = 4, META_SLOTS = 16 };
+enum { META_R = 0, META_ALIVE = 1, META_C = 2, META_FINAL_ROWS = 4, META_SLOTS = 16 };
 
 struct PlanPtrs {
     int32_t *meta, *counts, *kept, *offsets, *n, *stage_off, *unit_base, *send_rows, *unit_rows;
@@ -44,7 +44,7 @@ struct Shape {
     int32_t cache;     // CachePolicy bits: which streams of the movers use non-temporal accesses
     int32_t padded;    // 1: FINAL is [E][C][H] (expert e at row e*C), 0: compact
     int32_t rl;        // lanes that share one token in the route kernel (1, 2, 4 or 8)
-    int32_t fast_plan; // 1: plan_positions_kernel rebuilds the scans per workgroup; 0: ticketed scan + positions_kernel
+    int32_t fast_plan; // 1: every workgroup reduces the histogram table; 0: block_scan_kernel scans it first
 };
 
 // A set bit makes that stream non-temporal (streaming, no reuse expected); a clear bit leaves
@@ -112,26 +112,37 @@ __host__ __device__ inline int route_row_stride(int E, int L) { return L * (((E 
 
 // One workgroup routes TB consecutive tokens of ONE unit; s.rl lanes share a token (1 for few experts).
 //  1. the [nt][E] logits tile is staged in LDS (coalesced, odd row stride);
-//  2. k selection passes per token over its LDS row: the next winner is the largest
-//     element that comes after the previous winner in (value desc, index asc) order,
-//     so ties resolve to the lower index with no "taken" mask; with s.rl > 1 each lane
-//     scans every s.rl-th expert and the lanes of a token agree by xor-shuffles;
+//  2. k selections per token: the next winner is the largest element that comes after the previous winner in (value
+//     desc, index asc) order, so ties resolve to the lower index with no "taken" mask.  Lane `sub` of a token has every
+//     s.rl-th expert, in four groups of at most GS consecutive ones, and keeps the best remaining element of each group:
+//     only the group that the last winner came from has to be scanned again.  The lanes of a token agree by xor-shuffles.
 //  3. gates in fp64 from the winners' logits, one rounding to fp32;
 //  4. every lane ORs its bit into mask[expert][wave] in LDS; popcounts of those
 //     masks give the workgroup's expert histogram and each pair's stable rank inside
-//     the workgroup (lanes hold consecutive tokens, so bit order is token order);
-//  5. (only when s.fast_plan == 0) the last workgroup to finish (ticket counter)
-//     turns the per-workgroup histograms into every plan table: exclusive scans
-//     over workgroups per expert, capacity clip, expert offsets, per-unit block
-//     tables.  With s.fast_plan == 1 plan_positions_kernel does that instead.
+//     the workgroup (lanes hold consecutive tokens, so bit order is token order).
 // No atomics decide a position: the result is deterministic.
+// What bounds it is the selection's instructions (and, for renorm = 0, E fp64 exponentials per token).  Measured with k whole
+// scans per token and one load at a time: 65536 tokens, 64 experts, top-8 31 us, now 20; 32768 tokens, 256 experts, top-8
+// about 65, now 27.
+//
+// The lanes of a token (L = s.rl of them, 1, 2, 4 or 8, neighbours in the wave) agree through DPP moves: quads by
+// permutation, the two quads of eight lanes by the half-row mirror, whose lanes hold the same pair by then.
+template <int MASK>
+__device__ __forceinline__ int xor_lanes(int v)
+{
+    static_assert(MASK == 1 || MASK == 2 || MASK == 4, "xor_lanes: lanes of one token");
+    constexpr int kCtrl = MASK == 1 ? 0xb1 : MASK == 2 ? 0x4e : 0x141;
+    return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, false);
+}
+
+template <int L, int GS>
 __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restrict__ logits,
                                                          int32_t *__restrict__ topk_idx,
                                                          float *__restrict__ gates, PlanPtrs p, Shape s)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int E = s.E, k = s.k, TB = s.TB;
-    const int stride = route_row_stride(E, s.rl);
+    const int stride = route_row_stride(E, L);
     const int NW = TB > kWave ? TB / kWave : 1;
     float *s_l = reinterpret_cast<float *>(smem);
     int *s_sel = reinterpret_cast<int *>(s_l + (size_t)TB * stride);
@@ -139,11 +150,8 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
         smem + (((size_t)TB * stride * 4 + (size_t)TB * k * 4 + 7) & ~(size_t)7));
     double *s_w = reinterpret_cast<double *>(s_mask + (size_t)E * NW);     // [TB][k] unnormalised weights
     double *s_den = s_w + (size_t)TB * k;                                  // [TB] softmax denominators (renorm = 0)
-    __shared__ int s_last;
-    __shared__ int s_cnt[256];
-    __shared__ int s_off[257];
 
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const int u = b / s.bpu, ib = b - u * s.bpu;
     const int t_begin = u * s.Tu + ib * TB;
@@ -154,18 +162,31 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
     {
         const float *src = logits + (size_t)t_begin * E;
         const int total = nt * E;
-        for (int i = tid; i < total; i += blockDim.x) {
-            float v = src[i];
-            if (v != v) v = -INFINITY;
-            const int tok = i / E;
-            s_l[tok * stride + (i - tok * E)] = v;
+        // element i is column i % E of token i / E: one division, then steps.  Eight loads are requested before the first is
+        // laid down: one at a time the tile arrives at one memory latency per element of a lane.
+        constexpr int LD = 8;
+        const int nthr = blockDim.x, step_tok = nthr / E, step_col = nthr % E;
+        int tok = tid / E, col = tid % E;
+        for (int i0 = tid; i0 < total; i0 += LD * nthr) {
+            float v[LD];
+#pragma unroll
+            for (int q = 0; q < LD; ++q) v[q] = src[i0 + q * nthr < total ? i0 + q * nthr : i0];
+#pragma unroll
+            for (int q = 0; q < LD; ++q) {
+                if (i0 + q * nthr < total) s_l[tok * stride + col] = v[q] != v[q] ? -INFINITY : v[q];
+                tok += step_tok;
+                col += step_col;
+                if (col >= E) {
+                    col -= E;
+                    ++tok;
+                }
+            }
         }
     }
     __syncthreads();
 
-    // token handled by this lane, and which of the token's s.rl lanes it is
-    const int L = s.rl;
-    const int tok = tid / L, sub = tid - tok * L;
+    // token handled by this lane, and which of the token's L lanes it is
+    const int tok = tid / L, sub = tid % L;
     const int tword = tok >> 6;                     // mask word and bit of the token inside the workgroup
     const unsigned long long tbit = 1ull << (tok & 63);
     const int t = t_begin + tok;
@@ -175,31 +196,58 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
         int *sel = s_sel + tok * k;
         float pv = INFINITY, top_logit = 0.f;
         int pi = -1;
+        // best element after (pv, pi) among this lane's elements g * GS .. g * GS + GS - 1
+        auto scan = [&](int g, float &bv, int &best) {
+            float v[GS];
+#pragma unroll
+            for (int q = 0; q < GS; ++q) {          // independent LDS reads
+                const int e = sub + (g * GS + q) * L;
+                v[q] = row[e < E ? e : E - 1];
+            }
+            best = -1;
+            bv = 0.f;
+#pragma unroll
+            for (int q = 0; q < GS; ++q) {
+                const int e = sub + (g * GS + q) * L;
+                const bool after_prev = (v[q] < pv) || (v[q] == pv && e > pi);
+                if (e < E && after_prev && (best < 0 || v[q] > bv)) { best = e; bv = v[q]; }
+            }
+        };
+        float gv[4];
+        int gi[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) scan(g, gv[g], gi[g]);
         for (int j = 0; j < k; ++j) {
             int best = -1;
             float bv = 0.f;
-            auto consider = [&](int e, float v) {
-                const bool after_prev = (v < pv) || (v == pv && e > pi);
-                if (after_prev && (best < 0 || v > bv)) { best = e; bv = v; }
-            };
-            int e = sub;
-            for (; e + 7 * L < E; e += 8 * L) {     // eight independent LDS reads in flight per step
-                float v[8];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = row[e + q * L];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) consider(e + q * L, v[q]);
-            }
-            for (; e < E; e += L) consider(e, row[e]);
-            for (int mk = 1; mk < L; mk <<= 1) {    // the token's lanes agree on (value desc, index asc)
-                const float ov = __shfl_xor(bv, mk, kWave);
-                const int oi = __shfl_xor(best, mk, kWave);
+            for (int g = 0; g < 4; ++g)
+                if (gi[g] >= 0 && (best < 0 || gv[g] > bv)) { best = gi[g]; bv = gv[g]; }
+            auto agree = [&](auto mask) {           // on (value desc, index asc)
+                const float ov = __int_as_float(xor_lanes<decltype(mask)::value>(__float_as_int(bv)));
+                const int oi = xor_lanes<decltype(mask)::value>(best);
                 if (oi >= 0 && (best < 0 || ov > bv || (ov == bv && oi < best))) { best = oi; bv = ov; }
-            }
+            };
+            if constexpr (L > 1) agree(std::integral_constant<int, 1>{});
+            if constexpr (L > 2) agree(std::integral_constant<int, 2>{});
+            if constexpr (L > 4) agree(std::integral_constant<int, 4>{});
             if (best < 0) best = (pi + 1 < E) ? pi + 1 : E - 1;   // unreachable for k <= E; keeps indices in range
             pv = bv;
             pi = best;
             if (j == 0) top_logit = bv;
+            if (j + 1 < k) {
+                // the group of the winner, if it is this lane's, has lost its best element; groups of other lanes' winners
+                // are scanned in vain
+                const int g = (best / L) / GS;
+                float nv;
+                int ni;
+                scan(g, nv, ni);
+                if (best % L == sub) {
+#pragma unroll
+                    for (int o = 0; o < 4; ++o)
+                        if (o == g) { gv[o] = nv; gi[o] = ni; }
+                }
+            }
             if (sub == 0) {
                 sel[j] = best;
                 topk_idx[(size_t)t * k + j] = best;
@@ -255,130 +303,49 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
     }
 
     if (b == 0 && tid == 0) p.meta[META_ALIVE] = 0;   // counted by the kernel that finishes the positions
-    if (s.fast_plan) return;
-
-    // ---- ticket: the last workgroup builds the tables
-    __threadfence();
-    __syncthreads();
-    if (tid == 0) s_last = (atomicAdd(&p.meta[META_DONE], 1) == s.num_blocks - 1);
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-
-    const int nblk = s.num_blocks;
-    const int nwaves = blockDim.x >> 6;
-    const int C = s.C;
-    // A: per expert, exclusive scan of the workgroup histograms in workgroup (= token) order
-    for (int e = wave; e < E; e += nwaves) {
-        int carry = 0;
-        for (int b0 = 0; b0 < nblk; b0 += kWave) {
-            const int bb = b0 + lane;
-            const int v = bb < nblk ? p.block_counts[(size_t)bb * E + e] : 0;
-            const int incl = wave_inclusive_scan(v, lane);
-            if (bb < nblk) p.block_base[(size_t)bb * E + e] = carry + incl - v;
-            carry += __shfl(incl, kWave - 1, kWave);
-        }
-        if (lane == 0) s_cnt[e] = carry;
-    }
-    __syncthreads();
-    // B: capacity clip and expert offsets (expert order = (EP rank, local expert) order)
-    if (wave == 0) {
-        int carry = 0;
-        for (int e0 = 0; e0 < E; e0 += kWave) {
-            const int e = e0 + lane;
-            const int cnt = e < E ? s_cnt[e] : 0;
-            const int kp = cnt < C ? cnt : C;
-            const int incl = wave_inclusive_scan(kp, lane);
-            if (e < E) {
-                const int off = s.padded ? e * C : carry + incl - kp;
-                p.counts[e] = cnt;
-                p.kept[e] = kp;
-                p.kept_prefix[e] = carry + incl - kp;
-                p.offsets[e] = off;
-                s_off[e] = off;
-            }
-            carry += __shfl(incl, kWave - 1, kWave);
-        }
-        if (lane == 0) {
-            p.kept_prefix[E] = carry;
-            p.offsets[E] = s.padded ? E * C : carry;
-            p.meta[META_FINAL_ROWS] = s.padded ? E * C : carry;
-            p.meta[META_R] = carry;
-            p.meta[META_C] = C;
-        }
-    }
-    __syncthreads();
-    // C: per (unit, expert) block sizes and FINAL bases
-    const int UE = s.U * E;
-    for (int i = tid; i < UE; i += blockDim.x) {
-        const int uu = i / E, e = i - uu * E;
-        const int base = p.block_base[(size_t)uu * s.bpu * E + e];
-        const int next = (uu + 1 < s.U) ? p.block_base[(size_t)(uu + 1) * s.bpu * E + e] : s_cnt[e];
-        const int lo = base < C ? base : C, hi = next < C ? next : C;
-        p.n[i] = hi - lo;
-        p.unit_base[i] = s_off[e] + lo;
-    }
-    __syncthreads();
-    // D: STAGE block offsets = exclusive scan of n in (unit, expert) order; unit starts; per-destination rows
-    if (wave == 0) {
-        int carry = 0;
-        for (int i0 = 0; i0 < UE; i0 += kWave) {
-            const int i = i0 + lane;
-            const int v = i < UE ? p.n[i] : 0;
-            const int incl = wave_inclusive_scan(v, lane);
-            if (i < UE) {
-                const int off = carry + incl - v;
-                p.stage_off[i] = off;
-                if (i % E == 0) p.unit_rows[i / E] = off;
-            }
-            carry += __shfl(incl, kWave - 1, kWave);
-        }
-        if (lane == 0) p.unit_rows[s.U] = carry;
-    }
-    const int E_loc = E / s.ep;
-    for (int i = tid; i < s.U * s.ep; i += blockDim.x) {
-        const int uu = i / s.ep, d = i - uu * s.ep;
-        int sum = 0;
-        for (int el = 0; el < E_loc; ++el) sum += p.n[uu * E + d * E_loc + el];
-        p.send_rows[i] = sum;
-    }
-    if (tid == 0) p.meta[META_DONE] = 0;   // ready for the next call
 }
 
-// Finishes the plan: one lane per token turns (rank inside workgroup, workgroup base)
-// into the global stable rank, applies the capacity and writes the pair's rows in
-// FINAL and STAGE plus the STAGE->FINAL row map used by the regather copy.
-__global__ __launch_bounds__(256) void positions_kernel(const int32_t *__restrict__ topk_idx, PlanPtrs p, Shape s)
+// Exclusive scans of the route workgroups' histograms, per expert, in workgroup (= token) order, for tables that are too
+// large for every workgroup of the next kernel to reduce: block_base[b][e] = pairs of e in workgroups before b, and
+// counts[e].  A workgroup takes 64 experts, one per lane, so that a wave reads whole lines; its 16 waves take a run of rows
+// each, sum it, and walk it again with the sum of the runs before.  Up to 16 loads in flight per lane: the table sits in
+// the L2, and one load at a time the scan would be a chain of round trips (a scan by the last route workgroup to finish,
+// expert by expert, took 270 us on a table of 512 x 256; this takes 7).
+constexpr int kScanWaves = 16;
+__global__ __launch_bounds__(kScanWaves * kWave) void block_scan_kernel(PlanPtrs p, Shape s)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    bool any = false;
-    if (t < s.T) {
-        const int E = s.E, k = s.k;
-        const int u = t / s.Tu;
-        const int b = u * s.bpu + (t - u * s.Tu) / s.TB;
-        const int32_t *bb = p.block_base + (size_t)b * E;
-        const int32_t *ub = p.block_base + (size_t)u * s.bpu * E;
-        for (int j = 0; j < k; ++j) {
-            const int e = topk_idx[(size_t)t * k + j];
-            const int r = bb[e] + p.local_rank[(size_t)t * k + j];
-            int pf = -1, ps = -1;
-            if (r < s.C) {
-                pf = p.offsets[e] + r;
-                ps = p.stage_off[u * E + e] + (r - ub[e]);
-                // always true for tables built by route_plan_kernel; guards a workspace that was never initialised
-                if ((unsigned)pf < (unsigned)s.max_rows && (unsigned)ps < (unsigned)s.max_rows) {
-                    p.row_map[ps] = pf;
-                    any = true;
-                } else {
-                    pf = ps = -1;
-                }
-            }
-            p.pos_final[(size_t)t * k + j] = pf;
-            p.pos_stage[(size_t)t * k + j] = ps;
+    constexpr int LD = 16;
+    __shared__ int s_sum[kScanWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int E = s.E, nb = s.num_blocks, e = blockIdx.x * kWave + lane;
+    const bool on = e < E;
+    const int run = (nb + kScanWaves - 1) / kScanWaves;
+    const int lo = min(wave * run, nb), hi = min(lo + run, nb);
+    auto load = [&](int b0, int (&c)[LD]) {
+#pragma unroll
+        for (int q = 0; q < LD; ++q) c[q] = on && b0 + q < hi ? p.block_counts[(size_t)(b0 + q) * E + e] : 0;
+    };
+    int sum = 0;
+    for (int b0 = lo; b0 < hi; b0 += LD) {
+        int c[LD];
+        load(b0, c);
+#pragma unroll
+        for (int q = 0; q < LD; ++q) sum += c[q];
+    }
+    s_sum[wave][lane] = sum;
+    __syncthreads();
+    int before = 0;
+    for (int v = 0; v < wave; ++v) before += s_sum[v][lane];
+    if (wave == kScanWaves - 1 && on) p.counts[e] = before + sum;
+    for (int b0 = lo; b0 < hi; b0 += LD) {
+        int c[LD];
+        load(b0, c);
+#pragma unroll
+        for (int q = 0; q < LD; ++q) {
+            if (on && b0 + q < hi) p.block_base[(size_t)(b0 + q) * E + e] = before;
+            before += c[q];
         }
     }
-    const unsigned long long m = __ballot(any);
-    if ((threadIdx.x & (kWave - 1)) == 0 && m) atomicAdd(&p.meta[META_ALIVE], __popcll(m));
 }
 
 // Shared-memory result of rebuilding the scans for one route workgroup b (see block_plan).
@@ -426,21 +393,30 @@ __device__ __forceinline__ BlockSums sum_blocks(const int32_t *__restrict__ bloc
     return a;
 }
 
-// Every workgroup that calls this re-reads the whole [num_blocks][E] histogram table (a few KiB,
-// L2 resident) and reduces it to four sums per expert; two wave scans over the experts then give
+// With a small table every workgroup that calls this re-reads the whole [num_blocks][E] histogram table (a few KiB,
+// L2 resident) and reduces it to four sums per expert; with a large one (s.fast_plan = 0) block_scan_kernel has left the
+// scans, and the sums are four rows of them.  Two wave scans over the experts then give
 // the expert offsets and the unit's STAGE block offsets, using the telescoped form
 //   sum_{u' < u} n[u'][e] = min(P[u][e], C),  P[u][e] = pairs of e before unit u,
-// so no table over all units is needed.  There is no serial tail and no ticket; the price is the
-// redundant table read.  All threads of the workgroup must call it; it ends with a barrier.
+// so no table over all units is needed and there is no serial tail.  All threads of the workgroup must call it; it ends with a barrier.
 __device__ __forceinline__ void block_plan(BlockPlan &bp, int b, const PlanPtrs &p, const Shape &s)
 {
     const int E = s.E, C = s.C;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int u = b / s.bpu;
-    for (int e = tid; e < E; e += blockDim.x)
-        bp.before[e] = bp.unit[e] = bp.pre[e] = bp.total[e] = 0;
-    __syncthreads();
-    {
+    if (!s.fast_plan) {
+        const int first = u * s.bpu, last = first + s.bpu;
+        for (int e = tid; e < E; e += blockDim.x) {
+            const int total = p.counts[e], before = p.block_base[(size_t)first * E + e];
+            bp.total[e] = total;
+            bp.before[e] = before;
+            bp.unit[e] = (last < s.num_blocks ? p.block_base[(size_t)last * E + e] : total) - before;
+            bp.pre[e] = p.block_base[(size_t)b * E + e] - before;
+        }
+    } else {
+        for (int e = tid; e < E; e += blockDim.x)
+            bp.before[e] = bp.unit[e] = bp.pre[e] = bp.total[e] = 0;
+        __syncthreads();
         const int total = s.num_blocks * E;
         const int first = u * s.bpu, last = first + s.bpu;     // blocks of this unit: [first, last)
         const int nthr = blockDim.x;
@@ -527,7 +503,7 @@ __device__ __forceinline__ bool place_pair(const BlockPlan &bp, const Shape &s, 
     return false;
 }
 
-// Plan + positions in one pass, for problems whose histogram table is small: workgroup b owns the
+// Plan + positions in one pass: workgroup b owns the
 // tokens of route workgroup b, rebuilds the scans (block_plan) and writes its tokens' positions.
 // The first workgroup of each unit writes that unit's rows of the public tables; workgroup 0
 // writes the per-expert ones.
@@ -569,7 +545,7 @@ __device__ __forceinline__ void plan_positions_block(BlockPlan &bp, int b, const
             p.unit_base[u * E + e] = bp.off[e] + lo;
         }
         if (b == 0) {
-            p.counts[e] = bp.total[e];
+            if (s.fast_plan) p.counts[e] = bp.total[e];      // else written by the scan
             p.kept[e] = bp.total[e] < C ? bp.total[e] : C;
             p.offsets[e] = bp.off[e];
             p.kept_prefix[e] = bp.kpre[e];
@@ -620,15 +596,21 @@ __device__ __forceinline__ void plan_positions_block(BlockPlan &bp, int b, const
     }
     for (int idx = tid + PRE * nthr; idx < npairs; idx += nthr) place(idx, topk_idx[pair0 + idx], p.local_rank[pair0 + idx]);
     __syncthreads();
-    // tokens with a kept pair
-    for (int i0 = 0; i0 < nt; i0 += nthr) {
-        const int i = i0 + tid;
-        const unsigned long long m = __ballot(i < nt && bp.alive[i] != 0);
-        if (lane == 0 && m) atomicAdd(&p.meta[META_ALIVE], __popcll(m));
+    // tokens with a kept pair: one addition to the shared counter per workgroup (one per wave makes a queue at the L2)
+    int mine = 0;
+    for (int i = tid; i < nt; i += nthr) mine += bp.alive[i];
+    if (tid < kWave) bp.total[tid] = 0;                          // the plan's sums are no longer needed
+    __syncthreads();
+    if (mine) atomicAdd(&bp.total[lane], mine);
+    __syncthreads();
+    if (tid < kWave) {
+        const int sum = __shfl(wave_inclusive_scan(bp.total[lane], lane), kWave - 1, kWave);
+        if (lane == 0 && sum) atomicAdd(&p.meta[META_ALIVE], sum);
     }
 }
 
-__global__ __launch_bounds__(256) void plan_positions_kernel(const int32_t *__restrict__ topk_idx, PlanPtrs p, Shape s)
+constexpr int kPlanThreads = 256;
+__global__ __launch_bounds__(kPlanThreads) void plan_positions_kernel(const int32_t *__restrict__ topk_idx, PlanPtrs p, Shape s)
 {
     __shared__ BlockPlan bp;
     plan_positions_block(bp, blockIdx.x, topk_idx, p, s);
