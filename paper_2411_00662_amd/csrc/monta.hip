@@ -498,6 +498,29 @@ int launch_gate_small_any(const u32x4 *x, const u32x4 *w, float *logits, int64_t
     return 1;
 }
 
+template <int XR, int WR, int NST>
+int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
+{
+    using G = ShortTile<XR, WR, NST>;
+    static LdsOptIn lds_opt_in;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_short_kernel<XR, WR, NST>), G::kLdsBytes, lds_opt_in)) return rc;
+    const int64_t grid = (T + XR - 1) / XR * ((E + WR - 1) / WR);
+    if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E);
+    return MONTA_OK;
+}
+
+template <bool BF16>
+int launch_gate_split(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int64_t cpr, int E, int nb, hipStream_t st)
+{
+    const int64_t grid = (T + 15) / 16 * ((E + 16 * nb - 1) / (16 * nb));
+    if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+    if (nb == 4) hipLaunchKernelGGL((gate_split_kernel<BF16, 4>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
+    else if (nb == 2) hipLaunchKernelGGL((gate_split_kernel<BF16, 2>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
+    else hipLaunchKernelGGL((gate_split_kernel<BF16, 1>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
+    return MONTA_OK;
+}
+
 template <bool RAGGED_LAST>
 int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, unsigned grid, hipStream_t st)
 {
@@ -996,13 +1019,25 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
     ProfScope ps(MONTA_K_GATE, st);
     if (cfg->dtype == MONTA_BF16) {
         // validate() guarantees H % 8 == 0 (rows are whole 16-byte vectors) and E <= 256 (at most 8 tiles).
-        // Few token tiles: one workgroup per CU with a deep step; many: shallower steps, several workgroups per CU.
+        // Few tiles of 16 tokens x 16 experts: the hidden axis is split, too.  Up to some ten thousand tokens: tiles as small
+        // as leave at most two workgroups per CU (2.0 tiles of 32 x 64: 43 us for 8192 x 7168, 128 experts, 46 with 32 x 128;
+        // at 4 per CU 62 against 36, 8192 x 4096, 256 experts), except where a tile of the k-split form holds all experts
+        // and the tokens are few (4096 x 4096, 64 experts: 21 and 22 us; 3072 tokens: 18 and 22).
+        // Otherwise, few token tiles: one workgroup per CU with a deep step; many: shallower steps, several workgroups per CU.
         const int64_t tiles32 = (T + 31) / 32;
         const u32x4 *xv = static_cast<const u32x4 *>(x), *wv = static_cast<const u32x4 *>(w_gate);
         rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
+        const int64_t tiles16 = (T + 15) / 16 * ((E + 15) / 16);
+        auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
+        const bool whole_steps = H % 64 == 0 && H <= kBigMaxHidden && tiles32 < 1024 && !(E > 32 && E <= 64 && T <= 4096);
         if (rc <= 0) {
             if (rc) return rc;
         }
+        else if (tiles16 <= 512)
+            rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, E > 16 && tiles16 > 256 ? 2 : 1, st);
+        else if (whole_steps && tiles(32, 64) <= 512) rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
+        else if (whole_steps && tiles(32, 128) <= 512) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
+        else if (whole_steps) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
         else if (E <= 32)
             rc = tiles32 >= 512 ? launch_gate<1, 1, 512, true>(xv, wv, logits, T, H, E, st)
                                 : launch_gate<1, 1, 1024, true>(xv, wv, logits, T, H, E, st);
@@ -1020,8 +1055,11 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
                                  : launch_gate<1, 8, 128, false>(xv, wv, logits, T, H, E, st);
         if (rc) return rc;
     } else {
-        hipLaunchKernelGGL(gate_f32_kernel, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st,
-                           static_cast<const float4 *>(x), static_cast<const float4 *>(w_gate), logits, T, H, E);
+        // 64 experts per workgroup read x a quarter as often, 16 give four times the workgroups
+        const int64_t tiles16 = (T + 15) / 16 * ((E + 15) / 16);
+        rc = launch_gate_split<false>(static_cast<const u32x4 *>(x), static_cast<const u32x4 *>(w_gate), logits, T, H / 4, E,
+                                      E <= 16 || tiles16 <= 256 ? 1 : 4, st);
+        if (rc) return rc;
     }
     HIP_TRY(hipGetLastError());
     return MONTA_OK;

@@ -1802,37 +1802,6 @@ __global__ __launch_bounds__(THREADS) void gate_small_kernel(const u32x4 *__rest
     }
 }
 
-// fp32 activations: one wave per token, eight experts at a time, fp32 fused multiply-adds and a shuffle reduction
-__global__ __launch_bounds__(256) void gate_f32_kernel(const float4 *__restrict__ x, const float4 *__restrict__ w,
-                                                       float *__restrict__ logits, int64_t T, int H, int E)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= T) return;
-    const int vpr = H / 4;
-    const float4 *xr = x + t * vpr;
-    for (int e0 = 0; e0 < E; e0 += 8) {
-        float acc[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-        for (int v = lane; v < vpr; v += 64) {
-            const float4 xv = xr[v];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (e0 + j < E) {
-                    const float4 wv = w[(int64_t)(e0 + j) * vpr + v];
-                    acc[j] = fmaf(xv.x, wv.x, fmaf(xv.y, wv.y, fmaf(xv.z, wv.z, fmaf(xv.w, wv.w, acc[j]))));
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) acc[j] += __shfl_xor(acc[j], off, 64);
-            if (lane == 0 && e0 + j < E) logits[t * E + e0 + j] = acc[j];
-        }
-    }
-}
-
 // ------------------------------------------------------------ expert layer
 //
 // y[r][n] = sum_k x_final[r][k] * w[e][n][k] for the rows r of expert e's range in the expert-major buffer
@@ -2114,15 +2083,17 @@ struct ShortTile {
     static_assert(XR % 32 == 0 && WR % 64 == 0 && NST >= 3 && kYounger < 64, "short tile: shape");
 };
 
-template <int XR, int WR, int NST>
-__device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, unsigned short *__restrict__ y,
-                                                  const ExpertArgs &a, int row0, int row_end, int col0, unsigned char *lds)
+// T: unsigned short, y is rounded to bf16; float, the sums themselves are stored (N columns, any N) and are taken in two
+// levels, 512 elements of the hidden axis at a time, so that a long row costs no precision.
+template <int XR, int WR, int NST, typename T>
+__device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int H,
+                                                  int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds)
 {
     using G = ShortTile<XR, WR, NST>;
     constexpr int RB = XR / 16, CB = WR / 64;                      // 16-row blocks, 16-column blocks of a wave
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 15, g = lane >> 4;
-    const int nsteps = a.H / 64;
-    const uint32_t rowb = (uint32_t)a.H * 2;
+    const int nsteps = H / 64;
+    const uint32_t rowb = (uint32_t)H * 2;
     const int lr = lane >> 3;
     // row of the lane in chunk c: 8 c + lane / 8, so (row / 2) % 8 = (4 c + lr / 2) % 8
     auto offset = [&](int c) { return (uint32_t)(c * 8 + lr) * rowb + (((lane & 7) ^ ((4 * c + (lr >> 1)) & 7)) * 16); };
@@ -2148,44 +2119,74 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     for (int i = 0; i < RB; ++i)
 #pragma unroll
         for (int j = 0; j < CB; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    constexpr bool kLevels = std::is_same<T, float>::value;
+    f32x4 total[kLevels ? RB : 1][kLevels ? CB : 1];
+    if constexpr (kLevels) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < CB; ++j) total[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
     const unsigned char *px = lds + m * 128, *pw = lds + (XR + wave * (WR / 4) + m) * 128;
-    const int nb = (row_end - row0 + 15) / 16;                     // 16-row blocks with rows of the segment
+    const int nb = (int)((row_end - row0 + 15) / 16);              // 16-row blocks with rows of the segment
 
 #pragma unroll
     for (int q = 0; q < NST - 1; ++q) issue(q, q);
     int slot = 0;
-    for (int step = 0; step < nsteps; ++step) {
-        __builtin_amdgcn_s_waitcnt(G::kWait);                      // stage `step` has landed (loads finish in order)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): this wave's reads of the previous stage
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        issue(step + NST - 1, slot == 0 ? NST - 1 : slot - 1);     // the slot of stage step-1, free now
-        const int buf = slot * G::kStageBytes;
+    auto walk = [&](int from, int to) {
+        for (int step = from; step < to; ++step) {
+            __builtin_amdgcn_s_waitcnt(G::kWait);                      // stage `step` has landed (loads finish in order)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): this wave's reads of the previous stage
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            issue(step + NST - 1, slot == 0 ? NST - 1 : slot - 1);     // the slot of stage step-1, free now
+            const int buf = slot * G::kStageBytes;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int ko = ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
-            bf16x8 fw[CB];
+            for (int ks = 0; ks < 2; ++ks) {
+                const int ko = ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
+                bf16x8 fw[CB];
 #pragma unroll
-            for (int j = 0; j < CB; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(pw + buf + ko + j * 2048);
+                for (int j = 0; j < CB; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(pw + buf + ko + j * 2048);
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+                    if (i < nb) {
+                        const bf16x8 fx = *reinterpret_cast<const bf16x8 *>(px + buf + ko + i * 2048);
+#pragma unroll
+                        for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fx, acc[i][j], 0, 0, 0);
+                    }
+            }
+            slot = slot == NST - 1 ? 0 : slot + 1;
+        }
+    };
+    if constexpr (kLevels) {
+        for (int from = 0; from < nsteps; from += 8) {
+            walk(from, min(from + 8, nsteps));
 #pragma unroll
             for (int i = 0; i < RB; ++i)
-                if (i < nb) {
-                    const bf16x8 fx = *reinterpret_cast<const bf16x8 *>(px + buf + ko + i * 2048);
 #pragma unroll
-                    for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fx, acc[i][j], 0, 0, 0);
+                for (int j = 0; j < CB; ++j) {
+                    total[i][j] += acc[i][j];
+                    acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
                 }
         }
-        slot = slot == NST - 1 ? 0 : slot + 1;
+    } else {
+        walk(0, nsteps);
     }
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        const int r = row0 + i * 16 + m;
+        const int64_t r = row0 + i * 16 + m;
         if (r < row_end) {
 #pragma unroll
             for (int j = 0; j < CB; ++j) {
                 const int n = col0 + wave * (WR / 4) + j * 16 + 4 * g;
-                if (n < a.N) *reinterpret_cast<uint2 *>(y + (int64_t)r * a.N + n) = pack_bf16x4(acc[i][j]);
+                if constexpr (std::is_same<T, float>::value) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (n + v < N) y[r * N + n + v] = total[i][j][v];
+                } else {
+                    if (n < N) *reinterpret_cast<uint2 *>(y + r * N + n) = pack_bf16x4(acc[i][j]);
+                }
             }
         }
     }
@@ -2216,8 +2217,8 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
     const uint32_t rowb = (uint32_t)a.H * 2;
     expert_short_tile<XR, WR, NST>(make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb),
-                                   make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb), y, a,
-                                   row0, row_end, col0, short_lds);
+                                   make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb), y, a.H,
+                                   a.N, row0, row_end, col0, short_lds);
 }
 
 template <bool RAGGED_LAST>
@@ -2313,7 +2314,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= 64) {                                                // the loop for tiles with little arithmetic
         static_assert(ShortTile<64, 256, 3>::kLdsBytes <= kBigLdsBytes, "short tile: stages must fit the kernel's LDS");
-        expert_short_tile<64, 256, 3>(rx, rw, y, a, row0, row_end, col0, big_lds);
+        expert_short_tile<64, 256, 3>(rx, rw, y, a.H, a.N, row0, row_end, col0, big_lds);
         return;
     }
 
@@ -2448,6 +2449,133 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     (void)y;
     (void)a;
 #endif
+}
+
+// Gate projection of a few thousand tokens on more than 8 experts: the same tiles, tokens x experts, sums stored as they are.
+// Bound by the trips of x and of the weights through the L2: T E row (1 / XR + 1 / WR) bytes.  Against 32-token workgroups
+// with the k-slices dealt to 8 waves: 16384 x 7168, 256 experts 193 -> 90 us, 8192 x 4096, 256 experts 63 -> 36, 1024 x 7168,
+// 256 experts 92 -> 36, 16384 x 4096, 32 experts 36 -> 25.
+template <int XR, int WR, int NST>
+__global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
+                                                            float *__restrict__ logits, int64_t T, int H, int E)
+{
+    extern __shared__ __align__(16) unsigned char gshort_lds[];
+    const int nct = (E + WR - 1) / WR, cpr = H / 8;
+    const int64_t t0 = (int64_t)(blockIdx.x / nct) * XR;
+    const int e0 = (int)(blockIdx.x % nct) * WR;
+    const int64_t t1 = t0 + XR < T ? t0 + XR : T;
+    const uint32_t rowb = (uint32_t)H * 2;
+    expert_short_tile<XR, WR, NST>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
+                                   make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, H, E, t0, t1, e0,
+                                   gshort_lds);
+}
+
+// Gate projection with the hidden axis split over the 8 waves of a workgroup: 16 tokens x 16 NB experts each.  For fp32
+// activations (16x16x4 fp32 MFMA) and for so few bf16 tokens that a tile's walk along the whole hidden axis is what takes the
+// time.  A wave streams its share straight into registers, D steps of 128 bytes per row ahead; lane l holds 16 bytes of row
+// l % 16, at the same place of x and of w, so which element of the hidden axis meets which MFMA does not matter.  The waves'
+// sums are added through LDS in a fixed order.  Rows past the end repeat the last one and are not stored.  Steps past a
+// wave's share multiply zeros: an MFMA takes no notice of a lane mask, so it may not stand under a condition that the
+// compiler cannot prove uniform.
+// Measured, bf16, workgroups that walk the whole hidden axis before: 64 x 7168, 64 experts 27 -> 16 us; 256 x 4096, 256
+// experts 57 -> 10.  fp32, a wave per token and eight experts at a time before: 8192 x 4096, 8 / 64 experts 48 / 325 -> 26 / 75.
+template <bool BF16, int NB>
+__global__ __launch_bounds__(512) void gate_split_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
+                                                         float *__restrict__ logits, int64_t T, int64_t cpr, int E)
+{
+    constexpr int D = NB == 1 ? 4 : NB == 2 ? 3 : 2, W = 8;
+    __shared__ f32x4 red[W][NB][kWave];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, g = lane >> 4;
+    const int nct = (E + 16 * NB - 1) / (16 * NB);
+    const int64_t t0 = (int64_t)(blockIdx.x / nct) * 16;
+    const int e0 = (int)(blockIdx.x % nct) * 16 * NB;
+    const u32x4 *px = x + (t0 + m < T ? t0 + m : T - 1) * cpr + g;
+    const u32x4 *pw[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) pw[n] = w + (int64_t)(e0 + n * 16 + m < E ? e0 + n * 16 + m : E - 1) * cpr + g;
+
+    // C independent sums per result (by half of the step and, in fp32, by element of a piece): no MFMA waits for the one
+    // before it, and the chains of additions stay short
+    constexpr int C = BF16 ? 2 : 8;
+    f32x4 acc[NB][C];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[n][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](int n, int h, u32x4 fw, u32x4 fx) {
+        if constexpr (BF16) {
+            acc[n][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw), __builtin_bit_cast(bf16x8, fx),
+                                                                acc[n][h], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[n][4 * h + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fw[i]), __uint_as_float(fx[i]),
+                                                                         acc[n][4 * h + i], 0, 0, 0);
+        }
+    };
+    // whole steps: 8 pieces of 16 bytes per row, pieces g and 4 + g for this lane; steps past the wave's share multiply zeros
+    const int nsteps = (int)(cpr / 8), first = (int)((int64_t)nsteps * wave / W), last = (int)((int64_t)nsteps * (wave + 1) / W);
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    u32x4 fx[D][2], fw[D][NB][2];
+    auto fetch = [&](int d, int step) {
+        const int64_t c = (int64_t)min(step, nsteps - 1) * 8;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            fx[d][h] = px[c + 4 * h];
+#pragma unroll
+            for (int n = 0; n < NB; ++n) fw[d][n][h] = pw[n][c + 4 * h];
+        }
+    };
+    if (first < last) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) fetch(d, first + d);
+        for (int s = first; s < last; s += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int n = 0; n < NB; ++n)
+                        mma(n, h, s + d < last ? fw[d][n][h] : zero, s + d < last ? fx[d][h] : zero);
+                fetch(d, s + d + D);
+            }
+        }
+    }
+    if (wave == W - 1 && cpr % 8) {                                // the rest of the row: what lies past it counts as zero
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t c = (int64_t)nsteps * 8 + 4 * h;
+            const bool in = c + g < cpr;
+            const u32x4 vx = in ? px[c] : zero;
+#pragma unroll
+            for (int n = 0; n < NB; ++n) mma(n, h, in ? pw[n][c] : zero, vx);
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+#pragma unroll
+        for (int d = C / 2; d >= 1; d /= 2)
+#pragma unroll
+            for (int c = 0; c < d; ++c) acc[n][c] += acc[n][c + d];
+        red[wave][n][lane] = acc[n][0];
+    }
+    __syncthreads();
+    for (int n = wave; n < NB; n += W) {
+        f32x4 sum[W];
+#pragma unroll
+        for (int v = 0; v < W; ++v) sum[v] = red[v][n][lane];
+#pragma unroll
+        for (int d = W / 2; d >= 1; d /= 2)
+#pragma unroll
+            for (int v = 0; v < d; ++v) sum[v] += sum[v + d];
+        if (t0 + m < T) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int e = e0 + n * 16 + 4 * g + v;
+                if (e < E) logits[(t0 + m) * E + e] = sum[0][v];
+            }
+        }
+    }
 }
 
 // fp32 activations: a 64 x 64 tile of y per workgroup of 4 waves (each 32 x 32, one accumulator of the 32x32x2 fp32 MFMA,

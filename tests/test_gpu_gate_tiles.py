@@ -1,0 +1,43 @@
+"""Gate projection on the edges of its tiles: token, expert and hidden counts around the 16 x 16 tiles with a split hidden
+axis (fewer steps than waves, steps that do not divide among them, rows that end inside a step) and around the larger tiles
+of a few thousand tokens.  Small-integer inputs: every partial sum is an integer below 2^24, so any order of additions gives
+the same fp32 value and the comparison is exact."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from workloads import BF16, FP32
+
+pytestmark = pytest.mark.gpu
+
+SPLIT = [(1, 4, 1), (16, 28, 16), (17, 32, 17), (31, 60, 33), (40, 64, 9), (5, 224, 255), (48, 480, 48), (300, 448, 256), (260, 2044, 10)]
+TILES = [(2049, 64, 80), (4128, 128, 65), (8161, 64, 32), (8192, 192, 129), (16383, 64, 200), (4100, 320, 64), (4097, 64, 16)]
+
+
+def check(T, H, E, dtype):
+    import paper_2411_00662_amd as m
+    from paper_2411_00662_amd import buffers as bufs
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(T + H + E)
+    x = rng.integers(-4, 5, size=(T, H)).astype(np.float32)
+    w = rng.integers(-4, 5, size=(E, H)).astype(np.float32)
+    act = workloads.f32_to_bf16_bits if dtype == BF16 else np.ascontiguousarray
+    cfg = m.make_cfg(T, H, dtype, E, 1, 1, 1, 1, 0.0)
+    out = torch.full((T + 1, E), float("nan"), device="cuda:0")
+    m.monta_gate(cfg, bufs.to_device_act(cfg, act(x)), bufs.to_device_act(cfg, act(w)), out[:T])
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.all(np.isnan(got[T]))
+    np.testing.assert_array_equal(got[:T], (x.astype(np.float64) @ w.astype(np.float64).T).astype(np.float32))
+
+
+@pytest.mark.parametrize("T,H,E", SPLIT + TILES)
+def test_gate_fp32(T, H, E):
+    check(T, H, E, FP32)
+
+
+@pytest.mark.parametrize("T,H,E", [(T, (H + 7) // 8 * 8, E) for T, H, E in SPLIT] + TILES)
+def test_gate_bf16(T, H, E):
+    check(T, H, E, BF16)
