@@ -537,12 +537,13 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, const Exp
     const int64_t row_tiles = (rows_bound + kBigBM - 1) / kBigBM + a.E;      // each expert may end in a ragged tile
     const int64_t nct = (a.N + kBigBN - 1) / kBigBN;
     // whole blocks of 256 workgroups: the kernel hands out tile numbers in such blocks, 32 per XCD
-    const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
-    if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+    auto rounded = [](int64_t n) { return (n + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds); };
+    const int64_t grid = rounded(row_tiles * nct), grid_last = rounded((row_tiles + a.E) * nct);     // ragged tiles may come in halves
+    if (grid_last > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
     // The segments' ragged last tiles go to the end of the numbering only when there are few of them, at most one round
     // of 256 workgroups: measured on MI355X, eight segments of about 2048 rows 464 us against 480 with the ragged tiles in
     // place; 64 segments of 191 rows, where every tile is ragged, 448 against 440.
-    if ((int64_t)a.E * nct <= 256) return launch_expert_big_t<true>(x_final, w_exp, y, a, (unsigned)grid, st);
+    if ((int64_t)a.E * nct <= 256) return launch_expert_big_t<true>(x_final, w_exp, y, a, (unsigned)grid_last, st);
     return launch_expert_big_t<false>(x_final, w_exp, y, a, (unsigned)grid, st);
 }
 

@@ -2048,6 +2048,7 @@ __global__ __launch_bounds__(64 * WM * WN, (64 * WM * WN <= 256 ? 2 : 1)) void e
 // (805 without the early touch); eight uneven segments of about 2048 rows (4.3 rounds of workgroups) 553 -> 448.  What
 // bounds it now: the matrix pipe at the clock the chip holds under this load, and the last round of a launch.
 constexpr int kBigBM = 256, kBigBN = 256, kBigThreads = 256;
+constexpr int kShortRows = 64;                                    // ragged tiles up to this many rows run as short tiles
 constexpr int kBigStageBytes = (kBigBM + kBigBN) * 128;
 constexpr int kBigLdsBytes = 2 * kBigStageBytes + 2048;           // two stages, and 512 bytes per wave for the early touches
 
@@ -2270,6 +2271,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     } else if (RAGGED_LAST) {
         // ragged tiles: position L / nct in the order (rows in the ragged tile, descending; expert, ascending).  The
         // tile buffers are not in use yet, so their first bytes serve as the scratch of the ranking (E <= 256).
+        // Those of at most 64 rows, the last ones, are split into halves of 128 columns: they last as long as their weights
+        // take to arrive, and twice the workgroups have twice the loads on their way.
         const int64_t Lr = L - whole;
         int *scr = reinterpret_cast<int *>(big_lds);
         int my_rem = 0;
@@ -2280,21 +2283,21 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         }
         if (tid == 0) scr[256] = -1;
         __syncthreads();
-        if (my_rem > 0) {
-            int rank = 0;
-            for (int o = 0; o < a.E; ++o) {
-                const int ro = scr[o];
-                rank += (ro > my_rem || (ro == my_rem && o < tid)) ? 1 : 0;
-            }
-            if (rank == Lr / nct) scr[256] = tid;
+        int rank = 0, long_ones = 0;
+        for (int o = 0; o < a.E; ++o) {
+            const int ro = scr[o];
+            long_ones += ro > kShortRows ? 1 : 0;
+            rank += (ro > my_rem || (ro == my_rem && o < tid)) ? 1 : 0;
         }
+        const int64_t halves = Lr - (int64_t)long_ones * nct;      // number among the half tiles
+        if (my_rem > 0 && rank == (halves < 0 ? Lr / nct : long_ones + halves / (2 * nct))) scr[256] = tid;
         __syncthreads();
         const int eh = scr[256];
         __syncthreads();                                           // everyone has read it before the tiles stream in
         if (eh >= 0 && eh < a.E) {
             e = eh;
             const int lo = a.lo[e], hi = a.hi_base[e] + (a.hi_len ? a.hi_len[e] : 0);
-            ct = (int)(Lr % nct);
+            ct = (int)(halves < 0 ? Lr % nct : halves % (2 * nct));
             row0 = lo + (int)(((int64_t)hi - lo) / BM) * BM;
             row_end = hi < a.max_rows ? hi : a.max_rows;
         }
@@ -2307,14 +2310,17 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     share = __builtin_amdgcn_readfirstlane(share);
     ct = __builtin_amdgcn_readfirstlane(ct);
     if (e >= a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup
-    const int col0 = ct * BN;
+    constexpr int kShortCols = RAGGED_LAST ? 128 : 256, kStages = RAGGED_LAST ? 5 : 3;
+    static_assert(ShortTile<64, kShortCols, kStages>::kLdsBytes <= kBigLdsBytes, "short tile: stages must fit the kernel's LDS");
+    const int xr = min(row_end - row0, BM);
+    const int cols = xr <= kShortRows ? kShortCols : BN, col0 = ct * cols;
+    if (col0 >= a.N) return;                                       // the second half of a last column tile may be empty
     const uint32_t rowb = (uint32_t)a.H * 2;
-    const int xr = min(row_end - row0, BM), wr = min(a.N - col0, BN);
+    const int wr = min(a.N - col0, cols);
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
-    if (xr <= 64) {                                                // the loop for tiles with little arithmetic
-        static_assert(ShortTile<64, 256, 3>::kLdsBytes <= kBigLdsBytes, "short tile: stages must fit the kernel's LDS");
-        expert_short_tile<64, 256, 3>(rx, rw, y, a.H, a.N, row0, row_end, col0, big_lds);
+    if (xr <= kShortRows) {                                        // tiles with little arithmetic
+        expert_short_tile<64, kShortCols, kStages>(rx, rw, y, a.H, a.N, row0, row_end, col0, big_lds);
         return;
     }
 
