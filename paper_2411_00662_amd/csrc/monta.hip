@@ -521,18 +521,20 @@ int launch_gate_split(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     return MONTA_OK;
 }
 
-template <bool RAGGED_LAST>
-int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, unsigned grid, hipStream_t st)
+template <bool RAGGED_LAST, bool DEEP_W>
+int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t grid, hipStream_t st)
 {
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_big_kernel<RAGGED_LAST>), kBigLdsBytes, lds_opt_in)) return rc;
-    hipLaunchKernelGGL(expert_big_kernel<RAGGED_LAST>, dim3(grid), dim3(kBigThreads), kBigLdsBytes, st,
+    constexpr int lds = big_lds_bytes(DEEP_W);
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_big_kernel<RAGGED_LAST, DEEP_W>), lds, lds_opt_in)) return rc;
+    hipLaunchKernelGGL((expert_big_kernel<RAGGED_LAST, DEEP_W>), dim3((unsigned)grid), dim3(kBigThreads), lds, st,
                        static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
                        static_cast<unsigned short *>(y), a);
     return MONTA_OK;
 }
 
-int launch_expert_big(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, hipStream_t st)
+int launch_expert_big(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
+                      int64_t rows_per_expert, hipStream_t st)
 {
     const int64_t row_tiles = (rows_bound + kBigBM - 1) / kBigBM + a.E;      // each expert may end in a ragged tile
     const int64_t nct = (a.N + kBigBN - 1) / kBigBN;
@@ -543,8 +545,11 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, const Exp
     // The segments' ragged last tiles go to the end of the numbering only when there are few of them, at most one round
     // of 256 workgroups: measured on MI355X, eight segments of about 2048 rows 464 us against 480 with the ragged tiles in
     // place; 64 segments of 191 rows, where every tile is ragged, 448 against 440.
-    if ((int64_t)a.E * nct <= 256) return launch_expert_big_t<true>(x_final, w_exp, y, a, (unsigned)grid_last, st);
-    return launch_expert_big_t<false>(x_final, w_exp, y, a, (unsigned)grid, st);
+    const bool ragged_last = (int64_t)a.E * nct <= 256, deep_w = rows_per_expert <= kBigBM;
+    if (ragged_last) return deep_w ? launch_expert_big_t<true, true>(x_final, w_exp, y, a, grid_last, st)
+                                   : launch_expert_big_t<true, false>(x_final, w_exp, y, a, grid_last, st);
+    return deep_w ? launch_expert_big_t<false, true>(x_final, w_exp, y, a, grid, st)
+                  : launch_expert_big_t<false, false>(x_final, w_exp, y, a, grid, st);
 }
 
 template <int XR, int WR, int NST>
@@ -580,7 +585,7 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
     constexpr int64_t kFewTiles = 640;
     if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 56 || tiles(64, 128) <= kFewTiles) return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
-    return launch_expert_big(x_final, w_exp, y, a, rows_bound, st);
+    return launch_expert_big(x_final, w_exp, y, a, rows_bound, r, st);
 }
 
 template <int BM, int BN, int WM, int WN>
@@ -682,13 +687,14 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
         a.hi_base = p.offsets;
         a.hi_len = p.kept;
     }
-    // worst case of the rows in play: every pair of the slice's tokens kept
-    int64_t rows_bound = slice < 0 ? (int64_t)s.max_rows : std::min<int64_t>(s.max_rows, (int64_t)(s.T / s.S) * s.k);
+    // worst case of the rows in play: every pair of the slice's tokens kept, as far as the capacity lets them (the rows of a
+    // padded layout beyond them are never multiplied)
+    const int64_t kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
+    const int64_t rows_bound = slice < 0 ? kept_bound : std::min<int64_t>(kept_bound, (int64_t)(s.T / s.S) * s.k);
     ProfScope ps(MONTA_K_EXPERT, st);
     if (cfg->dtype == MONTA_BF16) {
         // The direct-to-LDS kernels take whole 64-element steps.  The choice of tile looks at the whole problem, not at the
         // slice, so that a slice runs as the whole would.
-        const int64_t kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
         if (cfg->hidden % 64 == 0 && cfg->hidden <= kBigMaxHidden)
             rc = launch_expert_tiled(x_final, w_exp, y, a, rows_bound, kept_bound, st);
         else

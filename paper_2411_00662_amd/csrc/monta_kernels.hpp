@@ -2031,11 +2031,15 @@ __global__ __launch_bounds__(64 * WM * WN, (64 * WM * WN <= 256 ? 2 : 1)) void e
 //    per four MFMAs, so no MFMA waits for the LDS.
 //  - Register moves.  Left to itself the compiler rotates the accumulators through copies (about one per MFMA); the MFMA
 //    is therefore written with its accumulator tied in place, and the order of reads, loads and MFMAs is pinned.
-//  - Loads.  A step's tile (256 rows of x, 256 of w, 128 bytes each) goes straight to one of two LDS buffers while the
-//    other is read; the buffer is free once its second slice has been read, so the loads of stage s+2 are issued under the
-//    second slice of stage s and have until the end of the first slice of stage s+1.  That covers an L2 hit but no miss:
-//    each workgroup also touches, one stage ahead, one line per row of its share of the tiles it shares with the other
-//    workgroups on its XCD (its own eighth of a weight tile, its quarter of an x tile), so that misses are taken early.
+//  - Loads.  A step's tile (256 rows of x, 256 of w, 128 bytes each) goes straight to LDS while the stage before it is
+//    multiplied; a stage's buffer is free once its second slice has been read, so the loads of stage s+2 are issued under the
+//    second slice of stage s and have until the end of the first slice of stage s+1.  That covers an L2 hit but no miss.
+//    Where several row tiles share a weight tile (DEEP_W = false) each workgroup also touches, one stage ahead, one line per
+//    row of its share of the tiles it shares with the other workgroups on its XCD (its own eighth of a weight tile, its quarter
+//    of an x tile), so that misses are taken early.  Where a weight tile has one or two users it comes from memory whatever is
+//    done; there the LDS holds a third stage of w instead, whose loads are issued a stage earlier (DEEP_W = true).  Measured,
+//    third stage against touches: 64 experts, 7168 x 2048, 191 rows each 419 and 445 us, 256 rows 593 and 606, 384 rows 764 and
+//    683; 8 experts, 4096 x 4096, 256 rows 114 and 119, 2048 rows 459 and 449.
 // Rows are 128 bytes in LDS without padding; the 16-byte piece c of row r sits at position c ^ ((r / 2) % 8): a fragment
 // read has 16 lanes (16 consecutive rows, one piece each) share the 64 banks, two rows fill them, so the pieces must
 // differ among the even rows and among the odd rows.  The LDS position of a lane's data is fixed by the instruction, so
@@ -2049,8 +2053,9 @@ __global__ __launch_bounds__(64 * WM * WN, (64 * WM * WN <= 256 ? 2 : 1)) void e
 // bounds it now: the matrix pipe at the clock the chip holds under this load, and the last round of a launch.
 constexpr int kBigBM = 256, kBigBN = 256, kBigThreads = 256;
 constexpr int kShortRows = 64;                                    // ragged tiles up to this many rows run as short tiles
-constexpr int kBigStageBytes = (kBigBM + kBigBN) * 128;
-constexpr int kBigLdsBytes = 2 * kBigStageBytes + 2048;           // two stages, and 512 bytes per wave for the early touches
+constexpr int kBigXBytes = kBigBM * 128, kBigWBytes = kBigBN * 128;       // one stage of x, of w
+// two stages of x; of w three, which takes all of a CU's 160 KiB, or two and 512 bytes per wave for the early touches
+constexpr int big_lds_bytes(bool deep_w) { return 2 * kBigXBytes + (deep_w ? 3 * kBigWBytes : 2 * kBigWBytes + 2048); }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes)
 {
@@ -2092,7 +2097,9 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 {
     using G = ShortTile<XR, WR, NST>;
     constexpr int RB = XR / 16, CB = WR / 64;                      // 16-row blocks, 16-column blocks of a wave
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 15, g = lane >> 4;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));      // share nothing with the caller's other path, which has no register left to keep it in
+    const int lane = tid & 63, wave = tid >> 6, m = lane & 15, g = lane >> 4;
     const int nsteps = H / 64;
     const uint32_t rowb = (uint32_t)H * 2;
     const int lr = lane >> 3;
@@ -2222,7 +2229,7 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
                                    a.N, row0, row_end, col0, short_lds);
 }
 
-template <bool RAGGED_LAST>
+template <bool RAGGED_LAST, bool DEEP_W>
 __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                                     unsigned short *__restrict__ y, ExpertArgs a)
 {
@@ -2248,6 +2255,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     int64_t whole = 0;
     const ExpertTileHit hit = RAGGED_LAST ? find_expert_tile<BM, true>(a, nct, L, lane, &whole)
                                           : find_expert_tile<BM, false>(a, nct, L, lane);
+    constexpr int WST = DEEP_W ? 3 : 2;                            // stages of w
+    constexpr int kWaitStage = DEEP_W ? 0x0078 : 0x0072, kWaitFirst = DEEP_W ? 0x4f78 : 0x4f70;       // vmcnt(24), vmcnt(16)
     int e = hit.e, row0 = 0, row_end = 0, ct = 0;
     int sharers = 1, share = 0;                                    // row tiles side by side on one weight tile; which of them
     if (e < a.E) {
@@ -2311,7 +2320,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     ct = __builtin_amdgcn_readfirstlane(ct);
     if (e >= a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup
     constexpr int kShortCols = RAGGED_LAST ? 128 : 256, kStages = RAGGED_LAST ? 5 : 3;
-    static_assert(ShortTile<64, kShortCols, kStages>::kLdsBytes <= kBigLdsBytes, "short tile: stages must fit the kernel's LDS");
+    static_assert(ShortTile<64, kShortCols, kStages>::kLdsBytes <= big_lds_bytes(DEEP_W), "short tile: stages must fit the kernel's LDS");
     const int xr = min(row_end - row0, BM);
     const int cols = xr <= kShortRows ? kShortCols : BN, col0 = ct * cols;
     if (col0 >= a.N) return;                                       // the second half of a last column tile may be empty
@@ -2326,24 +2335,35 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
 
     // A step's tile is 32 + 32 chunks of 8 rows (1 KiB); this wave fetches chunks 8 wave .. 8 wave + 7 of x and of w.
     const int lr = lane >> 3;
-    uint32_t off[8];
+    uint32_t off2[2];                                             // chunks 16 rows apart have the same swizzle
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < 2; ++q) {
         const int trow = (wave * 8 + q) * 8 + lr;
-        off[q] = (uint32_t)trow * rowb + (((lane & 7) ^ ((trow >> 1) & 7)) * 16);
+        off2[q] = (uint32_t)trow * rowb + (((lane & 7) ^ ((trow >> 1) & 7)) * 16);
     }
-    auto issue = [&](int q, bool is_w, int step, int buf) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            is_w ? rw : rx, (lds_void *)(big_lds + buf * kBigStageBytes + (is_w ? BM * 128 : 0) + (wave * 8 + q) * 1024), 16,
-            off[q], step * 128, 0, 0);
+    auto off = [&](int q) {
+        uint32_t rows = (uint32_t)(q >> 1) * (16 * rowb);
+        asm volatile("" : "+s"(rows));                             // added at each use: eight offsets kept would be spilled
+        return off2[q & 1] + rows;
     };
+    unsigned char *const w_lds = big_lds + 2 * kBigXBytes;
+    auto issue_x = [&](int q, int step, int at) {                 // `at`: byte offset of the stage among those of x, of w
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(big_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, 0);
+    };
+    auto issue_w = [&](int q, int step, int at) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, 0);
+    };
+
+    // the early touches (not with the third stage of w)
     const uint32_t touch_w = lane * sharers / 64 == share ? (uint32_t)(wave * 64 + lane) * rowb : kOutOfRange;
     const uint32_t touch_x = lane < 16 ? (uint32_t)((ct & 3) * 64 + wave * 16 + lane) * rowb : kOutOfRange;
     auto touch = [&](int step) {
-        const int so = min(step, nsteps - 1) * 128;
-        lds_void *sink = (lds_void *)(big_lds + 2 * kBigStageBytes + wave * 512);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sink, 4, touch_w, so, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, sink, 4, touch_x, so, 0, 0);
+        if constexpr (!DEEP_W) {
+            const int so = min(step, nsteps - 1) * 128;
+            lds_void *sink = (lds_void *)(w_lds + 2 * kBigWBytes + wave * 512);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sink, 4, touch_w, so, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, sink, 4, touch_x, so, 0, 0);
+        }
     };
 
     // The waves form a 2 x 2 grid.  In a ragged tile the rows are split evenly between the two row halves: nb 16-row
@@ -2356,14 +2376,14 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int n = 0; n < 8; ++n) acc[i][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const unsigned char *px = big_lds + (wrow + m) * 128, *pw = big_lds + (BM + wn * 128 + m) * 128;
+    const unsigned char *px = big_lds + (wrow + m) * 128, *pw = w_lds + (wn * 128 + m) * 128;
     const int k0 = (g ^ ((m >> 1) & 7)) * 16, k1 = ((4 + g) ^ ((m >> 1) & 7)) * 16;      // this lane's piece, slice 0 and 1
     bf16x8 fx[2][8], fw[2][8];
-    auto read_w = [&](int set, int i, int buf, int ko) {
-        fw[set][i] = *reinterpret_cast<const bf16x8 *>(pw + buf * kBigStageBytes + ko + i * 2048);
+    auto read_w = [&](int set, int i, int at, int ko) {
+        fw[set][i] = *reinterpret_cast<const bf16x8 *>(pw + at + ko + i * 2048);
     };
-    auto read_x = [&](int set, int i, int buf, int ko) {
-        fx[set][i] = *reinterpret_cast<const bf16x8 *>(px + buf * kBigStageBytes + ko + i * 2048);
+    auto read_x = [&](int set, int i, int at, int ko) {
+        fx[set][i] = *reinterpret_cast<const bf16x8 *>(px + at + ko + i * 2048);
     };
     // no instruction near it reads the accumulator: the next MFMA on the same one is a whole slice away, and the epilogue
     // waits first
@@ -2375,30 +2395,38 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // One slice: 64 MFMAs on fragment set `set`; between them the 16 reads of the other set (buffer `buf`, piece offset ko)
-    // and, if LOADS, the 16 loads of stage `step` into buffer `to`.
-    auto slice = [&](int set, int buf, int ko, bool loads, int step, int to) {
+    // One slice: 64 MFMAs on fragment set `set`; between them the 16 reads of the other set (stages at xat and wat, piece
+    // offset ko) and, if LOADS, the 8 loads of x for step sx and then the 8 of w for step sw, into the stages at xto and wto.
+    auto slice = [&](int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            if (q < 8) read_w(set ^ 1, q, buf, ko);
-            else read_x(set ^ 1, q - 8, buf, ko);
+            if (q < 8) read_w(set ^ 1, q, wat, ko);
+            else read_x(set ^ 1, q - 8, xat, ko);
             mma(set, q / 2, (q & 1) * 4 + 0);
             mma(set, q / 2, (q & 1) * 4 + 1);
-            if (loads) issue(q / 2, q & 1, step, to);
+            if (loads) {
+                if (q < 8) issue_x(q, sx, xto);
+                else issue_w(q - 8, sw, wto);
+            }
             mma(set, q / 2, (q & 1) * 4 + 2);
             mma(set, q / 2, (q & 1) * 4 + 3);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     // the same for a ragged tile: only the wave's nb blocks with rows are multiplied
-    auto slice_ragged = [&](int set, int buf, int ko, bool loads, int step, int to) {
+    auto slice_ragged = [&](int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            read_w(set ^ 1, i, buf, ko);
-            read_x(set ^ 1, i, buf, ko);
+            read_w(set ^ 1, i, wat, ko);
+            read_x(set ^ 1, i, xat, ko);
             if (loads) {
-                issue(i, true, step, to);
-                issue(i, false, step, to);
+                if (i < 4) {
+                    issue_x(2 * i, sx, xto);
+                    issue_x(2 * i + 1, sx, xto);
+                } else {
+                    issue_w(2 * i - 8, sw, wto);
+                    issue_w(2 * i - 7, sw, wto);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
             if (i < nb) {
@@ -2408,23 +2436,30 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         }
     };
     auto run = [&](auto slice_fn) {
+        int xat = 0, wat = 0;                                      // where stage s is
         for (int s = 0; s < nsteps; ++s) {
-            const int buf = s & 1;
-            slice_fn(0, buf, k1, false, 0, 0);
-            // vmcnt(2) lgkmcnt(0): stage s+1 is in LDS (only the two early touches are younger), and this wave has read
-            // all of stage s
-            __builtin_amdgcn_s_waitcnt(0x0072);
+            slice_fn(0, xat, wat, k1, false, 0, 0, 0, 0);
+            // lgkmcnt(0): this wave has read all of stage s; vmcnt(8 or 2): stage s+1 is in LDS, younger are only the 8 loads
+            // of w for stage s+2, or the two early touches
+            __builtin_amdgcn_s_waitcnt(kWaitStage);
             barrier();
-            // past the end the last stage is fetched again, into the buffer that is not read any more
-            slice_fn(1, buf ^ 1, k0, true, min(s + 2, nsteps - 1), buf);
+            // past the end the last stage is fetched again, into buffers that are not read any more
+            const int wnext = wat == (WST - 1) * kBigWBytes ? 0 : wat + kBigWBytes;
+            slice_fn(1, xat ^ kBigXBytes, wnext, k0, true, min(s + 2, nsteps - 1), xat, min(s + WST, nsteps - 1), wat);
             touch(s + 3);
+            xat ^= kBigXBytes;
+            wat = wnext;
         }
     };
 #pragma unroll
-    for (int q = 0; q < 16; ++q) issue(q / 2, q & 1, 0, 0);
+    for (int q = 0; q < 16; ++q) q & 1 ? issue_w(q / 2, 0, 0) : issue_x(q / 2, 0, 0);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) issue(q / 2, q & 1, min(1, nsteps - 1), 1);
-    __builtin_amdgcn_s_waitcnt(0x4f70);                            // vmcnt(16): stage 0
+    for (int q = 0; q < 16; ++q) q & 1 ? issue_w(q / 2, min(1, nsteps - 1), kBigWBytes) : issue_x(q / 2, min(1, nsteps - 1), kBigXBytes);
+    if constexpr (DEEP_W) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) issue_w(q, min(2, nsteps - 1), 2 * kBigWBytes);
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitFirst);                        // stage 0
     touch(2);
     barrier();
 #pragma unroll
@@ -2437,14 +2472,16 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     asm volatile("s_nop 15\n\ts_nop 15");                          // the last MFMAs' results
     __builtin_amdgcn_sched_barrier(0);
 
-    // acc[i][n][v]: row 16 i + m of the wave's rows, output feature 16 n + 4 g + v of its columns
+    // acc[i][n][v]: row 16 i + lane % 16 of the wave's rows, output feature 16 n + 4 (lane / 16) + v of its columns.  The lane is
+    // asked for again: kept in a register through the loop it would be spilled.
+    const int l2 = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int r = row0 + wrow + i * 16 + m;
+        const int r = row0 + wrow + i * 16 + (l2 & 15);
         if (i < nb && r < row_end) {
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
-                const int c = col0 + wn * 128 + n * 16 + 4 * g;
+                const int c = col0 + wn * 128 + n * 16 + 4 * (l2 >> 4);
                 if (c < a.N) *reinterpret_cast<uint2 *>(y + (int64_t)r * a.N + c) = pack_bf16x4(acc[i][n]);
             }
         }

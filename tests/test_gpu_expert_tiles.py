@@ -47,12 +47,25 @@ def check(m, sizes, H, N, dtype):
     assert np.all(got[T].view(np.uint8) == 0x5A)
 
 
-# rows of a ragged tile around its 32-row steps (two halves of 16-row blocks), around the 64 rows of the short loop and
-# around whole tiles; columns of one lane group, of one and of two tiles, and so many that the ragged tiles stay in place
+# rows of a ragged tile around its 32-row steps (two halves of 16-row blocks), around the 64 rows of the short tile and around
+# whole tiles; columns of one lane group and of one and of two tiles
 @pytest.mark.parametrize("H", [64, 128, 192])
-@pytest.mark.parametrize("N", [8, 248, 264, 6664])
+@pytest.mark.parametrize("N", [8, 248, 264])
 def test_long_segments(m, H, N):
     check(m, [65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 321, 64], H, N, BF16)
+
+
+# so many tiles that they are 256 x 256: ragged tiles last (2056 and 4104 features) or in place (6664), up to 256 rows per expert
+# on average or more; one step of the hidden axis, fewer than the stages, and more
+@pytest.mark.parametrize("H", [64, 128, 320])
+@pytest.mark.parametrize("sizes,N", [
+    ([65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 513, 64, 700], 2056),
+    ([577, 320, 61, 257], 4104),
+    ([65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 321, 64], 6664),
+    ([300, 512, 769, 33, 255], 6664 * 2),
+], ids=["last-short", "last-long", "inplace-short", "inplace-long"])
+def test_big_tiles(m, sizes, N, H):
+    check(m, sizes, H, N, BF16)
 
 
 # few rows per expert: row counts around the 16-row blocks and past one tile, hidden sizes of fewer steps than waves and
