@@ -245,15 +245,14 @@ int monta_combine(const monta_cfg *cfg, const void *y, const float *gates, void 
 /* For callers that cannot allocate device memory or hand over a workspace: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  The whole step with identity experts --
  * monta_route_dispatch_regather followed by monta_combine(y = final_) -- with the plan tables kept in a
- * file-scope device array of the library (16 MiB per GPU, held until the process ends) instead of a caller
+ * file-scope device array of the library (16.5 MiB per GPU, held until the process ends) instead of a caller
  * workspace.  The caller still passes every input and output: logits [T][E], x [T][H], topk_idx / gates [T][k],
  * stage / final_ [max_rows][H], out [T][H], all device pointers as in the calls above; results are bit-identical
  * to those calls.  Calls no hipMalloc / hipFree and creates no stream or event: pipeline mode 0 is replaced by
  * the default mode, and with event profiling enabled the call is refused (MONTA_ERR_INVALID).  Problems
- * whose tables (monta_ws_layout.ws_bytes) exceed 16 MiB are refused with MONTA_ERR_TOO_LARGE before any GPU
- * work; the five named workloads need at most 8.2 MiB.  Every call on one GPU shares that GPU's array: the
- * counters in it are cleared by a small kernel at the start of each call, the tables are overwritten, and two
- * calls that overlap in time on one GPU (different streams or threads) race -- the caller must order them.  The
+ * whose tables (monta_ws_layout.ws_bytes, with 256 tokens per route workgroup where they fit) exceed 16 MiB are
+ * refused with MONTA_ERR_TOO_LARGE before any GPU work; the five named workloads need at most 8.2 MiB.  Every call
+ * on one GPU shares that GPU's array: the tables in it are overwritten, and two calls that overlap in time on one GPU (different streams or threads) race -- the caller must order them.  The
  * first call on a device looks the array's address up (hipGetSymbolAddress): make one call before capturing the
  * entry point into a HIP graph; captured, it records kernel nodes only. */
 int monta_route_dispatch_combine_static(const monta_cfg *cfg, const float *logits, const void *x, int32_t *topk_idx,

@@ -1517,9 +1517,7 @@ int monta_route_dispatch_combine_static(const monta_cfg *cfg, const float *logit
     void *ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // the array keeps the previous call's contents (possibly of another shape): put the counters back to zero
-    hipLaunchKernelGGL(ws_init_kernel, dim3(1), dim3(kWave), 0, st, plan_ptrs(g, ws).meta);
-    HIP_TRY(hipGetLastError());
+    // the array keeps the previous call's contents, possibly of another shape: no kernel reads what this call has not written
     if ((rc = route_dispatch_regather_impl(g, logits, x, topk_idx, gates, stage, final_, ws, st))) return rc;
     return combine_impl(g, cfg->dtype, final_, gates, out, ws, st);
 }
