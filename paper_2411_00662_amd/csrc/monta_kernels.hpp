@@ -2063,6 +2063,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
 }
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr uint32_t kOutOfRange = 0x80000000u;                      // a lane offset past every descriptor: no access
+
+// Scalar offset of a step's 128 bytes in every row of a tile of `nsteps` steps.  The range check of a buffer load compares the
+// lane's offset with num_records - scalar offset in 32 bits, and the smallest descriptor is one row of nsteps * 128 bytes: the
+// scalar offset must stay below that, or the difference wraps and every lane offset counts as in range.  Steps past the end,
+// whose lanes are out of range anyway, therefore take 0.
+__host__ __device__ constexpr uint32_t step_offset(int step, int nsteps) { return step < nsteps ? (uint32_t)step * 128u : 0u; }
+constexpr bool step_offsets_stay_inside(int nsteps, int past)
+{
+    for (int step = 0; step < nsteps + past; ++step) {
+        const uint32_t records = (uint32_t)nsteps * 128u, so = step_offset(step, nsteps);
+        if (so >= records || kOutOfRange < records - so) return false;
+    }
+    return true;
+}
+static_assert(step_offsets_stay_inside(1, 8) && step_offsets_stay_inside(2, 8) && step_offsets_stay_inside(7, 8),
+              "a one-row tile must refuse the loads of the steps past its end");
 constexpr int kBigMaxHidden = 1 << 20;                             // a tile's 256 rows end far below it
 
 // four fp32 -> four bf16, nearest-even, as 8 bytes
@@ -2113,14 +2129,15 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     auto issue = [&](int step, int slot) {
         unsigned char *base = lds + slot * G::kStageBytes;
         const uint32_t past = step < nsteps ? 0u : kOutOfRange;
+        const uint32_t so = step_offset(step, nsteps);
 #pragma unroll
         for (int q = 0; q < G::kCW; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * G::kCW + q) * 1024), 16, ow[q] | past,
-                                                     step * 128, 0, 0);
+                                                     so, 0, 0);
 #pragma unroll
         for (int q = 0; q < G::kCX; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * G::kCX + q) * 1024), 16, ox[q] | past,
-                                                     step * 128, 0, 0);
+                                                     so, 0, 0);
     };
     f32x4 acc[RB][CB];
 #pragma unroll

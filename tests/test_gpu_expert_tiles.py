@@ -76,6 +76,15 @@ def test_few_rows(m, sizes, H, N):
     check(m, sizes, H, N, BF16)
 
 
+# one row of x in a tile, the smallest descriptor, with about as many steps as there are stages in flight, so that loads past
+# the row's end are issued (tiles of 32 x 64, and of 64 x 128 where the columns are many; ragged tiles of one row of the
+# 256 x 256 form are among its own cases above)
+@pytest.mark.parametrize("H", [64, 128, 192, 256])
+@pytest.mark.parametrize("sizes,N", [([1, 33], 8), ([65], 16264)], ids=["32x64", "64x128"])
+def test_one_row_tiles(m, sizes, N, H):
+    check(m, sizes, H, N, BF16)
+
+
 def test_few_rows_many_columns(m):
     """More column tiles than one round of workgroups; segments of several row tiles."""
     check(m, [5, 30, 1, 12], 128, 8200, BF16)
