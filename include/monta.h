@@ -221,7 +221,12 @@ int monta_allgather_regather(const monta_cfg *cfg, const void *stage, void *gath
  * monta_regather for j = 0..S-1: STAGE and FINAL hold the same bytes, and everything
  * has finished, in stream order, when the call's work on `stream` completes.  By
  * default every row is read once and stored to both places in one pass; how the two
- * passes overlap where they are kept apart is chosen by monta_set_pipeline_mode(). */
+ * passes overlap where they are kept apart is chosen by monta_set_pipeline_mode().
+ * By default final_ may share memory with x (all of x is then packed before a row of
+ * final_ is written); with an explicit mode only if slices = 1, since slice j reaches
+ * final_ before slice j+1 is packed.  The rows of stage in use may share no memory with
+ * x or with the rows of final_ in use.  This holds for every call that packs and regathers,
+ * monta_route_dispatch_expert with overlap = 1 counting as an explicit mode. */
 int monta_dispatch_regather(const monta_cfg *cfg, const void *x, void *stage, void *final_,
                             const void *ws, void *stream);
 
@@ -275,8 +280,9 @@ int monta_combine_staged(const monta_cfg *cfg, const void *y_stage, const float 
 /* The return pipeline on one stream.  With pipeline mode 0 or 1, launch j fetches slice j back and, in disjoint
  * workgroups of the same grid, combines the tokens of slice j-1 (S+1 launches); with mode 2, fetch and combine of
  * every slice are two plain kernels.  The default (-1) does both in one pass, each row of y read once, stored to its
- * row of y_stage and added; where the memory of y, y_stage and out overlaps it keeps them apart and groups consecutive
- * slices (groups of up to 256 MiB, two plain kernels per group once a group is that large or the problem is one group). */
+ * row of y_stage and added; where out shares memory with y it fetches every row and then combines (two launches).
+ * With an explicit mode out may share memory with y only if slices = 1.  The rows of y_stage in use may share no
+ * memory with the rows of y in use or with out. */
 int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage, const float *gates, void *out,
                              const void *ws, void *stream);
 
@@ -288,21 +294,21 @@ int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage,
  *   2  one stream, strictly serial pack(0), regather(0), pack(1), ...
  *  -1  (default) no separate passes: one launch reads every token row once and stores it to its rows
  *      of STAGE and of FINAL, so STAGE is not read back.  Where FINAL shares memory with x the passes
- *      stay apart, in a realisation chosen from the sizes, as the paper's planner picks its chunk count
- *      from the traffic: consecutive slices are grouped into one launch until a launch's share of STAGE
- *      reaches 256 MiB; the groups run as in 1 while their copies are short, as in 2 once a group
- *      moves 192 MiB or more.  A problem that fits one group runs in three launches: plan + pack of
- *      the first slices (about one round of workgroups), pack of the rest co-scheduled with the
- *      regather of the first, regather of the rest.
+ *      stay apart: one launch packs all slices (the one that finishes the plan, if the shape allows), the
+ *      next regathers them.
  * With 0, 1 or 2 every launch covers exactly one slice.  STAGE keeps its [slice][tp rank][expert]
  * layout in every case; only the launches differ.
  * Returns MONTA_ERR_INVALID for other values.  Process-wide. */
 int monta_set_pipeline_mode(int mode);
 int monta_get_pipeline_mode(void);
-/* Host only: how the two passes are launched for cfg, under the current switch, where they are kept apart: the
- * realisation (0, 1 or 2), the slices the first launch covers, the slices each later launch covers, and whether the
- * kernel that finishes the plan also packs the first launch's slices.  Benchmarks that set a mode use it to attribute
- * bytes to launches; the default mode's single pass has nothing to group. */
+/* Host only: a launch grouping of the two passes for cfg: the realisation (0, 1 or 2), the slices the first launch
+ * covers, the slices each later launch covers, and whether the kernel that finishes the plan also packs the first
+ * launch's slices.  With an explicit mode it is what the calls do; benchmarks use it to attribute bytes to launches.
+ * With the default mode, whose calls have nothing to group, it is the grouping that suits the sizes, for a program
+ * that issues the passes itself: consecutive slices until a launch's share of STAGE reaches 256 MiB, as in 1 while
+ * their copies are short, as in 2 once a group moves 192 MiB or more; a problem that fits one group in three
+ * launches, plan + pack of the first slices (about one round of workgroups), pack of the rest co-scheduled with the
+ * regather of the first, regather of the rest. */
 int monta_pipeline_query(const monta_cfg *cfg, int32_t *mode, int32_t *first_slices, int32_t *slices_per_launch,
                          int32_t *plan_fused);
 

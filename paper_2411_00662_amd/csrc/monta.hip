@@ -711,22 +711,22 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     return MONTA_OK;
 }
 
-// How one call runs the two passes of the slice pipeline where they are kept apart (single_pass() says when they are not):
-// the realisation (0, 1 or 2) and how many consecutive slices one launch covers.  An explicit mode keeps one slice per
-// launch.  The default (-1) chooses from the sizes, as the paper's
-// planner chooses its chunk count from the traffic (section "Network-traffic-aware"): measured on MI355X,
-//  - a launch boundary costs a few microseconds of idle memory system, so slices that move only tens of
-//    megabytes are grouped until a launch's share of STAGE reaches 256 MiB (the size of the memory-side cache:
-//    what the pack writes is still there when the regather reads it); a problem that fits one group runs as
-//    plan + pack of everything, then one regather;
-//  - co-scheduling pack(j) with regather(j-1) in one grid saves a boundary per slice, which decides it while
-//    a group's copies take a few tens of microseconds; once they take hundreds, two plain kernels run faster
-//    than the mixed grid (the regather alone reaches 6.6-7.0 TB/s, the mixed grid 6.2-6.7).
+// How the two passes of the slice pipeline are launched where they are kept apart (single_pass() says when they are not):
+// the realisation (0, 1 or 2) and how many consecutive slices one launch covers.
 struct PipePlan {
     int mode;
     int first;      // slices in the first launch group
     int spg;        // slices in every later group
 };
+
+// What the calls do.  An explicit mode keeps one slice per launch.  With the default they come here only because FINAL shares
+// memory with x: every row of x has to be packed before the first row of FINAL is written, so one launch packs all slices and
+// the next regathers them.
+PipePlan pipeline_plan(const Geometry &g)
+{
+    if (g.modes.pipeline >= 0) return {g.modes.pipeline, 1, 1};
+    return {1, g.s.S, g.s.S};
+}
 
 // Can the kernel that finishes the plan also pack (plan_pack_kernel)?  It needs a histogram table small enough to
 // rebuild in every pack workgroup and token groups that never straddle two route workgroups.
@@ -747,7 +747,7 @@ bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
 
 // By default the dispatch runs in one pass (place_kernel): each row is read once and stored to its rows in STAGE and in
 // FINAL.  An explicit pipeline mode asks for the two passes, and they are kept where FINAL shares memory with x: rows of x
-// still to be read would be overwritten.
+// still to be read would be overwritten (pipeline_plan() then packs everything first).
 bool single_pass(const Geometry &g, const void *x, const void *final_)
 {
     return g.modes.pipeline < 0 && !overlap(x, (int64_t)g.s.T * g.row_bytes, final_, g.max_rows * g.row_bytes);
@@ -811,9 +811,19 @@ int launch_plan_place(const Geometry &g, const PlanPtrs &p, int span, const int3
     return MONTA_OK;
 }
 
-PipePlan pipeline_plan(const Geometry &g)
+// What monta_pipeline_query answers.  With the default mode, whose calls launch no groups, it is the grouping that suits the
+// sizes for a program that issues the passes itself, as the paper's planner chooses its chunk count from the traffic (section
+// "Network-traffic-aware"): measured on MI355X,
+//  - a launch boundary costs a few microseconds of idle memory system, so slices that move only tens of
+//    megabytes are grouped until a launch's share of STAGE reaches 256 MiB (the size of the memory-side cache:
+//    what the pack writes is still there when the regather reads it); a problem that fits one group runs as
+//    plan + pack of everything, then one regather;
+//  - co-scheduling pack(j) with regather(j-1) in one grid saves a boundary per slice, which decides it while
+//    a group's copies take a few tens of microseconds; once they take hundreds, two plain kernels run faster
+//    than the mixed grid (the regather alone reaches 6.6-7.0 TB/s, the mixed grid 6.2-6.7).
+PipePlan grouping_by_size(const Geometry &g)
 {
-    if (g.modes.pipeline >= 0) return {g.modes.pipeline, 1, 1};
+    if (g.modes.pipeline >= 0) return pipeline_plan(g);
     const int S = g.s.S;
     const int64_t slice_bytes = slice_rows_bound(g, 1) * g.row_bytes;      // what one slice may put into STAGE
     if (slice_bytes >= kGroupBytes) return {2, 1, 1};
@@ -1418,41 +1428,24 @@ int monta_unregather_combine(const monta_cfg *cfg, const void *y, void *y_stage,
         !overlap(y_stage, y_bytes, out, out_bytes))
         return launch_return(g, p, cfg->dtype, y, y_stage, gates, out, st);
     const int per_slice = s.tp * s.Tu;
-    // Launch grouping as in the forward pipeline, by the same measurements: with an explicit pipeline mode launch j
-    // fetches slice j back and, in disjoint workgroups of the same grid, combines the tokens of slice j-1; by
-    // default consecutive slices are grouped until a group's rows reach 256 MiB, and a group that large (or a
-    // problem that is one group) runs as two plain kernels, fetch then combine.
-    int spg = 1;
-    bool serial = false;
-    if (g.modes.pipeline < 0) {
-        const int64_t slice_bytes = slice_rows_bound(g, 1) * g.row_bytes;
-        if (slice_bytes >= kGroupBytes) serial = true;
-        else {
-            spg = (int)(kGroupBytes / slice_bytes);
-            if (spg > s.S) spg = s.S;
-            const int groups = (s.S + spg - 1) / spg;
-            spg = (s.S + groups - 1) / groups;
-            serial = groups == 1 || spg * slice_bytes >= kGroupBytes * 3 / 4;
-        }
-    } else {
-        serial = g.modes.pipeline == 2;
-    }
-    const int G = (s.S + spg - 1) / spg;
-    auto lo = [&](int gi) { return gi * spg; };
-    auto hi = [&](int gi) { return (gi + 1) * spg < s.S ? (gi + 1) * spg : s.S; };
-    if (serial) {
+    // One slice per launch with an explicit pipeline mode: launch j fetches slice j back and, in disjoint workgroups of the
+    // same grid, combines the tokens of slice j-1; with mode 2 both are kernels of their own.  By default the two passes are
+    // apart only because out shares memory with y (or a buffer with another beyond the rows in use): every row of y has to be
+    // fetched before the first row of out is written, so one launch fetches all slices and the next combines them.
+    const int spg = g.modes.pipeline < 0 ? s.S : 1;
+    const int G = s.S / spg;
+    if (g.modes.pipeline < 0 || g.modes.pipeline == 2) {
         for (int gi = 0; gi < G; ++gi) {
-            if ((rc = launch_unregather_combine(g, p, cfg->dtype, y, y_stage, gates, out, lo(gi) * s.tp, hi(gi) * s.tp, 0, 0, st)))
+            if ((rc = launch_unregather_combine(g, p, cfg->dtype, y, y_stage, gates, out, gi * spg * s.tp, (gi + 1) * spg * s.tp, 0, 0, st)))
                 return rc;
-            if ((rc = launch_unregather_combine(g, p, cfg->dtype, y, y_stage, gates, out, 0, 0, lo(gi) * per_slice,
-                                                (hi(gi) - lo(gi)) * per_slice, st)))
+            if ((rc = launch_unregather_combine(g, p, cfg->dtype, y, y_stage, gates, out, 0, 0, gi * spg * per_slice, spg * per_slice, st)))
                 return rc;
         }
         return MONTA_OK;
     }
     for (int gi = 0; gi <= G; ++gi) {
-        const int u0 = gi < G ? lo(gi) * s.tp : 0, u1 = gi < G ? hi(gi) * s.tp : 0;
-        const int t0 = gi > 0 ? lo(gi - 1) * per_slice : 0, nt = gi > 0 ? (hi(gi - 1) - lo(gi - 1)) * per_slice : 0;
+        const int u0 = gi < G ? gi * s.tp : 0, u1 = gi < G ? (gi + 1) * s.tp : 0;
+        const int t0 = gi > 0 ? (gi - 1) * per_slice : 0, nt = gi > 0 ? per_slice : 0;
         if ((rc = launch_unregather_combine(g, p, cfg->dtype, y, y_stage, gates, out, u0, u1, t0, nt, st))) return rc;
     }
     return MONTA_OK;
@@ -1529,7 +1522,7 @@ int monta_pipeline_query(const monta_cfg *cfg, int32_t *mode, int32_t *first_sli
     Geometry g;
     int rc = validate(cfg, &g);
     if (rc) return rc;
-    const PipePlan pp = pipeline_plan(g);
+    const PipePlan pp = grouping_by_size(g);
     *mode = pp.mode;
     *first_slices = pp.first < g.s.S ? pp.first : g.s.S;
     *slices_per_launch = pp.spg;

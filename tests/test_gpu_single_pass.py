@@ -82,14 +82,59 @@ def test_single_pass_equals_two_passes(m, w):
         assert np.array_equal(bufs.to_host_act(cfg, b.final, t["final_rows"]), ref.final[:t["final_rows"]])
 
 
-def test_final_in_the_memory_of_x(m):
-    """FINAL may reuse the memory of x where the whole of x is packed first (one slice): the passes are then kept apart."""
+ALIASED = [
+    Workload("alias1", 1024, 512, BF16, 8, 2, 4, 2, 1, 0.0),
+    Workload("alias4", 1024, 512, BF16, 8, 2, 4, 2, 4, 0.0),                        # plan and pack of all slices in one grid
+    Workload("aliasdrop", 1320, 264, BF16, 6, 3, 3, 5, 4, 0.7, zipf_s=0.8),         # plan and pack in two
+    Workload("aliaspad", 600, 264, BF16, 7, 3, 7, 5, 2, 0.5, zipf_s=0.8, padded=1),
+]
+
+
+def shared_memory(first, second, where):
+    """One allocation for two buffers of so many rows that starts with the first: (rows in all, start of the second)."""
+    at = {"start": 0, "second": 1, "inside": max(first - second, 1), "straddling": first - second // 2}[where]
+    return max(first, at + second), at
+
+
+@pytest.mark.parametrize("fused", [False, True], ids=["plan-apart", "plan-fused"])
+@pytest.mark.parametrize("where", ["start", "inside", "straddling"])
+@pytest.mark.parametrize("w", ALIASED, ids=lambda w: w.name)
+def test_final_in_the_memory_of_x(m, w, where, fused):
+    """By default FINAL may reuse the memory of x, whatever the number of slices: all of x is packed first."""
     import torch
-    w = Workload("alias", 1024, 512, BF16, 8, 2, 4, 2, 1, 0.0)
     logits, x = make_inputs(w)
-    cfg, want, _, _ = run(m, w, 2, False, logits, x)
+    cfg, want, _, t2 = run(m, w, 2, False, logits, x)
     b = m.alloc_buffers(cfg, logits, x, canary=0xA5)
-    b.final[:w.tokens] = b.x
-    m.monta_route_dispatch_regather(cfg, b.logits, b.final, b.topk_idx, b.gates, b.stage, b.final, b.ws)
+    rows = b.layout.max_rows
+    total, at = shared_memory(rows, w.tokens, where)
+    mem = torch.zeros((total, w.hidden), dtype=b.x.dtype, device="cuda:0")
+    shared_x, shared_final = mem[at:at + w.tokens], mem[:rows]
+    shared_x.copy_(b.x)
+    m.monta_set_pipeline_mode(-1)
+    if fused:
+        m.monta_route_dispatch_regather(cfg, b.logits, shared_x, b.topk_idx, b.gates, b.stage, shared_final, b.ws)
+    else:
+        m.monta_route(cfg, b.logits, b.topk_idx, b.gates, b.ws)
+        m.monta_dispatch_regather(cfg, shared_x, b.stage, shared_final, b.ws)
     torch.cuda.synchronize()
-    assert same_bytes(b.final, want.final) and same_bytes(b.stage, want.stage)
+    n = t2["final_rows"]
+    assert same_bytes(shared_final[:n], want.final[:n]) and same_bytes(b.stage, want.stage)
+
+
+@pytest.mark.parametrize("where", ["second", "inside", "straddling"])
+@pytest.mark.parametrize("w", ALIASED, ids=lambda w: w.name)
+def test_out_in_the_memory_of_y(m, w, where):
+    """By default out may reuse the memory of y, whatever the number of slices: all of y is fetched first."""
+    import torch
+    logits, x = make_inputs(w)
+    cfg, want, want_stage, _ = run(m, w, 2, False, logits, x)
+    b = m.alloc_buffers(cfg, logits, x, canary=0xA5)
+    rows = b.layout.max_rows
+    total, at = shared_memory(rows, w.tokens, where)
+    mem = torch.zeros((total, w.hidden), dtype=b.x.dtype, device="cuda:0")
+    y, out = mem[:rows], mem[at:at + w.tokens]
+    y.copy_(want.final)
+    m.monta_set_pipeline_mode(-1)
+    m.monta_unregather_combine(cfg, y, b.stage, want.gates, out, want.ws)
+    torch.cuda.synchronize()
+    assert same_bytes(out, want.out) and same_bytes(b.stage, want_stage)
