@@ -415,13 +415,13 @@ def test_copy_kernel_and_profile_counters(m):
 
 
 def test_hip_graph_replays_match_eager(m):
-    """The step captured in a HIP graph (no memset nodes: the library clears its counters in kernels) and
+    """The step captured in a HIP graph (kernel nodes only: the library records no memset) and
     replayed several times, with eager work and synchronisations in between, gives the eager bits every time."""
     import torch
     from paper_2411_00662_amd import buffers as bufs
     w = Workload("graph", 4096, 1024, BF16, 8, 2, 4, 2, 4, 0.8, zipf_s=0.6)
     cfg = cfg_of(m, w)
-    m.monta_set_pipeline_mode(-1)        # the default: launch groups chosen by size (three launches here)
+    m.monta_set_pipeline_mode(-1)        # the default: route, plan and rows, combine
     inputs = [workloads.make_inputs(w, seed=s) for s in (1, 2, 3)]
     b = m.alloc_buffers(cfg, *inputs[0], canary=0)
     stream = torch.cuda.Stream()

@@ -5,7 +5,8 @@ stored to its row of y_stage and added.  Bar: every table, STAGE, FINAL (canary 
 bit for bit what the two passes give (pipeline mode 2, itself held against the oracle elsewhere), and STAGE / FINAL are
 the oracle's.  The shapes sit on the edges of the kernels: fewer lanes per row than choices, rows shared by part of a
 wave, by one wave, by whole workgroups and by more than one pass; workgroups of several rows; token counts that no
-group of rows divides; the padded layout; tables too large for a workgroup to rebuild.
+group of rows divides; the padded layout; histogram tables that every workgroup of the mover rebuilds (at most 2048
+counters), that only the plan's own workgroups rebuild (at most 4096), and that a kernel scans first.
 """
 import numpy as np
 import pytest
@@ -26,7 +27,11 @@ SHAPES = [
     Workload("one", 1, 4096, BF16, 8, 2, 8, 1, 1, 0.0),
     Workload("odd", 37, 2048, BF16, 8, 2, 8, 1, 1, 0.0),
     Workload("rounds", 12288, 1024, BF16, 4, 2, 4, 1, 3, 0.9, zipf_s=0.5),          # more than one round: rows per workgroup
-    Workload("wide", 2048, 128, BF16, 64, 8, 8, 4, 8, 0.5, zipf_s=1.2),             # table too large to rebuild per workgroup
+    Workload("wide", 2048, 128, BF16, 64, 8, 8, 4, 8, 0.5, zipf_s=1.2),             # 2048 counters: the most a mover rebuilds
+    Workload("plan", 4096, 128, BF16, 64, 8, 8, 1, 1, 0.5, zipf_s=1.2),             # 4096: plan and rows in two kernels
+    Workload("scan", 2048, 128, BF16, 256, 8, 8, 4, 8, 0.5, zipf_s=1.2),            # 8192: scanned, plan and rows in one
+    Workload("scanpad", 2100, 264, FP32, 100, 3, 4, 5, 6, 0.6, zipf_s=0.8, padded=1),
+    Workload("scanlong", 8192, 2048, BF16, 64, 8, 8, 4, 4, 0.7, zipf_s=0.5),        # scanned, above 320 MiB: in two
     Workload("padded", 600, 264, BF16, 7, 3, 7, 5, 2, 0.5, zipf_s=0.8, padded=1),
     Workload("padded16", 512, 4096, BF16, 8, 2, 8, 1, 1, 2.0, padded=1),
 ]
@@ -42,12 +47,13 @@ def m():
     return mod
 
 
-def run(m, w, mode, fused, logits, x):
+def run(m, w, mode, fused, logits, x, plan_mode=-1):
     import torch
     cfg = m.make_cfg(w.tokens, w.hidden, w.dtype, w.experts, w.top_k, w.ep, w.tp, w.slices, w.capacity_factor, w.renorm, w.padded)
     b = m.alloc_buffers(cfg, logits, x, canary=0xA5)
     y_stage = b.stage.clone()
     m.monta_set_pipeline_mode(mode)
+    m.monta_set_plan_mode(plan_mode)
     if fused:
         m.monta_route_dispatch_regather(cfg, b.logits, b.x, b.topk_idx, b.gates, b.stage, b.final, b.ws)
     else:
@@ -63,14 +69,16 @@ def same_bytes(a, b):
     return torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
+# plan mode 0 scans the table whatever its size
+@pytest.mark.parametrize("plan_mode", [-1, 0], ids=["plan-by-size", "plan-scanned"])
 @pytest.mark.parametrize("w", SHAPES, ids=lambda w: w.name)
-def test_single_pass_equals_two_passes(m, w):
+def test_single_pass_equals_two_passes(m, w, plan_mode):
     from paper_2411_00662_amd import buffers as bufs
     logits, x = make_inputs(w)
     cfg, b2, ys2, t2 = run(m, w, 2, False, logits, x)
     ref = oracle.forward(logits, x, k=w.top_k, ep=w.ep, tp=w.tp, S=w.slices, cf=w.capacity_factor, renorm=w.renorm, padded=w.padded)
     for fused in (False, True):
-        _, b, ys, t = run(m, w, -1, fused, logits, x)
+        _, b, ys, t = run(m, w, -1, fused, logits, x, plan_mode)
         R = t["R"]
         for name in ("counts", "kept", "offsets", "n", "stage_off", "unit_base", "send_rows", "unit_rows", "pos_final", "pos_stage"):
             assert np.array_equal(t[name], t2[name]), name
