@@ -12,6 +12,9 @@ from workloads import BF16, FP32
 pytestmark = pytest.mark.gpu
 
 SPLIT = [(1, 4, 1), (16, 28, 16), (17, 32, 17), (31, 60, 33), (40, 64, 9), (5, 224, 255), (48, 480, 48), (300, 448, 256), (260, 2044, 10)]
+# fp32 with at most four experts: a wave per token; rows shorter than a wave, and with a remainder; both sides of its limit
+FEW = [(1, 4, 1), (2, 252, 4), (7, 256, 2), (5, 260, 3), (1025, 1028, 4), (33, 8196, 1), (3072, 516, 4), (3073, 516, 4),
+       (13000, 512, 3)]
 TILES = [(2049, 64, 80), (4128, 128, 65), (8161, 64, 32), (8192, 192, 129), (16383, 64, 200), (4100, 320, 64), (4097, 64, 16)]
 
 
@@ -33,7 +36,7 @@ def check(T, H, E, dtype):
     np.testing.assert_array_equal(got[:T], (x.astype(np.float64) @ w.astype(np.float64).T).astype(np.float32))
 
 
-@pytest.mark.parametrize("T,H,E", SPLIT + TILES)
+@pytest.mark.parametrize("T,H,E", SPLIT + FEW + TILES)
 def test_gate_fp32(T, H, E):
     check(T, H, E, FP32)
 
