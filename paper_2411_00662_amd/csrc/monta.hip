@@ -1047,25 +1047,36 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
     ProfScope ps(MONTA_K_GATE, st);
     if (cfg->dtype == MONTA_BF16) {
         // validate() guarantees H % 8 == 0 (rows are whole 16-byte vectors) and E <= 256 (at most 8 tiles).
-        // Few tiles of 16 tokens x 16 experts: the hidden axis is split, too.  Up to some ten thousand tokens: tiles as small
-        // as leave at most two workgroups per CU (2.0 tiles of 32 x 64: 43 us for 8192 x 7168, 128 experts, 46 with 32 x 128;
-        // at 4 per CU 62 against 36, 8192 x 4096, 256 experts), except where a tile of the k-split form holds all experts
-        // and the tokens are few (4096 x 4096, 64 experts: 21 and 22 us; 3072 tokens: 18 and 22).
-        // Otherwise, few token tiles: one workgroup per CU with a deep step; many: shallower steps, several workgroups per CU.
+        // Few tiles of 16 tokens x 16 experts (or 32, where that makes them one round): the hidden axis is split, too; tiles of 32
+        // that would be more than a round lose to twice the tiles of 16 (2560 x 5120, 40 experts: 35 and 24 us).  Up to some ten
+        // thousand tokens: tiles as small as leave at most two workgroups per CU (8192 x 7168, 128 experts: 41 us in 512 tiles of
+        // 32 x 64, 48 in 32 x 128; 8192 x 4096, 256 experts: 62 in 1024 tiles of 32 x 64, 37 in 32 x 128; rows of 16 KiB 62 and
+        // 50), three where one of 32 x 64 holds all experts (20480 x 5120, 48 experts: 40, in 64 x 128 58; at more than three 64
+        // and 59).  Otherwise the k-split forms, a workgroup per 32 tokens: few of them with a deep step, one per CU; many with
+        // shallower steps, several per CU.  These are also the better ones
+        //  - for 33 .. 64 experts up to 4096 tokens (4096 x 4096, 64 experts: 21 us, 32 x 64 22; 3072 tokens: 18 and 22);
+        //  - for 17 .. 48 experts and 4097 .. 8192 tokens, at most one 32-token tile per CU, unless the rows are short (6144 x 3072,
+        //    32 experts: 14 us, 32 x 64 16; 6144 x 7168: 28 and 34; 8192 x 2048: 11 and 12; but 6144 x 1536: 9.4 and 9.5).  Rows of
+        //    8 KiB slow this form down where it has about 256 tiles: 8192 x 4096 26 and 22, 6144 x 4096 19 and 21.
+        // Up to 16 experts it would be faster than two rounds of split tiles, too (5000 x 3072: 12 us, split 16), but its sums are
+        // less exact: 9.9e-8 off 64 bits against 9.1e-8.
         const int64_t tiles32 = (T + 31) / 32;
         const u32x4 *xv = static_cast<const u32x4 *>(x), *wv = static_cast<const u32x4 *>(w_gate);
         rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
-        const int64_t tiles16 = (T + 15) / 16 * ((E + 15) / 16);
         auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
-        const bool whole_steps = H % 64 == 0 && H <= kBigMaxHidden && tiles32 < 1024 && !(E > 32 && E <= 64 && T <= 4096);
+        const bool mid = T > 4096 && T <= (H == 4096 ? 6144 : 8192);
+        const bool k_split = mid ? H >= 2048 && E > 16 && E <= (H < 3072 ? 32 : 48) : T <= 4096 && E > 32 && E <= 64;
+        const bool short_tiles = H % 64 == 0 && H <= kBigMaxHidden && tiles32 < 1024 && !k_split;
+        const int64_t tiles16 = tiles(16, 16), round = 256;
+        const bool long_rows = H >= 8192 && E > 64 && E <= 128 && tiles(32, 64) > 384;
         if (rc <= 0) {
             if (rc) return rc;
         }
-        else if (tiles16 <= 512)
-            rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, E > 16 && tiles16 > 256 ? 2 : 1, st);
-        else if (whole_steps && tiles(32, 64) <= 512) rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
-        else if (whole_steps && tiles(32, 128) <= 512) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
-        else if (whole_steps) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
+        else if (tiles16 <= 2 * round)
+            rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, tiles16 > round && E > 16 && tiles(16, 32) <= round ? 2 : 1, st);
+        else if (short_tiles && !long_rows && tiles(32, 64) <= (E <= 64 ? 768 : 512)) rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
+        else if (short_tiles && tiles(32, 128) <= 512) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
+        else if (short_tiles) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
         else if (E <= 32)
             rc = tiles32 >= 512 ? launch_gate<1, 1, 512, true>(xv, wv, logits, T, H, E, st)
                                 : launch_gate<1, 1, 1024, true>(xv, wv, logits, T, H, E, st);

@@ -41,6 +41,14 @@ def test_gate_fp32(T, H, E):
     check(T, H, E, FP32)
 
 
-@pytest.mark.parametrize("T,H,E", [(T, (H + 7) // 8 * 8, E) for T, H, E in SPLIT] + TILES)
+# both sides of the lines between the forms: one and two rounds of split tiles, 4096 and 8192 tokens, 16 / 17, 32 / 33 and 48 / 49
+# experts on short, middling, 8-KiB and long rows, two and three short tiles per CU
+RULE = [(2048, 128, 48), (2560, 128, 40), (1024, 192, 65), (1536, 192, 65), (8192, 320, 16), (8193, 320, 16), (5000, 2112, 16),
+        (5000, 2112, 17), (6144, 2048, 32), (6144, 2048, 33), (6144, 4096, 48), (6145, 4096, 48), (8192, 3072, 48), (8193, 3072, 48),
+        (8192, 3072, 49), (5000, 4160, 24), (5000, 200, 24), (16385, 64, 64), (24576, 128, 33), (24577, 128, 64), (24577, 64, 16),
+        (6200, 8192, 65), (6144, 8192, 128)]
+
+
+@pytest.mark.parametrize("T,H,E", [(T, (H + 7) // 8 * 8, E) for T, H, E in SPLIT] + TILES + RULE)
 def test_gate_bf16(T, H, E):
     check(T, H, E, BF16)
