@@ -556,7 +556,12 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, const Exp
     // The segments' ragged last tiles go to the end of the numbering only when there are few of them, at most one round
     // of 256 workgroups: measured on MI355X, eight segments of about 2048 rows 464 us against 480 with the ragged tiles in
     // place; 64 segments of 191 rows, where every tile is ragged, 448 against 440.
-    const bool ragged_last = (int64_t)a.E * nct <= 256, deep_w = rows_per_expert <= kBigBM;
+    const bool ragged_last = (int64_t)a.E * nct <= 256;
+    // The third stage of weights in LDS: where a weight tile has one user, or two, the second of them a ragged tile that runs at
+    // the end, after the first (8 experts, 8192 x 8192, 320 rows: 550 us, with the third stage 502; 64 experts, 4096 x 512: 182 and
+    // 164; but 32 experts, 4096 x 4096, where the ragged tile runs beside it, 391 and 433, and 1024 x 1024, whose walk is short,
+    // 84 and 85).
+    const bool deep_w = rows_per_expert <= kBigBM || (ragged_last && a.H >= 4096 && rows_per_expert <= kBigBM * 3 / 2);
     if (ragged_last) return deep_w ? launch_expert_big_t<true, true>(x_final, w_exp, y, a, grid_last, st)
                                    : launch_expert_big_t<true, false>(x_final, w_exp, y, a, grid_last, st);
     return deep_w ? launch_expert_big_t<false, true>(x_final, w_exp, y, a, grid, st)
@@ -579,26 +584,6 @@ int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, const
     return MONTA_OK;
 }
 
-// Which tile: with r rows per expert, a kernel of R x C tiles has about experts * (r / R + 1/2) * N / C of them, and a
-// launch that leaves CUs idle is slower with large tiles than with small ones.  Measured on MI355X (us for tiles of 32 x 64,
-// 64 x 128, 256 x 256):
-//   8 experts, 4096 x 4096:   r = 16: 41, 41, 73   32: 53, 42, 75   96: 84, 59, 92   128: 105, 101, 97   256: -, 144, 113
-//   2 experts, 8192 x 8192:   r = 16: 40, 75, 108  48: 57, 79, 119  128: 110, 102, 168   256: -, 177, 215   512: -, 261, 219
-//   64 experts, 2048 x 2048:  r = 16: 98, 113, 125  48: 129, 118, 132  64: 149, 128, 134  128: 224, 175, 156
-//   64 experts, 7168 x 2048:  r = 16: 311, 312, 310  64: 511, 388, 389  96: 620, 438, 395
-//   8 experts, 1024 x 1024:   r = 128: 10, 14, 28   512: -, 28, 37   1024: -, 43, 37
-// So a tile is taken where most experts fit one of its rows' tiles, or where its tiles number at most 2.5 per CU.
-int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
-                        int64_t kept_bound, hipStream_t st)
-{
-    const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
-    auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
-    constexpr int64_t kFewTiles = 640;
-    if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
-    if (r <= 56 || tiles(64, 128) <= kFewTiles) return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
-    return launch_expert_big(x_final, w_exp, y, a, rows_bound, r, st);
-}
-
 template <int BM, int BN, int WM, int WN>
 int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, hipStream_t st)
 {
@@ -615,6 +600,38 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
                        static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
                        static_cast<unsigned short *>(y), a);
     return MONTA_OK;
+}
+
+// Which tile: with r rows per expert, a kernel of R x C tiles has about experts * (r / R + 1/2) * N / C of them, and a
+// launch that leaves CUs idle is slower with large tiles than with small ones.  Measured on MI355X (us for tiles of 32 x 64,
+// 64 x 128, 256 x 256, and the register-staged 128 x 256):
+//   8 experts, 4096 x 4096:   r = 16: 41, 41, 45, 147   48: 57, 44, 45, 150   96: 90, 60, 82, 156   128: 109, 93, 87, 155
+//   2 experts, 8192 x 8192:   r = 16: 40, 70, 71, 260   48: 58, 79, 77, 262   128: 108, 103, 148, 273   384: 257, 188, 193, 266
+//   64 experts, 2048 x 2048:  r = 16: 98, 112, 123, 130   48: 128, 117, 131, 139   96: 181, 137, 142, 143   128: 225, 161, 144, 187
+//   64 experts, 7168 x 2048:  r = 16: 310, 311, 309, 312   64: 511, 389, 333, 333   96: 630, 431, 341, 343   192: -, 671, 408, 590
+// So a tile is taken where most experts fit one of its rows' tiles, or where its tiles number at most 2.5 per CU; on short rows,
+// where a large tile's first loads and its stores weigh most, at most 5 per CU (64 experts, 1024 x 1024, r = 96: 45, 35, 38, 48;
+// 128 experts, 512 x 512, r = 96: 33, 24, 37, 33).  The register-staged tile, which has no such rule of its own, is taken
+//  - on rows of 4096 elements and more where each of at most 64 experts fits one row of its tiles and these come in nearly full
+//    rounds of two per CU (64 experts, 4096 x 4096, r = 48: 471, 415, 432, 369   80: 621, 480, 475, 379; 32 experts 80: 312, 246,
+//    250, 188; 64 experts, 4096 x 1536, three quarters of a round, 80: 241, 192, 211, 174; but 5120 x 1536, 40: 241, 177, 207, 210).  With
+//    more experts a skewed load leaves many without rows, and there it is the worst form (256 experts, 4096 x 512, r = 64: even
+//    293, 251, 257, 208; skewed 117, 106, 115, 159);
+//  - on rows of at most 512 (128 experts, 512 x 512, r = 192: 56, 39, 43, 29; 256 experts: 120, 74, 57, 55, skewed 60, 35, 40, 32).
+int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
+                        int64_t kept_bound, hipStream_t st)
+{
+    const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
+    auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
+    constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kRound = 512;
+    const int64_t one_row = active * ((a.N + 255) / 256), rounds = (one_row + kRound - 1) / kRound;
+    const bool full_rounds = one_row * 10 >= rounds * kRound * (r < 64 ? 9 : 7);
+    if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
+    if (a.H >= 4096 && a.E <= 64 && r <= 100 && full_rounds) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
+    if (r <= 56 || tiles(64, 128) <= (a.H <= 1024 ? kFewTilesShortRows : kFewTiles))
+        return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
+    if (a.H <= 512 && a.E <= 128 && r <= 384) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
+    return launch_expert_big(x_final, w_exp, y, a, rows_bound, r, st);
 }
 
 int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int32_t *topk_idx, float *gates,

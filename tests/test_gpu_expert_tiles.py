@@ -47,6 +47,35 @@ def check(m, sizes, H, N, dtype):
     assert np.all(got[T].view(np.uint8) == 0x5A)
 
 
+# many experts on short rows, and few rows per expert on long ones, in nearly full rounds: the register-staged tiles
+def test_short_rows_many_experts(m):
+    check(m, [120 + (37 * e) % 33 for e in range(64)], 128, 1032, BF16)
+
+
+def test_long_rows_full_rounds(m):
+    """Close to 1 GB of weights: made, and multiplied for the reference, on the GPU (fp32 products and sums of these integers are
+    exact in any order; one rounding to bf16)."""
+    import torch
+    sizes, H, N = [40, 1, 0, 100, 33, 64, 65, 17], 4096, 57 * 256 + 8
+    T, E = sum(sizes), len(sizes)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randint(-4, 5, (T, H), generator=g, device="cuda").bfloat16()
+    w = torch.randint(-4, 5, (E, N, H), generator=g, device="cuda", dtype=torch.int8).bfloat16()
+    logits = torch.zeros((T, E), device="cuda")
+    expert = torch.repeat_interleave(torch.arange(E, device="cuda"), torch.tensor(sizes, device="cuda"))
+    logits[torch.arange(T, device="cuda"), expert] = 4.0
+    cfg = m.make_cfg(T, H, BF16, E, 1, 1, 1, 1, 0.0)
+    b = m.alloc_buffers(cfg, logits.cpu().numpy())
+    m.monta_route_dispatch_regather(cfg, b.logits, x, b.topk_idx, b.gates, b.stage, b.final, b.ws)
+    y = torch.full((T + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    m.monta_expert_linear(cfg, b.final, w, N, y[:T], b.ws)
+    assert bool(torch.isnan(y[T]).all())
+    for e in range(E):
+        rows = expert == e
+        if bool(rows.any()):
+            assert torch.equal(y[:T][rows], (x[rows].float() @ w[e].float().t()).bfloat16())
+
+
 # rows of a ragged tile around its 32-row steps (two halves of 16-row blocks), around the 64 rows of the short tile and around
 # whole tiles; columns of one lane group and of one and of two tiles
 @pytest.mark.parametrize("H", [64, 128, 192])
