@@ -324,7 +324,10 @@ int monta_get_plan_mode(void);
  * (streaming) accesses: 1 pack loads, 2 pack stores, 4 regather loads, 8 regather
  * stores, 16 combine loads, 32 combine stores.  A clear bit leaves that stream
  * cacheable, which pays when the next kernel finds the data in the memory-side cache.
- * -1 (default) lets the library choose from the working-set size.  Process-wide. */
+ * -1 (default) lets the library choose from the working-set size.  Process-wide.
+ * The single passes have fewer streams.  The dispatch's loads of x obey bit 1, its stores
+ * to STAGE bit 2, its stores to FINAL bit 8; the return path's loads of y obey bit 4, its
+ * stores to y_stage bit 8, its stores to out bit 32, and bit 16 has no effect there. */
 int monta_set_cache_policy(int policy);
 int monta_get_cache_policy(void);
 
@@ -345,7 +348,7 @@ int monta_copy(void *dst, const void *src, size_t bytes, void *stream);
  * returns the summed duration and the launch count of one kernel class since the
  * last reset.  Meant for benchmarks: it adds host work per launch. */
 enum monta_kernel_id {
-    MONTA_K_ROUTE = 0,      /* top-k + gates + histogram + scan               */
+    MONTA_K_ROUTE = 0,      /* top-k + gates + histogram                      */
     MONTA_K_POSITIONS = 1,  /* per-pair positions and row map                 */
     MONTA_K_PACK = 2,
     MONTA_K_REGATHER = 3,
@@ -362,7 +365,8 @@ enum monta_kernel_id {
     MONTA_K_PLACE = 14,     /* pack and regather in one pass                  */
     MONTA_K_PLAN_PLACE = 15, /* the same with the plan tables finished in the same grid */
     MONTA_K_RETURN = 16,    /* the mirrored return path in one pass           */
-    MONTA_K_COUNT = 17
+    MONTA_K_SCAN = 17,      /* scan of a histogram table too large to rebuild  */
+    MONTA_K_COUNT = 18
 };
 int monta_profile_enable(int on);
 int monta_profile_reset(void);

@@ -19,7 +19,8 @@ FP32, BF16 = 0, 1
 (K_ROUTE, K_POSITIONS, K_PACK, K_REGATHER, K_PACK_REGATHER, K_COMBINE, K_COPY, K_PLAN_PACK, K_UNREGATHER,
  K_UNREGATHER_COMBINE, K_ALLGATHER, K_GATE, K_EXPERT) = range(13)
 KERNEL_NAMES = ["route_plan", "positions", "pack", "regather", "pack_regather", "combine", "copy", "plan_pack",
-                "unregather", "unregather_combine", "allgather", "gate", "expert", "allgather_regather", "place", "plan_place", "return"]
+                "unregather", "unregather_combine", "allgather", "gate", "expert", "allgather_regather", "place", "plan_place", "return",
+                "block_scan"]
 
 
 class MontaError(RuntimeError):
