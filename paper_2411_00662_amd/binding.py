@@ -180,14 +180,15 @@ _raw_stream = None
 
 def _current_raw_stream() -> int:
     """The current device's current stream as a handle.  torch.cuda.current_stream() builds a Stream object around it, which
-    takes longer (2.8 us, against 0.3) than launching a kernel; a small step makes two such calls."""
+    takes longer (2.8 us, against 0.3) than launching a kernel; a small step makes two such calls.  The two functions behind it
+    are not part of torch's documented interface: where one is missing the Stream object serves."""
     global _raw_stream
     if _raw_stream is None:
         import torch
         torch.cuda.current_stream()         # initialises the runtime
-        _raw_stream = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-    get, device = _raw_stream
-    return get(device())
+        get, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        _raw_stream = (lambda: get(device())) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
 
 
 def _stream(stream) -> int:

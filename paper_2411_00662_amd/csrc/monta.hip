@@ -510,14 +510,16 @@ int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     return MONTA_OK;
 }
 
+// nb: groups of 16 experts per workgroup, 1 or 2 (bf16), 1 or 4 (fp32)
 template <bool BF16>
 int launch_gate_split(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int64_t cpr, int E, int nb, hipStream_t st)
 {
     const int64_t grid = (T + 15) / 16 * ((E + 16 * nb - 1) / (16 * nb));
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    if (nb == 4) hipLaunchKernelGGL((gate_split_kernel<BF16, 4>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
-    else if (nb == 2) hipLaunchKernelGGL((gate_split_kernel<BF16, 2>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
-    else hipLaunchKernelGGL((gate_split_kernel<BF16, 1>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
+    constexpr int kMany = BF16 ? 2 : 4;
+    if (nb == kMany) hipLaunchKernelGGL((gate_split_kernel<BF16, kMany>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
+    else if (nb == 1) hipLaunchKernelGGL((gate_split_kernel<BF16, 1>), dim3((unsigned)grid), dim3(512), 0, st, x, w, logits, T, cpr, E);
+    else return MONTA_ERR_UNSUPPORTED;
     return MONTA_OK;
 }
 
@@ -654,7 +656,10 @@ int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int3
     auto with_groups = [&](auto lc) -> int {
         if (per_lane <= 8) return launch(lc, std::integral_constant<int, 2>{});
         if (per_lane <= 16) return launch(lc, std::integral_constant<int, 4>{});
-        return launch(lc, std::integral_constant<int, 8>{});
+        // one or two lanes share a token only below 16 and 32 experts, four or eight have at most 28 and 32 each (LDS budget)
+        if constexpr (decltype(lc)::value >= 4)
+            if (per_lane <= 32) return launch(lc, std::integral_constant<int, 8>{});
+        return MONTA_ERR_UNSUPPORTED;
     };
     int rc;
     if (g.s.rl == 1) rc = with_groups(std::integral_constant<int, 1>{});
@@ -729,7 +734,7 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
             rc = launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
         if (rc) return rc;
     } else {
-            const int64_t row_tiles = rows_bound / kF32Tile + s.E, nct = (out_features + kF32Tile - 1) / kF32Tile;
+        const int64_t row_tiles = rows_bound / kF32Tile + s.E, nct = (out_features + kF32Tile - 1) / kF32Tile;
         const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
         if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(expert_f32_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const u32x4 *>(x_final),

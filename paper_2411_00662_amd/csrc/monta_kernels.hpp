@@ -115,7 +115,7 @@ __host__ __device__ inline int route_row_stride(int E, int L) { return L * (((E 
 //  2. k selections per token: the next winner is the largest element that comes after the previous winner in (value
 //     desc, index asc) order, so ties resolve to the lower index with no "taken" mask.  Lane `sub` of a token has every
 //     s.rl-th expert, in four groups of at most GS consecutive ones, and keeps the best remaining element of each group:
-//     only the group that the last winner came from has to be scanned again.  The lanes of a token agree by xor-shuffles.
+//     only the group that the last winner came from has to be scanned again.  The lanes of a token agree through DPP moves.
 //  3. gates in fp64 from the winners' logits, one rounding to fp32;
 //  4. every lane ORs its bit into mask[expert][wave] in LDS; popcounts of those
 //     masks give the workgroup's expert histogram and each pair's stable rank inside
@@ -2563,8 +2563,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
 
 // Gate projection of a few thousand tokens on more than 8 experts: the same tiles, tokens x experts, sums stored as they are.
 // Bound by the trips of x and of the weights through the L2: T E row (1 / XR + 1 / WR) bytes.  Against 32-token workgroups
-// with the k-slices dealt to 8 waves: 16384 x 7168, 256 experts 193 -> 90 us, 8192 x 4096, 256 experts 63 -> 36, 1024 x 7168,
-// 256 experts 92 -> 36, 16384 x 4096, 32 experts 36 -> 25.
+// with the k-slices dealt to 8 waves: 16384 x 7168, 256 experts 190 -> 91 us, 8192 x 4096, 256 experts 61 -> 37, 1024 x 7168,
+// 256 experts 92 -> 35; with 32 experts one tile holds them all in both forms: 16384 x 4096 37 and 37.
 template <int XR, int WR, int NST>
 __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                             float *__restrict__ logits, int64_t T, int H, int E)
