@@ -186,9 +186,11 @@ def _current_raw_stream() -> int:
     if _raw_stream is None:
         import torch
         torch.cuda.current_stream()         # initialises the runtime
-        get, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
-        _raw_stream = (lambda: get(device())) if get and device else (lambda: torch.cuda.current_stream().cuda_stream)
-    return _raw_stream()
+        _raw_stream = tuple(getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        if None in _raw_stream:
+            _raw_stream = (lambda _: torch.cuda.current_stream().cuda_stream), (lambda: None)
+    get, device = _raw_stream
+    return get(device())
 
 
 def _stream(stream) -> int:
