@@ -22,7 +22,7 @@ using namespace monta;
 
 
 thread_local int g_last_hip = 0;
-std::atomic<int> g_pipeline_mode{-1};  // -1: chosen from the bytes one slice moves
+std::atomic<int> g_pipeline_mode{-1};  // -1: one pass; 0, 1, 2: separate passes, one slice per launch
 std::atomic<int> g_plan_mode{-1};      // -1: per-workgroup rebuild when the histogram table is small; 0: always the scan kernel
 std::atomic<int> g_cache_policy{-1};   // -1: chosen from the working-set size
 
