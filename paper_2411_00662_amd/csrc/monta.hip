@@ -498,15 +498,15 @@ int launch_gate_small_any(const u32x4 *x, const u32x4 *w, float *logits, int64_t
     return 1;
 }
 
-template <int XR, int WR, int NST>
+template <int XR, int WR, int NST, bool F32 = false>
 int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
 {
     using G = ShortTile<XR, WR, NST>;
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_short_kernel<XR, WR, NST>), G::kLdsBytes, lds_opt_in)) return rc;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t grid = (T + XR - 1) / XR * ((E + WR - 1) / WR);
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E);
+    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E);
     return MONTA_OK;
 }
 
@@ -534,16 +534,23 @@ int launch_gate_f32_few(const float4 *x, const float4 *w, float *logits, int64_t
     return MONTA_OK;
 }
 
-template <bool RAGGED_LAST, bool DEEP_W>
-int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t grid, hipStream_t st)
+template <bool RAGGED_LAST, bool DEEP_W, bool TAIL>
+int launch_expert_big_k(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t grid, hipStream_t st)
 {
     static LdsOptIn lds_opt_in;
     constexpr int lds = big_lds_bytes(DEEP_W);
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_big_kernel<RAGGED_LAST, DEEP_W>), lds, lds_opt_in)) return rc;
-    hipLaunchKernelGGL((expert_big_kernel<RAGGED_LAST, DEEP_W>), dim3((unsigned)grid), dim3(kBigThreads), lds, st,
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_big_kernel<RAGGED_LAST, DEEP_W, TAIL>), lds, lds_opt_in)) return rc;
+    hipLaunchKernelGGL((expert_big_kernel<RAGGED_LAST, DEEP_W, TAIL>), dim3((unsigned)grid), dim3(kBigThreads), lds, st,
                        static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
                        static_cast<unsigned short *>(y), a);
     return MONTA_OK;
+}
+
+template <bool RAGGED_LAST, bool DEEP_W>
+int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t grid, hipStream_t st)
+{
+    return a.H % 64 ? launch_expert_big_k<RAGGED_LAST, DEEP_W, true>(x_final, w_exp, y, a, grid, st)
+                    : launch_expert_big_k<RAGGED_LAST, DEEP_W, false>(x_final, w_exp, y, a, grid, st);
 }
 
 int launch_expert_big(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
@@ -570,19 +577,18 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, const Exp
                   : launch_expert_big_t<false, false>(x_final, w_exp, y, a, grid, st);
 }
 
-template <int XR, int WR, int NST>
+template <int XR, int WR, int NST, bool F32 = false>
 int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, hipStream_t st)
 {
     using G = ShortTile<XR, WR, NST>;
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST>), G::kLdsBytes, lds_opt_in)) return rc;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t row_tiles = rows_bound / XR + std::min<int64_t>(a.E, rows_bound);
     const int64_t nct = (a.N + WR - 1) / WR;
     const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((expert_short_kernel<XR, WR, NST>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st,
-                       static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp),
-                       static_cast<unsigned short *>(y), a);
+    hipLaunchKernelGGL((expert_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st,
+                       static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp), y, a);
     return MONTA_OK;
 }
 
@@ -619,7 +625,10 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
 //    250, 188; 64 experts, 4096 x 1536, three quarters of a round, 80: 241, 192, 211, 174; but 5120 x 1536, 40: 241, 177, 207, 210).  With
 //    more experts a skewed load leaves many without rows, and there it is the worst form (256 experts, 4096 x 512, r = 64: even
 //    293, 251, 257, 208; skewed 117, 106, 115, 159);
-//  - on rows of at most 512 (128 experts, 512 x 512, r = 192: 56, 39, 43, 29; 256 experts: 120, 74, 57, 55, skewed 60, 35, 40, 32).
+//  - on rows of at most 512 (128 experts, 512 x 512, r = 192: 56, 39, 43, 29; 256 experts: 120, 74, 57, 55, skewed 60, 35, 40, 32);
+//  - on rows that are not whole steps, whose lines the large tile fetches twice, where an expert's second large tile would be
+//    half empty (16 experts, 8184 x 2048, r = 300: 614, 378, 363, 326; 64 experts, 3000 x 1024: 472, 279, 285, 265; r = 1000: 1537,
+//    773, 536, 614; r = 150: 270, 176, 121, 152).
 int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
                         int64_t kept_bound, hipStream_t st)
 {
@@ -633,7 +642,31 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
     if (r <= 56 || tiles(64, 128) <= (a.H <= 1024 ? kFewTilesShortRows : kFewTiles))
         return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
     if (a.H <= 512 && a.E <= 128 && r <= 384) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
+    if (a.H % 64 && r > kBigBM && r <= kBigBM * 3 / 2) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     return launch_expert_big(x_final, w_exp, y, a, rows_bound, r, st);
+}
+
+// fp32: tiles of 32 x 64, three stages, up to four workgroups per CU (up to 24 rows per expert, where the weights' trip from memory
+// is what takes the time, four: 16 experts of 2048 x 1024, 2 rows 27.9 and 24.9 us; 8 of 1024 x 1024, 200 rows 42 and 52); 64 x 64 where most experts fit one tile's rows and not the
+// half, which reads the weights once instead of twice, unless that leaves CUs without two tiles.  Measured on MI355X, 32 x 64 and
+// 64 x 64, 48 rows per expert: 16 experts of 5120 x 2048 214 and 190 us, 256 of 512 x 512 99 and 91; 2 of 4096 x 4096 62 and 87, 8 of
+// 516 x 516 10.9 and 15.5.  200 rows: 256 of 512 x 512 289 and 295, 64 of 1000 x 512 145 and 147.  Wider tiles, 32 x 128 and 64 x
+// 128, were nowhere faster by more than 3 % and up to twice slower.
+int launch_expert_f32(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
+                      int64_t kept_bound, hipStream_t st)
+{
+    if (a.H > kBigMaxHidden) {
+        const int64_t row_tiles = rows_bound / kF32Tile + a.E, nct = (a.N + kF32Tile - 1) / kF32Tile;
+        const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
+        if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+        hipLaunchKernelGGL(expert_f32_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const u32x4 *>(x_final),
+                           static_cast<const u32x4 *>(w_exp), static_cast<float *>(y), a);
+        return MONTA_OK;
+    }
+    const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
+    if (r > 32 && r <= 64 && active * ((a.N + 63) / 64) >= 512) return launch_expert_short_t<64, 64, 3, true>(x_final, w_exp, y, a, rows_bound, st);
+    if (r <= 24) return launch_expert_short_t<32, 64, 4, true>(x_final, w_exp, y, a, rows_bound, st);
+    return launch_expert_short_t<32, 64, 3, true>(x_final, w_exp, y, a, rows_bound, st);
 }
 
 int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int32_t *topk_idx, float *gates,
@@ -726,19 +759,16 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     const int64_t rows_bound = slice < 0 ? kept_bound : std::min<int64_t>(kept_bound, (int64_t)(s.T / s.S) * s.k);
     ProfScope ps(MONTA_K_EXPERT, st);
     if (cfg->dtype == MONTA_BF16) {
-        // The direct-to-LDS kernels take whole 64-element steps.  The choice of tile looks at the whole problem, not at the
-        // slice, so that a slice runs as the whole would.
-        if (cfg->hidden % 64 == 0 && cfg->hidden <= kBigMaxHidden)
+        // The offsets inside a direct-to-LDS tile have 31 bits.  The choice of tile looks at the whole problem, not at the slice,
+        // so that a slice runs as the whole would.
+        if (cfg->hidden <= kBigMaxHidden)
             rc = launch_expert_tiled(x_final, w_exp, y, a, rows_bound, kept_bound, st);
         else
             rc = launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
         if (rc) return rc;
     } else {
-        const int64_t row_tiles = rows_bound / kF32Tile + s.E, nct = (out_features + kF32Tile - 1) / kF32Tile;
-        const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
-        if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL(expert_f32_kernel, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const u32x4 *>(x_final),
-                           static_cast<const u32x4 *>(w_exp), static_cast<float *>(y), a);
+        rc = launch_expert_f32(x_final, w_exp, y, a, rows_bound, kept_bound, st);
+        if (rc) return rc;
     }
     HIP_TRY(hipGetLastError());
     return MONTA_OK;

@@ -2115,14 +2115,14 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr uint32_t kOutOfRange = 0x80000000u;                      // a lane offset past every descriptor: no access
 
 // Scalar offset of a step's 128 bytes in every row of a tile of `nsteps` steps.  The range check of a buffer load compares the
-// lane's offset with num_records - scalar offset in 32 bits, and the smallest descriptor is one row of nsteps * 128 bytes: the
-// scalar offset must stay below that, or the difference wraps and every lane offset counts as in range.  Steps past the end,
+// lane's offset with num_records - scalar offset in 32 bits, and the smallest descriptor is one row, whose last step may hold a
+// single piece of 16 bytes: the scalar offset must stay below that, or the difference wraps and every lane offset counts as in range.  Steps past the end,
 // whose lanes are out of range anyway, therefore take 0.
 __host__ __device__ constexpr uint32_t step_offset(int step, int nsteps) { return step < nsteps ? (uint32_t)step * 128u : 0u; }
 constexpr bool step_offsets_stay_inside(int nsteps, int past)
 {
     for (int step = 0; step < nsteps + past; ++step) {
-        const uint32_t records = (uint32_t)nsteps * 128u, so = step_offset(step, nsteps);
+        const uint32_t records = (uint32_t)(nsteps - 1) * 128u + 16u, so = step_offset(step, nsteps);
         if (so >= records || kOutOfRange < records - so) return false;
     }
     return true;
@@ -2145,7 +2145,8 @@ __device__ __forceinline__ uint2 pack_bf16x4(f32x4 v)
 // NST - 1 steps in flight.  Four waves, each all rows x WR / 4 columns.  Every wave issues the same number of loads per step,
 // also past the end (out of range: no traffic), because the wait for a stage counts the younger loads.  The barrier is the
 // bare instruction behind a wait for the LDS reads: the compiler's own barrier would wait for every outstanding load, the
-// next stages' included.
+// next stages' included.  A row is `cpr` pieces of 16 bytes, a step 8 of them; the pieces of the last step that lie past the end
+// of the row are out of range, too, and multiply as zeros.
 template <int XR, int WR, int NST>
 struct ShortTile {
     static constexpr int kStageBytes = (XR + WR) * 128, kLdsBytes = NST * kStageBytes;
@@ -2155,39 +2156,47 @@ struct ShortTile {
     static_assert(XR % 32 == 0 && WR % 64 == 0 && NST >= 3 && kYounger < 64, "short tile: shape");
 };
 
+// F32: the activations and weights are fp32, 32 of them per step; a lane's 16 bytes are then four elements for four 16x16x4
+// MFMAs, each of which takes the same element of the four pieces of half a step.
 // T: unsigned short, y is rounded to bf16; float, the sums themselves are stored (N columns, any N) and are taken in two
-// levels, 512 elements of the hidden axis at a time, so that a long row costs no precision.
-template <int XR, int WR, int NST, typename T>
-__device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int H,
+// levels, 8 steps of the hidden axis at a time, so that a long row costs no precision.  VEC: rows of y are whole 16-byte vectors.
+template <int XR, int WR, int NST, bool F32, bool VEC, typename T>
+__device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
                                                   int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds)
 {
     using G = ShortTile<XR, WR, NST>;
     constexpr int RB = XR / 16, CB = WR / 64;                      // 16-row blocks, 16-column blocks of a wave
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));      // share nothing with the caller's other path, which has no register left to keep it in
-    const int lane = tid & 63, wave = tid >> 6, m = lane & 15, g = lane >> 4;
-    const int nsteps = H / 64;
-    const uint32_t rowb = (uint32_t)H * 2;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = lane & 15, g = lane >> 4;
+    const int nsteps = (cpr + 7) / 8;
+    const uint32_t rowb = (uint32_t)cpr * 16;
     const int lr = lane >> 3;
     // row of the lane in chunk c: 8 c + lane / 8, so (row / 2) % 8 = (4 c + lr / 2) % 8
-    auto offset = [&](int c) { return (uint32_t)(c * 8 + lr) * rowb + (((lane & 7) ^ ((4 * c + (lr >> 1)) & 7)) * 16); };
+    auto piece = [&](int c) { return (lane & 7) ^ ((4 * c + (lr >> 1)) & 7); };
+    auto offset = [&](int c) { return (uint32_t)(c * 8 + lr) * rowb + piece(c) * 16; };
     uint32_t ox[G::kCX], ow[G::kCW];
 #pragma unroll
     for (int q = 0; q < G::kCX; ++q) ox[q] = offset(wave * G::kCX + q);
 #pragma unroll
     for (int q = 0; q < G::kCW; ++q) ow[q] = offset(wave * G::kCW + q);
-    auto issue = [&](int step, int slot) {
-        unsigned char *base = lds + slot * G::kStageBytes;
-        const uint32_t past = step < nsteps ? 0u : kOutOfRange;
-        const uint32_t so = step_offset(step, nsteps);
+    auto load = [&](unsigned char *base, uint32_t so, auto lane_offset) {
 #pragma unroll
         for (int q = 0; q < G::kCW; ++q)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * G::kCW + q) * 1024), 16, ow[q] | past,
-                                                     so, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * G::kCW + q) * 1024), 16,
+                                                     lane_offset(wave * G::kCW + q, ow[q]), so, 0, 0);
 #pragma unroll
         for (int q = 0; q < G::kCX; ++q)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * G::kCX + q) * 1024), 16, ox[q] | past,
-                                                     so, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * G::kCX + q) * 1024), 16,
+                                                     lane_offset(wave * G::kCX + q, ox[q]), so, 0, 0);
+    };
+    auto issue_whole = [&](int step, int slot) {                   // the row holds all 8 pieces of the step
+        load(lds + slot * G::kStageBytes, step_offset(step, nsteps), [&](int, uint32_t o) { return o; });
+    };
+    auto issue_any = [&](int step, int slot) {
+        const int left = cpr - step * 8;                           // pieces of the row in this step; none past the end
+        load(lds + slot * G::kStageBytes, step_offset(step, nsteps),
+             [&](int c, uint32_t o) { return piece(c) < left ? o : kOutOfRange; });
     };
     f32x4 acc[RB][CB];
 #pragma unroll
@@ -2205,49 +2214,74 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     const unsigned char *px = lds + m * 128, *pw = lds + (XR + wave * (WR / 4) + m) * 128;
     const int nb = (int)((row_end - row0 + 15) / 16);              // 16-row blocks with rows of the segment
 
+    // one 16-row block times the wave's columns: half a step, or, of fp32 elements, element v of its pieces
+    auto multiply = [&](const f32x4(&fw)[CB], const f32x4 &fx, f32x4(&to)[CB], int v) {
 #pragma unroll
-    for (int q = 0; q < NST - 1; ++q) issue(q, q);
+        for (int j = 0; j < CB; ++j) {
+            if constexpr (F32) to[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][v], fx[v], to[j], 0, 0, 0);
+            else to[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[j]), __builtin_bit_cast(bf16x8, fx), to[j], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < NST - 1; ++q) issue_any(q, q);
     int slot = 0;
-    auto walk = [&](int from, int to) {
+    // steps [from, to), whose loads ahead are of whole steps or not; the first BLOCKS blocks of rows are multiplied
+    auto walk = [&](auto blocks, auto whole, int from, int to) {
+        constexpr int BLOCKS = decltype(blocks)::value;
         for (int step = from; step < to; ++step) {
             __builtin_amdgcn_s_waitcnt(G::kWait);                      // stage `step` has landed (loads finish in order)
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): this wave's reads of the previous stage
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            issue(step + NST - 1, slot == 0 ? NST - 1 : slot - 1);     // the slot of stage step-1, free now
+            const int free_slot = slot == 0 ? NST - 1 : slot - 1;      // of stage step-1
+            if constexpr (decltype(whole)::value) issue_whole(step + NST - 1, free_slot);
+            else issue_any(step + NST - 1, free_slot);
             const int buf = slot * G::kStageBytes;
+            // all fragments of the step first, so that the reads' latency is paid once
+            f32x4 fw[2][CB], fx[2][BLOCKS];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                const int ko = ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
-                bf16x8 fw[CB];
+                const int at = buf + ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
 #pragma unroll
-                for (int j = 0; j < CB; ++j) fw[j] = *reinterpret_cast<const bf16x8 *>(pw + buf + ko + j * 2048);
+                for (int j = 0; j < CB; ++j) fw[ks][j] = *reinterpret_cast<const f32x4 *>(pw + at + j * 2048);
 #pragma unroll
-                for (int i = 0; i < RB; ++i)
-                    if (i < nb) {
-                        const bf16x8 fx = *reinterpret_cast<const bf16x8 *>(px + buf + ko + i * 2048);
-#pragma unroll
-                        for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j], fx, acc[i][j], 0, 0, 0);
-                    }
+                for (int i = 0; i < BLOCKS; ++i) fx[ks][i] = *reinterpret_cast<const f32x4 *>(px + at + i * 2048);
             }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int v = 0; v < (F32 ? 4 : 1); ++v)
+#pragma unroll
+                    for (int i = 0; i < BLOCKS; ++i) multiply(fw[ks], fx[ks][i], acc[i], v);
             slot = slot == NST - 1 ? 0 : slot + 1;
         }
     };
-    if constexpr (kLevels) {
-        for (int from = 0; from < nsteps; from += 8) {
-            walk(from, min(from + 8, nsteps));
+    // With at most half of the row blocks in use only those are multiplied.  One choice before the loop, as for the steps that are
+    // not whole: with a condition per block inside it a step waits for one read after the other (2 rows each of 16 experts of 5120 x
+    // 152, 48 workgroups: 21.8 us, now 16.4; 2 experts of 8192 x 64, 60 rows: 38 and 25).
+    auto run = [&](auto blocks) {
+        const int whole_to = cpr / 8 - (NST - 1);                      // up to here the step NST - 1 ahead is a whole one
+        constexpr int kSpan = kLevels ? 8 : 1 << 30;
+        for (int from = 0; from < nsteps; from += kSpan) {
+            const int to = kLevels ? min(from + kSpan, nsteps) : nsteps, mid = min(max(whole_to, from), to);
+            walk(blocks, std::true_type{}, from, mid);
+            walk(blocks, std::false_type{}, mid, to);
+            if constexpr (kLevels) {
 #pragma unroll
-            for (int i = 0; i < RB; ++i)
+                for (int i = 0; i < decltype(blocks)::value; ++i)
 #pragma unroll
-                for (int j = 0; j < CB; ++j) {
-                    total[i][j] += acc[i][j];
-                    acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                }
+                    for (int j = 0; j < CB; ++j) {
+                        total[i][j] += acc[i][j];
+                        acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    }
+            } else {
+                break;
+            }
         }
-    } else {
-        walk(0, nsteps);
-    }
+    };
+    if (2 * nb <= RB) run(std::integral_constant<int, RB / 2>{});
+    else run(std::integral_constant<int, RB>{});
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         const int64_t r = row0 + i * 16 + m;
@@ -2256,9 +2290,13 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
             for (int j = 0; j < CB; ++j) {
                 const int n = col0 + wave * (WR / 4) + j * 16 + 4 * g;
                 if constexpr (std::is_same<T, float>::value) {
+                    if constexpr (VEC) {
+                        if (n < N) *reinterpret_cast<f32x4 *>(y + r * N + n) = total[i][j];
+                    } else {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (n + v < N) y[r * N + n + v] = total[i][j][v];
+                        for (int v = 0; v < 4; ++v)
+                            if (n + v < N) y[r * N + n + v] = total[i][j][v];
+                    }
                 } else {
                     if (n < N) *reinterpret_cast<uint2 *>(y + r * N + n) = pack_bf16x4(acc[i][j]);
                 }
@@ -2270,15 +2308,21 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 // Few rows per expert (a decoding step): every weight is read once for a handful of rows, and the layer lasts as long as
 // the weights take to arrive from memory.  Two workgroups per CU, 128 KiB of loads in flight per CU.  Measured on MI355X,
 // register-staged 128 x 256 tiles before, now (floor: the weights at 6.4 TB/s): 8 experts of 4096 x 4096, 16 rows each 138 ->
-// 41 us (42); 64 of 7168 x 2048, 16 rows 314 -> 311 us (294); 64 of 2048 x 2048 133 -> 98 us (84).  Streaming the weights
-// straight into registers in the MFMA's layout (16 rows x 64 bytes per load) was measured too: 61, 434 and 121 us.
-template <int XR, int WR, int NST>
+// 41 us (42); 64 of 7168 x 2048, 16 rows 314 -> 311 us (294); 64 of 2048 x 2048 133 -> 98 us (84); rows that are not whole steps:
+// 2 of 7464 x 1904, 16 rows 199 -> 33 us, 8 of 1032 x 4096, 16 rows 55 -> 15 us (11).  Streaming the weights straight into
+// registers in the MFMA's layout (16 rows x 64 bytes per load) was measured too: 61, 434 and 121 us.
+// fp32, any number of rows: the same tiles, where the barrier and the reads of a step cost less than its MFMAs (16 of 32 clocks
+// each for a wave of the 32 x 64 tile).  A 64 x 64 tile with one step in flight through registers before, now: 2 experts of 4096 x
+// 4096, 8 rows each 108 -> 49 us (21), 10 of 516 x 516, about 240 rows 30 -> 19 us, 8 of 1024 x 1024, 600 rows 113 -> 100 us
+// (70 at the 143 TFLOP/s of a library GEMM); error against 64 bits at 8192 elements 1.6e-6 -> 3.1e-7 (two levels of sums).
+template <int XR, int WR, int NST, bool F32>
 __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
-                                                              unsigned short *__restrict__ y, ExpertArgs a)
+                                                              void *__restrict__ y, ExpertArgs a)
 {
+    using T = std::conditional_t<F32, float, unsigned short>;
     extern __shared__ __align__(16) unsigned char short_lds[];
     const int lane = threadIdx.x & 63;
-    const int cpr = a.H / 8, nct = (a.N + WR - 1) / WR;
+    const int cpr = F32 ? a.H / 4 : a.H / 8, nct = (a.N + WR - 1) / WR;
     // numbers are dealt to the XCDs in blocks of 32, row tiles fastest: row tiles of one weight tile meet in one L2
     const int64_t j = blockIdx.x / kXcds;
     const int64_t L = (j / 32) * (32 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 32 + j % 32;
@@ -2290,13 +2334,14 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     const int seg_end = __builtin_amdgcn_readfirstlane(hit.hi < a.max_rows ? hit.hi : a.max_rows);
     if (row0 < 0 || row0 >= seg_end) return;
     const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
-    const uint32_t rowb = (uint32_t)a.H * 2;
-    expert_short_tile<XR, WR, NST>(make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb),
-                                   make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb), y, a.H,
-                                   a.N, row0, row_end, col0, short_lds);
+    const uint32_t rowb = (uint32_t)cpr * 16;
+    expert_short_tile<XR, WR, NST, F32, F32>(make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb),
+                                             make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb),
+                                             static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
 }
 
-template <bool RAGGED_LAST, bool DEEP_W>
+// TAIL: rows are not whole steps; the last step's pieces past the end of a row are out of range.
+template <bool RAGGED_LAST, bool DEEP_W, bool TAIL>
 __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                                     unsigned short *__restrict__ y, ExpertArgs a)
 {
@@ -2304,7 +2349,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     constexpr int BM = kBigBM, BN = kBigBN, P = 8;                 // P: row tiles of a panel
     extern __shared__ __align__(16) unsigned char big_lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cpr = a.H / 8, nsteps = a.H / 64;
+    const int cpr = a.H / 8, nsteps = (cpr + 7) / 8;
     const int nct = (a.N + BN - 1) / BN;
 
     // Tile of this workgroup.  Hardware deals consecutive workgroups round robin to the 8 XCDs, each with its own L2;
@@ -2391,12 +2436,12 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const int xr = min(row_end - row0, BM);
     const int cols = xr <= kShortRows ? kShortCols : BN, col0 = ct * cols;
     if (col0 >= a.N) return;                                       // the second half of a last column tile may be empty
-    const uint32_t rowb = (uint32_t)a.H * 2;
+    const uint32_t rowb = (uint32_t)cpr * 16;
     const int wr = min(a.N - col0, cols);
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= kShortRows) {                                        // tiles with little arithmetic
-        expert_short_tile<64, kShortCols, kStages>(rx, rw, y, a.H, a.N, row0, row_end, col0, big_lds);
+        expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds);
         return;
     }
 
@@ -2412,6 +2457,18 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         uint32_t rows = (uint32_t)(q >> 1) * (16 * rowb);
         asm volatile("" : "+s"(rows));                             // added at each use: eight offsets kept would be spilled
         return off2[q & 1] + rows;
+    };
+    // Before the first loads of step `step`, at whatever is the last step: the lane offsets of the pieces past the end of a row go
+    // out of range, for good (what is loaded after them is the last step again, into buffers that are not read any more).
+    auto trim = [&](int step) {
+        if constexpr (TAIL) {
+            const int left = step >= nsteps - 1 ? cpr - (nsteps - 1) * 8 : 8;
+            int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+            asm volatile("" : "+v"(l));                            // found again each time: kept, the pieces would be spilled
+#pragma unroll
+            for (int q = 0; q < 2; ++q)                            // rows 8 apart: pieces 4 apart, the wave's 64 rows make no difference
+                off2[q] |= ((l & 7) ^ ((4 * q + (l >> 4)) & 7)) >= left ? kOutOfRange : 0u;
+        }
     };
     unsigned char *const w_lds = big_lds + 2 * kBigXBytes;
     auto issue_x = [&](int q, int step, int at) {                 // `at`: byte offset of the stage among those of x, of w
@@ -2472,6 +2529,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
             mma(set, q / 2, (q & 1) * 4 + 0);
             mma(set, q / 2, (q & 1) * 4 + 1);
             if (loads) {
+                if (q == 0 && !DEEP_W) trim(sx);
+                if (q == 8 && DEEP_W) trim(sw);
                 if (q < 8) issue_x(q, sx, xto);
                 else issue_w(q - 8, sw, wto);
             }
@@ -2487,6 +2546,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
             read_w(set ^ 1, i, wat, ko);
             read_x(set ^ 1, i, xat, ko);
             if (loads) {
+                if (i == 0 && !DEEP_W) trim(sx);
+                if (i == 4 && DEEP_W) trim(sw);
                 if (i < 4) {
                     issue_x(2 * i, sx, xto);
                     issue_x(2 * i + 1, sx, xto);
@@ -2518,11 +2579,14 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
             wat = wnext;
         }
     };
+    trim(0);
 #pragma unroll
     for (int q = 0; q < 16; ++q) q & 1 ? issue_w(q / 2, 0, 0) : issue_x(q / 2, 0, 0);
+    trim(1);
 #pragma unroll
     for (int q = 0; q < 16; ++q) q & 1 ? issue_w(q / 2, min(1, nsteps - 1), kBigWBytes) : issue_x(q / 2, min(1, nsteps - 1), kBigXBytes);
     if constexpr (DEEP_W) {
+        trim(2);
 #pragma unroll
         for (int q = 0; q < 8; ++q) issue_w(q, min(2, nsteps - 1), 2 * kBigWBytes);
     }
@@ -2565,19 +2629,19 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
 // Bound by the trips of x and of the weights through the L2: T E row (1 / XR + 1 / WR) bytes.  Against 32-token workgroups
 // with the k-slices dealt to 8 waves: 16384 x 7168, 256 experts 190 -> 91 us, 8192 x 4096, 256 experts 61 -> 37, 1024 x 7168,
 // 256 experts 92 -> 35; with 32 experts one tile holds them all in both forms: 16384 x 4096 37 and 37.
-template <int XR, int WR, int NST>
+template <int XR, int WR, int NST, bool F32>
 __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                             float *__restrict__ logits, int64_t T, int H, int E)
 {
     extern __shared__ __align__(16) unsigned char gshort_lds[];
-    const int nct = (E + WR - 1) / WR, cpr = H / 8;
+    const int nct = (E + WR - 1) / WR, cpr = F32 ? H / 4 : H / 8;
     const int64_t t0 = (int64_t)(blockIdx.x / nct) * XR;
     const int e0 = (int)(blockIdx.x % nct) * WR;
     const int64_t t1 = t0 + XR < T ? t0 + XR : T;
-    const uint32_t rowb = (uint32_t)H * 2;
-    expert_short_tile<XR, WR, NST>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
-                                   make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, H, E, t0, t1, e0,
-                                   gshort_lds);
+    const uint32_t rowb = (uint32_t)cpr * 16;
+    expert_short_tile<XR, WR, NST, F32, false>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
+                                               make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, cpr, E, t0,
+                                               t1, e0, gshort_lds);
 }
 
 // Gate projection with the hidden axis split over the 8 waves of a workgroup: 16 tokens x 16 NB experts each.  For fp32
@@ -2688,12 +2752,11 @@ __global__ __launch_bounds__(512) void gate_split_kernel(const u32x4 *__restrict
     }
 }
 
-// fp32 activations: a 64 x 64 tile of y per workgroup of 4 waves (each 32 x 32, one accumulator of the 32x32x2 fp32 MFMA,
-// which rounds like fp32 fused multiply-adds), 32 elements of the hidden axis per step through registers into LDS.  A lane
-// takes four consecutive elements of its row with one LDS read: half g of the wave elements 8 p + 4 g .. + 3, element i of
-// both halves in MFMA i.  Rows are padded by 16 bytes.  Bound by the fp32 matrix rate (142 TFLOP/s in a library GEMM) where
-// the tiles fill the chip: 8192 tokens, top-2 of 8, 2048 x 2048 254 ms with one output per thread, 1.32 ms now (104
-// TFLOP/s); 1155 x 516, 10 experts, top-3, three tenths of the pairs dropped 2212 -> 29 us.
+// fp32 rows of more than kBigMaxHidden elements, whose tiles do not fit the 31-bit offsets of the direct loads: a 64 x 64 tile of y
+// per workgroup of 4 waves (each 32 x 32, one accumulator of the 32x32x2 fp32 MFMA), 32 elements of the hidden axis per step through
+// registers into LDS.  A lane takes four consecutive elements of its row with one LDS read: half g of the wave elements 8 p + 4 g ..
+// + 3, element i of both halves in MFMA i.  Rows are padded by 16 bytes.  One step in flight: 108 us for 8 rows of 4096 x 4096, where
+// the tiles above take 50.
 constexpr int kF32Tile = 64, kF32Step = 32, kF32RowStride = kF32Step * 4 + 16;
 
 __global__ __launch_bounds__(256) void expert_f32_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,

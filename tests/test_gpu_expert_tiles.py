@@ -126,3 +126,30 @@ def test_few_rows_many_columns(m):
 @pytest.mark.parametrize("N", [4, 32, 64, 132])
 def test_fp32_tiles(m, H, N):
     check(m, [1, 31, 32, 33, 0, 64, 65, 130], H, N, FP32)
+
+
+# rows that are not whole steps: a last step of one, of some and of all but one pieces of 16 bytes, alone, after fewer steps than
+# there are stages and after more; the pieces past a row's end belong to the next row (integers as well) or to nothing
+@pytest.mark.parametrize("H", [8, 56, 72, 184, 200, 328])
+@pytest.mark.parametrize("sizes,N", [
+    ([1, 17, 33, 0, 16], 72),                                                  # 32 x 64
+    ([65, 64, 1], 16264),                                                      # 64 x 128
+    ([65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 513, 64, 700], 2056),  # 256 x 256, the ragged tiles last ...
+    ([577, 320, 61, 257, 500], 4104),                                          # ... with the third stage of weights or without
+    ([65, 96, 97, 0, 129, 224, 225, 240, 255, 256, 257, 321, 64], 6664),       # in place
+    ([480, 512, 769, 33, 512], 6664 * 2),
+    ([300, 290, 310, 257, 384, 280, 1, 320], 1032),                            # register-staged
+], ids=["32x64", "64x128", "last-short", "last-long", "inplace-short", "inplace-long", "staged"])
+def test_ragged_steps(m, sizes, N, H):
+    check(m, sizes, H, N, BF16)
+
+
+# fp32 tiles of 64 x 64, and several levels of sums
+@pytest.mark.parametrize("H", [4, 36, 60, 260, 1100])
+def test_fp32_one_tile_per_expert(m, H):
+    check(m, [33, 40, 64, 1, 65, 48, 0, 47], H, 4100, FP32)
+
+
+@pytest.mark.parametrize("H", [508, 516, 1100])
+def test_fp32_levels(m, H):
+    check(m, [1, 16, 17, 33, 200], H, 132, FP32)
