@@ -743,6 +743,11 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     a.H = cfg->hidden;
     a.N = out_features;
     a.max_rows = s.max_rows;
+    // Weights of half the memory-side cache (256 MB) or more are gone from it by the next call: that is the case from 128 MiB on if
+    // three sets are used in turn (16 experts of 4096 x 1024, 16 rows: 29.5 us, streamed 26.1; 100 MB 19.1 and 18.1, 67 MB 13.0 and
+    // 15.0).  Rows and base have to be whole 128-byte lines.
+    const int64_t w_row = (int64_t)cfg->hidden * (cfg->dtype == MONTA_BF16 ? 2 : 4);
+    a.stream_w = (int64_t)s.E * out_features * w_row >= (128ll << 20) && w_row % 128 == 0 && !misaligned(w_exp, 128);
     // rows of expert e: its whole kept segment [offsets[e], offsets[e] + kept[e]), or the part of it filled by the
     // slice's units, which starts at unit_base[first unit of the slice][e] and ends where the next slice's starts
     a.lo = slice < 0 ? p.offsets : p.unit_base + (int64_t)slice * s.tp * s.E;

@@ -1891,6 +1891,7 @@ struct ExpertArgs {
     const int32_t *hi_base; // [E] one past its last row is hi_base[e] + hi_len[e] ...
     const int32_t *hi_len;  // [E] ... or hi_base[e] alone if this is nullptr
     int32_t E, H, N, max_rows;
+    int32_t stream_w;       // 1: weights that one workgroup reads are requested as streaming (kStreamLoad)
 };
 
 // The expert whose tiles include logical tile number L, found without walking the experts one by one (a walk costs
@@ -2112,6 +2113,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
 }
 typedef __attribute__((address_space(3))) void lds_void;
+// Cache bits of a buffer load: `nt`, no reuse expected.  On weights that only one workgroup reads and that would not stay in the
+// memory-side cache until the next call it is worth 10-17 %, as the lines push nothing else out on their way.  Where it is not: on
+// rows that are not whole lines (a line at the seam of two rows is fetched twice), on a tile with a second reader, on weights
+// that the cache does hold; and in the register-staged tiles it changes nothing (64 experts of 7168 x 2048, 60 rows: 333 us with
+// and without).  8 experts of 4096 x 4096, 16 rows: 55.5 and 46.4 us (42 at 6.4 TB/s); 64 of 7168 x 2048, 16 rows 311 and
+// 277; but 16 of 8184 x 2048 112 and 127; 16 of 4096 x 1024 in 32 x 64 tiles, 40 rows 31 and 37; 8 of 2048 x 2048 12.7 and 14.8.
+constexpr int kStreamLoad = 2;
 constexpr uint32_t kOutOfRange = 0x80000000u;                      // a lane offset past every descriptor: no access
 
 // Scalar offset of a step's 128 bytes in every row of a tile of `nsteps` steps.  The range check of a buffer load compares the
@@ -2160,7 +2168,8 @@ struct ShortTile {
 // MFMAs, each of which takes the same element of the four pieces of half a step.
 // T: unsigned short, y is rounded to bf16; float, the sums themselves are stored (N columns, any N) and are taken in two
 // levels, 8 steps of the hidden axis at a time, so that a long row costs no precision.  VEC: rows of y are whole 16-byte vectors.
-template <int XR, int WR, int NST, bool F32, bool VEC, typename T>
+// AUX_W: cache bits of the weights' loads.
+template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, typename T>
 __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
                                                   int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds)
 {
@@ -2184,7 +2193,7 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 #pragma unroll
         for (int q = 0; q < G::kCW; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (XR / 8 + wave * G::kCW + q) * 1024), 16,
-                                                     lane_offset(wave * G::kCW + q, ow[q]), so, 0, 0);
+                                                     lane_offset(wave * G::kCW + q, ow[q]), so, 0, AUX_W);
 #pragma unroll
         for (int q = 0; q < G::kCX; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * G::kCX + q) * 1024), 16,
@@ -2335,9 +2344,12 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     if (row0 < 0 || row0 >= seg_end) return;
     const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
     const uint32_t rowb = (uint32_t)cpr * 16;
-    expert_short_tile<XR, WR, NST, F32, F32>(make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb),
-                                             make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb),
-                                             static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
+    const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb);
+    const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb);
+    if (a.stream_w && __builtin_amdgcn_readfirstlane(hit.tiles) == 1)
+        expert_short_tile<XR, WR, NST, F32, F32, kStreamLoad>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
+    else
+        expert_short_tile<XR, WR, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
 }
 
 // TAIL: rows are not whole steps; the last step's pieces past the end of a row are out of range.
@@ -2371,6 +2383,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     constexpr int kWaitStage = DEEP_W ? 0x0078 : 0x0072, kWaitFirst = DEEP_W ? 0x4f78 : 0x4f70;       // vmcnt(24), vmcnt(16)
     int e = hit.e, row0 = 0, row_end = 0, ct = 0;
     int sharers = 1, share = 0;                                    // row tiles side by side on one weight tile; which of them
+    int alone = 0;                                                 // 1: the tile holds all rows of its expert
     if (e < a.E) {
         const int tiles = hit.tiles, full = tiles / P;             // whole panels
         int rt;
@@ -2389,6 +2402,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         }
         row0 = hit.lo + rt * BM;
         row_end = hit.hi < a.max_rows ? hit.hi : a.max_rows;
+        alone = hit.hi - hit.lo <= BM;
     } else if (RAGGED_LAST) {
         // ragged tiles: position L / nct in the order (rows in the ragged tile, descending; expert, ascending).  The
         // tile buffers are not in use yet, so their first bytes serve as the scratch of the ranking (E <= 256).
@@ -2421,6 +2435,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
             ct = (int)(halves < 0 ? Lr % nct : halves % (2 * nct));
             row0 = lo + (int)(((int64_t)hi - lo) / BM) * BM;
             row_end = hi < a.max_rows ? hi : a.max_rows;
+            alone = row0 == lo;
         }
     }
     // the same for the whole workgroup: into scalar registers
@@ -2430,6 +2445,9 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     sharers = __builtin_amdgcn_readfirstlane(sharers);
     share = __builtin_amdgcn_readfirstlane(share);
     ct = __builtin_amdgcn_readfirstlane(ct);
+    // Streamed weights only in the form whose tiles mostly have one user and whose rows are whole lines.
+    constexpr bool kMayStream = DEEP_W && !TAIL;
+    const bool stream = kMayStream && a.stream_w && __builtin_amdgcn_readfirstlane(alone);
     if (e >= a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup
     constexpr int kShortCols = RAGGED_LAST ? 128 : 256, kStages = RAGGED_LAST ? 5 : 3;
     static_assert(ShortTile<64, kShortCols, kStages>::kLdsBytes <= big_lds_bytes(DEEP_W), "short tile: stages must fit the kernel's LDS");
@@ -2441,7 +2459,10 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= kShortRows) {                                        // tiles with little arithmetic
-        expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds);
+        if (kMayStream && stream)
+            expert_short_tile<64, kShortCols, kStages, false, false, kMayStream ? kStreamLoad : 0>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds);
+        else
+            expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds);
         return;
     }
 
@@ -2476,6 +2497,9 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     };
     auto issue_w = [&](int q, int step, int at) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, 0);
+    };
+    auto stream_w = [&](int q, int step, int at) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, kStreamLoad);
     };
 
     // the early touches (not with the third stage of w)
@@ -2521,7 +2545,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     };
     // One slice: 64 MFMAs on fragment set `set`; between them the 16 reads of the other set (stages at xat and wat, piece
     // offset ko) and, if LOADS, the 8 loads of x for step sx and then the 8 of w for step sw, into the stages at xto and wto.
-    auto slice = [&](int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
+    auto slice = [&](auto load_w, int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             if (q < 8) read_w(set ^ 1, q, wat, ko);
@@ -2532,7 +2556,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
                 if (q == 0 && !DEEP_W) trim(sx);
                 if (q == 8 && DEEP_W) trim(sw);
                 if (q < 8) issue_x(q, sx, xto);
-                else issue_w(q - 8, sw, wto);
+                else load_w(q - 8, sw, wto);
             }
             mma(set, q / 2, (q & 1) * 4 + 2);
             mma(set, q / 2, (q & 1) * 4 + 3);
@@ -2540,7 +2564,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         }
     };
     // the same for a ragged tile: only the wave's nb blocks with rows are multiplied
-    auto slice_ragged = [&](int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
+    auto slice_ragged = [&](auto load_w, int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             read_w(set ^ 1, i, wat, ko);
@@ -2552,8 +2576,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
                     issue_x(2 * i, sx, xto);
                     issue_x(2 * i + 1, sx, xto);
                 } else {
-                    issue_w(2 * i - 8, sw, wto);
-                    issue_w(2 * i - 7, sw, wto);
+                    load_w(2 * i - 8, sw, wto);
+                    load_w(2 * i - 7, sw, wto);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -2563,17 +2587,17 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
             }
         }
     };
-    auto run = [&](auto slice_fn) {
+    auto run = [&](auto slice_fn, auto load_w) {
         int xat = 0, wat = 0;                                      // where stage s is
         for (int s = 0; s < nsteps; ++s) {
-            slice_fn(0, xat, wat, k1, false, 0, 0, 0, 0);
+            slice_fn(load_w, 0, xat, wat, k1, false, 0, 0, 0, 0);
             // lgkmcnt(0): this wave has read all of stage s; vmcnt(8 or 2): stage s+1 is in LDS, younger are only the 8 loads
             // of w for stage s+2, or the two early touches
             __builtin_amdgcn_s_waitcnt(kWaitStage);
             barrier();
             // past the end the last stage is fetched again, into buffers that are not read any more
             const int wnext = wat == (WST - 1) * kBigWBytes ? 0 : wat + kBigWBytes;
-            slice_fn(1, xat ^ kBigXBytes, wnext, k0, true, min(s + 2, nsteps - 1), xat, min(s + WST, nsteps - 1), wat);
+            slice_fn(load_w, 1, xat ^ kBigXBytes, wnext, k0, true, min(s + 2, nsteps - 1), xat, min(s + WST, nsteps - 1), wat);
             touch(s + 3);
             xat ^= kBigXBytes;
             wat = wnext;
@@ -2598,8 +2622,18 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         read_w(0, i, 0, k0);
         read_x(0, i, 0, k0);
     }
-    if (nb == 8) run(slice);
-    else run(slice_ragged);
+    if constexpr (kMayStream) {
+        if (stream) {
+            if (nb == 8) run(slice, stream_w);
+            else run(slice_ragged, stream_w);
+        } else {
+            if (nb == 8) run(slice, issue_w);
+            else run(slice_ragged, issue_w);
+        }
+    } else {
+        if (nb == 8) run(slice, issue_w);
+        else run(slice_ragged, issue_w);
+    }
     asm volatile("s_nop 15\n\ts_nop 15");                          // the last MFMAs' results
     __builtin_amdgcn_sched_barrier(0);
 

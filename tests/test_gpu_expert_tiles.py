@@ -52,28 +52,46 @@ def test_short_rows_many_experts(m):
     check(m, [120 + (37 * e) % 33 for e in range(64)], 128, 1032, BF16)
 
 
-def test_long_rows_full_rounds(m):
-    """Close to 1 GB of weights: made, and multiplied for the reference, on the GPU (fp32 products and sums of these integers are
-    exact in any order; one rounding to bf16)."""
+def check_on_gpu(m, sizes, H, N, dtype):
+    """Large weights: made, and multiplied for the reference, on the GPU (fp32 products and sums of these integers are exact in any
+    order; one rounding to bf16)."""
     import torch
-    sizes, H, N = [40, 1, 0, 100, 33, 64, 65, 17], 4096, 57 * 256 + 8
+    t = torch.float32 if dtype == FP32 else torch.bfloat16
     T, E = sum(sizes), len(sizes)
     g = torch.Generator(device="cuda").manual_seed(5)
-    x = torch.randint(-4, 5, (T, H), generator=g, device="cuda").bfloat16()
-    w = torch.randint(-4, 5, (E, N, H), generator=g, device="cuda", dtype=torch.int8).bfloat16()
+    x = torch.randint(-4, 5, (T, H), generator=g, device="cuda").to(t)
+    w = torch.randint(-4, 5, (E, N, H), generator=g, device="cuda", dtype=torch.int8).to(t)
     logits = torch.zeros((T, E), device="cuda")
     expert = torch.repeat_interleave(torch.arange(E, device="cuda"), torch.tensor(sizes, device="cuda"))
     logits[torch.arange(T, device="cuda"), expert] = 4.0
-    cfg = m.make_cfg(T, H, BF16, E, 1, 1, 1, 1, 0.0)
+    cfg = m.make_cfg(T, H, dtype, E, 1, 1, 1, 1, 0.0)
     b = m.alloc_buffers(cfg, logits.cpu().numpy())
     m.monta_route_dispatch_regather(cfg, b.logits, x, b.topk_idx, b.gates, b.stage, b.final, b.ws)
-    y = torch.full((T + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y = torch.full((T + 1, N), float("nan"), dtype=t, device="cuda")
     m.monta_expert_linear(cfg, b.final, w, N, y[:T], b.ws)
     assert bool(torch.isnan(y[T]).all())
     for e in range(E):
         rows = expert == e
         if bool(rows.any()):
-            assert torch.equal(y[:T][rows], (x[rows].float() @ w[e].float().t()).bfloat16())
+            assert torch.equal(y[:T][rows], (x[rows].float() @ w[e].float().t()).to(t))
+
+
+def test_long_rows_full_rounds(m):
+    """Close to 1 GB of weights."""
+    check_on_gpu(m, [40, 1, 0, 100, 33, 64, 65, 17], 4096, 57 * 256 + 8, BF16)
+
+
+# 128 MiB of weights and more, which are streamed where an expert's rows fit one tile and not where they take two
+@pytest.mark.parametrize("sizes,H,N,dtype", [
+    ([16, 1, 0, 17, 33, 5, 32, 40], 4096, 2056, BF16),                                   # 32 x 64
+    ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 4096, 2056, BF16),                              # 64 x 128
+    ([150, 256, 257, 65, 0, 64, 300, 255, 33] * 2, 4096, 2056, BF16),                    # 256 x 256, the ragged tiles last
+    ([150, 256, 257, 65, 0, 64, 300, 255] * 4, 2048, 2056, BF16),                        # in place
+    ([16, 1, 0, 17, 33, 5, 32, 40], 2048, 2052, FP32),
+    ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 1024, 2052, FP32),
+], ids=["32x64", "64x128", "last", "inplace", "fp32", "fp32-64x64"])
+def test_streamed_weights(m, sizes, H, N, dtype):
+    check_on_gpu(m, sizes, H, N, dtype)
 
 
 # rows of a ragged tile around its 32-row steps (two halves of 16-row blocks), around the 64 rows of the short tile and around
