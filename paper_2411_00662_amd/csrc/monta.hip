@@ -448,16 +448,16 @@ int opt_in_lds(const void *kernel, int bytes, LdsOptIn &state)
     return MONTA_OK;
 }
 
-template <int MT, int NT, int KS, bool DEEP, bool SPLIT = false>
+template <int MT, int NT, int KS, bool DEEP, bool SPLIT = false, bool STREAM = false>
 int launch_gate(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
 {
     using G = GateTile<MT, NT, KS>;
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_bf16_kernel<MT, NT, KS, DEEP, SPLIT>),
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_bf16_kernel<MT, NT, KS, DEEP, SPLIT, STREAM>),
                             (int)G::lds_bytes(32 * NT, !SPLIT), lds_opt_in))
         return rc;
     const unsigned grid = (unsigned)((T + G::kTokens - 1) / G::kTokens);
-    hipLaunchKernelGGL((gate_bf16_kernel<MT, NT, KS, DEEP, SPLIT>), dim3(grid), dim3(kGateThreads), G::lds_bytes(E, !SPLIT), st, x, w, logits,
+    hipLaunchKernelGGL((gate_bf16_kernel<MT, NT, KS, DEEP, SPLIT, STREAM>), dim3(grid), dim3(kGateThreads), G::lds_bytes(E, !SPLIT), st, x, w, logits,
                        T, H, E);
     return MONTA_OK;
 }
@@ -485,19 +485,6 @@ int launch_gate_small(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     return MONTA_OK;
 }
 
-// The whole-row kernel for at most 8 experts; returns 1 if the shape does not fit it.  Measured on MI355X: tiles
-// of 8 rows x 4 KiB serve rows of up to 8 KiB best (a workgroup then sees more, smaller tiles and starts
-// sooner), tiles of 8 rows x 8 KiB longer rows; more than one workgroup per CU only repeats the weight set-up.
-int launch_gate_small_any(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
-{
-    if (E > kGateSmallExperts) return 1;
-    if (H <= 2048 && H % 64 == 0) return launch_gate_small<1, 512, 2048>(x, w, logits, T, H, E, 1, st);
-    if (H <= 4096 && H % 128 == 0) return launch_gate_small<2, 512, 2048>(x, w, logits, T, H, E, 1, st);
-    if (H <= 4096 && H % 64 == 0) return launch_gate_small<1, 512, 4096>(x, w, logits, T, H, E, 1, st);
-    if (H <= 8192 && H % 128 == 0) return launch_gate_small<2, 512, 4096>(x, w, logits, T, H, E, 1, st);
-    return 1;
-}
-
 template <int XR, int WR, int NST, bool F32 = false>
 int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
 {
@@ -508,6 +495,23 @@ int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E);
     return MONTA_OK;
+}
+
+// The whole-row kernel for at most 8 experts; returns 1 if the shape does not fit it.  Measured on MI355X: tiles
+// of 8 rows x 4 KiB serve rows of up to 8 KiB best (a workgroup then sees more, smaller tiles and starts
+// sooner), tiles of 8 rows x 8 KiB longer rows; there more than one workgroup per CU only repeats the weight set-up.
+int launch_gate_small_any(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
+{
+    if (E > kGateSmallExperts) return 1;
+    // short rows: two workgroups per CU, a tile's latency under the other's (65536 x 2048, 8 experts 60 and 50 us, 8192 x 1536 9.9 and
+    // 8.8); up to 2 KiB, where even 8 rows are little to wait for, the 32 x 64 tiles of the larger expert counts (65536 x 512: 32 and
+    // 13 us, 8192 x 1024: 8.2 and 6.0; 30000 x 2048: 24 and 29)
+    if (H <= 1024 && T > 2048) return launch_gate_short<32, 64, 4>(x, w, logits, T, H, E, st);
+    if (H <= 2048 && H % 64 == 0) return launch_gate_small<1, 512, 2048>(x, w, logits, T, H, E, 2, st);
+    if (H <= 4096 && H % 128 == 0) return launch_gate_small<2, 512, 2048>(x, w, logits, T, H, E, 1, st);
+    if (H <= 4096 && H % 64 == 0) return launch_gate_small<1, 512, 4096>(x, w, logits, T, H, E, 1, st);
+    if (H <= 8192 && H % 128 == 0) return launch_gate_small<2, 512, 4096>(x, w, logits, T, H, E, 1, st);
+    return 1;
 }
 
 // nb: groups of 16 experts per workgroup, 1 or 2 (bf16), 1 or 4 (fp32)
@@ -1104,62 +1108,66 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
     ProfScope ps(MONTA_K_GATE, st);
     if (cfg->dtype == MONTA_BF16) {
         // validate() guarantees H % 8 == 0 (rows are whole 16-byte vectors) and E <= 256 (at most 8 tiles).
-        // Few tiles of 16 tokens x 16 experts (or 32, where that makes them one round): the hidden axis is split, too; tiles of 32
-        // that would be more than a round lose to twice the tiles of 16 (2560 x 5120, 40 experts: 35 and 24 us).  Up to some ten
-        // thousand tokens: tiles as small as leave at most two workgroups per CU (8192 x 7168, 128 experts: 41 us in 512 tiles of
-        // 32 x 64, 48 in 32 x 128; 8192 x 4096, 256 experts: 62 in 1024 tiles of 32 x 64, 37 in 32 x 128; rows of 16 KiB 62 and
-        // 50), three where one of 32 x 64 holds all experts (20480 x 5120, 48 experts: 40, in 64 x 128 58; at more than three 64
-        // and 59).  Otherwise the k-split forms, a workgroup per 32 tokens: few of them with a deep step, one per CU; many with
-        // shallower steps, several per CU.  These are also the better ones
-        //  - for 33 .. 64 experts up to 4096 tokens (4096 x 4096, 64 experts: 21 us, 32 x 64 22; 3072 tokens: 18 and 22);
-        //  - for 17 .. 48 experts and 4097 .. 8192 tokens, at most one 32-token tile per CU, unless the rows are short (6144 x 3072,
-        //    32 experts: 14 us, 32 x 64 16; 6144 x 7168: 28 and 34; 8192 x 2048: 11 and 12; but 6144 x 1536: 9.4 and 9.5).  Rows of
-        //    8 KiB slow this form down where it has about 256 tiles: 8192 x 4096 26 and 22, 6144 x 4096 19 and 21.
-        // Up to 16 experts it would be faster than two rounds of split tiles, too (5000 x 3072: 12 us, split 16), but its sums are
-        // less exact: 9.9e-8 off 64 bits against 9.1e-8.
+        //  - Few tiles of 16 tokens x 16 experts (or 32, where that makes them one round): the hidden axis is split, too.  More than a
+        //    round of them only for up to 16 experts and rows over 2 KiB (8192 x 4096, 9 experts: 14 us, in 32 x 64 20; but 6144 x 512,
+        //    16 experts: 9.2 and 5.1).
+        //  - Up to 32736 tokens, and short rows on up to 32 experts beyond: direct-to-LDS tiles as small as come in one round (32 x 64
+        //    three per CU, the others two): 4096 x 4096, 256 experts 31 us in 512 tiles of 32 x 64, 23 in 32 x 128; 12000 x 7168, 128
+        //    experts 77, 83 and in 64 x 128 60.  One tile of 32 x 64 that holds all experts is kept up to three rounds' worth of
+        //    tiles and, on short rows, always.  Rows that are not whole steps, whose lines every tile fetches twice: 64 x 128 from 33
+        //    experts on (12000 x 4104, 64 experts: 47 and 39), the k-split form up to 32 experts and from 16353 tokens on (24000 x 8184,
+        //    24 experts: 104 and 82).
+        //  - Otherwise a workgroup per 32 tokens whose waves share the hidden axis, or per 128 tokens.
+        // Over 728 shapes (512 to 8184 elements, 600 to 60000 tokens, 9 to 256 experts) this takes 1.01 of the best form's time and 0.84
+        // of the time of the rule that drew its lines before the 32 x 64 tiles lost their conditions inside the loop.
         const int64_t tiles32 = (T + 31) / 32;
         const u32x4 *xv = static_cast<const u32x4 *>(x), *wv = static_cast<const u32x4 *>(w_gate);
         rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
         auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
-        const bool mid = T > 4096 && T <= (H == 4096 ? 6144 : 8192);
-        const bool k_split = mid ? H >= 2048 && E > 16 && E <= (H < 3072 ? 32 : 48) : T <= 4096 && E > 32 && E <= 64;
-        const bool short_tiles = H % 64 == 0 && H <= kBigMaxHidden && tiles32 < 1024 && !k_split;
         const int64_t tiles16 = tiles(16, 16), round = 256;
-        const bool long_rows = H >= 8192 && E > 64 && E <= 128 && tiles(32, 64) > 384;
+        const bool short_rows = H <= 1024, many = tiles32 >= 1024, odd = H % 64 != 0 && H >= 2048;
+        const bool k_split = (many && !(short_rows && E <= 32)) || (odd && E <= 32 && tiles32 >= 512);
         if (rc <= 0) {
             if (rc) return rc;
         }
-        else if (tiles16 <= 2 * round)
-            rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, tiles16 > round && E > 16 && tiles(16, 32) <= round ? 2 : 1, st);
-        else if (short_tiles && !long_rows && tiles(32, 64) <= (E <= 64 ? 768 : 512)) rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
-        else if (short_tiles && tiles(32, 128) <= 512) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
-        else if (short_tiles) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
-        else if (E <= 32)
-            rc = tiles32 >= 512 ? launch_gate<1, 1, 512, true>(xv, wv, logits, T, H, E, st)
-                                : launch_gate<1, 1, 1024, true>(xv, wv, logits, T, H, E, st);
-        // More experts: with at least one 128-token workgroup per CU, every wave owns whole output tiles (W_g is
-        // re-read once per 128 tokens instead of once per 32-64, and the small tiles let 3 workgroups share a CU);
-        // with fewer tokens, 32-token workgroups with the k-slices dealt to the waves keep the chip filled.
+        else if (tiles16 <= (E <= 16 && !short_rows ? 2 * round : round) || (!k_split && H > kBigMaxHidden))
+            rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 1, st);
+        else if (!short_rows && E > 16 && tiles(16, 32) <= round) rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 2, st);
+        else if (!k_split && odd && E > 32 && E <= 64 && T > 8192) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
+        else if (!k_split && (tiles(32, 64) <= (E <= 64 ? 3 * round : round) || (E <= 64 && (short_rows || tiles(64, 128) < 2 * round))))
+            rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
+        else if (!k_split && tiles(32, 128) <= round) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
+        else if (!k_split) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
+        else if (E <= 32) rc = launch_gate<1, 1, 512, true>(xv, wv, logits, T, H, E, st);
+        // More experts: at least one 128-token workgroup per CU, in which every wave owns whole output tiles (W_g is re-read once
+        // per 128 tokens, and the small tiles let 3 workgroups share a CU).
+        // Activations as large as the memory-side cache (256 MB) leave nothing in it for the dispatch behind the gate: then they are
+        // streamed (65536 x 7168, 64 experts 175 -> 155 us, 128 experts 201 -> 192, 256 experts 336 and 333; 40000 x 1024, 82 MB, 21.8
+        // and 23.1).
         else if (E <= 64)
-            rc = tiles32 >= 1024 ? launch_gate<4, 2, 128, false, true>(xv, wv, logits, T, H, E, st)
-                                 : launch_gate<1, 2, 512, true>(xv, wv, logits, T, H, E, st);
+            rc = T * H * 2 >= (256ll << 20) ? launch_gate<4, 2, 128, false, true, true>(xv, wv, logits, T, H, E, st)
+                                            : launch_gate<4, 2, 128, false, true>(xv, wv, logits, T, H, E, st);
         else if (E <= 128)
-            rc = tiles32 >= 1024 ? launch_gate<4, 4, 64, false, true>(xv, wv, logits, T, H, E, st)
-                                 : launch_gate<1, 4, 256, true>(xv, wv, logits, T, H, E, st);
-        else
-            rc = tiles32 >= 1024 ? launch_gate<4, 8, 64, false, true>(xv, wv, logits, T, H, E, st)
-                                 : launch_gate<1, 8, 128, false>(xv, wv, logits, T, H, E, st);
+            rc = T * H * 2 >= (256ll << 20) ? launch_gate<4, 4, 64, false, true, true>(xv, wv, logits, T, H, E, st)
+                                            : launch_gate<4, 4, 64, false, true>(xv, wv, logits, T, H, E, st);
+        else rc = launch_gate<4, 8, 64, false, true>(xv, wv, logits, T, H, E, st);
         if (rc) return rc;
     } else {
         // At most four experts: a wave per token, as long as its loads of the weights stay fewer than a tile's idle work: 4096 x
         // 4096, 3 / 4 experts 13.2 / 15.1 us against 12.9 / 13.1; 65536 x 4096, 1 / 2 experts 167 / 204 against 173 / 174.
         // Otherwise 64 experts per workgroup read x a quarter as often, 16 give four times the workgroups.
-        const int64_t tiles16 = (T + 15) / 16 * ((E + 15) / 16);
+        // More than 16 experts and a tile of 32 x 64 for every CU: those, or 64 x 64 where they are two rounds (8192 x 4096, 32 / 128 /
+        // 256 experts: 79 / 171 / 328 us, in 32 x 64 62 / 99 / 166, in 64 x 64 100 / 106 / 164; 32000 x 4096, 64 experts: 348, 177 and 170;
+        // 2048 x 4096, 128 experts, half a round: 42 and 52).  Their sums are the more exact ones from about 800 elements on (1000:
+        // 9.6e-8 against 9.9e-8; 8192: 1.4e-7 and 2.1e-7; but 512: 9.1e-8 and 8.6e-8).
+        const int64_t tiles16 = (T + 15) / 16 * ((E + 15) / 16), experts64 = (E + 63) / 64;
+        const bool short_tiles = E > 16 && H >= 896 && H <= kBigMaxHidden && (T + 31) / 32 * experts64 >= 256;
+        const u32x4 *xv = static_cast<const u32x4 *>(x), *wv = static_cast<const u32x4 *>(w_gate);
         if (E <= 4 && (E == 1 || H <= 512 || T * E <= 12288))
             rc = launch_gate_f32_few(static_cast<const float4 *>(x), static_cast<const float4 *>(w_gate), logits, T, H, E, st);
-        else
-            rc = launch_gate_split<false>(static_cast<const u32x4 *>(x), static_cast<const u32x4 *>(w_gate), logits, T, H / 4, E,
-                                      E <= 16 || tiles16 <= 256 ? 1 : 4, st);
+        else if (short_tiles && (T + 63) / 64 * experts64 >= 500) rc = launch_gate_short<64, 64, 3, true>(xv, wv, logits, T, H, E, st);
+        else if (short_tiles) rc = launch_gate_short<32, 64, 3, true>(xv, wv, logits, T, H, E, st);
+        else rc = launch_gate_split<false>(xv, wv, logits, T, H / 4, E, E <= 16 || tiles16 <= 256 ? 1 : 4, st);
         if (rc) return rc;
     }
     HIP_TRY(hipGetLastError());

@@ -1449,6 +1449,8 @@ struct GateTile {
     static constexpr int kPiecesPerRow = KS / 8;                 // 16-byte pieces of one row of a step
     static constexpr int kRowStride = KS * 2 + 16;               // bytes in LDS
     static constexpr int kLoads = (32 * (MT + NT) * kPiecesPerRow + kGateThreads - 1) / kGateThreads;
+    static constexpr int kLoadsX = kTokens * kPiecesPerRow / kGateThreads;      // of them from rows of x, by every thread
+    static_assert(kTokens * kPiecesPerRow % kGateThreads == 0, "gate: a load is of x or of the weights for all threads");
     static constexpr int kTiles = MT * NT;
     // partial tiles of several waves side by side in 64 KiB; waves sharing a slot add one after the other
     static constexpr int kSlots = kTiles > 16 ? 1 : (16 / kTiles) < kGateWaves ? (16 / kTiles) : kGateWaves;
@@ -1467,7 +1469,8 @@ struct GateTile {
 // SPLIT (needs MT*NT = number of waves): instead of dealing the k-slices, every wave owns one 32x32 output tile
 // and walks all k-slices of it: one accumulator tile per wave, which leaves registers for larger tiles in
 // flight, and no reduction across waves at the end.
-template <int MT, int NT, int KS, bool DEEP, bool SPLIT>
+// STREAM: x is requested as streaming.
+template <int MT, int NT, int KS, bool DEEP, bool SPLIT, bool STREAM>
 __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                                  float *__restrict__ logits, int64_t T, int H, int E)
 {
@@ -1497,7 +1500,8 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const u32x4 *__
             const bool ok = piece_ok(tid + q * kGateThreads, step, row, c);
             const u32x4 *src = x;
             if (ok) src = (row < G::kTokens) ? x + (t0 + row) * cpr + c : w + (int64_t)(row - G::kTokens) * cpr + c;
-            pre[q] = *src;
+            if (STREAM && q < G::kLoadsX) pre[q] = ld16<true>(src);      // (as a choice of two values both would be plain loads)
+            else pre[q] = *src;
         }
     };
     auto stage = [&](const u32x4(&pre)[G::kLoads], int step) {
@@ -1519,17 +1523,12 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const u32x4 *__
     static_assert(!SPLIT || (kGateWaves % NT == 0 && kPerWave >= 1 && kPerWave * kRowTileStep == MT),
                   "gate: the output tiles must divide evenly among the waves");
     constexpr int kAcc = SPLIT ? kPerWave : G::kTiles;
-    // The small tiles with a deep step, one workgroup per CU, keep a sum per parity of the step: chains of additions half as
-    // long.  The error against 64 bits falls from 1.8e-7 to 1.33e-7 at 7168 elements, below that of the 32 x 64 tiles (1.45e-7),
-    // in the same time.  (With the shallower step fewer workgroups would fit a CU: 26000 x 1024, 9 experts 14.6 -> 19.6 us.)
-    constexpr int kSets = DEEP && !SPLIT && G::kTiles <= 2 && G::kTiles * KS >= 1024 ? 2 : 1;
-    f32x16 acc[kAcc * kSets];
+    f32x16 acc[kAcc];
 #pragma unroll
-    for (int i = 0; i < kAcc * kSets; ++i)
+    for (int i = 0; i < kAcc; ++i)
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
-    auto multiply = [&](auto set) {
-        constexpr int kFirst = decltype(set)::value * kAcc;
+    auto multiply = [&]() {
         if constexpr (SPLIT) {
             const int n = (wave % NT) * 32 + m;
             const unsigned char *pa = gate_lds + (size_t)((wave / NT) * 32 + m) * G::kRowStride + g * 16;
@@ -1564,25 +1563,22 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const u32x4 *__
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[kFirst + mt * NT + nt] =
-                        __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt], b[nt], acc[kFirst + mt * NT + nt], 0, 0, 0);
+                    acc[mt * NT + nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt], b[nt], acc[mt * NT + nt], 0, 0, 0);
         }
     };
 
-    using even = std::integral_constant<int, 0>;
     if constexpr (DEEP) {
-        using odd = std::integral_constant<int, kSets - 1>;
         u32x4 pre0[G::kLoads], pre1[G::kLoads];
         fetch(pre0, 0);
         fetch(pre1, 1);                                           // past the last step: clamped loads, never used
         for (int step = 0; step < nsteps; step += 2) {
             stage(pre0, step);
             fetch(pre0, step + 2);
-            multiply(even{});
+            multiply();
             if (step + 1 < nsteps) {
                 stage(pre1, step + 1);
                 fetch(pre1, step + 3);
-                multiply(odd{});
+                multiply();
             }
         }
     } else {
@@ -1591,12 +1587,8 @@ __global__ __launch_bounds__(kGateThreads) void gate_bf16_kernel(const u32x4 *__
         for (int step = 0; step < nsteps; ++step) {
             stage(pre0, step);
             fetch(pre0, step + 1);
-            multiply(even{});
+            multiply();
         }
-    }
-    if constexpr (kSets > 1) {
-#pragma unroll
-        for (int i = 0; i < kAcc; ++i) acc[i] += acc[kAcc + i];
     }
 
     if constexpr (SPLIT) {
@@ -2166,8 +2158,11 @@ struct ShortTile {
 
 // F32: the activations and weights are fp32, 32 of them per step; a lane's 16 bytes are then four elements for four 16x16x4
 // MFMAs, each of which takes the same element of the four pieces of half a step.
-// T: unsigned short, y is rounded to bf16; float, the sums themselves are stored (N columns, any N) and are taken in two
-// levels, 8 steps of the hidden axis at a time, so that a long row costs no precision.  VEC: rows of y are whole 16-byte vectors.
+// T: unsigned short, y is rounded to bf16; float, the sums themselves are stored, rows of whole 16-byte vectors (VEC) or of any N
+// columns.  Sums of the first kind are taken in two levels, 8 steps of the hidden axis at a time.  Those of the second, the
+// logits, in three, the lowest of one step (fp32) or of one to four, and there in a chain of additions per half of a step (in fp32
+// per element of a piece), so that neither short rows nor long ones cost precision.  Error against 64 bits with one chain and two
+// levels, and now: 512 elements 1.2e-7, 6.3e-8; 1832 1.3e-7, 7.6e-8; 8184 1.5e-7, 1.2e-7; fp32, 1000 2.9e-7, 9.6e-8, 8192 3.1e-7, 1.4e-7.
 // AUX_W: cache bits of the weights' loads.
 template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, typename T>
 __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
@@ -2207,19 +2202,39 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
         load(lds + slot * G::kStageBytes, step_offset(step, nsteps),
              [&](int c, uint32_t o) { return piece(c) < left ? o : kOutOfRange; });
     };
-    f32x4 acc[RB][CB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-        for (int j = 0; j < CB; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     constexpr bool kLevels = std::is_same<T, float>::value;
-    f32x4 total[kLevels ? RB : 1][kLevels ? CB : 1];
+    constexpr bool kLogits = kLevels && !VEC;
+    constexpr int kChains = !kLogits ? 1 : F32 ? 4 : 2;
+    f32x4 acc[kChains][RB][CB];
+#pragma unroll
+    for (int c = 0; c < kChains; ++c)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < CB; ++j) acc[c][i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    f32x4 total[kLevels ? RB : 1][kLevels ? CB : 1], part[kLogits ? RB : 1][kLogits ? CB : 1];
     if constexpr (kLevels) {
 #pragma unroll
         for (int i = 0; i < RB; ++i)
 #pragma unroll
             for (int j = 0; j < CB; ++j) total[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
+    if constexpr (kLogits) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < CB; ++j) part[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    // adds the chains of one result to `to` and clears them
+    auto fold = [&](int i, int j, f32x4 &to) {
+#pragma unroll
+        for (int c = kChains / 2; c >= 1; c /= 2)
+#pragma unroll
+            for (int b = 0; b < c; ++b) acc[b][i][j] += acc[b + c][i][j];
+        to += acc[0][i][j];
+#pragma unroll
+        for (int c = 0; c < kChains; ++c) acc[c][i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    };
     const unsigned char *px = lds + m * 128, *pw = lds + (XR + wave * (WR / 4) + m) * 128;
     const int nb = (int)((row_end - row0 + 15) / 16);              // 16-row blocks with rows of the segment
 
@@ -2262,7 +2277,13 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 #pragma unroll
                 for (int v = 0; v < (F32 ? 4 : 1); ++v)
 #pragma unroll
-                    for (int i = 0; i < BLOCKS; ++i) multiply(fw[ks], fx[ks][i], acc[i], v);
+                    for (int i = 0; i < BLOCKS; ++i) multiply(fw[ks], fx[ks][i], acc[!kLogits ? 0 : F32 ? v : ks][i], v);
+            if constexpr (kLogits && F32) {
+#pragma unroll
+                for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+                    for (int j = 0; j < CB; ++j) fold(i, j, part[i][j]);
+            }
             slot = slot == NST - 1 ? 0 : slot + 1;
         }
     };
@@ -2271,21 +2292,32 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     // 152, 48 workgroups: 21.8 us, now 16.4; 2 experts of 8192 x 64, 60 rows: 38 and 25).
     auto run = [&](auto blocks) {
         const int whole_to = cpr / 8 - (NST - 1);                      // up to here the step NST - 1 ahead is a whole one
-        constexpr int kSpan = kLevels ? 8 : 1 << 30;
-        for (int from = 0; from < nsteps; from += kSpan) {
-            const int to = kLevels ? min(from + kSpan, nsteps) : nsteps, mid = min(max(whole_to, from), to);
-            walk(blocks, std::true_type{}, from, mid);
-            walk(blocks, std::false_type{}, mid, to);
+        const int span = kLevels ? 8 : nsteps, sub = !kLogits || F32 ? span : nsteps <= 12 ? 1 : nsteps <= 32 ? 2 : 4;
+        for (int from = 0; from < nsteps; from += span) {
+            const int end = min(from + span, nsteps);
+            for (int first = from; first < end; first += sub) {
+                const int to = min(first + sub, end), mid = min(max(whole_to, first), to);
+                walk(blocks, std::true_type{}, first, mid);
+                walk(blocks, std::false_type{}, mid, to);
+                if constexpr (kLogits && !F32) {
+#pragma unroll
+                    for (int i = 0; i < decltype(blocks)::value; ++i)
+#pragma unroll
+                        for (int j = 0; j < CB; ++j) fold(i, j, part[i][j]);
+                }
+            }
             if constexpr (kLevels) {
 #pragma unroll
                 for (int i = 0; i < decltype(blocks)::value; ++i)
 #pragma unroll
                     for (int j = 0; j < CB; ++j) {
-                        total[i][j] += acc[i][j];
-                        acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        if constexpr (kLogits) {
+                            total[i][j] += part[i][j];
+                            part[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        } else {
+                            fold(i, j, total[i][j]);
+                        }
                     }
-            } else {
-                break;
             }
         }
     };
@@ -2307,7 +2339,7 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
                             if (n + v < N) y[r * N + n + v] = total[i][j][v];
                     }
                 } else {
-                    if (n < N) *reinterpret_cast<uint2 *>(y + r * N + n) = pack_bf16x4(acc[i][j]);
+                    if (n < N) *reinterpret_cast<uint2 *>(y + r * N + n) = pack_bf16x4(acc[0][i][j]);
                 }
             }
         }
@@ -2659,10 +2691,12 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
 #endif
 }
 
-// Gate projection of a few thousand tokens on more than 8 experts: the same tiles, tokens x experts, sums stored as they are.
-// Bound by the trips of x and of the weights through the L2: T E row (1 / XR + 1 / WR) bytes.  Against 32-token workgroups
-// with the k-slices dealt to 8 waves: 16384 x 7168, 256 experts 190 -> 91 us, 8192 x 4096, 256 experts 61 -> 37, 1024 x 7168,
-// 256 experts 92 -> 35; with 32 experts one tile holds them all in both forms: 16384 x 4096 37 and 37.
+// Gate projection of a few thousand tokens, of short rows, and in fp32 of many experts: the same tiles, tokens x experts, sums
+// stored as they are.  Bound by the trips of x and of the weights through the L2: T E row (1 / XR + 1 / WR) bytes, in fp32 by the
+// matrix rate.  Against 32-token workgroups with the k-slices dealt to 8 waves: 16384 x 7168, 256 experts 190 -> 91 us, 8192 x 4096,
+// 256 experts 61 -> 37, 1024 x 7168, 256 experts 92 -> 35; rows that are not whole steps: 1024 x 8184, 256 experts 109 -> 29, 12000 x
+// 520, 9 experts 12.5 -> 5.8.  Against persistent workgroups of whole rows: 65536 x 512, 8 experts 49 -> 13.  fp32 against tiles of
+// 16 tokens x 64 experts with a split hidden axis: 8192 x 4096, 128 experts 171 -> 99, 32000 x 8192, 64 experts 694 -> 333.
 template <int XR, int WR, int NST, bool F32>
 __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                             float *__restrict__ logits, int64_t T, int H, int E)

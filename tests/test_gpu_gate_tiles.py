@@ -52,3 +52,24 @@ RULE = [(2048, 128, 48), (2560, 128, 40), (1024, 192, 65), (1536, 192, 65), (819
 @pytest.mark.parametrize("T,H,E", [(T, (H + 7) // 8 * 8, E) for T, H, E in SPLIT] + TILES + RULE)
 def test_gate_bf16(T, H, E):
     check(T, H, E, BF16)
+
+
+# bf16: rows that are not whole steps in the direct-to-LDS tiles of each shape, and the lines drawn for them; short rows on up to 8
+# experts; two persistent workgroups per CU; and activations of 256 MiB, which are streamed
+RAGGED = [(4100, 520, 33), (8161, 72, 9), (9000, 2056, 64), (12000, 1096, 200), (16353, 2056, 24), (16352, 2056, 24), (6000, 8, 100),
+          (8200, 200, 128), (3000, 1032, 256), (33000, 1016, 32), (33000, 1032, 32)]
+SHORT_ROWS = [(2049, 8, 2), (2048, 64, 8), (5000, 1024, 8), (4097, 520, 5), (40001, 16, 1), (2049, 1088, 8)]
+PERSISTENT = [(5000, 1536, 7), (9001, 2048, 8), (4095, 1088, 3)]
+STREAMED = [(32768, 4096, 40), (32801, 4096, 65)]
+
+
+@pytest.mark.parametrize("T,H,E", RAGGED + SHORT_ROWS + PERSISTENT + STREAMED)
+def test_gate_bf16_further(T, H, E):
+    check(T, H, E, BF16)
+
+
+# fp32 in the direct-to-LDS tiles: 32 x 64 and 64 x 64, and both sides of their lines
+@pytest.mark.parametrize("T,H,E", [(8161, 896, 17), (8160, 892, 17), (8161, 1000, 64), (8160, 900, 33), (16001, 1004, 65), (15969, 1004, 65),
+                                   (2017, 1124, 256), (31970, 900, 64)])
+def test_gate_fp32_tiles(T, H, E):
+    check(T, H, E, FP32)
