@@ -57,6 +57,7 @@ def algorithmic_bytes(w, tabs, one_pass=False):
     }
     out["place"] = (alive + 2 * R) * row + 2 * T * k * 4
     out["plan_place"] = (alive + 2 * R) * row + out["plan"]
+    out["small_step"] = out["plan_place"] + out["route"]
     out["total"] = (alive + T + (3 if one_pass else 4) * R) * row + idx_bytes
     return out
 
@@ -150,7 +151,7 @@ def measure(args, w, steps, warmup, full):
         pad_bytes = (tabs["final_rows"] - ab["R"]) * ab["row"]      # zero-filled by the regather of slice 0
         ab["total"] += pad_bytes
         ab["regather_s"][0] += pad_bytes
-        for name in ("regather", "place", "plan_place"):
+        for name in ("regather", "place", "plan_place", "small_step"):
             ab[name] += pad_bytes
     if mirror:
         ab["total"] += (1 if mode < 0 else 2) * ab["R"] * ab["row"]
@@ -208,7 +209,7 @@ def measure(args, w, steps, warmup, full):
             for gi in range(1, G):
                 seq += [("pack", pack_g[gi]), ("regather", reg_g[gi])]
         per_launch = {"combine": ab["combine"], "gate": ab.get("gate"), "place": ab["place"], "plan_place": ab["plan_place"],
-                      "return": ab.get("return")}
+                      "small_step": ab["small_step"], "return": ab.get("return")}
         for kname in ("pack", "regather", "pack_regather", "plan_pack"):
             vals = [v for n_, v in seq if n_ == kname]
             per_launch[kname] = sum(vals) / len(vals) if vals else None
@@ -234,7 +235,7 @@ def measure(args, w, steps, warmup, full):
                 per_launch["unregather"] = sum(un_g) / len(un_g)
                 per_launch["combine"] = sum(cb_g) / len(cb_g)
         movers = [kname for kname in ("pack", "regather", "pack_regather", "combine", "plan_pack", "unregather",
-                                      "unregather_combine", "gate", "place", "plan_place", "return") if kname in kernels]
+                                      "unregather_combine", "gate", "place", "plan_place", "small_step", "return") if kname in kernels]
         dom = max(movers, key=lambda kname: kernels[kname]["us_per_step"])
         achieved = per_launch[dom] / (kernels[dom]["avg_us"] * 1e-6) / 1e9
         # HBM-side bytes per launch of that kernel from rocprofv3 counters (profiles/traffic.json, written by
@@ -272,8 +273,8 @@ def measure(args, w, steps, warmup, full):
                 v[kk] = round(v[kk], 3)
         res["roofline"] = roofline
         res["kernels"] = kernels
-        one = "place" in kernels or "plan_place" in kernels
-        res["pipeline"] = {"realisation": "one pass", "plan_fused": "plan_place" in kernels} if one else {"realisation": pmode, "first_launch_slices": first, "slices_per_launch": spg, "plan_fused_with_first_pack": fused}
+        one = any(n in kernels for n in ("place", "plan_place", "small_step"))
+        res["pipeline"] = {"realisation": "one pass", "plan_fused": "place" not in kernels} if one else {"realisation": pmode, "first_launch_slices": first, "slices_per_launch": spg, "plan_fused_with_first_pack": fused}
 
     if args.calib_copy_mib > 0:
         nbytes = args.calib_copy_mib << 20

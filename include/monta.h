@@ -366,7 +366,8 @@ enum monta_kernel_id {
     MONTA_K_PLAN_PLACE = 15, /* the same with the plan tables finished in the same grid */
     MONTA_K_RETURN = 16,    /* the mirrored return path in one pass           */
     MONTA_K_SCAN = 17,      /* scan of a histogram table too large to rebuild  */
-    MONTA_K_COUNT = 18
+    MONTA_K_SMALL_STEP = 18, /* routing, plan, rows and combine of a small problem in one launch */
+    MONTA_K_COUNT = 19
 };
 int monta_profile_enable(int on);
 int monta_profile_reset(void);

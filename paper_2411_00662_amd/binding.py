@@ -20,7 +20,7 @@ FP32, BF16 = 0, 1
  K_UNREGATHER_COMBINE, K_ALLGATHER, K_GATE, K_EXPERT) = range(13)
 KERNEL_NAMES = ["route_plan", "positions", "pack", "regather", "pack_regather", "combine", "copy", "plan_pack",
                 "unregather", "unregather_combine", "allgather", "gate", "expert", "allgather_regather", "place", "plan_place", "return",
-                "block_scan"]
+                "block_scan", "small_step"]
 
 
 class MontaError(RuntimeError):

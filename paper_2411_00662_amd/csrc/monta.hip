@@ -125,6 +125,11 @@ int validate(const monta_cfg *c, Geometry *g)
     s.Tu = (int32_t)(c->tokens / U);
     s.C = (int32_t)capacity_of(c);
     s.renorm = c->renorm;
+    s.by_E = fast_div(s.E);
+    s.by_k = fast_div(s.k);
+    s.by_k1 = fast_div(s.k > 1 ? s.k - 1 : 1);
+    s.by_Tu = fast_div(s.Tu < 1 << 14 ? s.Tu : 1);      // used for small problems
+    s.by_ep = fast_div(s.ep);
     s.vpr = (int32_t)(row / 16);
     const int lpr_max = kMoverThreads;
     s.lpr = pow2ceil(s.vpr) < lpr_max ? pow2ceil(s.vpr) : lpr_max;
@@ -201,6 +206,13 @@ void fill_layout(const Geometry &g, monta_ws_layout *L)
     L->off_local_rank = take((int64_t)s.T * s.k);
     L->off_kept_prefix = take(s.E + 1);
     L->ws_bytes = off;
+}
+
+int64_t ws_bytes(const Geometry &g)
+{
+    monta_ws_layout L;
+    fill_layout(g, &L);
+    return L.ws_bytes;
 }
 
 PlanPtrs plan_ptrs(const Geometry &g, const void *ws)
@@ -676,26 +688,25 @@ int launch_expert_f32(const void *x_final, const void *w_exp, void *y, const Exp
 int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int32_t *topk_idx, float *gates,
                  hipStream_t st)
 {
-    // a lane's elements in four groups: of 2, 4 or 8
     const int per_lane = (g.s.E + g.s.rl - 1) / g.s.rl;
-    auto launch = [&](auto lc, auto gs) -> int {
-        constexpr int L = decltype(lc)::value, GS = decltype(gs)::value;
+    auto launch = [&](auto lc, auto ne) -> int {
+        constexpr int L = decltype(lc)::value, NE = decltype(ne)::value;
         static LdsOptIn lds_opt_in;
         if (g.route_lds > 48 * 1024)
-            if (int rc = opt_in_lds(reinterpret_cast<const void *>(route_plan_kernel<L, GS>), (int)kRouteLdsBudget, lds_opt_in))
+            if (int rc = opt_in_lds(reinterpret_cast<const void *>(route_plan_kernel<L, NE>), (int)kRouteLdsBudget, lds_opt_in))
                 return rc;
         ProfScope ps(MONTA_K_ROUTE, st);
-        hipLaunchKernelGGL((route_plan_kernel<L, GS>), dim3(g.s.num_blocks), dim3(g.route_threads), g.route_lds, st, logits,
+        hipLaunchKernelGGL((route_plan_kernel<L, NE>), dim3(g.s.num_blocks), dim3(g.route_threads), g.route_lds, st, logits,
                            topk_idx, gates, p, g.s);
         HIP_TRY(hipGetLastError());
         return MONTA_OK;
     };
-    auto with_groups = [&](auto lc) -> int {
-        if (per_lane <= 8) return launch(lc, std::integral_constant<int, 2>{});
-        if (per_lane <= 16) return launch(lc, std::integral_constant<int, 4>{});
+    auto with_groups = [&](auto lc) -> int {        // a lane's elements
+        if (per_lane <= 8) return launch(lc, std::integral_constant<int, 8>{});
+        if (per_lane <= 16) return launch(lc, std::integral_constant<int, 16>{});
         // one or two lanes share a token only below 16 and 32 experts, four or eight have at most 28 and 32 each (LDS budget)
         if constexpr (decltype(lc)::value >= 4)
-            if (per_lane <= 32) return launch(lc, std::integral_constant<int, 8>{});
+            if (per_lane <= 32) return launch(lc, std::integral_constant<int, 32>{});
         return MONTA_ERR_UNSUPPORTED;
     };
     int rc;
@@ -708,6 +719,95 @@ int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int3
     hipLaunchKernelGGL(block_scan_kernel, dim3((g.s.E + kWave - 1) / kWave), dim3(kScanWaves * kWave), 0, st, p, g.s);
     HIP_TRY(hipGetLastError());
     return MONTA_OK;
+}
+
+// Do the bytes [a, a + na) and [b, b + nb) share any?
+bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
+{
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa < pb + (uintptr_t)nb && pb < pa + (uintptr_t)na;
+}
+
+// Lanes per token of small_step_kernel, 0 if the problem is not a small one: all tokens have to be covered by one pass of a
+// workgroup's threads, their logits and the plan by its LDS.  And routing them all in every workgroup must not take longer than
+// routing a share of them and waiting for the others, which grows with tokens x experts and, where each row's workgroup does it, with
+// the choices.  Measured on MI355X, GPU time in us, several launches and one: routing 64 x 8, top-2 7.8 and 4.9; 128 x 64, top-8 10.5
+// and 9.1, 256 x 64 10.6 and 14.4; 512 x 16, top-2 8.2 and 6.8, 512 x 32, top-4 8.8 and 11.4; 64 x 256, top-8 17.5 and 13.2.  With the
+// rows (4096 elements): 64 x 8, top-2 8.4 and 5.5, 512 x 8 10.6 and 8.3, 1024 x 8 13.3 and 15.5; 256 x 32, top-4 11.3 and 10.9, 128 x
+// 64, top-8 12.8 and 14.1.  The whole step 64 x 8 12.8 and 7.7, 512 x 8 18.2 and 10.8.
+constexpr int kSmallTokens = 512, kSmallUnits = 4096, kSmallPerLogits = 8192, kSmallPerChoices = 32768, kSmallAnyway = 64;
+int small_lanes(const Geometry &g, bool rows)
+{
+    const Shape &s = g.s;
+    if (g.modes.plan >= 0 || s.T > kSmallTokens || (int64_t)s.U * s.E > kSmallUnits) return 0;
+    if (s.T > kSmallAnyway && (s.T * s.E > kSmallPerLogits || (rows && s.T * s.E * s.k > kSmallPerChoices))) return 0;
+    int L = 1;
+    while (L < 16 && s.E / (2 * L) >= 8 && s.T * 2 * L <= 1024) L *= 2;
+    const int per_lane = (s.E + L - 1) / L;
+    if (s.T * L > 1024 || per_lane > (L == 4 || L == 8 ? 32 : 16) || small_lds(s.T, s.E, s.k, s.U, L).bytes > (int)kRouteLdsBudget) return 0;
+    return L;
+}
+
+int launch_small(const Geometry &g, const PlanPtrs &p, int L, SmallWhat what, const float *logits, const void *x, int32_t *topk_idx,
+                 float *gates, void *stage, void *final_, void *out, bool bf16, hipStream_t st)
+{
+    const Shape &s = g.s;
+    int threads = kMoverThreads;
+    while (threads < s.T * L || (threads < 1024 && threads < s.U * kWave)) threads *= 2;     // a wave per unit, up to 16
+    const int rows = threads / s.lpr;
+    const unsigned grid = 3 + (what == SMALL_ROUTE ? 0u : (unsigned)((s.T + rows - 1) / rows));
+    const SmallLds lay = small_lds(s.T, s.E, s.k, s.U, L);
+    const size_t lds = (size_t)lay.bytes;
+    const int per_lane = (s.E + L - 1) / L;
+    auto launch = [&](auto lc, auto ne) -> int {
+        constexpr int LN = decltype(lc)::value, NE = decltype(ne)::value;
+        static LdsOptIn lds_opt_in;
+        if (lds > 48 * 1024)
+            if (int rc = opt_in_lds(reinterpret_cast<const void *>(small_step_kernel<LN, NE>), (int)kRouteLdsBudget, lds_opt_in)) return rc;
+        ProfScope ps(MONTA_K_SMALL_STEP, st);
+        hipLaunchKernelGGL((small_step_kernel<LN, NE>), dim3(grid), dim3(threads), lds, st, logits, static_cast<const u32x4 *>(x), topk_idx,
+                           gates, static_cast<u32x4 *>(stage), static_cast<u32x4 *>(final_), static_cast<u32x4 *>(out), p, s, lay, (int)what,
+                           bf16 ? 1 : 0);
+        HIP_TRY(hipGetLastError());
+        return MONTA_OK;
+    };
+    auto with_groups = [&](auto lc) -> int {        // a lane's elements
+        constexpr int LN = decltype(lc)::value;
+        if (per_lane <= 8) return launch(lc, std::integral_constant<int, 8>{});
+        if (per_lane <= 16) return launch(lc, std::integral_constant<int, 16>{});
+        if constexpr (LN == 4 || LN == 8) return launch(lc, std::integral_constant<int, 32>{});
+        return MONTA_ERR_UNSUPPORTED;
+    };
+    if (L == 1) return with_groups(std::integral_constant<int, 1>{});
+    if (L == 2) return with_groups(std::integral_constant<int, 2>{});
+    if (L == 4) return with_groups(std::integral_constant<int, 4>{});
+    if (L == 8) return with_groups(std::integral_constant<int, 8>{});
+    return with_groups(std::integral_constant<int, 16>{});
+}
+
+// May the rows be moved by workgroups that read the logits while others store (small_step_kernel)?  Only if nothing that is stored
+// shares memory with what is read; the other forms read all logits before they store a row.  `out` and its bytes: 0 without it.
+// ws_bytes: 0 if the plan tables are the library's own.
+bool small_rows_apart(const Geometry &g, const float *logits, const void *x, const int32_t *topk_idx, const float *gates, const void *stage,
+                      const void *final_, const void *out, const void *ws, int64_t ws_bytes)
+{
+    struct Range {
+        const void *p;
+        int64_t n;
+    };
+    const Shape &s = g.s;
+    const int64_t xb = (int64_t)s.T * g.row_bytes, fb = g.max_rows * g.row_bytes, tk = (int64_t)s.T * s.k * 4;
+    const Range read[] = {{logits, (int64_t)s.T * s.E * 4}, {x, xb}};
+    const Range stored[] = {{topk_idx, tk}, {gates, tk}, {stage, fb}, {final_, fb}, {out, out ? xb : 0}, {ws, ws_bytes}};
+    constexpr int kStored = sizeof(stored) / sizeof(stored[0]);
+    for (int i = 0; i < kStored; ++i) {
+        if (!stored[i].n) continue;
+        for (const Range &r : read)
+            if (overlap(r.p, r.n, stored[i].p, stored[i].n)) return false;
+        for (int j = 0; j < i; ++j)                 // what two launches would store one after the other
+            if (stored[j].n && overlap(stored[i].p, stored[i].n, stored[j].p, stored[j].n)) return false;
+    }
+    return true;
 }
 
 int check_ws(const void *ws)
@@ -808,13 +908,6 @@ bool plan_pack_shape_ok(const Geometry &g)
     const int rows_per_wg = kMoverThreads / s.lpr;
     return s.fast_plan && (int64_t)s.num_blocks * s.E <= 2048 && s.Tu % s.TB == 0 && rows_per_wg <= s.TB &&
            kMoverThreads >= s.TB;
-}
-
-// Do the bytes [a, a + na) and [b, b + nb) share any?
-bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
-{
-    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
-    return pa < pb + (uintptr_t)nb && pb < pa + (uintptr_t)na;
 }
 
 // By default the dispatch runs in one pass (place_kernel): each row is read once and stored to its rows in STAGE and in
@@ -921,6 +1014,7 @@ int route_impl(const Geometry &g, const float *logits, int32_t *topk_idx, float 
 {
     const Shape &s = g.s;
     PlanPtrs p = plan_ptrs(g, ws);
+    if (const int L = small_lanes(g, false)) return launch_small(g, p, L, SMALL_ROUTE, logits, nullptr, topk_idx, gates, nullptr, nullptr, nullptr, false, st);
     if (int rc = launch_route(g, p, logits, topk_idx, gates, st)) return rc;
     ProfScope ps(MONTA_K_POSITIONS, st);
     hipLaunchKernelGGL(plan_positions_kernel, dim3(s.num_blocks), dim3(kPlanThreads), 0, st, topk_idx, p, s);
@@ -995,6 +1089,9 @@ int route_dispatch_regather_impl(const Geometry &g, const float *logits, const v
     const Shape &s = g.s;
     if (single_pass(g, x, final_)) {
         const PlanPtrs p = plan_ptrs(g, ws);
+        const int L = g.modes.cache < 0 ? small_lanes(g, true) : 0;
+        if (L && small_rows_apart(g, logits, x, topk_idx, gates, stage, final_, nullptr, ws, ws_bytes(g)))
+            return launch_small(g, p, L, SMALL_PLACE, logits, x, topk_idx, gates, stage, final_, nullptr, false, st);
         if (const int span = plan_place_span(g)) {
             if ((rc = launch_route(g, p, logits, topk_idx, gates, st))) return rc;
             return launch_plan_place(g, p, span, topk_idx, x, stage, final_, st);
@@ -1602,6 +1699,9 @@ int monta_route_dispatch_combine_static(const monta_cfg *cfg, const float *logit
     void *ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int lanes = g.modes.cache < 0 && single_pass(g, x, final_) ? small_lanes(g, true) : 0;
+    if (lanes && small_rows_apart(g, logits, x, topk_idx, gates, stage, final_, out, nullptr, 0))
+        return launch_small(g, plan_ptrs(g, ws), lanes, SMALL_COMBINE, logits, x, topk_idx, gates, stage, final_, out, cfg->dtype == MONTA_BF16, st);
     // the array keeps the previous call's contents, possibly of another shape: no kernel reads what this call has not written
     if ((rc = route_dispatch_regather_impl(g, logits, x, topk_idx, gates, stage, final_, ws, st))) return rc;
     return combine_impl(g, cfg->dtype, final_, gates, out, ws, st);

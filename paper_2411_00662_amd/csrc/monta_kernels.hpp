@@ -31,6 +31,13 @@ struct PlanPtrs {
     int32_t *pos_final, *pos_stage, *row_map, *block_counts, *block_base, *local_rank, *kept_prefix;
 };
 
+// n / d for 0 <= n < 2^16 and d < 2^15, by a multiplication: an integer division takes about 40 instructions
+struct FastDiv {
+    uint32_t d, m;
+};
+inline FastDiv fast_div(int d) { return {(uint32_t)d, d > 1 ? (uint32_t)((1ull << 32) / (uint32_t)d + 1) : 0u}; }
+__device__ __forceinline__ int operator/(int n, FastDiv f) { return f.m ? (int)__umulhi((uint32_t)n, f.m) : n; }
+
 struct Shape {
     int32_t T, E, k, ep, tp, S, U, Tu;
     int32_t TB;        // tokens per route workgroup
@@ -44,6 +51,7 @@ struct Shape {
     int32_t cache;     // CachePolicy bits: which streams of the movers use non-temporal accesses
     int32_t padded;    // 1: FINAL is [E][C][H] (expert e at row e*C), 0: compact
     int32_t rl;        // lanes that share one token in the route kernel (1, 2, 4 or 8)
+    FastDiv by_E, by_k, by_k1, by_Tu, by_ep;       // for the pairs of a route workgroup (by_k1: k - 1) and for small problems
     int32_t fast_plan; // 1: every workgroup reduces the histogram table; 0: block_scan_kernel scans it first
 };
 
@@ -55,15 +63,20 @@ enum CachePolicy {
 
 // ------------------------------------------------------------------ helpers
 
-__device__ __forceinline__ int wave_inclusive_scan(int v, int lane)
+// Inclusive sum over the wave by DPP moves: shifts inside the rows of 16 lanes, then the rows' totals.  All 64 lanes take part.
+// (Six shuffles through the LDS instead took about 600 clocks, and a plan needs several scans in a row.)
+__device__ __forceinline__ int wave_inclusive_scan(int v)
 {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        int o = __shfl_up(v, d, kWave);
-        if (lane >= d) v += o;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);        // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);        // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);        // row_bcast:31 into rows 2 and 3
     return v;
 }
+// the sum over the wave, from its inclusive scan
+__device__ __forceinline__ int wave_total(int scan) { return __builtin_amdgcn_readlane(scan, kWave - 1); }
 
 template <bool NT>
 __device__ __forceinline__ u32x4 ld16(const u32x4 *p)
@@ -130,12 +143,133 @@ __host__ __device__ inline int route_row_stride(int E, int L) { return L * (((E 
 template <int MASK>
 __device__ __forceinline__ int xor_lanes(int v)
 {
-    static_assert(MASK == 1 || MASK == 2 || MASK == 4, "xor_lanes: lanes of one token");
-    constexpr int kCtrl = MASK == 1 ? 0xb1 : MASK == 2 ? 0x4e : 0x141;
+    static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8, "xor_lanes: lanes of one token");
+    constexpr int kCtrl = MASK == 1 ? 0xb1 : MASK == 2 ? 0x4e : MASK == 4 ? 0x141 : 0x140;
     return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, false);
 }
 
-template <int L, int GS>
+// Steps 1, 2 and the masks of 4: the choices of `nt` tokens whose logits start at src.  Bit tok % 64 of s_mask[e * expert_step +
+// tok / 64 * word_step] (cleared by the caller) is set where token tok chose e.  idx_out: also to memory, if it is not null.
+// s_den: sums of all exponentials, if it is not null.  All threads of the workgroup; ends without a barrier.
+template <int L, int NE>
+__device__ __forceinline__ void route_select(const float *__restrict__ src, int nt, int E, int k, int stride, float *s_l, int *s_sel,
+                                             unsigned long long *s_mask, int expert_step, int word_step, double *s_den,
+                                             int32_t *__restrict__ idx_out, FastDiv by_E)
+{
+    const int tid = threadIdx.x;
+    {
+        const int total = nt * E;
+        // element i is column i % E of token i / E: one division, then steps.  Eight loads are requested before the first is
+        // laid down: one at a time the tile arrives at one memory latency per element of a lane.
+        constexpr int LD = 8;
+        const int nthr = blockDim.x, step_tok = nthr / by_E, step_col = nthr - step_tok * E;
+        int tok = tid / by_E, col = tid - tok * E;
+        for (int i0 = tid; i0 < total; i0 += LD * nthr) {
+            float v[LD];
+#pragma unroll
+            for (int q = 0; q < LD; ++q) v[q] = src[i0 + q * nthr < total ? i0 + q * nthr : i0];
+#pragma unroll
+            for (int q = 0; q < LD; ++q) {
+                if (i0 + q * nthr < total) s_l[tok * stride + col] = v[q] != v[q] ? -INFINITY : v[q];
+                tok += step_tok;
+                col += step_col;
+                if (col >= E) {
+                    col -= E;
+                    ++tok;
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    // token handled by this lane, and which of the token's L lanes it is
+    const int tok = tid / L, sub = tid % L;
+    const int tword = tok >> 6;                     // mask word and bit of the token inside the workgroup
+    const unsigned long long tbit = 1ull << (tok & 63);
+    const bool active = tok < nt;
+    if (active) {
+        const float *row = s_l + tok * stride;
+        int *sel = s_sel + tok * k;
+        // The lane's elements as unsigned keys of the same order (zeros of both signs alike); 0: taken, or no element.
+        uint32_t key[NE];
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int e = sub + q * L;
+            const uint32_t u = __float_as_uint(row[e < E ? e : E - 1] + 0.f);
+            key[q] = e < E ? u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u) : 0u;
+        }
+        int first = 0;
+        for (int j = 0; j < k; ++j) {
+            uint32_t most = key[0];
+#pragma unroll
+            for (int q = 1; q < NE; ++q) most = max(most, key[q]);
+            auto larger = [&](auto mask) { most = max(most, (uint32_t)xor_lanes<decltype(mask)::value>((int)most)); };
+            if constexpr (L > 1) larger(std::integral_constant<int, 1>{});
+            if constexpr (L > 2) larger(std::integral_constant<int, 2>{});
+            if constexpr (L > 4) larger(std::integral_constant<int, 4>{});
+            if constexpr (L > 8) larger(std::integral_constant<int, 8>{});
+            int at = E;                             // the lowest place of that value: in this lane, then among the token's lanes
+#pragma unroll
+            for (int q = NE - 1; q >= 0; --q) at = key[q] == most ? sub + q * L : at;
+            auto lower = [&](auto mask) { at = min(at, xor_lanes<decltype(mask)::value>(at)); };
+            if constexpr (L > 1) lower(std::integral_constant<int, 1>{});
+            if constexpr (L > 2) lower(std::integral_constant<int, 2>{});
+            if constexpr (L > 4) lower(std::integral_constant<int, 4>{});
+            if constexpr (L > 8) lower(std::integral_constant<int, 8>{});
+            const int best = min(at, E - 1);        // E only if k > E; keeps indices in range
+            if (j == 0) first = best;
+            const int mine = best % L == sub ? best / L : -1;
+#pragma unroll
+            for (int q = 0; q < NE; ++q) key[q] = mine == q ? 0u : key[q];
+            if (sub == 0) {
+                sel[j] = best;
+                if (idx_out) idx_out[tok * k + j] = best;
+                atomicOr(&s_mask[best * expert_step + tword * word_step], tbit);
+            }
+        }
+        if (s_den) {
+            // softmax over all E: the token's lanes each sum their experts, then add up across the lanes
+            const double top_logit = (double)row[first];
+            double part = 0.0;
+            for (int e = sub; e < E; e += L) part += exp((double)row[e] - top_logit);
+            for (int mk = 1; mk < L; mk <<= 1) part += __shfl_xor(part, mk, kWave);
+            if (sub == 0) s_den[tok] = part;
+        }
+    }
+}
+
+// Step 3 for tokens [0, nt), by threads tid of nthr, in two parts with a barrier between: w_j = exp(l_j - l_0) in fp64 (w_0 = 1
+// needs no call), one (token, choice) pair per lane so that every lane has an exp to do, not only one per token; then the
+// denominator, summed in j order (or taken from s_den, the sums over all experts, if that is not null), one division, one rounding
+// to fp32: store(pair, gate).
+__device__ __forceinline__ void route_weights(int nt, int k, int stride, const float *s_l, const int *s_sel, double *s_w, FastDiv by_k1,
+                                              int tid, int nthr)
+{
+    for (int tk = tid; tk < nt; tk += nthr) s_w[tk * k] = 1.0;
+    for (int idx = tid; idx < nt * (k - 1); idx += nthr) {               // only the choices j >= 1 need an exp
+        const int tk = idx / by_k1, j = 1 + idx - tk * (k - 1);
+        const float *row = s_l + tk * stride;
+        const int *sel = s_sel + tk * k;
+        s_w[tk * k + j] = exp((double)row[sel[j]] - (double)row[sel[0]]);
+    }
+}
+template <typename F>
+__device__ __forceinline__ void route_gates(int nt, int k, const double *s_w, const double *s_den, FastDiv by_k, int tid, int nthr, F store)
+{
+    for (int idx = tid; idx < nt * k; idx += nthr) {
+        const int tk = idx / by_k;
+        double denom = 0.0;
+        if (!s_den) {
+            const double *wt = s_w + tk * k;
+            for (int j = 0; j < k; ++j) denom += wt[j];
+        } else {
+            denom = s_den[tk];
+        }
+        store(idx, (float)(s_w[idx] / denom));
+    }
+}
+
+template <int L, int NE>
 __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restrict__ logits,
                                                          int32_t *__restrict__ topk_idx,
                                                          float *__restrict__ gates, PlanPtrs p, Shape s)
@@ -159,133 +293,14 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
     if (nt > TB) nt = TB;
 
     for (int i = tid; i < E * NW; i += blockDim.x) s_mask[i] = 0ull;
-    {
-        const float *src = logits + (size_t)t_begin * E;
-        const int total = nt * E;
-        // element i is column i % E of token i / E: one division, then steps.  Eight loads are requested before the first is
-        // laid down: one at a time the tile arrives at one memory latency per element of a lane.
-        constexpr int LD = 8;
-        const int nthr = blockDim.x, step_tok = nthr / E, step_col = nthr % E;
-        int tok = tid / E, col = tid % E;
-        for (int i0 = tid; i0 < total; i0 += LD * nthr) {
-            float v[LD];
-#pragma unroll
-            for (int q = 0; q < LD; ++q) v[q] = src[i0 + q * nthr < total ? i0 + q * nthr : i0];
-#pragma unroll
-            for (int q = 0; q < LD; ++q) {
-                if (i0 + q * nthr < total) s_l[tok * stride + col] = v[q] != v[q] ? -INFINITY : v[q];
-                tok += step_tok;
-                col += step_col;
-                if (col >= E) {
-                    col -= E;
-                    ++tok;
-                }
-            }
-        }
-    }
+    route_select<L, NE>(logits + (size_t)t_begin * E, nt, E, k, stride, s_l, s_sel, s_mask, NW, 1, s.renorm ? nullptr : s_den,
+                        topk_idx + (size_t)t_begin * k, s.by_E);
     __syncthreads();
-
-    // token handled by this lane, and which of the token's L lanes it is
-    const int tok = tid / L, sub = tid % L;
-    const int tword = tok >> 6;                     // mask word and bit of the token inside the workgroup
-    const unsigned long long tbit = 1ull << (tok & 63);
-    const int t = t_begin + tok;
-    const bool active = tok < nt;
-    if (active) {
-        const float *row = s_l + tok * stride;
-        int *sel = s_sel + tok * k;
-        float pv = INFINITY, top_logit = 0.f;
-        int pi = -1;
-        // best element after (pv, pi) among this lane's elements g * GS .. g * GS + GS - 1
-        auto scan = [&](int g, float &bv, int &best) {
-            float v[GS];
-#pragma unroll
-            for (int q = 0; q < GS; ++q) {          // independent LDS reads
-                const int e = sub + (g * GS + q) * L;
-                v[q] = row[e < E ? e : E - 1];
-            }
-            best = -1;
-            bv = 0.f;
-#pragma unroll
-            for (int q = 0; q < GS; ++q) {
-                const int e = sub + (g * GS + q) * L;
-                const bool after_prev = (v[q] < pv) || (v[q] == pv && e > pi);
-                if (e < E && after_prev && (best < 0 || v[q] > bv)) { best = e; bv = v[q]; }
-            }
-        };
-        float gv[4];
-        int gi[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) scan(g, gv[g], gi[g]);
-        for (int j = 0; j < k; ++j) {
-            int best = -1;
-            float bv = 0.f;
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                if (gi[g] >= 0 && (best < 0 || gv[g] > bv)) { best = gi[g]; bv = gv[g]; }
-            auto agree = [&](auto mask) {           // on (value desc, index asc)
-                const float ov = __int_as_float(xor_lanes<decltype(mask)::value>(__float_as_int(bv)));
-                const int oi = xor_lanes<decltype(mask)::value>(best);
-                if (oi >= 0 && (best < 0 || ov > bv || (ov == bv && oi < best))) { best = oi; bv = ov; }
-            };
-            if constexpr (L > 1) agree(std::integral_constant<int, 1>{});
-            if constexpr (L > 2) agree(std::integral_constant<int, 2>{});
-            if constexpr (L > 4) agree(std::integral_constant<int, 4>{});
-            if (best < 0) best = (pi + 1 < E) ? pi + 1 : E - 1;   // unreachable for k <= E; keeps indices in range
-            pv = bv;
-            pi = best;
-            if (j == 0) top_logit = bv;
-            if (j + 1 < k) {
-                // the group of the winner, if it is this lane's, has lost its best element; groups of other lanes' winners
-                // are scanned in vain
-                const int g = (best / L) / GS;
-                float nv;
-                int ni;
-                scan(g, nv, ni);
-                if (best % L == sub) {
-#pragma unroll
-                    for (int o = 0; o < 4; ++o)
-                        if (o == g) { gv[o] = nv; gi[o] = ni; }
-                }
-            }
-            if (sub == 0) {
-                sel[j] = best;
-                topk_idx[(size_t)t * k + j] = best;
-                atomicOr(&s_mask[best * NW + tword], tbit);
-            }
-        }
-        if (!s.renorm) {
-            // softmax over all E: the token's lanes each sum their experts, then add up across the lanes
-            double part = 0.0;
-            for (int e = sub; e < E; e += L) part += exp((double)row[e] - (double)top_logit);
-            for (int mk = 1; mk < L; mk <<= 1) part += __shfl_xor(part, mk, kWave);
-            if (sub == 0) s_den[tok] = part;
-        }
-    }
+    route_weights(nt, k, stride, s_l, s_sel, s_w, s.by_k1, tid, blockDim.x);
     __syncthreads();
-    // gates: w_j = exp(l_j - l_0) in fp64 (w_0 = 1 needs no call), one (token, choice) pair per lane so that every
-    // lane of the workgroup has an exp to do, not only one lane per token; then the denominator is summed in j
-    // order (or taken from the sum over all experts), one division, one rounding to fp32.
+    route_gates(nt, k, s_w, s.renorm ? nullptr : s_den, s.by_k, tid, blockDim.x,
+                [&](int idx, float g) { gates[(size_t)t_begin * k + idx] = g; });
     const int npairs = nt * k;
-    for (int tk = tid; tk < nt; tk += blockDim.x) s_w[tk * k] = 1.0;
-    for (int idx = tid; idx < nt * (k - 1); idx += blockDim.x) {         // only the choices j >= 1 need an exp
-        const int tk = idx / (k - 1), j = 1 + idx - tk * (k - 1);
-        const float *row = s_l + tk * stride;
-        const int *sel = s_sel + tk * k;
-        s_w[tk * k + j] = exp((double)row[sel[j]] - (double)row[sel[0]]);
-    }
-    __syncthreads();
-    for (int idx = tid; idx < npairs; idx += blockDim.x) {
-        const int tk = idx / k;
-        double denom = 0.0;
-        if (s.renorm) {
-            const double *wt = s_w + tk * k;
-            for (int j = 0; j < k; ++j) denom += wt[j];
-        } else {
-            denom = s_den[tk];
-        }
-        gates[(size_t)t_begin * k + idx] = (float)(s_w[idx] / denom);
-    }
 
     for (int e = tid; e < E; e += blockDim.x) {
         int c = 0;
@@ -293,7 +308,7 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
         p.block_counts[(size_t)b * E + e] = c;
     }
     for (int idx = tid; idx < npairs; idx += blockDim.x) {      // one pair per lane again
-        const int tk = idx / k;
+        const int tk = idx / s.by_k;
         const int e = s_sel[idx];
         const int word = tk >> 6;
         int r = 0;
@@ -457,8 +472,8 @@ __device__ __forceinline__ void block_plan(BlockPlan &bp, int b, const PlanPtrs 
         for (int e0 = 0; e0 < E; e0 += kWave) {
             const int e = e0 + lane;
             const int v = e < E ? (bp.before[e] < C ? bp.before[e] : C) : 0;
-            const int incl = wave_inclusive_scan(v, lane);
-            base_u += __shfl(incl, kWave - 1, kWave);
+            const int incl = wave_inclusive_scan(v);
+            base_u += wave_total(incl);
         }
         for (int e0 = 0; e0 < E; e0 += kWave) {
             const int e = e0 + lane;
@@ -470,15 +485,15 @@ __device__ __forceinline__ void block_plan(BlockPlan &bp, int b, const PlanPtrs 
                 const int nxt = bp.before[e] + bp.unit[e];
                 nu = (nxt < C ? nxt : C) - lo;
             }
-            const int incl_off = wave_inclusive_scan(kp, lane);
-            const int incl_st = wave_inclusive_scan(nu, lane);
+            const int incl_off = wave_inclusive_scan(kp);
+            const int incl_st = wave_inclusive_scan(nu);
             if (e < E) {
                 bp.kpre[e] = carry_off + incl_off - kp;
                 bp.off[e] = s.padded ? e * C : carry_off + incl_off - kp;
                 bp.stage[e] = base_u + carry_stage + incl_st - nu;
             }
-            carry_off += __shfl(incl_off, kWave - 1, kWave);
-            carry_stage += __shfl(incl_st, kWave - 1, kWave);
+            carry_off += wave_total(incl_off);
+            carry_stage += wave_total(incl_st);
         }
         if (lane == 0) {
             bp.R = carry_off;
@@ -604,7 +619,7 @@ __device__ __forceinline__ void plan_positions_block(BlockPlan &bp, int b, const
     if (mine) atomicAdd(&bp.total[lane], mine);
     __syncthreads();
     if (tid < kWave) {
-        const int sum = __shfl(wave_inclusive_scan(bp.total[lane], lane), kWave - 1, kWave);
+        const int sum = wave_total(wave_inclusive_scan(bp.total[lane]));
         if (lane == 0 && sum) atomicAdd(&p.meta[META_ALIVE], sum);
     }
 }
@@ -719,10 +734,10 @@ __device__ __forceinline__ void regather_rows_t(u32x4 *stage, u32x4 *fin, const 
 // (0 <= i < E*C - R) belongs to the expert found by bisection over pad_before[e] = e*C - kept_prefix[e].
 // kept_prefix and kept: the plan tables, or the same values rebuilt in LDS.
 __device__ __forceinline__ void pad_rows(u32x4 *__restrict__ fin, const int32_t *kept_prefix, const int32_t *kept, int R,
-                                         const Shape &s, int wg, int nwg)
+                                         const Shape &s, int wg, int nwg, int nthr = kMoverThreads)
 {
     const int lpr = s.lpr, vpr = s.vpr, E = s.E, C = s.C;
-    const int rows_per_wg = kMoverThreads / lpr;
+    const int rows_per_wg = nthr / lpr;
     const int sub = threadIdx.x / lpr, lane = threadIdx.x - sub * lpr;
     int total = E * C - R;
     if (total > s.max_rows) total = s.max_rows;
@@ -1294,6 +1309,304 @@ __global__ __launch_bounds__(kMoverThreads) void combine_kernel(const u32x4 *__r
         combine_rows_t<BF16, NV, decltype(l)::value, decltype(st)::value>(y, gates, out, p.pos_final, s, 0, s.T,
                                                                           blockIdx.x, gridDim.x);
     });
+}
+
+// ---- small problems: routing, plan and rows in one launch
+//
+// A step of a few hundred tokens is three launches that wait for each other, each a chain of latencies (routing 5 us, plan and rows
+// 5, combine 4 for 64 tokens on 8 experts) with hardly any work in it.  Here every workgroup routes ALL tokens for itself, which
+// takes no longer than routing some of them as long as one pass of its threads covers them, and so knows every row without waiting
+// for another workgroup: the choices are bit masks per expert over the tokens, a pair's rank is a count of the bits before its
+// token, and what the units before send is a count of the bits before their first token.  Three workgroups write the
+// positions, the other plan tables, and the choices with the gates, the others each move threads / lanes-per-row rows.
+// WHAT: tables and gates alone (three workgroups), the rows as well, or the whole step with identity experts, in which a token's output is
+// added up from its row while that is in registers (the rows of its choices are copies of it) instead of being read back from FINAL.
+// What bounds it: a chain of latencies of about 8000 clocks (kernel arguments, logits, the choices one after the other, scans,
+// positions).  Measured on MI355X: 64 tokens, 8 experts, top-2, 4096 elements 12.8 us of GPU time in three launches, 7.7 in one;
+// where the lines lie stands at small_lanes.
+enum SmallWhat { SMALL_ROUTE = 0, SMALL_PLACE = 1, SMALL_COMBINE = 2 };
+
+// Dynamic LDS of the kernel (byte offsets; made on the host: in every workgroup it is a chain of a hundred scalar instructions).
+// NW: words of 64 tokens.
+struct SmallLds {
+    int stride, NW, sel, mask, w, den, gate, pre, total, off, kpre, base, stage, bytes;
+};
+inline SmallLds small_lds(int T, int E, int k, int U, int L)
+{
+    SmallLds l;
+    l.stride = route_row_stride(E, L);
+    l.NW = (T + kWave - 1) / kWave;
+    int64_t at = (int64_t)T * l.stride * 4;
+    auto take = [&](int64_t n) {
+        const int64_t o = (at + 7) & ~(int64_t)7;
+        at = o + n;
+        return (int)o;
+    };
+    l.sel = take((int64_t)T * k * 4);
+    l.mask = take((int64_t)E * l.NW * 8);
+    l.w = take((int64_t)T * k * 8);
+    l.den = take((int64_t)T * 8);
+    l.gate = take((int64_t)T * k * 4);
+    l.pre = take((int64_t)E * l.NW * 4);
+    l.total = take((int64_t)E * 4);
+    l.off = take((int64_t)E * 4);
+    l.kpre = take((int64_t)E * 4);
+    l.base = take(((int64_t)U + 1) * 4);
+    l.stage = take((int64_t)U * E * 4);
+    l.bytes = (int)at;
+    return l;
+}
+
+template <int L, int NE>
+__global__ __launch_bounds__(1024) void small_step_kernel(const float *__restrict__ logits, const u32x4 *__restrict__ x,
+                                                          int32_t *__restrict__ topk_idx, float *__restrict__ gates,
+                                                          u32x4 *__restrict__ stage, u32x4 *__restrict__ fin, u32x4 *__restrict__ out,
+                                                          PlanPtrs p, Shape s, SmallLds lds, int what, int bf16)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned long long s_alive[16];
+    const int T = s.T, E = s.E, k = s.k, U = s.U, Tu = s.Tu, C = s.C, vpr = s.vpr, lpr = s.lpr;
+    float *s_l = reinterpret_cast<float *>(smem);
+    int *s_sel = reinterpret_cast<int *>(smem + lds.sel);
+    unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(smem + lds.mask);      // [word][expert]
+    double *s_w = reinterpret_cast<double *>(smem + lds.w), *s_den = reinterpret_cast<double *>(smem + lds.den);
+    float *s_gate = reinterpret_cast<float *>(smem + lds.gate);                                 // of this workgroup's rows
+    int *s_pre = reinterpret_cast<int *>(smem + lds.pre), *s_total = reinterpret_cast<int *>(smem + lds.total);
+    int *s_off = reinterpret_cast<int *>(smem + lds.off), *s_kpre = reinterpret_cast<int *>(smem + lds.kpre);
+    int *s_base = reinterpret_cast<int *>(smem + lds.base), *s_stage = reinterpret_cast<int *>(smem + lds.stage);
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & (kWave - 1), wave = tid >> 6, nwaves = nthr >> 6;
+    const int NW = lds.NW, stride = lds.stride;
+    enum { PAIRS = 0, TABLES = 1, GATES = 2, ROWS = 3 };           // what workgroups 0, 1, 2 and the others write
+    const int role = blockIdx.x < ROWS ? (int)blockIdx.x : ROWS;
+    const bool mover = role == ROWS;
+
+    // the first pass of this thread's row is on its way while the tokens are routed
+    const int lshift = __builtin_ctz(lpr), rows = nthr >> lshift, sub = tid >> lshift, rl = tid - (sub << lshift);
+    const int t0 = mover ? ((int)blockIdx.x - ROWS) * rows : 0, t1 = mover ? min(t0 + rows, T) : T;
+    const int t = t0 + sub;
+    const bool have = mover && t < t1;
+    const u32x4 *src = x + (size_t)(have ? t : 0) * vpr;
+    u32x4 val[kVecInFlight];
+#pragma unroll
+    for (int q = 0; q < kVecInFlight; ++q)
+        if (have && rl + q * lpr < vpr) val[q] = src[rl + q * lpr];
+
+    for (int i = tid; i < E * NW; i += nthr) s_mask[i] = 0ull;
+    if (tid < 16) s_alive[tid] = 0ull;
+    const bool weighted = role == GATES || (mover && what == SMALL_COMBINE);
+    double *den = s.renorm || !weighted ? nullptr : s_den;
+    route_select<L, NE>(logits, T, E, k, stride, s_l, s_sel, s_mask, 1, E, den, role == GATES ? topk_idx : nullptr, s.by_E);
+    __syncthreads();
+    // Gates of all tokens, or of this workgroup's own: by the last waves first, beside the scans, which are the first waves' work.
+    const int rtid = nthr - 1 - tid;
+    if (weighted) route_weights(t1 - t0, k, stride, s_l + t0 * stride, s_sel + t0 * k, s_w + t0 * k, s.by_k1, rtid, nthr);
+    for (int e = tid; e < E; e += nthr) {
+        int c = 0;
+        for (int w = 0; w < NW; ++w) {
+            s_pre[w * E + e] = c;
+            c += __popcll(s_mask[w * E + e]);
+        }
+        s_total[e] = c;
+    }
+    __syncthreads();
+    if (weighted) {
+        route_gates(t1 - t0, k, s_w + t0 * k, den ? den + t0 : nullptr, s.by_k, rtid, nthr, [&](int idx, float g) {
+            if (mover) s_gate[idx] = g;
+            else gates[idx] = g;
+        });
+        if (role == GATES) return;
+    }
+    // pairs of expert e among the tokens before token `pos`
+    auto before = [&](int e, int pos) {
+        const int w = pos >> 6;
+        return w >= NW ? s_total[e] : s_pre[w * E + e] + __popcll(s_mask[w * E + e] & ((1ull << (pos & 63)) - 1ull));
+    };
+    // first rows: of the experts in FINAL (wave 0), of the blocks of the units that this workgroup needs in STAGE (wave 1 first);
+    // the counters of all experts are read before the first scan
+    constexpr int CH = 256 / kWave;
+    if (wave == 0) {
+        int kp[CH], carry = 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) kp[c] = c * kWave + lane < E ? min(s_total[c * kWave + lane], C) : 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (c * kWave >= E) break;
+            const int e = c * kWave + lane, incl = wave_inclusive_scan(kp[c]);
+            if (e < E) {
+                s_kpre[e] = carry + incl - kp[c];
+                s_off[e] = s.padded ? e * C : carry + incl - kp[c];
+            }
+            carry += wave_total(incl);
+        }
+        if (lane == 0) s_base[U] = carry;
+    }
+    const int u_end = (t1 - 1) / s.by_Tu;
+    for (int u = t0 / s.by_Tu + (wave == 0 ? nwaves - 1 : wave - 1); u <= u_end; u += nwaves) {
+        int lo[CH], nu[CH], sum = 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int e = c * kWave + lane;
+            lo[c] = nu[c] = 0;
+            if (c * kWave < E && e < E) {
+                lo[c] = min(before(e, u * Tu), C);
+                nu[c] = min(before(e, (u + 1) * Tu), C) - lo[c];
+            }
+            sum += lo[c];
+        }
+        int carry = wave_total(wave_inclusive_scan(sum));
+        if (lane == 0) s_base[u] = carry;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (c * kWave >= E) break;
+            const int e = c * kWave + lane, incl = wave_inclusive_scan(nu[c]);
+            if (e < E) s_stage[u * E + e] = carry + incl - nu[c];
+            carry += wave_total(incl);
+        }
+    }
+    __syncthreads();
+    // rows of choice j of token tok; false if it is dropped.  All earlier pairs of a kept one are kept.
+    auto place = [&](int tok, int j, int &pf, int &ps) {
+        const int e = s_sel[tok * k + j], u = tok / s.by_Tu;
+        const int r = before(e, tok), first = s_off[e], block = s_stage[u * E + e] - before(e, u * Tu);
+        const bool ok = r < C;
+        pf = ok ? first + r : -1;
+        ps = ok ? block + r : -1;
+        return ok;
+    };
+
+    if (role == PAIRS) {
+        for (int i = tid; i < T * k; i += nthr) {
+            const int tok = i / s.by_k;
+            int pf, ps;
+            if (place(tok, i - tok * k, pf, ps)) {
+                p.row_map[ps] = pf;
+                atomicOr(&s_alive[tok >> 6], 1ull << (tok & 63));
+            }
+            p.pos_final[i] = pf;
+            p.pos_stage[i] = ps;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            int alive = 0;
+            for (int w = 0; w < NW; ++w) alive += __popcll(s_alive[w]);
+            p.meta[META_ALIVE] = alive;
+        }
+        return;
+    }
+    if (role == TABLES) {
+        const int R = s_base[U], E_loc = E / s.ep;
+        for (int i = tid; i < U * E; i += nthr) {
+            const int u = i / s.by_E, e = i - u * E, lo = min(before(e, u * Tu), C);
+            p.n[i] = min(before(e, (u + 1) * Tu), C) - lo;
+            p.stage_off[i] = s_stage[i];
+            p.unit_base[i] = s_off[e] + lo;
+        }
+        for (int e = tid; e < E; e += nthr) {
+            p.counts[e] = s_total[e];
+            p.kept[e] = min(s_total[e], C);
+            p.offsets[e] = s_off[e];
+            p.kept_prefix[e] = s_kpre[e];
+        }
+        for (int u = tid; u <= U; u += nthr) p.unit_rows[u] = s_base[u];
+        for (int i = tid; i < U * s.ep; i += nthr) {        // rows for EP rank d = STAGE span of its experts inside the unit
+            const int u = i / s.by_ep, d = i - u * s.ep;
+            p.send_rows[i] = (d + 1 < s.ep ? s_stage[u * E + (d + 1) * E_loc] : s_base[u + 1]) - s_stage[u * E + d * E_loc];
+        }
+        if (tid == 0) {
+            p.offsets[E] = s.padded ? E * C : R;
+            p.kept_prefix[E] = R;
+            p.meta[META_R] = R;
+            p.meta[META_C] = C;
+            p.meta[META_FINAL_ROWS] = s.padded ? E * C : R;
+        }
+        return;
+    }
+
+    // One 16-byte vector of the output: the gate-weighted sum over the kept choices, in order, of copies of the row's vector
+    auto combined_as = [&](auto bf, u32x4 v, auto each_gate) {
+        constexpr bool BF16 = decltype(bf)::value;
+        constexpr int NF = BF16 ? 8 : 4;
+        double acc[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[f] = 0.0;
+        each_gate([&](double g) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if constexpr (BF16) {
+                    acc[2 * c] = __builtin_fma(g, bf16_lo(v[c]), acc[2 * c]);
+                    acc[2 * c + 1] = __builtin_fma(g, bf16_hi(v[c]), acc[2 * c + 1]);
+                } else {
+                    acc[c] = __builtin_fma(g, (double)__uint_as_float(v[c]), acc[c]);
+                }
+            }
+        });
+        u32x4 o;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if constexpr (BF16) o[c] = f64_to_bf16_rne(acc[2 * c]) | (f64_to_bf16_rne(acc[2 * c + 1]) << 16);
+            else o[c] = __float_as_uint((float)acc[c]);
+        }
+        return o;
+    };
+    auto combined = [&](u32x4 v, auto each_gate) {
+        return bf16 ? combined_as(std::true_type{}, v, each_gate) : combined_as(std::false_type{}, v, each_gate);
+    };
+    const int gbase = lpr >= kWave ? 0 : (lane & ~(lpr - 1)), gl = lane - gbase;
+    u32x4 *dst = out + (size_t)(have ? t : 0) * vpr;
+    if (k <= lpr) {
+        int ps = -1, pf = -1;
+        float my_g = 0.f;
+        const bool ok = have && gl < k && place(t, gl, pf, ps);
+        if (ok && what == SMALL_COMBINE) my_g = s_gate[sub * k + gl];
+        const unsigned int kmask = k >= 32 ? 0xffffffffu : ((1u << k) - 1u);
+        const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
+        for (int vbase = 0; vbase < vpr; vbase += lpr * kVecInFlight) {
+            const int v0 = vbase + rl;
+            if (vbase != 0) {
+#pragma unroll
+                for (int q = 0; q < kVecInFlight; ++q)
+                    if (have && v0 + q * lpr < vpr) val[q] = src[v0 + q * lpr];
+            }
+            for (unsigned int rem = kept; rem; rem &= rem - 1) {
+                const int j = __builtin_ctz(rem);
+                u32x4 *ds = stage + (size_t)__shfl(ps, gbase + j, kWave) * vpr, *df = fin + (size_t)__shfl(pf, gbase + j, kWave) * vpr;
+#pragma unroll
+                for (int q = 0; q < kVecInFlight; ++q)
+                    if (v0 + q * lpr < vpr) {
+                        st16<true>(ds + v0 + q * lpr, val[q]);
+                        df[v0 + q * lpr] = val[q];
+                    }
+            }
+            if (what == SMALL_COMBINE && have) {
+#pragma unroll
+                for (int q = 0; q < kVecInFlight; ++q) {
+                    const u32x4 o = combined(val[q], [&](auto add) {
+                        for (unsigned int rem = kept; rem; rem &= rem - 1) add((double)__shfl(my_g, gbase + __builtin_ctz(rem), kWave));
+                    });
+                    if (v0 + q * lpr < vpr) st16<true>(dst + v0 + q * lpr, o);
+                }
+            }
+        }
+    } else if (have) {
+        // fewer lanes per row than choices: rows of at most 256 bytes, one vector per lane
+        for (int j = 0; j < k; ++j) {
+            int pf, ps;
+            if (place(t, j, pf, ps) && rl < vpr) {
+                st16<true>(stage + (size_t)ps * vpr + rl, val[0]);
+                fin[(size_t)pf * vpr + rl] = val[0];
+            }
+        }
+        if (what == SMALL_COMBINE && rl < vpr) {
+            const u32x4 o = combined(val[0], [&](auto add) {
+                for (int j = 0; j < k; ++j) {
+                    int pf, ps;
+                    if (place(t, j, pf, ps)) add((double)s_gate[sub * k + j]);
+                }
+            });
+            st16<true>(dst + rl, o);
+        }
+    }
+    if (s.padded) pad_rows(fin, s_kpre, s_total, s_base[U], s, (int)blockIdx.x - ROWS, (int)gridDim.x - ROWS, nthr);
 }
 
 // The gather as a pass of its own: the STAGE rows of units [u0, u1) (one contiguous range, read from the
@@ -1921,7 +2234,7 @@ __device__ __forceinline__ ExpertTileHit find_expert_tile(const ExpertArgs &a, i
             const int64_t o = __shfl_up(incl, d, kWave);
             if (lane >= d) incl += o;
         }
-        const int64_t total = __shfl(incl, kWave - 1, kWave);
+        const int64_t total = wave_total(incl);
         if (L < before + total) {
             // an expert without tiles repeats its predecessor's running total, so the first lane past L has tiles
             const unsigned long long past = __ballot(L < before + incl);
