@@ -6,6 +6,10 @@ that the tensors are large enough for the shapes in ``cfg`` (the C side sees
 only pointers), and raises ``MontaError`` on a negative status.  No step of the
 path runs in Python, and there is no fallback: if ``libmonta.so`` has not been
 built, loading fails loudly.
+
+The calls of a step (routing, dispatch, combine, return, gate, experts) are marshalled
+by ``_host.so`` (csrc/host.cpp), which checks the same and hands whatever it does not
+take to the functions here.
 """
 from __future__ import annotations
 
@@ -14,6 +18,7 @@ import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libmonta.so")
+HOST_PATH = os.path.join(_PKG, "_host.so")
 
 FP32, BF16 = 0, 1
 (K_ROUTE, K_POSITIONS, K_PACK, K_REGATHER, K_PACK_REGATHER, K_COMBINE, K_COPY, K_PLAN_PACK, K_UNREGATHER,
@@ -130,6 +135,27 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_HOST_ENTRIES = ["monta_ws_layout_query", "monta_route", "monta_route_dispatch_regather", "monta_route_dispatch_combine_static",
+                 "monta_combine", "monta_unregather_combine", "monta_gate", "monta_expert_linear", "monta_route_dispatch_expert"]
+_native = None
+
+
+def _host():
+    """The native marshalling of the calls of a step, set up with this module's functions for what it does not take itself."""
+    global _native
+    if _native is None:
+        if not os.path.exists(HOST_PATH):
+            raise RuntimeError(f"{HOST_PATH} is missing: build it first (python -m paper_2411_00662_amd.build); "
+                               "there is no fallback path")
+        import torch  # noqa: F401  (its libraries have to be loaded before _host.so)
+        from . import _host as native
+        L = lib()
+        native.setup(monta_cfg, _ptr, _stream, _current_raw_stream, _check,
+                     tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _HOST_ENTRIES))
+        _native = native
+    return _native
+
+
 def monta_strerror(code: int) -> str:
     return lib().monta_strerror(int(code)).decode()
 
@@ -219,11 +245,7 @@ def monta_ws_init(cfg, ws, stream=None):
 
 
 def monta_route(cfg, logits, topk_idx, gates, ws, stream=None):
-    L = monta_ws_layout_query(cfg)
-    T, E, k = cfg.tokens, cfg.experts, cfg.top_k
-    _check(lib().monta_route(ctypes.byref(cfg), _ptr(logits, T * E * 4, "logits"), _ptr(topk_idx, T * k * 4, "topk_idx"),
-                             _ptr(gates, T * k * 4, "gates"), _ptr(ws, L.ws_bytes, "ws"), _stream(stream)),
-           "monta_route")
+    (_native or _host()).route(cfg, logits, topk_idx, gates, ws, stream)
 
 
 def monta_dispatch(cfg, x, stage, ws, slice=-1, stream=None):
@@ -250,23 +272,11 @@ def monta_dispatch_regather(cfg, x, stage, final_, ws, stream=None):
 
 
 def monta_route_dispatch_regather(cfg, logits, x, topk_idx, gates, stage, final_, ws, stream=None):
-    L = monta_ws_layout_query(cfg)
-    T, E, k = cfg.tokens, cfg.experts, cfg.top_k
-    row = cfg.hidden * _bpe(cfg)
-    _check(lib().monta_route_dispatch_regather(
-        ctypes.byref(cfg), _ptr(logits, T * E * 4, "logits"), _ptr(x, T * row, "x"), _ptr(topk_idx, T * k * 4, "topk_idx"),
-        _ptr(gates, T * k * 4, "gates"), _ptr(stage, L.max_rows * row, "stage"), _ptr(final_, L.max_rows * row, "final_"),
-        _ptr(ws, L.ws_bytes, "ws"), _stream(stream)), "monta_route_dispatch_regather")
+    (_native or _host()).route_dispatch_regather(cfg, logits, x, topk_idx, gates, stage, final_, ws, stream)
 
 
 def monta_route_dispatch_combine_static(cfg, logits, x, topk_idx, gates, stage, final_, out, stream=None):
-    L = monta_ws_layout_query(cfg)
-    T, E, k = cfg.tokens, cfg.experts, cfg.top_k
-    row = cfg.hidden * _bpe(cfg)
-    _check(lib().monta_route_dispatch_combine_static(
-        ctypes.byref(cfg), _ptr(logits, T * E * 4, "logits"), _ptr(x, T * row, "x"), _ptr(topk_idx, T * k * 4, "topk_idx"),
-        _ptr(gates, T * k * 4, "gates"), _ptr(stage, L.max_rows * row, "stage"), _ptr(final_, L.max_rows * row, "final_"),
-        _ptr(out, T * row, "out"), _stream(stream)), "monta_route_dispatch_combine_static")
+    (_native or _host()).route_dispatch_combine_static(cfg, logits, x, topk_idx, gates, stage, final_, out, stream)
 
 
 def monta_allgather_regather(cfg, stage, gathered, final_, ws, schedule=1, stream=None):
@@ -278,11 +288,7 @@ def monta_allgather_regather(cfg, stage, gathered, final_, ws, schedule=1, strea
 
 
 def monta_combine(cfg, y, gates, out, ws, stream=None):
-    L = monta_ws_layout_query(cfg)
-    row = cfg.hidden * _bpe(cfg)
-    _check(lib().monta_combine(ctypes.byref(cfg), _ptr(y, L.max_rows * row, "y"),
-                               _ptr(gates, cfg.tokens * cfg.top_k * 4, "gates"), _ptr(out, cfg.tokens * row, "out"),
-                               _ptr(ws, L.ws_bytes, "ws"), _stream(stream)), "monta_combine")
+    (_native or _host()).combine(cfg, y, gates, out, ws, stream)
 
 
 def monta_allgather(cfg, stage, gathered, ws, slice=-1, stream=None):
@@ -309,12 +315,7 @@ def monta_combine_staged(cfg, y_stage, gates, out, ws, slice=-1, stream=None):
 
 
 def monta_unregather_combine(cfg, y, y_stage, gates, out, ws, stream=None):
-    L = monta_ws_layout_query(cfg)
-    row = cfg.hidden * _bpe(cfg)
-    _check(lib().monta_unregather_combine(ctypes.byref(cfg), _ptr(y, L.max_rows * row, "y"),
-                                          _ptr(y_stage, L.max_rows * row, "y_stage"),
-                                          _ptr(gates, cfg.tokens * cfg.top_k * 4, "gates"), _ptr(out, cfg.tokens * row, "out"),
-                                          _ptr(ws, L.ws_bytes, "ws"), _stream(stream)), "monta_unregather_combine")
+    (_native or _host()).unregather_combine(cfg, y, y_stage, gates, out, ws, stream)
 
 
 def monta_set_pipeline_mode(mode: int):
@@ -350,32 +351,17 @@ def monta_get_cache_policy() -> int:
 
 
 def monta_gate(cfg, x, w_gate, logits, stream=None):
-    row = cfg.hidden * _bpe(cfg)
-    _check(lib().monta_gate(ctypes.byref(cfg), _ptr(x, cfg.tokens * row, "x"), _ptr(w_gate, cfg.experts * row, "w_gate"),
-                            _ptr(logits, cfg.tokens * cfg.experts * 4, "logits"), _stream(stream)), "monta_gate")
+    (_native or _host()).gate(cfg, x, w_gate, logits, stream)
 
 
 def monta_expert_linear(cfg, x_final, w_exp, out_features: int, y, ws, slice: int = -1, stream=None):
-    L = monta_ws_layout_query(cfg)
-    bpe = _bpe(cfg)
-    _check(lib().monta_expert_linear(ctypes.byref(cfg), _ptr(x_final, L.max_rows * cfg.hidden * bpe, "x_final"),
-                                     _ptr(w_exp, cfg.experts * int(out_features) * cfg.hidden * bpe, "w_exp"),
-                                     int(out_features), _ptr(y, L.max_rows * int(out_features) * bpe, "y"),
-                                     _ptr(ws, L.ws_bytes, "ws"), int(slice), _stream(stream)), "monta_expert_linear")
+    (_native or _host()).expert_linear(cfg, x_final, w_exp, int(out_features), y, ws, int(slice), stream)
 
 
 def monta_route_dispatch_expert(cfg, logits, x, topk_idx, gates, stage, final, w_exp, out_features: int, y, ws,
                                 overlap: int = 1, stream=None):
-    L = monta_ws_layout_query(cfg)
-    bpe = _bpe(cfg)
-    row = cfg.hidden * bpe
-    T, k = cfg.tokens, cfg.top_k
-    _check(lib().monta_route_dispatch_expert(
-        ctypes.byref(cfg), _ptr(logits, T * cfg.experts * 4, "logits"), _ptr(x, T * row, "x"),
-        _ptr(topk_idx, T * k * 4, "topk_idx"), _ptr(gates, T * k * 4, "gates"), _ptr(stage, L.max_rows * row, "stage"),
-        _ptr(final, L.max_rows * row, "final"), _ptr(w_exp, cfg.experts * int(out_features) * row, "w_exp"),
-        int(out_features), _ptr(y, L.max_rows * int(out_features) * bpe, "y"), _ptr(ws, L.ws_bytes, "ws"), int(overlap),
-        _stream(stream)), "monta_route_dispatch_expert")
+    (_native or _host()).route_dispatch_expert(cfg, logits, x, topk_idx, gates, stage, final, w_exp, int(out_features), y, ws,
+                                              int(overlap), stream)
 
 
 def monta_copy(dst, src, nbytes: int, stream=None):

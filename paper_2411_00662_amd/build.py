@@ -1,8 +1,9 @@
-"""Builds libmonta.so (HIP, gfx950) in-tree with hipcc.  Cross-compiles without a GPU."""
+"""Builds libmonta.so (HIP, gfx950) in-tree with hipcc, which cross-compiles without a GPU, and _host.so with the host compiler."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -10,6 +11,8 @@ SRC = os.path.join(PKG, "csrc", "monta.hip")
 DEPS = [SRC, os.path.join(PKG, "csrc", "monta_kernels.hpp"), os.path.join(PKG, "csrc", "monta_planner.hpp"),
         os.path.join(ROOT, "include", "monta.h")]
 LIB = os.path.join(PKG, "libmonta.so")
+HOST_SRC = os.path.join(PKG, "csrc", "host.cpp")
+HOST = os.path.join(PKG, "_host.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -20,7 +23,8 @@ HIPCC_FLAGS = [
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile the library.  With force=False an up-to-date library is kept."""
+    """Compile the library and the native half of the binding.  With force=False what is up to date is kept."""
+    build_host(force, verbose)
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in DEPS):
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -41,6 +45,26 @@ def build(force: bool = True, verbose: bool = False) -> str:
         os.remove(LIB)
         raise RuntimeError("kernels spill registers to scratch: " + ", ".join(f"{k} ({v} B/lane)" for k, v in spills))
     return LIB
+
+
+def build_host(force: bool = True, verbose: bool = False) -> str:
+    """Compile the native half of the binding against torch's headers."""
+    deps = [HOST_SRC, os.path.join(ROOT, "include", "monta.h")]
+    if not force and os.path.exists(HOST) and all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in deps):
+        return HOST
+    import torch
+    torch_dir = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
+           "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"], "-o", HOST, HOST_SRC,
+           "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if verbose or res.returncode != 0:
+        print(" ".join(cmd))
+        print(res.stdout, res.stderr)
+    if res.returncode != 0:
+        raise RuntimeError("the host compiler failed building _host.so")
+    return HOST
 
 
 def scratch_users(remarks: str):
