@@ -50,6 +50,7 @@ struct Shape {
     int32_t max_rows;  // rows STAGE / FINAL hold; every row index read from a table is checked against it
     int32_t cache;     // CachePolicy bits: which streams of the movers use non-temporal accesses
     int32_t padded;    // 1: FINAL is [E][C][H] (expert e at row e*C), 0: compact
+    int32_t lazy;      // 1: the single pass requests a token's row only when it knows that one of its choices is kept
     int32_t rl;        // lanes that share one token in the route kernel (1, 2, 4 or 8)
     FastDiv by_E, by_k, by_k1, by_Tu, by_ep;       // for the pairs of a route workgroup (by_k1: k - 1) and for small problems
     int32_t fast_plan; // 1: every workgroup reduces the histogram table; 0: block_scan_kernel scans it first
@@ -888,7 +889,9 @@ __device__ __forceinline__ void place_row(const u32x4 *__restrict__ src, u32x4 *
     }
 }
 
-// Tokens [t0, t0+nt), the rows of their choices taken from the plan tables.
+// Tokens [t0, t0+nt), the rows of their choices taken from the plan tables.  Where choices may be dropped (s.lazy) a row is
+// requested behind its token's table entries and not at all if none is kept: what bounds the pass is bytes, and enough other
+// workgroups are there to hide the entries' latency.
 template <bool WAVE, bool NTL, bool NTS, bool NTF>
 __device__ __forceinline__ void place_rows_t(const u32x4 *__restrict__ x, u32x4 *__restrict__ stage, u32x4 *__restrict__ fin,
                                              const PlanPtrs &p, const Shape &s, int t0, int nt, int wg, int nwg)
@@ -902,12 +905,15 @@ __device__ __forceinline__ void place_rows_t(const u32x4 *__restrict__ x, u32x4 
     for (int i = wg * rows_per_wg + sub; i < nt; i += nwg * rows_per_wg) {
         const int t = t0 + i;
         const u32x4 *src = x + (size_t)t * vpr;
-        // the row's first pass and the table entries are requested together; the row of a token whose choices were all
-        // dropped is read in vain
+        // otherwise the row's first pass and the table entries are requested together
         u32x4 val[kVecInFlight];
+        auto request = [&] {
 #pragma unroll
-        for (int q = 0; q < kVecInFlight; ++q)
-            if (lane + q * lpr < vpr) val[q] = ld16<NTL>(src + lane + q * lpr);
+            for (int q = 0; q < kVecInFlight; ++q)
+                if (lane + q * lpr < vpr) val[q] = ld16<NTL>(src + lane + q * lpr);
+        };
+        const bool lazy = s.lazy && (WAVE || k <= lpr);
+        if (!lazy) request();
         const size_t pair = (size_t)t * k;
         if (WAVE || k <= lpr) {
             int ps = -1, pf = -1;
@@ -917,6 +923,10 @@ __device__ __forceinline__ void place_rows_t(const u32x4 *__restrict__ x, u32x4 
             }
             const bool ok = (unsigned)ps < (unsigned)s.max_rows && (unsigned)pf < (unsigned)s.max_rows;
             const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
+            if (lazy) {
+                if (!kept) continue;
+                request();
+            }
             place_row<WAVE, NTL, NTS, NTF>(src, stage, fin, s, lane, gbase, kept, ps, pf, val);
         } else {
             // fewer lanes per row than choices (rows of at most 256 bytes): one choice after the other
@@ -946,7 +956,7 @@ __global__ __launch_bounds__(kMoverThreads) void place_kernel(const u32x4 *__res
 // The same ahead of the plan tables: the first n_plan workgroups finish the plan, each of the others rebuilds the scans
 // for the one route workgroup its `span` consecutive tokens belong to (the host checks the shape) and derives the rows of
 // their choices itself.  One rebuild serves all rows of a workgroup, and the first row and its routing are on their way
-// while it runs.
+// while it runs, also if s.lazy.
 template <bool WAVE, bool NTL, bool NTS, bool NTF>
 __device__ __forceinline__ void place_rows_selfplan_t(BlockPlan &bp, const u32x4 *__restrict__ x, u32x4 *__restrict__ stage,
                                                       u32x4 *__restrict__ fin, const int32_t *__restrict__ topk_idx,
@@ -963,24 +973,31 @@ __device__ __forceinline__ void place_rows_selfplan_t(BlockPlan &bp, const u32x4
     const int b = u * s.bpu + (t_first - u * s.Tu) / s.TB;
     u32x4 val[kVecInFlight];
     int e = 0, lr = 0;
-    auto request = [&](int t) {
+    auto request_row = [&](int t) {
         const u32x4 *src = x + (size_t)t * vpr;
 #pragma unroll
         for (int q = 0; q < kVecInFlight; ++q)
             if (lane + q * lpr < vpr) val[q] = ld16<NTL>(src + lane + q * lpr);
+    };
+    auto request = [&](int t, bool row) {
+        if (row) request_row(t);
         if (gl < k) {
             e = topk_idx[(size_t)t * k + gl];
             lr = p.local_rank[(size_t)t * k + gl];
         }
     };
-    if (t_first + sub < t_end) request(t_first + sub);
+    const bool lazy = s.lazy && (WAVE || k <= lpr);
+    if (t_first + sub < t_end) request(t_first + sub, true);
     block_plan(bp, b, p, s);
     for (int t = t_first + sub; t < t_end; t += rows_per_wg) {
-        if (t != t_first + sub) request(t);
+        const bool later = t != t_first + sub;
+        if (later) request(t, !lazy);
         if (WAVE || k <= lpr) {
             int ps = -1, pf = -1;
             const bool ok = gl < k && place_pair(bp, s, e, lr, pf, ps);
             const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
+            if (lazy && !kept) continue;
+            if (lazy && later) request_row(t);
             place_row<WAVE, NTL, NTS, NTF>(x + (size_t)t * vpr, stage, fin, s, lane, gbase, kept, ps, pf, val);
         } else {
             for (int j = 0; j < k; ++j) {
