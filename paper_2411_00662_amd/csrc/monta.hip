@@ -716,7 +716,7 @@ int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int3
     else rc = with_groups(std::integral_constant<int, 8>{});
     if (rc || g.s.fast_plan) return rc;
     ProfScope ps(MONTA_K_SCAN, st);
-    hipLaunchKernelGGL(block_scan_kernel, dim3((g.s.E + kWave - 1) / kWave), dim3(kScanWaves * kWave), 0, st, p, g.s);
+    hipLaunchKernelGGL(block_scan_kernel, dim3((g.s.E + kScanExperts - 1) / kScanExperts), dim3(kScanExperts * kWave), 0, st, p, g.s);
     HIP_TRY(hipGetLastError());
     return MONTA_OK;
 }

@@ -323,44 +323,54 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
 
 // Exclusive scans of the route workgroups' histograms, per expert, in workgroup (= token) order, for tables that are too
 // large for every workgroup of the next kernel to reduce: block_base[b][e] = pairs of e in workgroups before b, and
-// counts[e].  A workgroup takes 64 experts, one per lane, so that a wave reads whole lines; its 16 waves take a run of rows
-// each, sum it, and walk it again with the sum of the runs before.  Up to 16 loads in flight per lane: the table sits in
-// the L2, and one load at a time the scan would be a chain of round trips (a scan by the last route workgroup to finish,
-// expert by expert, took 270 us on a table of 512 x 256; this takes 7).
-constexpr int kScanWaves = 16;
-__global__ __launch_bounds__(kScanWaves * kWave) void block_scan_kernel(PlanPtrs p, Shape s)
+// counts[e].  A chain of latencies (the table sits in the L2), so a workgroup takes only 16 experts, half a line of a row, and 64
+// runs of rows at a time, one (expert, run) per thread: up to 1024 rows are one batch of loads, kept for the second walk, and
+// the 64 runs of an expert are one scan over a wave.  A table of 512 x 256 takes 4.3 us; 64 experts a workgroup, 16 runs walked
+// twice took 7.4 us, a scan by the last route workgroup to finish, expert by expert, 270.
+constexpr int kScanExperts = 16;
+__global__ __launch_bounds__(kScanExperts * kWave) void block_scan_kernel(PlanPtrs p, Shape s)
 {
     constexpr int LD = 16;
-    __shared__ int s_sum[kScanWaves][kWave];
+    __shared__ int s_sum[kScanExperts][kWave + 1];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int E = s.E, nb = s.num_blocks, e = blockIdx.x * kWave + lane;
+    const int col = threadIdx.x % kScanExperts, part = threadIdx.x / kScanExperts;
+    const int E = s.E, nb = s.num_blocks, e0 = blockIdx.x * kScanExperts, e = e0 + col;
     const bool on = e < E;
-    const int run = (nb + kScanWaves - 1) / kScanWaves;
-    const int lo = min(wave * run, nb), hi = min(lo + run, nb);
+    const int run = (nb + kWave - 1) / kWave;
+    const int lo = min(part * run, nb), hi = min(lo + run, nb);
     auto load = [&](int b0, int (&c)[LD]) {
 #pragma unroll
         for (int q = 0; q < LD; ++q) c[q] = on && b0 + q < hi ? p.block_counts[(size_t)(b0 + q) * E + e] : 0;
     };
-    int sum = 0;
-    for (int b0 = lo; b0 < hi; b0 += LD) {
+    int first[LD], sum = 0;
+    load(lo, first);
+#pragma unroll
+    for (int q = 0; q < LD; ++q) sum += first[q];
+    for (int b0 = lo + LD; b0 < hi; b0 += LD) {
         int c[LD];
         load(b0, c);
 #pragma unroll
         for (int q = 0; q < LD; ++q) sum += c[q];
     }
-    s_sum[wave][lane] = sum;
+    s_sum[col][part] = sum;
     __syncthreads();
-    int before = 0;
-    for (int v = 0; v < wave; ++v) before += s_sum[v][lane];
-    if (wave == kScanWaves - 1 && on) p.counts[e] = before + sum;
-    for (int b0 = lo; b0 < hi; b0 += LD) {
-        int c[LD];
-        load(b0, c);
+    const int mine = s_sum[wave][lane], incl = wave_inclusive_scan(mine);       // a wave scans the runs of one expert
+    s_sum[wave][lane] = incl - mine;
+    if (lane == kWave - 1 && e0 + wave < E) p.counts[e0 + wave] = incl;
+    __syncthreads();
+    int before = s_sum[col][part];
+    auto store = [&](int b0, const int (&c)[LD]) {
 #pragma unroll
         for (int q = 0; q < LD; ++q) {
             if (on && b0 + q < hi) p.block_base[(size_t)(b0 + q) * E + e] = before;
             before += c[q];
         }
+    };
+    store(lo, first);
+    for (int b0 = lo + LD; b0 < hi; b0 += LD) {
+        int c[LD];
+        load(b0, c);
+        store(b0, c);
     }
 }
 
