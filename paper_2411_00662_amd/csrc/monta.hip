@@ -952,12 +952,13 @@ int launch_place(const Geometry &g, const PlanPtrs &p, const void *x, void *stag
 int plan_place_span(const Geometry &g)
 {
     const Shape &s = g.s;
-    // A table that every workgroup reduces must be small.  Where the scans are there already the rows' own time decides: a
-    // launch less is worth it for short jobs (2048 tokens x 2 KiB, top-8 of 256: 45.6 -> 39.9 us; 32768 x 512 B, 285 MB: 92.6
-    // -> 85.9), long ones run better in the plain kernel (8192 x 4 KiB, 570 MB: 113.6 -> 116.3).
-    if (s.fast_plan ? (int64_t)s.num_blocks * s.E > 2048
-                    : ((int64_t)s.T + 2 * slice_rows_bound(g, s.S)) * g.row_bytes > (320ll << 20))
-        return 0;
+    // A table that every workgroup reduces must be small.  Otherwise the rows' own time decides: a launch less is worth it for
+    // short jobs, long ones run better in the plain kernel, whose workgroups take their rows in order.  Scans there already: 2048
+    // tokens x 2 KiB, top-8 of 256 45.6 -> 39.9 us, 32768 x 512 B, 285 MB 92.6 -> 85.9, but 8192 x 4 KiB, 570 MB 113.6 -> 116.3.  A
+    // small table, step in one kernel and in two: 167 MiB 54 and 56 us, 490 MiB 139 and 144, 843 MiB 240 and 245, 570 MiB 213 and 167,
+    // 1203 MiB 396 and 349, 1687 MiB 542 and 487, 2629 MiB 833 and 773; from 1 GiB on 0.86 to 1.00 over 24 shapes, below 0.77 to 1.08.
+    if (s.fast_plan && (int64_t)s.num_blocks * s.E > 2048) return 0;
+    if (((int64_t)s.T + 2 * slice_rows_bound(g, s.S)) * g.row_bytes > (s.fast_plan ? 1024ll : 320ll) << 20) return 0;
     auto fits = [&](int span) { return span <= s.TB && s.TB % span == 0 && (s.Tu % span == 0 || s.U == 1); };
     int span = kMoverThreads / s.lpr;
     if (!fits(span)) return 0;
