@@ -1,7 +1,7 @@
 // Argument marshalling of the calls that a program makes once or more per step, for binding.py.
 //
-// The same checks in Python take five attribute calls per tensor and a ctypes conversion per argument, 6 to 7 us for a call with
-// eight buffers, where a launch takes 2.5 us and the kernels of a small step 5 to 8.  A tensor that is not of torch's own classes
+// The same checks in Python take five attribute calls per tensor and a ctypes conversion per argument: a call with four buffers and
+// one launch was issued in 5.7 us, in 3.2 with this, where the kernels of a small step take 3 to 8.  A tensor that is not of torch's own classes
 // or does not pass a check, and everything that is no tensor, goes to binding.py's own function, which converts it or raises.
 // Measured on an MI355X machine: the two calls of a step of 256 tokens, 4 experts 14.2 -> 9.4 us, its first pass on new buffers 33.3 ->
 // 25.6; a call whose kernel takes longer than this marshalling gains it only where the GPU is waited for.
