@@ -785,11 +785,11 @@ int launch_small(const Geometry &g, const PlanPtrs &p, int L, SmallWhat what, co
     return with_groups(std::integral_constant<int, 16>{});
 }
 
-// May the rows be moved by workgroups that read the logits while others store (small_step_kernel)?  Only if nothing that is stored
-// shares memory with what is read; the other forms read all logits before they store a row.  `out` and its bytes: 0 without it.
-// ws_bytes: 0 if the plan tables are the library's own.
-bool small_rows_apart(const Geometry &g, const float *logits, const void *x, const int32_t *topk_idx, const float *gates, const void *stage,
-                      const void *final_, const void *out, const void *ws, int64_t ws_bytes)
+// May workgroups store while others still read the logits and the rows (small_step_kernel)?  Only if nothing that is stored shares
+// memory with what is read; the launches one after the other read a workgroup's logits before it stores, and all of them before a
+// row is stored.  A buffer that the call does not have is null; the plan tables are null, too, where they are the library's own.
+bool small_apart(const Geometry &g, const float *logits, const int32_t *topk_idx, const float *gates, const void *ws, const void *x = nullptr,
+                 const void *stage = nullptr, const void *final_ = nullptr, const void *out = nullptr)
 {
     struct Range {
         const void *p;
@@ -798,14 +798,14 @@ bool small_rows_apart(const Geometry &g, const float *logits, const void *x, con
     const Shape &s = g.s;
     const int64_t xb = (int64_t)s.T * g.row_bytes, fb = g.max_rows * g.row_bytes, tk = (int64_t)s.T * s.k * 4;
     const Range read[] = {{logits, (int64_t)s.T * s.E * 4}, {x, xb}};
-    const Range stored[] = {{topk_idx, tk}, {gates, tk}, {stage, fb}, {final_, fb}, {out, out ? xb : 0}, {ws, ws_bytes}};
+    const Range stored[] = {{topk_idx, tk}, {gates, tk}, {stage, fb}, {final_, fb}, {out, xb}, {ws, ws_bytes(g)}};
+    auto share = [](const Range &a, const Range &b) { return a.p && b.p && overlap(a.p, a.n, b.p, b.n); };
     constexpr int kStored = sizeof(stored) / sizeof(stored[0]);
     for (int i = 0; i < kStored; ++i) {
-        if (!stored[i].n) continue;
         for (const Range &r : read)
-            if (overlap(r.p, r.n, stored[i].p, stored[i].n)) return false;
+            if (share(r, stored[i])) return false;
         for (int j = 0; j < i; ++j)                 // what two launches would store one after the other
-            if (stored[j].n && overlap(stored[i].p, stored[i].n, stored[j].p, stored[j].n)) return false;
+            if (share(stored[i], stored[j])) return false;
     }
     return true;
 }
@@ -1020,7 +1020,9 @@ int route_impl(const Geometry &g, const float *logits, int32_t *topk_idx, float 
 {
     const Shape &s = g.s;
     PlanPtrs p = plan_ptrs(g, ws);
-    if (const int L = small_lanes(g, false)) return launch_small(g, p, L, SMALL_ROUTE, logits, nullptr, topk_idx, gates, nullptr, nullptr, nullptr, false, st);
+    const int L = small_lanes(g, false);
+    if (L && small_apart(g, logits, topk_idx, gates, ws))
+        return launch_small(g, p, L, SMALL_ROUTE, logits, nullptr, topk_idx, gates, nullptr, nullptr, nullptr, false, st);
     if (int rc = launch_route(g, p, logits, topk_idx, gates, st)) return rc;
     ProfScope ps(MONTA_K_POSITIONS, st);
     hipLaunchKernelGGL(plan_positions_kernel, dim3(s.num_blocks), dim3(kPlanThreads), 0, st, topk_idx, p, s);
@@ -1096,7 +1098,7 @@ int route_dispatch_regather_impl(const Geometry &g, const float *logits, const v
     if (single_pass(g, x, final_)) {
         const PlanPtrs p = plan_ptrs(g, ws);
         const int L = g.modes.cache < 0 ? small_lanes(g, true) : 0;
-        if (L && small_rows_apart(g, logits, x, topk_idx, gates, stage, final_, nullptr, ws, ws_bytes(g)))
+        if (L && small_apart(g, logits, topk_idx, gates, ws, x, stage, final_))
             return launch_small(g, p, L, SMALL_PLACE, logits, x, topk_idx, gates, stage, final_, nullptr, false, st);
         if (const int span = plan_place_span(g)) {
             if ((rc = launch_route(g, p, logits, topk_idx, gates, st))) return rc;
@@ -1706,7 +1708,7 @@ int monta_route_dispatch_combine_static(const monta_cfg *cfg, const float *logit
     if ((rc = static_scratch(&ws))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int lanes = g.modes.cache < 0 && single_pass(g, x, final_) ? small_lanes(g, true) : 0;
-    if (lanes && small_rows_apart(g, logits, x, topk_idx, gates, stage, final_, out, nullptr, 0))
+    if (lanes && small_apart(g, logits, topk_idx, gates, nullptr, x, stage, final_, out))
         return launch_small(g, plan_ptrs(g, ws), lanes, SMALL_COMBINE, logits, x, topk_idx, gates, stage, final_, out, cfg->dtype == MONTA_BF16, st);
     // the array keeps the previous call's contents, possibly of another shape: no kernel reads what this call has not written
     if ((rc = route_dispatch_regather_impl(g, logits, x, topk_idx, gates, stage, final_, ws, st))) return rc;

@@ -158,6 +158,49 @@ def test_shared_memory_takes_several_launches(m, shared):
         assert torch.equal(a, b)
 
 
+# what the launches one after the other define: the choices or gates of at most one routing workgroup's tokens anywhere in the logits'
+# memory, and with top-k = experts, where a token's gates are stored in place of its own logits, those of any number of tokens.  The
+# second shape's units are not divided by its rows per workgroup, so that its dispatch, too, routes by the call that monta_route makes.
+@pytest.mark.parametrize("call", ["route", "dispatch"])
+@pytest.mark.parametrize("T,E,k,tp,what,at", [(64, 8, 2, 1, "gates", 0), (64, 8, 2, 1, "gates", 37), (64, 8, 2, 1, "idx", 0),
+                                             (64, 8, 2, 1, "idx", 384), (62, 4, 4, 2, "gates", 0)])
+def test_routing_in_the_logits_memory(m, T, E, k, tp, what, at, call):
+    import torch
+    cfg = m.make_cfg(T, 512, m.BF16, E, k, 1, tp, 1, 0.5)
+    rng = np.random.default_rng(T + at)
+    logits = rng.normal(size=(T, E)).astype(np.float32)
+    x = workloads.f32_to_bf16_bits(rng.normal(size=(T, 512)).astype(np.float32))
+
+    def one(shared):
+        b = m.alloc_buffers(cfg, logits, x, canary=0xA5)
+        idx, gates = b.topk_idx, b.gates
+        if shared:
+            mem = b.logits.view(-1)[at:at + T * k]
+            if what == "gates":
+                gates = mem.view(T, k)
+            else:
+                idx = mem.view(torch.int32).view(T, k)
+        m.monta_profile_reset()
+        m.monta_profile_enable(True)
+        if call == "route":
+            m.monta_route(cfg, b.logits, idx, gates, b.ws)
+        else:
+            m.monta_route_dispatch_regather(cfg, b.logits, b.x, idx, gates, b.stage, b.final, b.ws)
+        m.monta_profile_enable(False)
+        assert m.monta_profile_read(m.KERNEL_NAMES.index("small_step"))[1] == (0 if shared else 1)
+        m.monta_profile_reset()
+        torch.cuda.synchronize()
+        t = m.read_tables(cfg, b.ws)
+        got = {n: np.asarray(t[n]).reshape(-1) for n in TABLES}
+        got.update(idx=idx.cpu().numpy(), gates=gates.view(torch.int32).cpu().numpy(), row_map=np.asarray(t["row_map"])[:t["R"]],
+                   stage=b.stage.view(torch.int16).cpu().numpy(), final=b.final.view(torch.int16).cpu().numpy())
+        return got
+
+    apart, shared = one(False), one(True)
+    for name in apart:
+        np.testing.assert_array_equal(shared[name], apart[name], err_msg=name)
+
+
 def test_replayed_from_a_hip_graph(m):
     import torch
     w = Workload("graph", 256, 1024, BF16, 8, 2, 4, 2, 2, 0.8, zipf_s=0.6)
