@@ -76,8 +76,16 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);        // row_bcast:31 into rows 2 and 3
     return v;
 }
-// the sum over the wave, from its inclusive scan
+// the sum over the wave, from its inclusive scan, in as many bits
 __device__ __forceinline__ int wave_total(int scan) { return __builtin_amdgcn_readlane(scan, kWave - 1); }
+__device__ __forceinline__ int64_t wave_total(int64_t scan)
+{
+    const uint32_t lo = (uint32_t)wave_total((int)(uint32_t)scan), hi = (uint32_t)wave_total((int)(uint32_t)((uint64_t)scan >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+static_assert(std::is_same<decltype(wave_total(int64_t{})), int64_t>::value, "a 64-bit sum over the wave stays one");
+template <typename T> int wave_inclusive_scan(T) = delete;        // wider values do not fit the 32-bit moves
+template <typename T> T wave_total(T) = delete;
 
 template <bool NT>
 __device__ __forceinline__ u32x4 ld16(const u32x4 *p)
