@@ -1215,33 +1215,52 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
         // validate() guarantees H % 8 == 0 (rows are whole 16-byte vectors) and E <= 256 (at most 8 tiles).
         //  - Few tiles of 16 tokens x 16 experts (or 32, where that makes them one round): the hidden axis is split, too.  More than a
         //    round of them only for up to 16 experts and rows over 2 KiB (8192 x 4096, 9 experts: 14 us, in 32 x 64 20; but 6144 x 512,
-        //    16 experts: 9.2 and 5.1).
-        //  - Up to 32736 tokens, and short rows on up to 32 experts beyond: direct-to-LDS tiles as small as come in one round (32 x 64
-        //    three per CU, the others two): 4096 x 4096, 256 experts 31 us in 512 tiles of 32 x 64, 23 in 32 x 128; 12000 x 7168, 128
-        //    experts 77, 83 and in 64 x 128 60.  One tile of 32 x 64 that holds all experts is kept up to three rounds' worth of
-        //    tiles and, on short rows, always.  Rows that are not whole steps, whose lines every tile fetches twice: 64 x 128 from 33
-        //    experts on (12000 x 4104, 64 experts: 47 and 39), the k-split form up to 32 experts and from 16353 tokens on (24000 x 8184,
-        //    24 experts: 104 and 82).
+        //    16 experts: 9.2 and 5.1), one round with 32 experts a tile for rows over 1 KiB (4096 x 1024, 17 experts: 5.6 and 6.4,
+        //    error against 64 bits 6.9e-8 and 7.0e-8; 2733 x 640, 20 experts: 6.4e-8 and 7.0e-8; but 2048 x 512, 40 experts: 7.0 us
+        //    and 5.8).
+        //  - Up to 32736 tokens, and short rows on up to 32 experts beyond: direct-to-LDS tiles.  32 x 64 come three per CU, the
+        //    others two; the larger, the fewer bytes, and the longer a workgroup's walk.
+        //    Up to 64 experts one tile of 32 x 64 holds them all: those up to three rounds' worth of tiles and, on short rows, always
+        //    (64 x 128 beyond: 25592 x 5120, 64 experts 60 and 56 us, three sets of activations in turn 86 and 70).
+        //    More experts: 32 x 64 up to a round of 256.  32 x 128 up to a round of those, unless the rows are short (4096 x 512, 256
+        //    experts: 7.7 us in 32 x 64, 8.4) or the last tile's columns are mostly idle (4644 x 5120, 160 experts: 31, 43 and in 64 x
+        //    128 40; but 4096 x 4096, 256 experts 31, 22 and 33).  Then 32 x 64 up to two rounds, and 64 x 128, except that rows of up to
+        //    4 KiB stay in 32 x 128 up to two rounds (12571 x 512, 65 experts: 11.9, 8.5 and 9.8; 12000 x 7168, 128 experts: 83, 77
+        //    and 60), as do rows of 8 KiB on more than 128 experts, a stride at which the 128 rows of weights of a larger tile
+        //    fall on few channels (8192 x 4096, 256 experts: 58, 37 and 43, in turn 61, 45 and 44; 192 experts 42, 36 and 43, in
+        //    turn 44, 39 and 43).
+        //    Rows that are not whole steps, whose lines every tile fetches twice: no two rounds of the smaller tiles (6188 x 1784, 192
+        //    experts: 24, 25 and 21), 64 x 128 from 33 experts on (12000 x 4104, 64 experts: 47 and 39), the k-split form up to 32
+        //    experts and from 16353 tokens on (24000 x 8184, 24 experts: 104 and 82).
         //  - Otherwise a workgroup per 32 tokens whose waves share the hidden axis, or per 128 tokens.
-        // Over 728 shapes (512 to 8184 elements, 600 to 60000 tokens, 9 to 256 experts) this takes 1.01 of the best form's time and 0.84
-        // of the time of the rule that drew its lines before the 32 x 64 tiles lost their conditions inside the loop.
+        // Over 1415 shapes of whole steps (64 to 8192 elements, 512 to 32736 tokens, 65 to 256 experts), one set of activations and
+        // several in turn, this takes 1.02 of the best tile's time.
         const int64_t tiles32 = (T + 31) / 32;
         const u32x4 *xv = static_cast<const u32x4 *>(x), *wv = static_cast<const u32x4 *>(w_gate);
         rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
         auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
-        const int64_t tiles16 = tiles(16, 16), round = 256;
-        const bool short_rows = H <= 1024, many = tiles32 >= 1024, odd = H % 64 != 0 && H >= 2048;
+        const int64_t tiles16 = tiles(16, 16), round = 256, n64 = tiles(32, 64), n128 = tiles(32, 128);
+        const bool whole = H % 64 == 0, short_rows = H <= 1024, many = tiles32 >= 1024, odd = !whole && H >= 2048;
         const bool k_split = (many && !(short_rows && E <= 32)) || (odd && E <= 32 && tiles32 >= 512);
+        auto use_32x64 = [&] {
+            if (odd && E > 32 && E <= 64 && T > 8192) return false;
+            if (E <= 64) return n64 <= 3 * round || short_rows;
+            if (n64 <= round) return true;
+            const bool wider = whole && !short_rows && n128 <= round && (H <= 2048 ? n64 == 2 * n128 : 2 * n64 >= 3 * n128);
+            return whole && !wider && n64 <= 2 * round;
+        };
+        auto use_32x128 = [&] {
+            if (E <= 64) return false;
+            return n128 <= (whole && (H <= 2048 || (H == 4096 && E > 128)) ? 2 * round : round);
+        };
         if (rc <= 0) {
             if (rc) return rc;
         }
         else if (tiles16 <= (E <= 16 && !short_rows ? 2 * round : round) || (!k_split && H > kBigMaxHidden))
             rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 1, st);
-        else if (!short_rows && E > 16 && tiles(16, 32) <= round) rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 2, st);
-        else if (!k_split && odd && E > 32 && E <= 64 && T > 8192) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
-        else if (!k_split && (tiles(32, 64) <= (E <= 64 ? 3 * round : round) || (E <= 64 && (short_rows || tiles(64, 128) < 2 * round))))
-            rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
-        else if (!k_split && tiles(32, 128) <= round) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
+        else if (H > 512 && E > 16 && tiles(16, 32) <= round) rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 2, st);
+        else if (!k_split && use_32x64()) rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
+        else if (!k_split && use_32x128()) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);
         else if (!k_split) rc = launch_gate_short<64, 128, 3>(xv, wv, logits, T, H, E, st);
         else if (E <= 32) rc = launch_gate<1, 1, 512, true>(xv, wv, logits, T, H, E, st);
         // More experts: at least one 128-token workgroup per CU, in which every wave owns whole output tiles (W_g is re-read once
