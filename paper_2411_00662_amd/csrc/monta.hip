@@ -1240,6 +1240,7 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
         rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
         auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
         const int64_t tiles16 = tiles(16, 16), round = 256, n64 = tiles(32, 64), n128 = tiles(32, 128);
+        const bool stream_x = T * H * 2 >= (300ll << 20);
         const bool whole = H % 64 == 0, short_rows = H <= 1024, many = tiles32 >= 1024, odd = !whole && H >= 2048;
         const bool k_split = (many && !(short_rows && E <= 32)) || (odd && E <= 32 && tiles32 >= 512);
         auto use_32x64 = [&] {
@@ -1265,14 +1266,15 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
         else if (E <= 32) rc = launch_gate<1, 1, 512, true>(xv, wv, logits, T, H, E, st);
         // More experts: at least one 128-token workgroup per CU, in which every wave owns whole output tiles (W_g is re-read once
         // per 128 tokens, and the small tiles let 3 workgroups share a CU).
-        // Activations as large as the memory-side cache (256 MB) leave nothing in it for the dispatch behind the gate: then they are
-        // streamed (65536 x 7168, 64 experts 175 -> 155 us, 128 experts 201 -> 192, 256 experts 336 and 333; 40000 x 1024, 82 MB, 21.8
-        // and 23.1).
+        // Activations well beyond the memory-side cache (256 MB) leave nothing in it for the dispatch behind the gate: then they are
+        // streamed.  At 256 MiB most of them are still there from whoever wrote them (32768 x 4096, 40 experts: one set used again
+        // 49 us and, streamed, 60, three in turn 66 and 59), at 300 no longer (38400 x 4096: 80 and 71, in turn 80 and 73); 65536 x
+        // 7168, 64 experts 175 -> 155, 128 experts 201 -> 192, 256 experts 336 and 333.
         else if (E <= 64)
-            rc = T * H * 2 >= (256ll << 20) ? launch_gate<4, 2, 128, false, true, true>(xv, wv, logits, T, H, E, st)
+            rc = stream_x ? launch_gate<4, 2, 128, false, true, true>(xv, wv, logits, T, H, E, st)
                                             : launch_gate<4, 2, 128, false, true>(xv, wv, logits, T, H, E, st);
         else if (E <= 128)
-            rc = T * H * 2 >= (256ll << 20) ? launch_gate<4, 4, 64, false, true, true>(xv, wv, logits, T, H, E, st)
+            rc = stream_x ? launch_gate<4, 4, 64, false, true, true>(xv, wv, logits, T, H, E, st)
                                             : launch_gate<4, 4, 64, false, true>(xv, wv, logits, T, H, E, st);
         else rc = launch_gate<4, 8, 64, false, true>(xv, wv, logits, T, H, E, st);
         if (rc) return rc;

@@ -55,12 +55,12 @@ def test_gate_bf16(T, H, E):
 
 
 # bf16: rows that are not whole steps in the direct-to-LDS tiles of each shape, and the lines drawn for them; short rows on up to 8
-# experts; two persistent workgroups per CU; and activations of 256 MiB, which are streamed
+# experts; two persistent workgroups per CU; and activations of 256 MiB, which are not streamed yet, and of 300 MiB, which are
 RAGGED = [(4100, 520, 33), (8161, 72, 9), (9000, 2056, 64), (12000, 1096, 200), (16353, 2056, 24), (16352, 2056, 24), (6000, 8, 100),
           (8200, 200, 128), (3000, 1032, 256), (33000, 1016, 32), (33000, 1032, 32)]
 SHORT_ROWS = [(2049, 8, 2), (2048, 64, 8), (5000, 1024, 8), (4097, 520, 5), (40001, 16, 1), (2049, 1088, 8)]
 PERSISTENT = [(5000, 1536, 7), (9001, 2048, 8), (4095, 1088, 3)]
-STREAMED = [(32768, 4096, 40), (32801, 4096, 65)]
+STREAMED = [(32768, 4096, 40), (32801, 4096, 65), (38400, 4096, 40), (38433, 4096, 65), (38480, 4088, 64)]
 
 
 # both sides of the lines between the direct-to-LDS tiles: one, two and three rounds of 32 x 64 and 32 x 128 on rows of up to 2 KiB, of
