@@ -836,6 +836,8 @@ int check_expert_args(const monta_cfg *cfg, const Geometry &g, const void *x_fin
     return MONTA_OK;
 }
 
+constexpr double kStreamWeightsFrom = 256 << 20, kCacheableWeights = 96 << 20;
+
 int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_final, const void *w_exp, int32_t out_features,
                         void *y, const void *ws, int slice, hipStream_t st)
 {
@@ -847,11 +849,19 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     a.H = cfg->hidden;
     a.N = out_features;
     a.max_rows = s.max_rows;
-    // Weights of half the memory-side cache (256 MB) or more are gone from it by the next call: that is the case from 128 MiB on if
-    // three sets are used in turn (16 experts of 4096 x 1024, 16 rows: 29.5 us, streamed 26.1; 100 MB 19.1 and 18.1, 67 MB 13.0 and
-    // 15.0).  Rows and base have to be whole 128-byte lines.
+    // Weights as large as the memory-side cache (256 MiB) do not stay in it from one call to the next as a whole.  A part of 96 MiB
+    // does, if the rest is streamed past it, and it costs nothing where other weights come between two calls.  8 experts of
+    // 4096 x 4096, 256 MiB, 16 rows, one set of weights used again, three in turn, five: plain 40.7, 54.1, 54.2 us, all streamed
+    // 46.6, 47.5, 47.4, all but 96 MiB 39.9, 47.3, 48.9; 16 of 2048 x 6144, 384 MiB 78, 77, 76, then 68, 68, 67 and 64, 68, 69; over 30
+    // shapes of 240 to 512 MiB the part is 0.82 to 1.05 of the better of the other two with one set, 0.97 to 1.03 with five.
+    // Below 256 MiB plain weights stay whole: 16 of 2048 x 2048, 128 MiB, 40 rows 21.5, 33.8 in turn, all streamed 28.7, 30.1.
+    // What counts are the experts that can have rows; as nobody knows which, each row of the weights has the same share.
+    // Rows and base have to be whole 128-byte lines.
     const int64_t w_row = (int64_t)cfg->hidden * (cfg->dtype == MONTA_BF16 ? 2 : 4);
-    a.stream_w = (int64_t)s.E * out_features * w_row >= (128ll << 20) && w_row % 128 == 0 && !misaligned(w_exp, 128);
+    const int64_t w_rows = (int64_t)s.E * out_features, kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
+    const double touched = (double)std::min<int64_t>(s.E, kept_bound) * out_features * w_row;
+    a.stream_from = touched >= kStreamWeightsFrom && w_row % 128 == 0 && !misaligned(w_exp, 128)
+                        ? (int64_t)(w_rows * (kCacheableWeights / touched)) : w_rows;
     // rows of expert e: its whole kept segment [offsets[e], offsets[e] + kept[e]), or the part of it filled by the
     // slice's units, which starts at unit_base[first unit of the slice][e] and ends where the next slice's starts
     a.lo = slice < 0 ? p.offsets : p.unit_base + (int64_t)slice * s.tp * s.E;
@@ -864,7 +874,6 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     }
     // worst case of the rows in play: every pair of the slice's tokens kept, as far as the capacity lets them (the rows of a
     // padded layout beyond them are never multiplied)
-    const int64_t kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
     const int64_t rows_bound = slice < 0 ? kept_bound : std::min<int64_t>(kept_bound, (int64_t)(s.T / s.S) * s.k);
     ProfScope ps(MONTA_K_EXPERT, st);
     if (cfg->dtype == MONTA_BF16) {

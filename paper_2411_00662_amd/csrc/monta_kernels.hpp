@@ -2231,7 +2231,8 @@ struct ExpertArgs {
     const int32_t *hi_base; // [E] one past its last row is hi_base[e] + hi_len[e] ...
     const int32_t *hi_len;  // [E] ... or hi_base[e] alone if this is nullptr
     int32_t E, H, N, max_rows;
-    int32_t stream_w;       // 1: weights that one workgroup reads are requested as streaming (kStreamLoad)
+    int64_t stream_from;    // first row of all experts' weights (expert * N + column) that is requested as streaming (kStreamLoad)
+                            // where one workgroup reads it
 };
 
 // The expert whose tiles include logical tile number L, found without walking the experts one by one (a walk costs
@@ -2457,8 +2458,8 @@ typedef __attribute__((address_space(3))) void lds_void;
 // memory-side cache until the next call it is worth 10-17 %, as the lines push nothing else out on their way.  Where it is not: on
 // rows that are not whole lines (a line at the seam of two rows is fetched twice), on a tile with a second reader, on weights
 // that the cache does hold; and in the register-staged tiles it changes nothing (64 experts of 7168 x 2048, 60 rows: 333 us with
-// and without).  8 experts of 4096 x 4096, 16 rows: 55.5 and 46.4 us (42 at 6.4 TB/s); 64 of 7168 x 2048, 16 rows 311 and
-// 277; but 16 of 8184 x 2048 112 and 127; 16 of 4096 x 1024 in 32 x 64 tiles, 40 rows 31 and 37; 8 of 2048 x 2048 12.7 and 14.8.
+// and without).  Three sets of weights in turn, plain and streamed: 64 experts of 7168 x 2048, 16 rows 311 and 277 us; but 16 of
+// 8184 x 2048 112 and 127; 16 of 4096 x 1024 in 32 x 64 tiles, 40 rows 31 and 37; 8 of 2048 x 2048 12.7 and 14.8.
 constexpr int kStreamLoad = 2;
 constexpr uint32_t kOutOfRange = 0x80000000u;                      // a lane offset past every descriptor: no access
 
@@ -2726,7 +2727,7 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     const uint32_t rowb = (uint32_t)cpr * 16;
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb);
-    if (a.stream_w && __builtin_amdgcn_readfirstlane(hit.tiles) == 1)
+    if ((int64_t)e * a.N + col0 >= a.stream_from && __builtin_amdgcn_readfirstlane(hit.tiles) == 1)
         expert_short_tile<XR, WR, NST, F32, F32, kStreamLoad>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
     else
         expert_short_tile<XR, WR, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
@@ -2827,13 +2828,13 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     ct = __builtin_amdgcn_readfirstlane(ct);
     // Streamed weights only in the form whose tiles mostly have one user and whose rows are whole lines.
     constexpr bool kMayStream = DEEP_W && !TAIL;
-    const bool stream = kMayStream && a.stream_w && __builtin_amdgcn_readfirstlane(alone);
     if (e >= a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup
     constexpr int kShortCols = RAGGED_LAST ? 128 : 256, kStages = RAGGED_LAST ? 5 : 3;
     static_assert(ShortTile<64, kShortCols, kStages>::kLdsBytes <= big_lds_bytes(DEEP_W), "short tile: stages must fit the kernel's LDS");
     const int xr = min(row_end - row0, BM);
     const int cols = xr <= kShortRows ? kShortCols : BN, col0 = ct * cols;
     if (col0 >= a.N) return;                                       // the second half of a last column tile may be empty
+    const bool stream = kMayStream && (int64_t)e * a.N + col0 >= a.stream_from && __builtin_amdgcn_readfirstlane(alone);
     const uint32_t rowb = (uint32_t)cpr * 16;
     const int wr = min(a.N - col0, cols);
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);

@@ -81,7 +81,8 @@ def test_long_rows_full_rounds(m):
     check_on_gpu(m, [40, 1, 0, 100, 33, 64, 65, 17], 4096, 57 * 256 + 8, BF16)
 
 
-# 128 MiB of weights and more, which are streamed where an expert's rows fit one tile and not where they take two
+# weights of 128 MiB, which are not streamed, and of 256 MiB and more, all but 96 MiB of which are where an expert's rows fit one tile
+# and not where they take two: the line lies inside an expert, on a column tile's edge or beside it
 @pytest.mark.parametrize("sizes,H,N,dtype", [
     ([16, 1, 0, 17, 33, 5, 32, 40], 4096, 2056, BF16),                                   # 32 x 64
     ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 4096, 2056, BF16),                              # 64 x 128
@@ -89,7 +90,11 @@ def test_long_rows_full_rounds(m):
     ([150, 256, 257, 65, 0, 64, 300, 255] * 4, 2048, 2056, BF16),                        # in place
     ([16, 1, 0, 17, 33, 5, 32, 40], 2048, 2052, FP32),
     ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 1024, 2052, FP32),
-], ids=["32x64", "64x128", "last", "inplace", "fp32", "fp32-64x64"])
+    ([16, 1, 0, 17, 33, 5, 32, 40], 4096, 4112, BF16),
+    ([1, 0, 0, 0, 9], 8192, 8200, BF16),
+    ([16, 1, 0, 17, 33, 5, 32, 40], 2048, 4104, FP32),
+    ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 1024, 4104, FP32),
+], ids=["32x64-plain", "64x128", "last", "inplace", "fp32-plain", "fp32-64x64-plain", "32x64", "32x64-few", "fp32", "fp32-64x64"])
 def test_streamed_weights(m, sizes, H, N, dtype):
     check_on_gpu(m, sizes, H, N, dtype)
 
