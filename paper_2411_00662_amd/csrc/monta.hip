@@ -644,20 +644,35 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
 //  - on rows of at most 512 (128 experts, 512 x 512, r = 192: 56, 39, 43, 29; 256 experts: 120, 74, 57, 55, skewed 60, 35, 40, 32);
 //  - on rows that are not whole steps, whose lines the large tile fetches twice, where an expert's second large tile would be
 //    half empty (16 experts, 8184 x 2048, r = 300: 614, 378, 363, 326; 64 experts, 3000 x 1024: 472, 279, 285, 265; r = 1000: 1537,
-//    773, 536, 614; r = 150: 270, 176, 121, 152).
+//    773, 536, 614; r = 150: 270, 176, 121, 152);
+//  - on such rows of up to 448 elements wherever the tiles are many, as a larger tile's walk is over before its loads are in flight
+//    (64 experts, 32 x 4096, r = 844: 407, 254, 218, 154; 256 experts, 120 x 256, r = 175: 37, 24, 58, 20).  Up to 56 rows per expert
+//    64 x 128 (256 experts, 88 x 3880, r = 19: 110, 79, 86, 85; 64 experts, 392 x 4096, r = 36: 54, 41, 52, 60), on rows of one step
+//    only up to 8 (256 experts, 48 x 1024, r = 22: 27, 19, 25, 18); 32 x 64 up to 5 tiles per CU where r is at most 16 (256
+//    experts, 48 x 4096, r = 4: 79, 60, 64, 59; 64 experts, 264 x 1184, r = 5: 10.9, 12.4, 15.3, 18.1).  Over 2600 shapes of such
+//    rows the choice takes 1.01 of the best form's time;
+//  - on such rows of up to 1104 elements and at most 256 features, one column tile (256 experts, 560 x 256, r = 196: 66, 44, 75, 37;
+//    64 experts, 1032 x 256, r = 766: 97, 60, 60, 50).
 int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
                         int64_t kept_bound, hipStream_t st)
 {
     const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
     auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
-    constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kRound = 512;
+    constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kRound = 512, kOddShortRow = 448, kOddNarrowRow = 1104;
     const int64_t one_row = active * ((a.N + 255) / 256), rounds = (one_row + kRound - 1) / kRound;
     const bool full_rounds = one_row * 10 >= rounds * kRound * (r < 64 ? 9 : 7);
+    if (a.H % 64 && a.H <= kOddShortRow) {
+        if (tiles(32, 64) <= (r <= 16 ? kFewTilesShortRows : kFewTiles)) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
+        if (r <= (a.H <= 64 ? 8 : 56) || tiles(64, 128) <= kFewTilesShortRows)
+            return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
+        return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
+    }
     if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
     if (a.H >= 4096 && a.E <= 64 && r <= 100 && full_rounds) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 56 || tiles(64, 128) <= (a.H <= 1024 ? kFewTilesShortRows : kFewTiles))
         return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
     if (a.H <= 512 && a.E <= 128 && r <= 384) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
+    if (a.H % 64 && a.H <= kOddNarrowRow && a.N <= kBigBN) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (a.H % 64 && r > kBigBM && r <= kBigBM * 3 / 2) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     return launch_expert_big(x_final, w_exp, y, a, rows_bound, r, st);
 }

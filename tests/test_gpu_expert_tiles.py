@@ -167,6 +167,21 @@ def test_ragged_steps(m, sizes, N, H):
     check(m, sizes, H, N, BF16)
 
 
+# such rows of up to 448 elements and just beyond: both sides of the lines between 32 x 64, 64 x 128 and the register-staged tiles
+@pytest.mark.parametrize("H", [8, 56, 72, 440, 456])
+@pytest.mark.parametrize("sizes,N", [([16, 17, 15, 16] * 16, 1280), ([16, 17, 15, 16] * 16, 1288), ([17, 18, 16, 17] * 16, 648),
+                                     ([8, 9, 7, 8] * 16, 4104), ([9, 10, 8, 9] * 16, 4104), ([56, 57, 55, 56] * 4, 7624),
+                                     ([57, 58, 57, 56] * 4, 7624), ([130, 1, 128, 129, 77, 255, 0, 31] * 3, 5128)],
+                         ids=["16", "16-many", "17", "8", "9", "56", "57", "many"])
+def test_short_ragged_steps(m, sizes, N, H):
+    check(m, sizes, H, N, BF16)
+
+
+@pytest.mark.parametrize("H,N", [(520, 248), (520, 256), (1096, 256), (520, 264), (1112, 256)])
+def test_ragged_steps_one_column_tile(m, H, N):
+    check(m, [130, 1, 128, 129, 577, 455, 0, 231] * 12, H, N, BF16)
+
+
 # fp32 tiles of 64 x 64, and several levels of sums
 @pytest.mark.parametrize("H", [4, 36, 60, 260, 1100])
 def test_fp32_one_tile_per_expert(m, H):
