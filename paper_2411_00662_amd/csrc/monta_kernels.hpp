@@ -2510,8 +2510,9 @@ struct ShortTile {
 // T: unsigned short, y is rounded to bf16; float, the sums themselves are stored, rows of whole 16-byte vectors (VEC) or of any N
 // columns.  Sums of the first kind are taken in two levels, 8 steps of the hidden axis at a time.  Those of the second, the
 // logits, in three, the lowest of one step (fp32) or of one to four, and there in a chain of additions per half of a step (in fp32
-// per element of a piece), so that neither short rows nor long ones cost precision.  Error against 64 bits with one chain and two
-// levels, and now: 512 elements 1.2e-7, 6.3e-8; 1832 1.3e-7, 7.6e-8; 8184 1.5e-7, 1.2e-7; fp32, 1000 2.9e-7, 9.6e-8, 8192 3.1e-7, 1.4e-7.
+// per element of a piece), so that neither short rows nor long ones cost precision; the middle one, on bf16 rows of up to 16 steps,
+// in a chain per even and odd step of each half of the row.  Error against 64 bits with one chain and two levels, and now: 512
+// elements 1.2e-7, 6.1e-8; 1536 1.3e-7, 7.4e-8; 8192 1.5e-7, 1.05e-7; fp32, 1000 2.9e-7, 9.6e-8, 8192 3.1e-7, 1.4e-7.
 // AUX_W: cache bits of the weights' loads.
 template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, typename T>
 __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
@@ -2598,42 +2599,95 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 #pragma unroll
     for (int q = 0; q < NST - 1; ++q) issue_any(q, q);
     int slot = 0;
-    // steps [from, to), whose loads ahead are of whole steps or not; the first BLOCKS blocks of rows are multiplied
-    auto walk = [&](auto blocks, auto whole, int from, int to) {
+    // step `step`, whose loads ahead are of whole steps or not: use(weights, rows) with the fragments of its first BLOCKS blocks of rows
+    auto advance = [&](auto blocks, auto whole, int step, auto use) {
         constexpr int BLOCKS = decltype(blocks)::value;
-        for (int step = from; step < to; ++step) {
-            __builtin_amdgcn_s_waitcnt(G::kWait);                      // stage `step` has landed (loads finish in order)
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): this wave's reads of the previous stage
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            const int free_slot = slot == 0 ? NST - 1 : slot - 1;      // of stage step-1
-            if constexpr (decltype(whole)::value) issue_whole(step + NST - 1, free_slot);
-            else issue_any(step + NST - 1, free_slot);
-            const int buf = slot * G::kStageBytes;
-            // all fragments of the step first, so that the reads' latency is paid once
-            f32x4 fw[2][CB], fx[2][BLOCKS];
+        __builtin_amdgcn_s_waitcnt(G::kWait);                          // stage `step` has landed (loads finish in order)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);                            // lgkmcnt(0): this wave's reads of the previous stage
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int free_slot = slot == 0 ? NST - 1 : slot - 1;          // of stage step-1
+        if constexpr (decltype(whole)::value) issue_whole(step + NST - 1, free_slot);
+        else issue_any(step + NST - 1, free_slot);
+        const int buf = slot * G::kStageBytes;
+        // all fragments of the step first, so that the reads' latency is paid once
+        f32x4 fw[2][CB], fx[2][BLOCKS];
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const int at = buf + ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
+        for (int ks = 0; ks < 2; ++ks) {
+            const int at = buf + ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
 #pragma unroll
-                for (int j = 0; j < CB; ++j) fw[ks][j] = *reinterpret_cast<const f32x4 *>(pw + at + j * 2048);
+            for (int j = 0; j < CB; ++j) fw[ks][j] = *reinterpret_cast<const f32x4 *>(pw + at + j * 2048);
 #pragma unroll
-                for (int i = 0; i < BLOCKS; ++i) fx[ks][i] = *reinterpret_cast<const f32x4 *>(px + at + i * 2048);
+            for (int i = 0; i < BLOCKS; ++i) fx[ks][i] = *reinterpret_cast<const f32x4 *>(px + at + i * 2048);
+        }
+        use(fw, fx);
+        slot = slot == NST - 1 ? 0 : slot + 1;
+    };
+    // steps [from, to), added to the chains
+    auto walk = [&](auto blocks, auto whole, int from, int to) {
+        for (int step = from; step < to; ++step)
+            advance(blocks, whole, step, [&](const auto &fw, const auto &fx) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int v = 0; v < (F32 ? 4 : 1); ++v)
+#pragma unroll
+                        for (int i = 0; i < decltype(blocks)::value; ++i)
+                            multiply(fw[ks], fx[ks][i], acc[!kLogits ? 0 : F32 ? v : ks][i], v);
+                if constexpr (kLogits && F32) {
+#pragma unroll
+                    for (int i = 0; i < decltype(blocks)::value; ++i)
+#pragma unroll
+                        for (int j = 0; j < CB; ++j) fold(i, j, part[i][j]);
+                }
+            });
+    };
+    // All steps of bf16 logits, a row of at most 16, with the sums of one step as the lowest level: added to the partial sums of the
+    // even or of the odd steps, with no chain to clear, which took a quarter of a short row's time (8192 x 512, 128 experts 7.3 us, now
+    // 6.5, 2500 x 512, 65 experts 5.5 and 4.8).  Two chains, as one came out less exact than the split tiles: 384 elements 6.3e-8 off
+    // 64 bits, now 5.9e-8, split tiles 5.9e-8; 640 7.0e-8, 6.4e-8 and 6.4e-8; 1024 7.0e-8, 6.8e-8 and 6.9e-8.
+    auto run_each = [&](auto blocks, int whole_to) {
+        constexpr int BLOCKS = decltype(blocks)::value;
+        f32x4 odd[BLOCKS][CB];
+        auto add_to = [&](auto sums) {
+            return [&, sums](const auto &fw, const auto &fx) {
+#pragma unroll
+                for (int i = 0; i < BLOCKS; ++i) {
+                    f32x4 half[2][CB];
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int j = 0; j < CB; ++j)
+                            half[ks][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ks][j]), __builtin_bit_cast(bf16x8, fx[ks][i]),
+                                                                                  (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < CB; ++j) sums[i][j] += half[0][j] + half[1][j];
+                }
+            };
+        };
+        auto walk_each = [&](auto whole, int from, int to) {          // `from` is an even step
+            for (int step = from; step < to; step += 2) {
+                advance(blocks, whole, step, add_to(&part[0]));
+                if (step + 1 < to) advance(blocks, whole, step + 1, add_to(&odd[0]));
             }
+        };
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
+        for (int i = 0; i < BLOCKS; ++i)
 #pragma unroll
-                for (int v = 0; v < (F32 ? 4 : 1); ++v)
+            for (int j = 0; j < CB; ++j) odd[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        const int span = nsteps <= 6 ? 6 : ((nsteps + 1) / 2 + 1) & ~1;                  // an even number, two of them from 7 steps on
+        for (int from = 0; from < nsteps; from += span) {
+            const int end = min(from + span, nsteps), mid = max(min(whole_to, end) & ~1, from);
+            walk_each(std::true_type{}, from, mid);
+            walk_each(std::false_type{}, mid, end);
 #pragma unroll
-                    for (int i = 0; i < BLOCKS; ++i) multiply(fw[ks], fx[ks][i], acc[!kLogits ? 0 : F32 ? v : ks][i], v);
-            if constexpr (kLogits && F32) {
+            for (int i = 0; i < BLOCKS; ++i)
 #pragma unroll
-                for (int i = 0; i < BLOCKS; ++i)
-#pragma unroll
-                    for (int j = 0; j < CB; ++j) fold(i, j, part[i][j]);
-            }
-            slot = slot == NST - 1 ? 0 : slot + 1;
+                for (int j = 0; j < CB; ++j) {
+                    total[i][j] += part[i][j] + odd[i][j];
+                    part[i][j] = odd[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                }
         }
     };
     // With at most half of the row blocks in use only those are multiplied.  One choice before the loop, as for the steps that are
@@ -2641,7 +2695,9 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     // 152, 48 workgroups: 21.8 us, now 16.4; 2 experts of 8192 x 64, 60 rows: 38 and 25).
     auto run = [&](auto blocks) {
         const int whole_to = cpr / 8 - (NST - 1);                      // up to here the step NST - 1 ahead is a whole one
-        const int span = kLevels ? 8 : nsteps, sub = !kLogits || F32 ? span : nsteps <= 12 ? 1 : nsteps <= 32 ? 2 : 4;
+        if constexpr (kLogits && !F32)
+            if (nsteps <= 16) return run_each(blocks, whole_to);
+        const int span = kLevels ? 8 : nsteps, sub = !kLogits || F32 ? span : nsteps <= 32 ? 2 : 4;
         for (int from = 0; from < nsteps; from += span) {
             const int end = min(from + span, nsteps);
             for (int first = from; first < end; first += sub) {

@@ -8,7 +8,9 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,H,E", [(4096, 1024, 17), (4096, 768, 32), (2048, 768, 64), (2574, 592, 32), (2733, 640, 20), (800, 1024, 128)])
+@pytest.mark.parametrize("T,H,E", [(4096, 1024, 17), (4096, 768, 32), (2048, 768, 64), (2574, 592, 32), (2733, 640, 20), (800, 1024, 128),
+                                   (5444, 384, 16), (3654, 360, 20), (1544, 320, 64), (2955, 320, 20), (2100, 256, 20), (2048, 512, 40),
+                                   (3000, 448, 24), (6000, 504, 12), (3000, 520, 20), (4096, 960, 24), (4096, 896, 17), (4096, 704, 25)])
 def test_error_of_many_tokens(T, H, E):
     import paper_2411_00662_amd as m
     if not torch.cuda.is_available():

@@ -64,11 +64,11 @@ STREAMED = [(32768, 4096, 40), (32801, 4096, 65), (38400, 4096, 40), (38433, 409
 
 
 # both sides of the lines between the direct-to-LDS tiles: one, two and three rounds of 32 x 64 and 32 x 128 on rows of up to 2 KiB, of
-# up to 4 KiB, of 8 KiB and others, with columns that fill their tiles or not; split tiles on rows of 1 to 2 KiB
+# up to 4 KiB, of 8 KiB and others, with columns that fill their tiles or not; split tiles on some rows of 1 to 2 KiB
 LINES = [(2730, 64, 129), (5461, 1024, 129), (5473, 64, 129), (8192, 512, 256), (8193, 64, 256), (8192, 1536, 128), (8193, 1536, 128),
          (3072, 1536, 129), (4096, 2112, 129), (4113, 2112, 129), (5473, 2112, 129), (8192, 4096, 192), (8193, 4096, 192), (8192, 4096, 128),
          (8193, 2112, 256), (24576, 1088, 33), (24577, 1088, 33), (24577, 1024, 64), (4096, 520, 17), (4097, 520, 17), (4096, 512, 17),
-         (6188, 1784, 192)]
+         (6188, 1784, 192), (4096, 576, 17), (4096, 1024, 24), (4096, 1024, 25), (4096, 952, 24)]
 
 
 @pytest.mark.parametrize("T,H,E", RAGGED + SHORT_ROWS + PERSISTENT + STREAMED + LINES)
