@@ -759,7 +759,7 @@ int small_lanes(const Geometry &g, bool rows)
     int L = 1;
     while (L < 16 && s.E / (2 * L) >= 8 && s.T * 2 * L <= 1024) L *= 2;
     const int per_lane = (s.E + L - 1) / L;
-    if (s.T * L > 1024 || per_lane > (L == 4 || L == 8 ? 32 : 16) || small_lds(s.T, s.E, s.k, s.U, L).bytes > (int)kRouteLdsBudget) return 0;
+    if (s.T * L > 1024 || per_lane > 16 || small_lds(s.T, s.E, s.k, s.U, L).bytes > (int)kRouteLdsBudget) return 0;
     return L;
 }
 
@@ -786,12 +786,8 @@ int launch_small(const Geometry &g, const PlanPtrs &p, int L, SmallWhat what, co
         HIP_TRY(hipGetLastError());
         return MONTA_OK;
     };
-    auto with_groups = [&](auto lc) -> int {        // a lane's elements
-        constexpr int LN = decltype(lc)::value;
-        if (per_lane <= 8) return launch(lc, std::integral_constant<int, 8>{});
-        if (per_lane <= 16) return launch(lc, std::integral_constant<int, 16>{});
-        if constexpr (LN == 4 || LN == 8) return launch(lc, std::integral_constant<int, 32>{});
-        return MONTA_ERR_UNSUPPORTED;
+    auto with_groups = [&](auto lc) -> int {        // a lane's elements: the limits above leave it 16 at most
+        return per_lane <= 8 ? launch(lc, std::integral_constant<int, 8>{}) : launch(lc, std::integral_constant<int, 16>{});
     };
     if (L == 1) return with_groups(std::integral_constant<int, 1>{});
     if (L == 2) return with_groups(std::integral_constant<int, 2>{});
@@ -979,8 +975,10 @@ int plan_place_span(const Geometry &g)
     // A table that every workgroup reduces must be small.  Otherwise the rows' own time decides: a launch less is worth it for
     // short jobs, long ones run better in the plain kernel, whose workgroups take their rows in order.  Scans there already: 2048
     // tokens x 2 KiB, top-8 of 256 45.6 -> 39.9 us, 32768 x 512 B, 285 MB 92.6 -> 85.9, but 8192 x 4 KiB, 570 MB 113.6 -> 116.3.  A
-    // small table, step in one kernel and in two: 167 MiB 54 and 56 us, 490 MiB 139 and 144, 843 MiB 240 and 245, 570 MiB 213 and 167,
-    // 1203 MiB 396 and 349, 1687 MiB 542 and 487, 2629 MiB 833 and 773; from 1 GiB on 0.86 to 1.00 over 24 shapes, below 0.77 to 1.08.
+    // small table, whole step in one kernel and in two over 80 shapes: from 1 GiB on two are never behind (1205 MiB 396 and 349 us,
+    // 1688 MiB 542 and 487, 2619 MiB 797 and 775, 1.00 to 1.14 times).  Below it bytes part them poorly, 0.92 to 1.31 times: mostly one
+    // leads (168 MiB 46.7 and 49.5, 492 MiB 139 and 144), but not on some rows of 2 to 8 KiB, several to a workgroup (29184 x 4 KiB,
+    // top-2, 570 MiB 213 and 167; 25088 x 8 KiB, 980 MiB 311 and 269).
     if (s.fast_plan && (int64_t)s.num_blocks * s.E > 2048) return 0;
     if (((int64_t)s.T + 2 * slice_rows_bound(g, s.S)) * g.row_bytes > (s.fast_plan ? 1024ll : 320ll) << 20) return 0;
     auto fits = [&](int span) { return span <= s.TB && s.TB % span == 0 && (s.Tu % span == 0 || s.U == 1); };

@@ -76,14 +76,8 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);        // row_bcast:31 into rows 2 and 3
     return v;
 }
-// the sum over the wave, from its inclusive scan, in as many bits
+// the sum over the wave, from its inclusive scan
 __device__ __forceinline__ int wave_total(int scan) { return __builtin_amdgcn_readlane(scan, kWave - 1); }
-__device__ __forceinline__ int64_t wave_total(int64_t scan)
-{
-    const uint32_t lo = (uint32_t)wave_total((int)(uint32_t)scan), hi = (uint32_t)wave_total((int)(uint32_t)((uint64_t)scan >> 32));
-    return (int64_t)((uint64_t)hi << 32 | lo);
-}
-static_assert(std::is_same<decltype(wave_total(int64_t{})), int64_t>::value, "a 64-bit sum over the wave stays one");
 template <typename T> int wave_inclusive_scan(T) = delete;        // wider values do not fit the 32-bit moves
 template <typename T> T wave_total(T) = delete;
 
@@ -134,21 +128,21 @@ __host__ __device__ inline int route_row_stride(int E, int L) { return L * (((E 
 
 // One workgroup routes TB consecutive tokens of ONE unit; s.rl lanes share a token (1 for few experts).
 //  1. the [nt][E] logits tile is staged in LDS (coalesced, odd row stride);
-//  2. k selections per token: the next winner is the largest element that comes after the previous winner in (value
-//     desc, index asc) order, so ties resolve to the lower index with no "taken" mask.  Lane `sub` of a token has every
-//     s.rl-th expert, in four groups of at most GS consecutive ones, and keeps the best remaining element of each group:
-//     only the group that the last winner came from has to be scanned again.  The lanes of a token agree through DPP moves.
+//  2. k selections per token.  Lane `sub` of a token keeps every L-th logit in registers, as an unsigned key of the same order;
+//     the largest key wins, among the lane's keys and then among the token's lanes, which agree through DPP moves, then the lowest
+//     index that has it, so ties resolve to the lower index; the winner's key is cleared.
 //  3. gates in fp64 from the winners' logits, one rounding to fp32;
 //  4. every lane ORs its bit into mask[expert][wave] in LDS; popcounts of those
 //     masks give the workgroup's expert histogram and each pair's stable rank inside
 //     the workgroup (lanes hold consecutive tokens, so bit order is token order).
 // No atomics decide a position: the result is deterministic.
 // What bounds it is the selection's instructions (and, for renorm = 0, E fp64 exponentials per token).  Measured with k whole
-// scans per token and one load at a time: 65536 tokens, 64 experts, top-8 31 us, now 20; 32768 tokens, 256 experts, top-8
-// about 65, now 27.
+// scans of the LDS tile per token and one load at a time: 65536 tokens, 64 experts, top-8 31 us, now 17; 32768 tokens, 256 experts,
+// top-8 about 65, now 23.
 //
-// The lanes of a token (L = s.rl of them, 1, 2, 4 or 8, neighbours in the wave) agree through DPP moves: quads by
-// permutation, the two quads of eight lanes by the half-row mirror, whose lanes hold the same pair by then.
+// The lanes of a token (L of them, s.rl = 1, 2, 4 or 8, for small problems up to 16, neighbours in the wave) agree through DPP moves:
+// quads by permutation, the two quads of eight lanes by the half-row mirror, the two eights by the row mirror, whose lanes hold
+// the same value by then.
 template <int MASK>
 __device__ __forceinline__ int xor_lanes(int v)
 {
@@ -2270,7 +2264,9 @@ __device__ __forceinline__ ExpertTileHit find_expert_tile(const ExpertArgs &a, i
             const int64_t o = __shfl_up(incl, d, kWave);
             if (lane >= d) incl += o;
         }
-        const int64_t total = wave_total(incl);
+        // 64 bits, and by a shuffle: from a lane read the compiler knows the tile's number for uniform and divides it in scalar code,
+        // four long chains of which cost every large tile's workgroup about 2 us (128 experts of 1024 x 480, 512 rows each 97 and 94)
+        const int64_t total = __shfl(incl, kWave - 1, kWave);
         if (L < before + total) {
             // an expert without tiles repeats its predecessor's running total, so the first lane past L has tiles
             const unsigned long long past = __ballot(L < before + incl);
