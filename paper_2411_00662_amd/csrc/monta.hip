@@ -847,7 +847,7 @@ int check_expert_args(const monta_cfg *cfg, const Geometry &g, const void *x_fin
     return MONTA_OK;
 }
 
-constexpr double kStreamWeightsFrom = 256 << 20, kCacheableWeights = 96 << 20;
+constexpr double kStreamWeightsFrom = 240 << 20, kCacheableWeights = 96 << 20;
 
 int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_final, const void *w_exp, int32_t out_features,
                         void *y, const void *ws, int slice, hipStream_t st)
@@ -860,17 +860,20 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     a.H = cfg->hidden;
     a.N = out_features;
     a.max_rows = s.max_rows;
-    // Weights as large as the memory-side cache (256 MiB) do not stay in it from one call to the next as a whole.  A part of 96 MiB
+    // Weights about as large as the memory-side cache (256 MiB) do not stay in it from one call to the next as a whole.  A part of 96 MiB
     // does, if the rest is streamed past it, and it costs nothing where other weights come between two calls.  8 experts of
     // 4096 x 4096, 256 MiB, 16 rows, one set of weights used again, three in turn, five: plain 40.7, 54.1, 54.2 us, all streamed
     // 46.6, 47.5, 47.4, all but 96 MiB 39.9, 47.3, 48.9; 16 of 2048 x 6144, 384 MiB 78, 77, 76, then 68, 68, 67 and 64, 68, 69; over 30
     // shapes of 240 to 512 MiB the part is 0.82 to 1.05 of the better of the other two with one set, 0.97 to 1.03 with five.
-    // Below 256 MiB plain weights stay whole: 16 of 2048 x 2048, 128 MiB, 40 rows 21.5, 33.8 in turn, all streamed 28.7, 30.1.
-    // What counts are the experts that can have rows; as nobody knows which, each row of the weights has the same share.
+    // The line lies at 240 MiB (8 of 4096 x 3840, 16 rows: 38.1, 49.7, 49.8, all but 96 MiB 39.2, 44.1, 45.2); below it plain weights stay whole:
+    // 16 of 2048 x 2048, 128 MiB, 40 rows 21.5, 33.8 in turn, all streamed 28.7, 30.1.
+    // What counts are the weights of the experts that have rows, in the mean of an even load (16 tokens, top-4 of 64, 5120 x 464: 290
+    // MiB, 40 experts with rows, one set 21.8 us and, by all 64, 24.1); as nobody knows which, each row of the weights has the same
+    // share.
     // Rows and base have to be whole 128-byte lines.
     const int64_t w_row = (int64_t)cfg->hidden * (cfg->dtype == MONTA_BF16 ? 2 : 4);
     const int64_t w_rows = (int64_t)s.E * out_features, kept_bound = std::min<int64_t>((int64_t)s.T * s.k, (int64_t)s.E * s.C);
-    const double touched = (double)std::min<int64_t>(s.E, kept_bound) * out_features * w_row;
+    const double with_rows = s.E * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)kept_bound)), touched = with_rows * out_features * w_row;
     a.stream_from = touched >= kStreamWeightsFrom && w_row % 128 == 0 && !misaligned(w_exp, 128)
                         ? (int64_t)(w_rows * (kCacheableWeights / touched)) : w_rows;
     // rows of expert e: its whole kept segment [offsets[e], offsets[e] + kept[e]), or the part of it filled by the
