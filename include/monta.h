@@ -234,7 +234,8 @@ int monta_dispatch_regather(const monta_cfg *cfg, const void *x, void *stage, vo
  * same tables.  By default, and in pipeline mode 1, for shapes whose histogram table is
  * small the kernel that finishes the plan also moves rows (all of them by default, slice
  * 0 in mode 1; those workgroups derive their rows themselves), so the first row does not
- * wait for the plan; otherwise the call is exactly the two calls in sequence. */
+ * wait for the plan; a small problem (up to 512 tokens) is routed and moved in one
+ * launch; otherwise the call is exactly the two calls in sequence. */
 int monta_route_dispatch_regather(const monta_cfg *cfg, const float *logits, const void *x, int32_t *topk_idx,
                                   float *gates, void *stage, void *final_, void *ws, void *stream);
 
@@ -316,7 +317,9 @@ int monta_pipeline_query(const monta_cfg *cfg, int32_t *mode, int32_t *first_sli
  * histogram table is small (num_blocks * experts <= 4096) every workgroup of the
  * positions kernel rebuilds the scans it needs from that table; otherwise, and always
  * with mode 0, a kernel of its own scans the table first.  Both produce identical
- * tables.  Process-wide. */
+ * tables.  With the default a small problem (up to 512 tokens, limits on tokens *
+ * experts) is routed in one launch without such a table; mode 0 keeps its launches
+ * apart.  Process-wide. */
 int monta_set_plan_mode(int mode);
 int monta_get_plan_mode(void);
 
@@ -324,7 +327,8 @@ int monta_get_plan_mode(void);
  * (streaming) accesses: 1 pack loads, 2 pack stores, 4 regather loads, 8 regather
  * stores, 16 combine loads, 32 combine stores.  A clear bit leaves that stream
  * cacheable, which pays when the next kernel finds the data in the memory-side cache.
- * -1 (default) lets the library choose from the working-set size.  Process-wide.
+ * -1 (default) lets the library choose from the working-set size; an explicit mask also
+ * keeps the rows of a small problem in a launch of their own.  Process-wide.
  * The single passes have fewer streams.  The dispatch's loads of x obey bit 1, its stores
  * to STAGE bit 2, its stores to FINAL bit 8; the return path's loads of y obey bit 4, its
  * stores to y_stage bit 8, its stores to out bit 32, and bit 16 has no effect there. */

@@ -91,10 +91,11 @@ def test_long_rows_full_rounds(m):
     ([16, 1, 0, 17, 33, 5, 32, 40], 2048, 2052, FP32),
     ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 1024, 2052, FP32),
     ([16, 1, 0, 17, 33, 5, 32, 40], 4096, 4112, BF16),
-    ([1, 0, 0, 0, 9], 8192, 8200, BF16),
+    ([1, 0, 0, 0, 9], 8192, 8200, BF16),                                                 # 4.5 of 5 experts counted
+    ([1, 0, 0, 1], 8192, 8200, BF16),                                                    # 1.75 of 4: below the line
     ([16, 1, 0, 17, 33, 5, 32, 40], 2048, 4104, FP32),
     ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 1024, 4104, FP32),
-], ids=["32x64-plain", "64x128", "last", "inplace", "fp32-plain", "fp32-64x64-plain", "32x64", "32x64-few", "fp32", "fp32-64x64"])
+], ids=["32x64-plain", "64x128", "last", "inplace", "fp32-plain", "fp32-64x64-plain", "32x64", "32x64-few", "32x64-two", "fp32", "fp32-64x64"])
 def test_streamed_weights(m, sizes, H, N, dtype):
     check_on_gpu(m, sizes, H, N, dtype)
 
@@ -191,3 +192,11 @@ def test_fp32_one_tile_per_expert(m, H):
 @pytest.mark.parametrize("H", [508, 516, 1100])
 def test_fp32_levels(m, H):
     check(m, [1, 16, 17, 33, 200], H, 132, FP32)
+
+
+# both sides of the longest row whose tiles fit the 31-bit offsets of the direct loads, 2^20 elements: the register-staged forms beyond
+@pytest.mark.parametrize("H,dtype", [(2 ** 20 - 8, BF16), (2 ** 20, BF16), (2 ** 20 + 8, BF16), (2 ** 20 - 4, FP32), (2 ** 20, FP32),
+                                     (2 ** 20 + 4, FP32)])
+@pytest.mark.parametrize("sizes", [[3, 1], [33, 0, 65]], ids=str)
+def test_longest_rows(m, sizes, H, dtype):
+    check_on_gpu(m, sizes, H, 72, dtype)

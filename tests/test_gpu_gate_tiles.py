@@ -81,3 +81,20 @@ def test_gate_bf16_further(T, H, E):
                                    (2017, 1124, 256), (31970, 900, 64)])
 def test_gate_fp32_tiles(T, H, E):
     check(T, H, E, FP32)
+
+
+# both sides of the longest row whose tiles fit the 31-bit offsets of the direct loads; made and multiplied for the reference on the GPU
+# (fp32 products and sums of these integers are exact in any order)
+@pytest.mark.parametrize("H,dtype", [(2 ** 20 - 8, BF16), (2 ** 20, BF16), (2 ** 20 + 8, BF16), (2 ** 20 - 4, FP32), (2 ** 20 + 4, FP32)])
+@pytest.mark.parametrize("T,E", [(5, 9), (272, 256)])
+def test_gate_longest_rows(T, E, H, dtype):
+    import paper_2411_00662_amd as m
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x, w = (torch.randint(-4, 5, (n, H), generator=g, device="cuda", dtype=torch.int8).to(torch.float32 if dtype == FP32 else torch.bfloat16)
+            for n in (T, E))
+    out = torch.full((T + 1, E), float("nan"), device="cuda")
+    m.monta_gate(m.make_cfg(T, H, dtype, E, 1, 1, 1, 1, 0.0), x, w, out[:T])
+    assert bool(torch.isnan(out[T]).all())
+    assert torch.equal(out[:T], x.float() @ w.float().t())

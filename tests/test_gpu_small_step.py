@@ -1,8 +1,8 @@
 """Small problems in one launch (every workgroup routes all tokens) against the same calls in several (which an explicit cache
 policy or plan mode asks for, and which are held against the oracle elsewhere): choices, gates, every plan table, STAGE, FINAL
 and the output, bit for bit.  The shapes sit on the edges: one token, a token more or less than a mask word, the most tokens,
-lanes per token from 1 to 8 and groups of 2, 4 and 8 experts, fewer lanes per row than choices, several rows per wave and several
-passes per row, units of one token, padding, drops, and sizes just outside."""
+lanes per token from 1 to 16 and up to 8 and up to 16 experts a lane, fewer lanes per row than choices, several rows per wave and
+several passes per row, units of one token, padding, drops, and sizes just outside."""
 import numpy as np
 import pytest
 
@@ -18,7 +18,7 @@ SHAPES = [
     Workload("units", 60, 264, BF16, 10, 3, 5, 12, 5, 0.7, zipf_s=0.8),                 # a unit is one token
     Workload("most", 512, 1024, BF16, 15, 4, 5, 4, 8, 0.5, zipf_s=1.0, renorm=0),
     Workload("most16", 512, 8192, BF16, 16, 2, 4, 1, 1, 0.9, zipf_s=0.5),               # two lanes a token
-    Workload("many", 100, 2048, BF16, 256, 32, 8, 1, 4, 0.6, zipf_s=0.6),               # eight lanes, four chunks of experts
+    Workload("many", 100, 2048, BF16, 256, 32, 8, 1, 4, 0.6, zipf_s=0.6),               # too many for one launch
     Workload("lds", 88, 64, FP32, 255, 8, 5, 4, 2, 0.0, renorm=0),
     Workload("four", 200, 136, BF16, 33, 6, 11, 2, 4, 1.25, zipf_s=1.2),                # four lanes a token
     Workload("eight", 128, 520, FP32, 64, 8, 8, 2, 2, 0.5, zipf_s=1.2),
@@ -29,6 +29,10 @@ SHAPES = [
     Workload("padded", 300, 264, BF16, 7, 3, 7, 5, 2, 0.5, zipf_s=0.8, padded=1),
     Workload("padded64", 64, 4096, BF16, 64, 1, 8, 1, 1, 2.0, padded=1),
     Workload("dropall", 256, 128, FP32, 2, 1, 2, 2, 2, 0.01, zipf_s=3.0),               # most tokens lose every choice
+    Workload("sixteen", 64, 1024, BF16, 128, 8, 8, 1, 1, 0.0),                          # sixteen lanes a token, four tokens a wave
+    Workload("sixteen-drops", 63, 520, FP32, 200, 6, 8, 3, 3, 0.6, zipf_s=1.2, renorm=0),   # 13 experts a lane, the last ones 12
+    Workload("sixteen-most", 64, 512, BF16, 256, 32, 8, 2, 2, 0.8, zipf_s=0.6, padded=1),
+    Workload("sixteen-few", 3, 264, BF16, 255, 7, 5, 1, 3, 0.8, zipf_s=1.0, renorm=0),
     Workload("outside", 513, 1024, BF16, 8, 2, 8, 1, 1, 0.0),
     Workload("logits", 65, 64, BF16, 126, 4, 6, 5, 1, 0.0),                             # 8190 logits; rows 32760 per choice
     Workload("outside-logits", 65, 64, BF16, 127, 4, 1, 5, 1, 0.9, zipf_s=0.5),         # routing in one launch no longer
