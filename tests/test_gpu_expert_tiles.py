@@ -175,12 +175,12 @@ def test_ragged_steps(m, sizes, N, H):
                                      ([57, 58, 57, 56] * 4, 7624), ([130, 1, 128, 129, 77, 255, 0, 31] * 3, 5128)],
                          ids=["16", "16-many", "17", "8", "9", "56", "57", "many"])
 def test_short_ragged_steps(m, sizes, N, H):
-    check(m, sizes, H, N, BF16)
+    check_on_gpu(m, sizes, H, N, BF16)
 
 
 @pytest.mark.parametrize("H,N", [(520, 248), (520, 256), (1096, 256), (520, 264), (1112, 256)])
 def test_ragged_steps_one_column_tile(m, H, N):
-    check(m, [130, 1, 128, 129, 577, 455, 0, 231] * 12, H, N, BF16)
+    check_on_gpu(m, [130, 1, 128, 129, 577, 455, 0, 231] * 12, H, N, BF16)
 
 
 # fp32 tiles of 64 x 64, and several levels of sums
