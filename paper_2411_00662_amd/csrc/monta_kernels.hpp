@@ -2749,10 +2749,11 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 
 // Few rows per expert (a decoding step): every weight is read once for a handful of rows, and the layer lasts as long as
 // the weights take to arrive from memory.  Two workgroups per CU, 128 KiB of loads in flight per CU.  Measured on MI355X,
-// register-staged 128 x 256 tiles before, now (floor: the weights at 6.4 TB/s): 8 experts of 4096 x 4096, 16 rows each 138 ->
-// 41 us (42); 64 of 7168 x 2048, 16 rows 314 -> 311 us (294); 64 of 2048 x 2048 133 -> 98 us (84); rows that are not whole steps:
-// 2 of 7464 x 1904, 16 rows 199 -> 33 us, 8 of 1032 x 4096, 16 rows 55 -> 15 us (11).  Streaming the weights straight into
-// registers in the MFMA's layout (16 rows x 64 bytes per load) was measured too: 61, 434 and 121 us.
+// register-staged 128 x 256 tiles before, now (floor: the weights at 6.4 TB/s): 8 experts of 4096 x 4096, 16 rows each, one set of
+// weights used again 138 -> 40 us, several in turn 48 (42); 64 of 7168 x 2048, 16 rows 314 -> 269 us (294; 311 before the streaming);
+// 64 of 2048 x 2048 133 -> 98 us (84); rows that are not whole steps: 2 of 7464 x 1904, 16 rows 199 -> 33 us, 8 of 1032 x 4096,
+// 16 rows 55 -> 15 us (11).  Streaming the weights straight into registers in the MFMA's layout (16 rows x 64 bytes per load) was
+// measured too: 61, 434 and 121 us.
 // fp32, any number of rows: the same tiles, where the barrier and the reads of a step cost less than its MFMAs (16 of 32 clocks
 // each for a wave of the 32 x 64 tile).  A 64 x 64 tile with one step in flight through registers before, now: 2 experts of 4096 x
 // 4096, 8 rows each 108 -> 49 us (21), 10 of 516 x 516, about 240 rows 30 -> 19 us, 8 of 1024 x 1024, 600 rows 113 -> 100 us
