@@ -2235,7 +2235,7 @@ struct ExpertArgs {
 // takes part and gets the same answer.  e == E: no such tile (a surplus workgroup).
 struct ExpertTileHit {
     int e, lo, hi, tiles;     // expert, its row range [lo, hi), its row tiles
-    int64_t L;                // tile number inside the expert
+    uint32_t L;               // tile number inside the expert: at most the number asked for, which is below 2^31, as grids are
 };
 
 // WHOLE: only the whole tiles of a segment count (its ragged last tile is numbered elsewhere); `all` returns the
@@ -2265,7 +2265,8 @@ __device__ __forceinline__ ExpertTileHit find_expert_tile(const ExpertArgs &a, i
             if (lane >= d) incl += o;
         }
         // 64 bits, and by a shuffle: from a lane read the compiler knows the tile's number for uniform and divides it in scalar code,
-        // four long chains of which cost every large tile's workgroup about 2 us (128 experts of 1024 x 480, 512 rows each 97 and 94)
+        // four long chains of which cost every large tile's workgroup about 2 us (128 experts of 1024 x 480, 512 rows each 97 and 94).
+        // The quotients themselves are of 32 bits: those of 64 cost short tiles up to 2 % (fp32, 8 of 512 x 2496, 105 rows 28.9 and 28.3)
         const int64_t total = __shfl(incl, kWave - 1, kWave);
         if (L < before + total) {
             // an expert without tiles repeats its predecessor's running total, so the first lane past L has tiles
@@ -2275,7 +2276,7 @@ __device__ __forceinline__ ExpertTileHit find_expert_tile(const ExpertArgs &a, i
             h.lo = __shfl(lo, src, kWave);
             h.hi = __shfl(hi, src, kWave);
             h.tiles = __shfl(tiles, src, kWave);
-            h.L = L - before - (__shfl(incl, src, kWave) - __shfl(cnt, src, kWave));
+            h.L = (uint32_t)(L - before - (__shfl(incl, src, kWave) - __shfl(cnt, src, kWave)));
             return h;
         }
         before += total;
@@ -2312,8 +2313,8 @@ __global__ __launch_bounds__(64 * WM * WN, (64 * WM * WN <= 256 ? 2 : 1)) void e
     const int e = hit.e;
     int row0 = 0, row_end = 0, ct = 0;
     if (e < a.E) {
-        ct = (int)(hit.L / hit.tiles);
-        row0 = hit.lo + (int)(hit.L % hit.tiles) * BM;
+        ct = (int)(hit.L / (uint32_t)hit.tiles);
+        row0 = hit.lo + (int)(hit.L % (uint32_t)hit.tiles) * BM;
         row_end = hit.hi < a.max_rows ? hit.hi : a.max_rows;
     }
     if (e == a.E || row0 < 0 || row0 >= row_end) return;          // surplus workgroup (uniform for the workgroup)
@@ -2772,8 +2773,8 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     const ExpertTileHit hit = find_expert_tile<XR>(a, nct, L, lane);
     const int e = __builtin_amdgcn_readfirstlane(hit.e);
     if (e >= a.E) return;                                          // surplus workgroup
-    const int ct = __builtin_amdgcn_readfirstlane((int)(hit.L / hit.tiles));
-    const int row0 = __builtin_amdgcn_readfirstlane(hit.lo + (int)(hit.L % hit.tiles) * XR);
+    const int ct = __builtin_amdgcn_readfirstlane((int)(hit.L / (uint32_t)hit.tiles));
+    const int row0 = __builtin_amdgcn_readfirstlane(hit.lo + (int)(hit.L % (uint32_t)hit.tiles) * XR);
     const int seg_end = __builtin_amdgcn_readfirstlane(hit.hi < a.max_rows ? hit.hi : a.max_rows);
     if (row0 < 0 || row0 >= seg_end) return;
     const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
@@ -2822,7 +2823,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         const int tiles = hit.tiles, full = tiles / P;             // whole panels
         int rt;
         if (hit.L < (int64_t)full * P * nct) {
-            const int p = (int)(hit.L / (P * nct)), rem = (int)(hit.L % (P * nct));
+            const int p = (int)(hit.L / (uint32_t)(P * nct)), rem = (int)(hit.L % (uint32_t)(P * nct));
             ct = rem / P;
             share = rem % P;
             rt = p * P + share;
@@ -3239,7 +3240,7 @@ __global__ __launch_bounds__(256) void expert_f32_kernel(const u32x4 *__restrict
     const int64_t L = (j / 32) * (32 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 32 + j % 32;
     const ExpertTileHit hit = find_expert_tile<kF32Tile>(a, nct, L, lane);
     if (hit.e >= a.E) return;                                      // surplus workgroup
-    const int row0 = hit.lo + (int)(hit.L % hit.tiles) * kF32Tile, col0 = (int)(hit.L / hit.tiles) * kF32Tile;
+    const int row0 = hit.lo + (int)(hit.L % (uint32_t)hit.tiles) * kF32Tile, col0 = (int)(hit.L / (uint32_t)hit.tiles) * kF32Tile;
     const int row_end = hit.hi < a.max_rows ? hit.hi : a.max_rows;
     if (row0 < 0 || row0 >= row_end) return;
 
