@@ -569,9 +569,14 @@ int launch_expert_big_t(const void *x_final, const void *w_exp, void *y, const E
                     : launch_expert_big_k<RAGGED_LAST, DEEP_W, false>(x_final, w_exp, y, a, grid, st);
 }
 
-int launch_expert_big(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound,
+int launch_expert_big(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound,
                       int64_t rows_per_expert, hipStream_t st)
 {
+    // Weights are streamed only on rows of more than 4096 elements.  Plain and streamed, three sets of weights in turn, us: 256
+    // experts of 512 x 7936, 74 rows 532 and 574, 128 of 2048 x 2048, 100 rows 271 and 282, 64 of 4096 x 2048, 150 rows 269 and 271,
+    // 4096 x 4096, 200 rows 546 and 545; but 5120 x 2560, 150 rows 382 and 380, 7168 x 2048, 120 rows 355 and 345, 32 of 8192 x 4096
+    // 449 and 434.
+    if (a.H <= 4096) a.stream_from = (int64_t)a.E * a.N;
     const int64_t row_tiles = (rows_bound + kBigBM - 1) / kBigBM + a.E;      // each expert may end in a ragged tile
     const int64_t nct = (a.N + kBigBN - 1) / kBigBN;
     // whole blocks of 256 workgroups: the kernel hands out tile numbers in such blocks, 32 per XCD
