@@ -599,9 +599,13 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, ExpertArg
 }
 
 template <int XR, int WR, int NST, bool F32 = false>
-int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, hipStream_t st)
+int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, hipStream_t st)
 {
     using G = ShortTile<XR, WR, NST>;
+    // No streamed weights in 64 x 128 tiles on rows below 1536 elements.  Plain and streamed, three sets of weights in turn, us: 256
+    // experts of 512 x 2048, 40 rows 124 and 126, 128 of 1024 x 2048 103 and 106, 128 of 1152 x 1536 88.5 and 91.0; but 128 of 1536 x
+    // 1024 80.0 and 79.5, 64 of 2048 x 2048, 48 rows 118 and 115, and in 32 x 64 tiles 128 of 1024 x 2048, 8 rows 90 and 82.
+    if (WR == 128 && a.H < 1536) a.stream_from = (int64_t)a.E * a.N;
     static LdsOptIn lds_opt_in;
     if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t row_tiles = rows_bound / XR + std::min<int64_t>(a.E, rows_bound);

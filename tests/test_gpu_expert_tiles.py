@@ -86,6 +86,8 @@ def test_long_rows_full_rounds(m):
 @pytest.mark.parametrize("sizes,H,N,dtype", [
     ([16, 1, 0, 17, 33, 5, 32, 40], 4096, 2056, BF16),                                   # 32 x 64
     ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 4096, 2056, BF16),                              # 64 x 128
+    ([40, 64, 65, 1, 0, 33, 48, 50] * 8, 1472, 2056, BF16),                              # plain on rows below 1536
+    ([40, 64, 65, 1, 0, 33, 48, 50] * 8, 1536, 2056, BF16),
     ([150, 256, 257, 65, 0, 64, 300, 255, 33] * 2, 4096, 2056, BF16),                    # 256 x 256: plain up to rows of 4096
     ([150, 256, 257, 65, 0, 64, 300, 255] * 4, 2048, 2056, BF16),
     ([150, 256, 257, 65, 0, 64, 300, 255, 33] * 2, 4160, 2056, BF16),                    # the ragged tiles last
@@ -97,7 +99,7 @@ def test_long_rows_full_rounds(m):
     ([1, 0, 0, 1], 8192, 8200, BF16),                                                    # 1.75 of 4: below the line
     ([16, 1, 0, 17, 33, 5, 32, 40], 2048, 4104, FP32),
     ([40, 64, 65, 1, 0, 33, 48, 50] * 2, 1024, 4104, FP32),
-], ids=["32x64-plain", "64x128", "last-plain", "inplace-plain", "last", "inplace", "fp32-plain", "fp32-64x64-plain", "32x64", "32x64-few", "32x64-two", "fp32", "fp32-64x64"])
+], ids=["32x64-plain", "64x128", "64x128-plain", "64x128-short", "last-plain", "inplace-plain", "last", "inplace", "fp32-plain", "fp32-64x64-plain", "32x64", "32x64-few", "32x64-two", "fp32", "fp32-64x64"])
 def test_streamed_weights(m, sizes, H, N, dtype):
     check_on_gpu(m, sizes, H, N, dtype)
 
