@@ -505,7 +505,13 @@ int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t grid = (T + XR - 1) / XR * ((E + WR - 1) / WR);
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E);
+    // Spread starts (walk_start) where the weights, which the tiles then read at different places, stay in every L2.  Three sets of
+    // activations in turn, in step and spread, us: 8192 x 4096, 64 experts 21.0 and 16.5; 16384 x 8192, 64 experts 71.3 and 61.5; 4096 x 8192,
+    // 128 experts 36.6 and 29.6; 16384 x 2048, 64 experts 15.4 and 14.0; but 1024 x 8192, 256 experts, 4 MiB of weights 31.9 and 33.0.
+    // In fp32 the matrix rate decides (16384 x 4096, 64 experts: 95.9 and 96.3).
+    const int64_t row = (int64_t)H * 2;
+    const int spread = !F32 && row % 4096 == 0 && E * row <= (2 << 20);
+    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E, spread);
     return MONTA_OK;
 }
 
@@ -599,13 +605,21 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, ExpertArg
 }
 
 template <int XR, int WR, int NST, bool F32 = false>
-int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, hipStream_t st)
+int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, int64_t rows_per_expert,
+                          hipStream_t st)
 {
     using G = ShortTile<XR, WR, NST>;
     // No streamed weights in 64 x 128 tiles on rows below 1536 elements.  Plain and streamed, three sets of weights in turn, us: 256
     // experts of 512 x 2048, 40 rows 124 and 126, 128 of 1024 x 2048 103 and 106, 128 of 1152 x 1536 88.5 and 91.0; but 128 of 1536 x
     // 1024 80.0 and 79.5, 64 of 2048 x 2048, 48 rows 118 and 115, and in 32 x 64 tiles 128 of 1024 x 2048, 8 rows 90 and 82.
     if (WR == 128 && a.H < 1536) a.stream_from = (int64_t)a.E * a.N;
+    // Spread starts (walk_start) where most experts fit one tile's rows; with more row tiles the rows, too, are read at many places at
+    // a time and leave the L2 (16 experts of 8192 x 1024, 37 rows in 32 x 64 tiles: in step 64, spread 76 us).  Three sets of weights in turn, in
+    // step and spread, us: 16 experts of 4096 x 2048, 8 rows 48.8 and 40.7; 6144 x 2048 68.9 and 60.7; 8192 x 1024 49.3 and 41.1; 32 of
+    // 2048 x 2048, 25 rows 56 and 43; 16 of 4096 x 2048, 37 rows in 64 x 128 tiles 58.5 and 43.4; fp32, 16 of 5120 x 1024, 8 rows 63.0
+    // and 53.0; 1024 x 2048 31.5 and 25.1.  With one set, part of it in the memory-side cache, 0.94 to 1.08 times as fast over these.  On rows
+    // of other lengths it loses: 7168 x 1024 41.2 and 43.6, 1024 x 4096 70 and 72.
+    a.spread = (int64_t)a.H * (F32 ? 4 : 2) % 4096 == 0 && rows_per_expert * 8 <= XR * 7;
     static LdsOptIn lds_opt_in;
     if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t row_tiles = rows_bound / XR + std::min<int64_t>(a.E, rows_bound);
@@ -671,15 +685,15 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
     const int64_t one_row = active * ((a.N + 255) / 256), rounds = (one_row + kRound - 1) / kRound;
     const bool full_rounds = one_row * 10 >= rounds * kRound * (r < 64 ? 9 : 7);
     if (a.H % 64 && a.H <= kOddShortRow) {
-        if (tiles(32, 64) <= (r <= 16 ? kFewTilesShortRows : kFewTiles)) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
+        if (tiles(32, 64) <= (r <= 16 ? kFewTilesShortRows : kFewTiles)) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
         if (r <= (a.H <= 64 ? 8 : 56) || tiles(64, 128) <= kFewTilesShortRows)
-            return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
+            return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, r, st);
         return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     }
-    if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, st);
+    if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
     if (a.H >= 4096 && a.E <= 64 && r <= 100 && full_rounds) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 56 || tiles(64, 128) <= (a.H <= 1024 ? kFewTilesShortRows : kFewTiles))
-        return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, st);
+        return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, r, st);
     if (a.H <= 512 && a.E <= 128 && r <= 384) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (a.H % 64 && a.H <= kOddNarrowRow && a.N <= kBigBN) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (a.H % 64 && r > kBigBM && r <= kBigBM * 3 / 2) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
@@ -704,9 +718,9 @@ int launch_expert_f32(const void *x_final, const void *w_exp, void *y, const Exp
         return MONTA_OK;
     }
     const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
-    if (r > 32 && r <= 64 && active * ((a.N + 63) / 64) >= 512) return launch_expert_short_t<64, 64, 3, true>(x_final, w_exp, y, a, rows_bound, st);
-    if (r <= 24) return launch_expert_short_t<32, 64, 4, true>(x_final, w_exp, y, a, rows_bound, st);
-    return launch_expert_short_t<32, 64, 3, true>(x_final, w_exp, y, a, rows_bound, st);
+    if (r > 32 && r <= 64 && active * ((a.N + 63) / 64) >= 512) return launch_expert_short_t<64, 64, 3, true>(x_final, w_exp, y, a, rows_bound, r, st);
+    if (r <= 24) return launch_expert_short_t<32, 64, 4, true>(x_final, w_exp, y, a, rows_bound, r, st);
+    return launch_expert_short_t<32, 64, 3, true>(x_final, w_exp, y, a, rows_bound, r, st);
 }
 
 int launch_route(const Geometry &g, const PlanPtrs &p, const float *logits, int32_t *topk_idx, float *gates,
@@ -865,7 +879,8 @@ int launch_expert_layer(const monta_cfg *cfg, const Geometry &g, const void *x_f
     int rc = MONTA_OK;
     PlanPtrs p = plan_ptrs(g, const_cast<void *>(ws));
     ExpertArgs a;
-    a.E = s.E;
+    a.spread = 0;
+    a.E = (int16_t)s.E;
     a.H = cfg->hidden;
     a.N = out_features;
     a.max_rows = s.max_rows;

@@ -2224,7 +2224,9 @@ struct ExpertArgs {
     const int32_t *lo;      // [E] first row of the expert's range
     const int32_t *hi_base; // [E] one past its last row is hi_base[e] + hi_len[e] ...
     const int32_t *hi_len;  // [E] ... or hi_base[e] alone if this is nullptr
-    int32_t E, H, N, max_rows;
+    int16_t E;              // one word for two fields: an argument of its own is one more trip to memory in a chain of them
+    int16_t spread;         // 1: the short tiles' walks along the hidden axis start at different steps (walk_start)
+    int32_t H, N, max_rows;
     int64_t stream_from;    // first row of all experts' weights (expert * N + column) that is requested as streaming (kStreamLoad)
                             // where one workgroup reads it
 };
@@ -2460,20 +2462,20 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kStreamLoad = 2;
 constexpr uint32_t kOutOfRange = 0x80000000u;                      // a lane offset past every descriptor: no access
 
-// Scalar offset of a step's 128 bytes in every row of a tile of `nsteps` steps.  The range check of a buffer load compares the
-// lane's offset with num_records - scalar offset in 32 bits, and the smallest descriptor is one row, whose last step may hold a
-// single piece of 16 bytes: the scalar offset must stay below that, or the difference wraps and every lane offset counts as in range.  Steps past the end,
-// whose lanes are out of range anyway, therefore take 0.
-__host__ __device__ constexpr uint32_t step_offset(int step, int nsteps) { return step < nsteps ? (uint32_t)step * 128u : 0u; }
-constexpr bool step_offsets_stay_inside(int nsteps, int past)
+// Scalar offset of the 128 bytes that follow those at `at` in every row of a tile of `turn` / 128 steps: from the last step round to the
+// first.  The range check of a buffer load compares the lane's offset with num_records - scalar offset in 32 bits, and the smallest
+// descriptor is one row, whose last step may hold a single piece of 16 bytes: the scalar offset must stay below that, or the difference
+// wraps and every lane offset counts as in range.  Steps past the end, whose lanes are out of range anyway, therefore go round, too.
+__host__ __device__ constexpr uint32_t next_step(uint32_t at, uint32_t turn) { return at + 128u == turn ? 0u : at + 128u; }
+constexpr bool step_offsets_stay_inside(int nsteps, int start, int past)
 {
-    for (int step = 0; step < nsteps + past; ++step) {
-        const uint32_t records = (uint32_t)(nsteps - 1) * 128u + 16u, so = step_offset(step, nsteps);
-        if (so >= records || kOutOfRange < records - so) return false;
-    }
+    const uint32_t turn = (uint32_t)nsteps * 128u, records = turn - 112u;
+    uint32_t at = (uint32_t)start * 128u;
+    for (int step = 0; step < nsteps + past; ++step, at = next_step(at, turn))
+        if (at >= records || kOutOfRange < records - at) return false;
     return true;
 }
-static_assert(step_offsets_stay_inside(1, 8) && step_offsets_stay_inside(2, 8) && step_offsets_stay_inside(7, 8),
+static_assert(step_offsets_stay_inside(1, 0, 8) && step_offsets_stay_inside(2, 1, 8) && step_offsets_stay_inside(7, 5, 8),
               "a one-row tile must refuse the loads of the steps past its end");
 constexpr int kBigMaxHidden = 1 << 20;                             // a tile's 256 rows end far below it
 
@@ -2486,13 +2488,22 @@ __device__ __forceinline__ uint2 pack_bf16x4(f32x4 v)
     return o;
 }
 
+// Where tile number `tile` starts its walk along the hidden axis.  Rows that are a multiple of 4096 bytes apart begin on the same memory
+// channels, so that workgroups which walk in step all wait for a few of them: 256 MiB of weights in rows of 8192 bytes, 64 rows a workgroup,
+// read and nothing else, arrive in 52 us, at 14336 bytes a row in 39 (6.9 TB/s); with the starts spread over the row in 39 and 39.  The
+// multiplier spreads consecutive tiles evenly over any number of steps.  Rows have to be whole steps.
+__device__ __forceinline__ int walk_start(int tile, int nsteps)
+{
+    return (int)(((uint32_t)tile * 40503u & 0xffffu) * (uint32_t)nsteps >> 16);
+}
+
 // A tile of at most XR rows x WR output features: so little arithmetic per step that the step is as long as its loads take
 // to arrive, so what counts is how many bytes are on their way.  Compact stages of XR + WR rows, NST of them, the loads of
 // NST - 1 steps in flight.  Four waves, each all rows x WR / 4 columns.  Every wave issues the same number of loads per step,
 // also past the end (out of range: no traffic), because the wait for a stage counts the younger loads.  The barrier is the
 // bare instruction behind a wait for the LDS reads: the compiler's own barrier would wait for every outstanding load, the
 // next stages' included.  A row is `cpr` pieces of 16 bytes, a step 8 of them; the pieces of the last step that lie past the end
-// of the row are out of range, too, and multiply as zeros.
+// of the row are out of range, too, and multiply as zeros.  The walk begins at step `start` (0 unless rows are whole steps) and goes round.
 template <int XR, int WR, int NST>
 struct ShortTile {
     static constexpr int kStageBytes = (XR + WR) * 128, kLdsBytes = NST * kStageBytes;
@@ -2513,7 +2524,7 @@ struct ShortTile {
 // AUX_W: cache bits of the weights' loads.
 template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, typename T>
 __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
-                                                  int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds)
+                                                  int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds, int start)
 {
     using G = ShortTile<XR, WR, NST>;
     constexpr int RB = XR / 16, CB = WR / 64;                      // 16-row blocks, 16-column blocks of a wave
@@ -2541,13 +2552,15 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + (wave * G::kCX + q) * 1024), 16,
                                                      lane_offset(wave * G::kCX + q, ox[q]), so, 0, 0);
     };
-    auto issue_whole = [&](int step, int slot) {                   // the row holds all 8 pieces of the step
-        load(lds + slot * G::kStageBytes, step_offset(step, nsteps), [&](int, uint32_t o) { return o; });
+    uint32_t so = (uint32_t)start * 128u;                          // of the step that is requested next
+    auto issue_whole = [&](int, int slot) {                        // the row holds all 8 pieces of the step
+        load(lds + slot * G::kStageBytes, so, [&](int, uint32_t o) { return o; });
+        so = next_step(so, (uint32_t)nsteps * 128u);
     };
     auto issue_any = [&](int step, int slot) {
         const int left = cpr - step * 8;                           // pieces of the row in this step; none past the end
-        load(lds + slot * G::kStageBytes, step_offset(step, nsteps),
-             [&](int c, uint32_t o) { return piece(c) < left ? o : kOutOfRange; });
+        load(lds + slot * G::kStageBytes, so, [&](int c, uint32_t o) { return piece(c) < left ? o : kOutOfRange; });
+        so = next_step(so, (uint32_t)nsteps * 128u);
     };
     constexpr bool kLevels = std::is_same<T, float>::value;
     constexpr bool kLogits = kLevels && !VEC;
@@ -2781,10 +2794,12 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     const uint32_t rowb = (uint32_t)cpr * 16;
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb);
+    // by the column tile, whichever the rows: a row's result does not depend on the launch that computes it
+    const int start = a.spread ? walk_start(e * nct + ct, cpr / 8) : 0;
     if ((int64_t)e * a.N + col0 >= a.stream_from && __builtin_amdgcn_readfirstlane(hit.tiles) == 1)
-        expert_short_tile<XR, WR, NST, F32, F32, kStreamLoad>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
+        expert_short_tile<XR, WR, NST, F32, F32, kStreamLoad>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
     else
-        expert_short_tile<XR, WR, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds);
+        expert_short_tile<XR, WR, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
 }
 
 // TAIL: rows are not whole steps; the last step's pieces past the end of a row are out of range.
@@ -2895,9 +2910,9 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= kShortRows) {                                        // tiles with little arithmetic
         if (kMayStream && stream)
-            expert_short_tile<64, kShortCols, kStages, false, false, kMayStream ? kStreamLoad : 0>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds);
+            expert_short_tile<64, kShortCols, kStages, false, false, kMayStream ? kStreamLoad : 0>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds, 0);
         else
-            expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds);
+            expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds, 0);
         return;
     }
 
@@ -3102,7 +3117,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
 // 16 tokens x 64 experts with a split hidden axis: 8192 x 4096, 128 experts 171 -> 99, 32000 x 8192, 64 experts 694 -> 333.
 template <int XR, int WR, int NST, bool F32>
 __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
-                                                            float *__restrict__ logits, int64_t T, int H, int E)
+                                                            float *__restrict__ logits, int64_t T, int H, int E, int spread)
 {
     extern __shared__ __align__(16) unsigned char gshort_lds[];
     const int nct = (E + WR - 1) / WR, cpr = F32 ? H / 4 : H / 8;
@@ -3112,7 +3127,7 @@ __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restr
     const uint32_t rowb = (uint32_t)cpr * 16;
     expert_short_tile<XR, WR, NST, F32, false>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
                                                make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, cpr, E, t0,
-                                               t1, e0, gshort_lds);
+                                               t1, e0, gshort_lds, spread ? walk_start((int)(blockIdx.x / nct), cpr / 8) : 0);
 }
 
 // Gate projection with the hidden axis split over the 8 waves of a workgroup: 16 tokens x 16 NB experts each.  For fp32

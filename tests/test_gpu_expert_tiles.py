@@ -204,3 +204,17 @@ def test_fp32_levels(m, H):
 @pytest.mark.parametrize("sizes", [[3, 1], [33, 0, 65]], ids=str)
 def test_longest_rows(m, sizes, H, dtype):
     check_on_gpu(m, sizes, H, 72, dtype)
+
+
+# rows a multiple of 4096 bytes apart, whose tiles start their walk at different steps: fewer steps than stages hold and more, a start in
+# every step, an expert without rows, experts of one tile and of two; the line at seven eighths of a tile's rows on average
+@pytest.mark.parametrize("sizes,H,N,dtype", [
+    ([28, 1, 0, 33, 16, 40, 27, 32] * 3, 2048, 2056, BF16),
+    ([28, 1, 0, 33, 16, 40, 27, 32] * 3, 6144, 2056, BF16),
+    ([56, 1, 0, 65, 48, 64, 33, 40] * 4, 2048, 2056, BF16),
+    ([28, 29, 28, 28] * 6, 2048, 2056, BF16),
+    ([29, 30, 28, 29] * 6, 2048, 2056, BF16),
+    ([28, 1, 0, 33, 16, 40, 27, 32] * 3, 1024, 2052, FP32),
+], ids=["32x64", "32x64-long", "64x128", "28", "29", "fp32"])
+def test_spread_starts(m, sizes, H, N, dtype):
+    check_on_gpu(m, sizes, H, N, dtype)
