@@ -631,6 +631,45 @@ int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, Exper
     return MONTA_OK;
 }
 
+template <int XB, int CB, int W, int NST, bool F32>
+int launch_expert_split(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, hipStream_t st)
+{
+    using G = SplitTile<XB, CB, W, NST>;
+    static LdsOptIn lds_opt_in;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_split_kernel<XB, CB, W, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
+    const int64_t row_tiles = rows_bound / (16 * XB) + std::min<int64_t>(a.E, rows_bound), nct = (a.N + 16 * CB - 1) / (16 * CB);
+    const int64_t grid = (row_tiles * nct + 8 * kXcds - 1) / (8 * kXcds) * (8 * kXcds);
+    if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((expert_split_kernel<XB, CB, W, NST, F32>), dim3((unsigned)grid), dim3(G::kThreads), G::kLdsBytes, st,
+                       static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp), y, a);
+    return MONTA_OK;
+}
+
+// Few tiles: with the hidden axis split, 1 if they are not few.  The tiles counted as in launch_expert_tiled.  Measured on MI355X over
+// 64 shapes (2 to 64 experts, 1 to 616 rows per expert, 88 to 8192 elements, 64 to 5600 features, a third of them fp32; three sets of weights in
+// turn), these lines and the 32 x 64 tiles beyond take 1.03 of the best of fourteen forms' time and 0.68 of those tiles' alone.
+//  - 16 x 16 where experts have up to 32 rows, about one and a half tiles per CU (us in 32 x 64, 16 x 16, 16 x 32, 32 x 32: 4 experts of 4096 x
+//    1024, 4 rows 15.7, 8.0, 8.1, 8.6; 16 of 2048 x 120, 14 rows 9.8, 4.6, 5.3, 6.0; 8 of 2048 x 704, 19 rows, 594 tiles 10.0, 8.8,
+//    8.9, 7.4; 2 of 4096 x 4504, 20 rows, 987 tiles 15.8 in blocks of 8, 17.2, 17.9, 19.4); eight waves for long rows and half a tile
+//    per CU (fp32, 8 of 8192 x 136: four waves 18.7, eight 14.1);
+//  - 16 x 32, then 32 x 32, up to one tile per CU, where rows are more: 3 of 6176 x 336, 83 rows 21.9, 14.6, 12.5, 15.2; 4 of 8192 x 688,
+//    47 rows 28.5, 19.7, 19.7, 14.5; but 2 of 5120 x 1984, 130 rows, 564 tiles of 32 x 32 25.1, 35.6, 31.5, 29.9;
+//  - not on short walks (4 of 208 x 232, 467 rows 4.2, 9.0, 6.9, 6.7), up to 23 steps only where the tiles are fewest (32 of 1024 x 112,
+//    4 rows, 168 tiles 5.9, 3.9; 2 of 512 x 4752, 3 rows, 408 tiles 5.2, 5.0, 4.8, 6.9, in blocks of 8 4.5).
+template <bool F32>
+int launch_expert_few(const void *x_final, const void *w_exp, void *y, const ExpertArgs &a, int64_t rows_bound, int64_t active, int64_t r,
+                      hipStream_t st)
+{
+    auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
+    const int64_t steps = ((int64_t)a.H * (F32 ? 4 : 2) + 127) / 128, small = tiles(16, 16);
+    if (steps < 8 || (steps < 24 && small > 256)) return 1;
+    if (steps >= 128 && small <= 128) return launch_expert_split<1, 1, 8, 4, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if (r <= 32 && small <= 400) return launch_expert_split<1, 1, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if (tiles(16, 32) <= 256) return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if (tiles(32, 32) <= 256) return launch_expert_split<2, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    return 1;
+}
+
 template <int BM, int BN, int WM, int WN>
 int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, hipStream_t st)
 {
@@ -684,6 +723,7 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
     constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kRound = 512, kOddShortRow = 448, kOddNarrowRow = 1104;
     const int64_t one_row = active * ((a.N + 255) / 256), rounds = (one_row + kRound - 1) / kRound;
     const bool full_rounds = one_row * 10 >= rounds * kRound * (r < 64 ? 9 : 7);
+    if (const int rc = launch_expert_few<false>(x_final, w_exp, y, a, rows_bound, active, r, st); rc <= 0) return rc;
     if (a.H % 64 && a.H <= kOddShortRow) {
         if (tiles(32, 64) <= (r <= 16 ? kFewTilesShortRows : kFewTiles)) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
         if (r <= (a.H <= 64 ? 8 : 56) || tiles(64, 128) <= kFewTilesShortRows)
@@ -718,6 +758,7 @@ int launch_expert_f32(const void *x_final, const void *w_exp, void *y, const Exp
         return MONTA_OK;
     }
     const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
+    if (const int rc = launch_expert_few<true>(x_final, w_exp, y, a, rows_bound, active, r, st); rc <= 0) return rc;
     if (r > 32 && r <= 64 && active * ((a.N + 63) / 64) >= 512) return launch_expert_short_t<64, 64, 3, true>(x_final, w_exp, y, a, rows_bound, r, st);
     if (r <= 24) return launch_expert_short_t<32, 64, 4, true>(x_final, w_exp, y, a, rows_bound, r, st);
     return launch_expert_short_t<32, 64, 3, true>(x_final, w_exp, y, a, rows_bound, r, st);

@@ -2802,6 +2802,143 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
         expert_short_tile<XR, WR, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
 }
 
+// Layers of so few tiles that one tile's walk along the hidden axis is what takes the time, not the bytes: a tile of 16 XB rows x 16 CB
+// features whose steps are dealt to the W waves of its workgroup.  Each wave has a ring of NST stages of its own and waits for nobody: no
+// barrier until the waves' sums are added, through LDS and in a fixed order.  16 x 16 tiles, four waves: 48 KiB, three workgroups per CU.
+// A walk of the 32 x 64 tiles takes 0.23 us a step with the loads of three steps in flight.  Measured on MI355X, those tiles and these, three
+// sets of weights in turn, us: 2 experts of 4096 x 512, 8 rows 12.7 and 5.2; 2 of 8192 x 488, 23 rows 28.0 and 9.5; 8 of 2048 x
+// 704, 19 rows 10.0 and 7.4; fp32, 8 of 8192 x 136, 2 rows 72 and 14, 4 of 4096 x 68, 258 rows 54 and 15.  Where the lines lie stands at
+// launch_expert_few.  fp32 error against 64 bits at 1024 elements 2.9e-7, now 1.6e-7: shorter chains.
+template <int XB, int CB, int W, int NST>
+struct SplitTile {
+    static constexpr int kStageBytes = (XB + CB) * 2048, kRingBytes = NST * kStageBytes, kLdsBytes = W * kRingBytes, kThreads = 64 * W;
+    static constexpr int kLoads = 2 * (XB + CB), kYounger = (NST - 2) * kLoads;        // of one step; issued after those of the stage waited for
+    static constexpr int kWait = 0x0f70 | (kYounger & 15) | ((kYounger >> 4) << 14);   // s_waitcnt vmcnt(kYounger)
+    static_assert(NST >= 3 && kYounger < 64 && kLdsBytes <= 160 * 1024, "split tile: shape");
+    static_assert(XB * CB * 1024 <= kRingBytes, "split tile: the waves' sums lie in the rings");
+};
+
+template <int XB, int CB, int W, int NST, bool F32>
+__global__ __launch_bounds__(64 * W) void expert_split_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w, void *__restrict__ y,
+                                                              ExpertArgs a)
+{
+    using G = SplitTile<XB, CB, W, NST>;
+    using T = std::conditional_t<F32, float, unsigned short>;
+    constexpr int XR = 16 * XB, WR = 16 * CB;
+    extern __shared__ __align__(16) unsigned char split_lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, g = lane >> 4, lr = lane >> 3;
+    const int cpr = F32 ? a.H / 4 : a.H / 8, nct = (a.N + WR - 1) / WR;
+    // tile numbers in blocks of 8 per XCD: so few of them, in blocks of 32, would leave XCDs without any
+    const int64_t j = blockIdx.x / kXcds;
+    const int64_t L = (j / 8) * (8 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 8 + j % 8;
+    const ExpertTileHit hit = find_expert_tile<XR>(a, nct, L, lane);
+    const int e = __builtin_amdgcn_readfirstlane(hit.e);
+    if (e >= a.E) return;                                          // surplus workgroup
+    const int ct = __builtin_amdgcn_readfirstlane((int)(hit.L / (uint32_t)hit.tiles));
+    const int row0 = __builtin_amdgcn_readfirstlane(hit.lo + (int)(hit.L % (uint32_t)hit.tiles) * XR);
+    const int seg_end = __builtin_amdgcn_readfirstlane(hit.hi < a.max_rows ? hit.hi : a.max_rows);
+    if (row0 < 0 || row0 >= seg_end) return;
+    const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
+    const uint32_t rowb = (uint32_t)cpr * 16;
+    const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb);
+    const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb);
+
+    // Rows in LDS and their swizzle as in the short tiles.  Every wave issues the same loads per step, also past the end of its share
+    // (out of range, at scalar offset 0: no traffic), because the wait for a stage counts the younger ones.
+    const int nsteps = (cpr + 7) / 8, first = nsteps * wave / W, last = nsteps * (wave + 1) / W;
+    unsigned char *const ring = split_lds + wave * G::kRingBytes;
+    auto piece = [&](int q) { return (lane & 7) ^ ((4 * q + (lr >> 1)) & 7); };
+    uint32_t off[2];                                               // chunks 16 rows apart have the same swizzle
+#pragma unroll
+    for (int q = 0; q < 2; ++q) off[q] = (uint32_t)(q * 8 + lr) * rowb + piece(q) * 16;
+    auto issue = [&](int step, int slot) {
+        const int left = step < last ? cpr - step * 8 : 0;         // pieces of the row in this step
+        const uint32_t so = step < last ? (uint32_t)step * 128u : 0u;
+        unsigned char *const base = ring + slot * G::kStageBytes;
+        uint32_t o[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) o[q] = piece(q) < left ? off[q] : kOutOfRange;
+#pragma unroll
+        for (int q = 0; q < 2 * CB; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(base + (2 * XB + q) * 1024), 16, o[q & 1] + (uint32_t)(q >> 1) * 16 * rowb, so, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 2 * XB; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + q * 1024), 16, o[q & 1] + (uint32_t)(q >> 1) * 16 * rowb, so, 0, 0);
+    };
+    // two chains per result, by half of the step, and two levels, 8 steps at a time
+    f32x4 acc[2][XB][CB], total[XB][CB];
+#pragma unroll
+    for (int i = 0; i < XB; ++i)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) acc[0][i][c] = acc[1][i][c] = total[i][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < NST - 1; ++q) issue(first + q, q);
+    int slot = 0;
+    for (int from = first; from < last; from += 8) {
+        const int to = min(from + 8, last);
+        for (int step = from; step < to; ++step) {
+            __builtin_amdgcn_s_waitcnt(G::kWait);                  // stage `step` has landed (loads finish in order)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xc07f);                    // lgkmcnt(0): the reads of the slot that is filled next
+            asm volatile("" ::: "memory");
+            issue(step + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+            f32x4 fw[2][CB], fx[2][XB];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const unsigned char *at = ring + slot * G::kStageBytes + m * 128 + ((4 * ks + g) ^ ((m >> 1) & 7)) * 16;
+#pragma unroll
+                for (int i = 0; i < XB; ++i) fx[ks][i] = *reinterpret_cast<const f32x4 *>(at + i * 2048);
+#pragma unroll
+                for (int c = 0; c < CB; ++c) fw[ks][c] = *reinterpret_cast<const f32x4 *>(at + (XB + c) * 2048);
+            }
+#pragma unroll
+            for (int v = 0; v < (F32 ? 4 : 1); ++v)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int i = 0; i < XB; ++i)
+#pragma unroll
+                        for (int c = 0; c < CB; ++c) {
+                            if constexpr (F32) acc[ks][i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[ks][c][v], fx[ks][i][v], acc[ks][i][c], 0, 0, 0);
+                            else acc[ks][i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[ks][c]),
+                                                                                         __builtin_bit_cast(bf16x8, fx[ks][i]), acc[ks][i][c], 0, 0, 0);
+                        }
+            slot = slot == NST - 1 ? 0 : slot + 1;
+        }
+#pragma unroll
+        for (int i = 0; i < XB; ++i)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                total[i][c] += acc[0][i][c] + acc[1][i][c];
+                acc[0][i][c] = acc[1][i][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);                            // what is still on its way would overwrite the sums
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    f32x4 *red = reinterpret_cast<f32x4 *>(split_lds);             // [wave][row block][column block][lane]
+#pragma unroll
+    for (int i = 0; i < XB; ++i)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) red[((wave * XB + i) * CB + c) * kWave + lane] = total[i][c];
+    __syncthreads();
+    for (int b = wave; b < XB * CB; b += W) {
+        f32x4 sum[W];
+#pragma unroll
+        for (int v = 0; v < W; ++v) sum[v] = red[(v * XB * CB + b) * kWave + lane];
+#pragma unroll
+        for (int d = W / 2; d >= 1; d /= 2)
+#pragma unroll
+            for (int v = 0; v < d; ++v) sum[v] += sum[v + d];
+        const int64_t r = row0 + (b / CB) * 16 + m;
+        const int n = col0 + (b % CB) * 16 + 4 * g;
+        if (r < row_end && n < a.N) {
+            if constexpr (F32) *reinterpret_cast<f32x4 *>(static_cast<T *>(y) + r * a.N + n) = sum[0];
+            else *reinterpret_cast<uint2 *>(static_cast<T *>(y) + r * a.N + n) = pack_bf16x4(sum[0]);
+        }
+    }
+}
+
 // TAIL: rows are not whole steps; the last step's pieces past the end of a row are out of range.
 template <bool RAGGED_LAST, bool DEEP_W, bool TAIL>
 __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,

@@ -218,3 +218,20 @@ def test_longest_rows(m, sizes, H, dtype):
 ], ids=["32x64", "32x64-long", "64x128", "28", "29", "fp32"])
 def test_spread_starts(m, sizes, H, N, dtype):
     check_on_gpu(m, sizes, H, N, dtype)
+
+
+# few tiles, their steps dealt to four or eight waves: rows around the 16-row blocks, one row, none; 8 steps, whole and not, two a wave; 23 and
+# 24, and shares of unequal length and of several levels of sums; columns of one lane group, of a block and more.  [40, 100, ...] take
+# 16 x 32 tiles and, with more columns, 32 x 32
+@pytest.mark.parametrize("H", [456, 512, 1024, 1472, 1480, 2568, 8192, 8200])
+@pytest.mark.parametrize("sizes,N", [([1], 8), ([16, 1, 7, 0, 17], 40), ([33, 31, 15, 32], 264), ([40, 100, 65, 0, 33], 136), ([40, 100, 65, 0, 33], 392)],
+                         ids=["one", "few", "32", "16x32", "32x32"])
+def test_split_tiles(m, sizes, N, H):
+    check_on_gpu(m, sizes, H, N, BF16)
+
+
+@pytest.mark.parametrize("H", [252, 256, 516, 740, 1284, 4096, 4100])
+@pytest.mark.parametrize("sizes,N", [([1], 4), ([16, 1, 7, 0, 17], 20), ([33, 31, 15, 32], 264), ([40, 100, 65, 0, 33], 132), ([40, 100, 65, 0, 33], 392)],
+                         ids=["one", "few", "32", "16x32", "32x32"])
+def test_split_tiles_fp32(m, sizes, N, H):
+    check_on_gpu(m, sizes, H, N, FP32)
