@@ -620,6 +620,12 @@ int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, Exper
     // and 53.0; 1024 x 2048 31.5 and 25.1.  With one set, part of it in the memory-side cache, 0.94 to 1.08 times as fast over these.  On rows
     // of other lengths it loses: 7168 x 1024 41.2 and 43.6, 1024 x 4096 70 and 72.
     a.spread = (int64_t)a.H * (F32 ? 4 : 2) % 4096 == 0 && rows_per_expert * 8 <= XR * 7;
+    // Tile numbers go to the XCDs in blocks of 32, so that an XCD's tiles share rows and weights.  Up to two tiles per CU of one row tile per
+    // expert in blocks of 8: an XCD reads about 1 TB/s, and half a block of 256 is four of them (one set of weights and three in turn, us: 8
+    // experts of 4096 x 2560, 4 rows 33.0, 38.8, in eights 26.4, 34.4; 4 of 7168 x 3072, 32 rows 42.3, 55.7 and 37.1, 55.4; 2 of 4096 x
+    // 4504, 20 rows 20.4 and 14.8; 32 of 1064 x 1616, one row 9.4, 10.8 and 10.0, 10.4; but 512 tiles, 8 of 4096 x 4096, 16 rows 40.0, 41.5 and, in fours, 41.8, 43.8; and with several row
+    // tiles, 4 of 4096 x 2048, 100 rows, 20.0 and 20.7, one by one 38).
+    a.deal = rows_per_expert <= XR && std::min<int64_t>(a.E, rows_bound) * ((a.N + WR - 1) / WR) < 512 ? 3 : 5;
     static LdsOptIn lds_opt_in;
     if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t row_tiles = rows_bound / XR + std::min<int64_t>(a.E, rows_bound);

@@ -2224,8 +2224,9 @@ struct ExpertArgs {
     const int32_t *lo;      // [E] first row of the expert's range
     const int32_t *hi_base; // [E] one past its last row is hi_base[e] + hi_len[e] ...
     const int32_t *hi_len;  // [E] ... or hi_base[e] alone if this is nullptr
-    int16_t E;              // one word for two fields: an argument of its own is one more trip to memory in a chain of them
-    int16_t spread;         // 1: the short tiles' walks along the hidden axis start at different steps (walk_start)
+    int16_t E;              // one word for three fields: an argument of its own is one more trip to memory in a chain of them
+    int8_t spread;          // 1: the short tiles' walks along the hidden axis start at different steps (walk_start)
+    int8_t deal;            // the short tiles' numbers go to the XCDs in blocks of 1 << deal
     int32_t H, N, max_rows;
     int64_t stream_from;    // first row of all experts' weights (expert * N + column) that is requested as streaming (kStreamLoad)
                             // where one workgroup reads it
@@ -2780,9 +2781,9 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     extern __shared__ __align__(16) unsigned char short_lds[];
     const int lane = threadIdx.x & 63;
     const int cpr = F32 ? a.H / 4 : a.H / 8, nct = (a.N + WR - 1) / WR;
-    // numbers are dealt to the XCDs in blocks of 32, row tiles fastest: row tiles of one weight tile meet in one L2
+    // numbers are dealt to the XCDs in blocks, row tiles fastest: row tiles of one weight tile meet in one L2
     const int64_t j = blockIdx.x / kXcds;
-    const int64_t L = (j / 32) * (32 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 32 + j % 32;
+    const int64_t L = ((((j >> a.deal) * kXcds) + (int64_t)(blockIdx.x % kXcds)) << a.deal) + (j & ((1 << a.deal) - 1));
     const ExpertTileHit hit = find_expert_tile<XR>(a, nct, L, lane);
     const int e = __builtin_amdgcn_readfirstlane(hit.e);
     if (e >= a.E) return;                                          // surplus workgroup
