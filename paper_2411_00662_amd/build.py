@@ -18,6 +18,9 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # keep the compiler from forming packed fp32 instructions out of scalar float code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first arguments of a kernel come in registers instead of by a load at its start, which takes 0.25 us (MI355X: a kernel of
+    # one load and one store 2.68 -> 2.44 us; 64 tokens, 8 experts, whole step 8.21 -> 7.98, gate of 600 x 1024 4.03 -> 3.76)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wextra",
 ]
 
