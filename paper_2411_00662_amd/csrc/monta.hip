@@ -53,7 +53,8 @@ int pow2ceil(int v)
     return p;
 }
 
-constexpr size_t kRouteLdsBudget = 120 * 1024;
+constexpr size_t kRouteTileBudget = 120 * 1024;     // route_tile_bytes
+constexpr size_t kRouteLdsBudget = 120 * 1024;      // dynamic LDS of the kernels that route
 constexpr int64_t kFewRouteBlocks = 128;
 // Routing and plan with 8192 counters: 73 us if every workgroup reduces them and only 32 workgroups run it (2048 tokens, 256
 // experts), 35 if a kernel scans them; with 256 workgroups 35 and 37.  At 2048 counters the launch costs more than it saves.
@@ -86,12 +87,14 @@ int route_lanes_per_token(int TB, int E)
     return rl;
 }
 
-size_t route_lds_bytes(int TB, int E, int k)
+// What decides how many tokens a route workgroup takes, and with it the layout of the workspace: about the bytes of its logits, its bit
+// masks, and three words per choice.
+size_t route_tile_bytes(int TB, int E, int k)
 {
-    const int NW = TB > kWave ? TB / kWave : 1;
-    const int stride = route_row_stride(E, route_lanes_per_token(TB, E));
-    size_t b = ((size_t)TB * stride * 4 + (size_t)TB * k * 4 + 7) & ~(size_t)7;    // logits tile, selections
-    return b + (size_t)E * NW * 8 + (size_t)TB * k * 8 + (size_t)TB * 8;            // bit masks, weights, denominators
+    const int NW = TB > kWave ? TB / kWave : 1, L = route_lanes_per_token(TB, E);
+    const int stride = L * (((E + L - 1) / L) | 1);
+    size_t b = ((size_t)TB * stride * 4 + (size_t)TB * k * 4 + 7) & ~(size_t)7;
+    return b + (size_t)E * NW * 8 + (size_t)TB * k * 8 + (size_t)TB * 8;
 }
 
 int validate(const monta_cfg *c, Geometry *g)
@@ -136,8 +139,8 @@ int validate(const monta_cfg *c, Geometry *g)
     // route workgroup: as many tokens as fit the LDS budget (gfx950 gives a workgroup up to 160 KiB),
     // at most 256, no more than a unit needs
     int TB = 256;
-    while (TB > 32 && (route_lds_bytes(TB, s.E, s.k) > kRouteLdsBudget || TB / 2 >= s.Tu)) TB >>= 1;
-    if (route_lds_bytes(TB, s.E, s.k) > kRouteLdsBudget) return MONTA_ERR_UNSUPPORTED;
+    while (TB > 32 && (route_tile_bytes(TB, s.E, s.k) > kRouteTileBudget || TB / 2 >= s.Tu)) TB >>= 1;
+    if (route_tile_bytes(TB, s.E, s.k) > kRouteTileBudget) return MONTA_ERR_UNSUPPORTED;
     // ... and no more than leaves every second CU a workgroup (down to one wave of tokens): 8192 tokens, 64 experts, top-8:
     // 28.5 us for routing and plan in workgroups of 256 tokens, 24.2 in 64; 16384 tokens, 32 experts: 19.1 and 18.2
     auto blocks = [&](int tb) { return (int64_t)((s.Tu + tb - 1) / tb) * U; };
@@ -151,7 +154,7 @@ int validate(const monta_cfg *c, Geometry *g)
     // the per-workgroup rebuild of the scans reads num_blocks*E counters in every workgroup; a larger table is scanned by a
     // kernel of its own
     s.fast_plan = (g->modes.plan != 0 && nb * s.E <= kRebuildMax) ? 1 : 0;
-    g->route_lds = route_lds_bytes(TB, s.E, s.k);
+    g->route_lds = (size_t)route_lds(TB, s.E, s.k).bytes;
     const int rl = route_lanes_per_token(TB, s.E);
     s.rl = rl;
     g->route_threads = TB * rl < kWave ? kWave : TB * rl;
@@ -829,7 +832,7 @@ int small_lanes(const Geometry &g, bool rows)
     int L = 1;
     while (L < 16 && s.E / (2 * L) >= 8 && s.T * 2 * L <= 1024) L *= 2;
     const int per_lane = (s.E + L - 1) / L;
-    if (s.T * L > 1024 || per_lane > 16 || small_lds(s.T, s.E, s.k, s.U, L).bytes > (int)kRouteLdsBudget) return 0;
+    if (s.T * L > 1024 || per_lane > 16 || small_lds(s.T, s.E, s.k, s.U).bytes > (int)kRouteLdsBudget) return 0;
     return L;
 }
 
@@ -841,7 +844,7 @@ int launch_small(const Geometry &g, const PlanPtrs &p, int L, SmallWhat what, co
     while (threads < s.T * L || (threads < 1024 && threads < s.U * kWave)) threads *= 2;     // a wave per unit, up to 16
     const int rows = threads / s.lpr;
     const unsigned grid = 3 + (what == SMALL_ROUTE ? 0u : (unsigned)((s.T + rows - 1) / rows));
-    const SmallLds lay = small_lds(s.T, s.E, s.k, s.U, L);
+    const SmallLds lay = small_lds(s.T, s.E, s.k, s.U);
     const size_t lds = (size_t)lay.bytes;
     const int per_lane = (s.E + L - 1) / L;
     auto launch = [&](auto lc, auto ne) -> int {

@@ -17,6 +17,7 @@ namespace monta {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kWave = 64;
 // Chosen by measurement on MI355X (128 and 512 threads, 2 and 8 vectors in flight were slower or equal).
@@ -120,25 +121,14 @@ __device__ __forceinline__ void with_policy3(bool ntl, bool nts, bool ntf, F f)
 
 // ------------------------------------------------------------ route + plan
 
-// Row stride (floats) of the logits tile in LDS.  A wave holds 64 / L tokens with L lanes each, lane (token, sub)
-// reads element sub + q * L of its row: with a stride that is L times an odd number the 64 lanes of a read hit 64
-// different banks (for L = 1 this is the usual odd stride).
-__host__ __device__ inline int route_row_stride(int E, int L) { return L * (((E + L - 1) / L) | 1); }
-
-
 // One workgroup routes TB consecutive tokens of ONE unit; s.rl lanes share a token (1 for few experts).
-//  1. the [nt][E] logits tile is staged in LDS (coalesced, odd row stride);
-//  2. k selections per token.  Lane `sub` of a token keeps every L-th logit in registers, as an unsigned key of the same order;
-//     the largest key wins, among the lane's keys and then among the token's lanes, which agree through DPP moves, then the lowest
-//     index that has it, so ties resolve to the lower index; the winner's key is cleared.
+//  1. lane `sub` of a token's L lanes keeps its logits in registers, every L-th four of them, as unsigned keys of
+//     the same order; the loads of a wave cover whole lines and nothing goes through the LDS;
+//  2. k selections per token, ties to the lower index (route_select);
 //  3. gates in fp64 from the winners' logits, one rounding to fp32;
-//  4. every lane ORs its bit into mask[expert][wave] in LDS; popcounts of those
-//     masks give the workgroup's expert histogram and each pair's stable rank inside
-//     the workgroup (lanes hold consecutive tokens, so bit order is token order).
+//  4. every selection ORs its token's bit into mask[expert][wave] in LDS; popcounts of those masks give the workgroup's expert
+//     histogram and each pair's stable rank inside the workgroup (bit order is token order).
 // No atomics decide a position: the result is deterministic.
-// What bounds it is the selection's instructions (and, for renorm = 0, E fp64 exponentials per token).  Measured with k whole
-// scans of the LDS tile per token and one load at a time: 65536 tokens, 64 experts, top-8 31 us, now 17; 32768 tokens, 256 experts,
-// top-8 about 65, now 23.
 //
 // The lanes of a token (L of them, s.rl = 1, 2, 4 or 8, for small problems up to 16, neighbours in the wave) agree through DPP moves:
 // quads by permutation, the two quads of eight lanes by the half-row mirror, the two eights by the row mirror, whose lanes hold
@@ -150,110 +140,273 @@ __device__ __forceinline__ int xor_lanes(int v)
     constexpr int kCtrl = MASK == 1 ? 0xb1 : MASK == 2 ? 0x4e : MASK == 4 ? 0x141 : 0x140;
     return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, false);
 }
-
-// Steps 1, 2 and the masks of 4: the choices of `nt` tokens whose logits start at src.  Bit tok % 64 of s_mask[e * expert_step +
-// tok / 64 * word_step] (cleared by the caller) is set where token tok chose e.  idx_out: also to memory, if it is not null.
-// s_den: sums of all exponentials, if it is not null.  All threads of the workgroup; ends without a barrier.
-template <int L, int NE>
-__device__ __forceinline__ void route_select(const float *__restrict__ src, int nt, int E, int k, int stride, float *s_l, int *s_sel,
-                                             unsigned long long *s_mask, int expert_step, int word_step, double *s_den,
-                                             int32_t *__restrict__ idx_out, FastDiv by_E)
+// combine(xor_lanes<1>), then <2> and so on, over the L lanes of a token
+template <int L, typename F>
+__device__ __forceinline__ void over_token_lanes(F combine)
 {
-    const int tid = threadIdx.x;
-    {
-        const int total = nt * E;
-        // element i is column i % E of token i / E: one division, then steps.  Eight loads are requested before the first is
-        // laid down: one at a time the tile arrives at one memory latency per element of a lane.
-        constexpr int LD = 8;
-        const int nthr = blockDim.x, step_tok = nthr / by_E, step_col = nthr - step_tok * E;
-        int tok = tid / by_E, col = tid - tok * E;
-        for (int i0 = tid; i0 < total; i0 += LD * nthr) {
-            float v[LD];
-#pragma unroll
-            for (int q = 0; q < LD; ++q) v[q] = src[i0 + q * nthr < total ? i0 + q * nthr : i0];
-#pragma unroll
-            for (int q = 0; q < LD; ++q) {
-                if (i0 + q * nthr < total) s_l[tok * stride + col] = v[q] != v[q] ? -INFINITY : v[q];
-                tok += step_tok;
-                col += step_col;
-                if (col >= E) {
-                    col -= E;
-                    ++tok;
-                }
-            }
-        }
-    }
-    __syncthreads();
+    if constexpr (L > 1) combine(std::integral_constant<int, 1>{});
+    if constexpr (L > 2) combine(std::integral_constant<int, 2>{});
+    if constexpr (L > 4) combine(std::integral_constant<int, 4>{});
+    if constexpr (L > 8) combine(std::integral_constant<int, 8>{});
+}
 
-    // token handled by this lane, and which of the token's L lanes it is
-    const int tok = tid / L, sub = tid % L;
-    const int tword = tok >> 6;                     // mask word and bit of the token inside the workgroup
-    const unsigned long long tbit = 1ull << (tok & 63);
-    const bool active = tok < nt;
-    if (active) {
-        const float *row = s_l + tok * stride;
-        int *sel = s_sel + tok * k;
-        // The lane's elements as unsigned keys of the same order (zeros of both signs alike); 0: taken, or no element.
-        uint32_t key[NE];
+__device__ __forceinline__ void keep_larger_first(uint32_t &a, uint32_t &b)
+{
+    const uint32_t hi = max(a, b), lo = min(a, b);
+    a = hi;
+    b = lo;
+}
+// 4 or 8 keys in descending order (5 and 19 exchanges)
+template <int K>
+__device__ __forceinline__ void sort_keys(uint32_t *v)
+{
+    static_assert(K == 4 || K == 8, "sort_keys: lists of 4 or 8");
+    auto cx = [&](int a, int b) { keep_larger_first(v[a], v[b]); };
+    if constexpr (K == 4) {
+        cx(0, 1), cx(2, 3), cx(0, 2), cx(1, 3), cx(1, 2);
+    } else {
+        cx(0, 1), cx(2, 3), cx(4, 5), cx(6, 7), cx(0, 2), cx(1, 3), cx(4, 6), cx(5, 7), cx(1, 2), cx(5, 6);
+        cx(0, 4), cx(1, 5), cx(2, 6), cx(3, 7), cx(2, 4), cx(3, 5), cx(1, 2), cx(3, 4), cx(5, 6);
+    }
+}
+// a: the K largest of two descending lists of K, in descending order; other(i) is element i of the second
+template <int K, typename F>
+__device__ __forceinline__ void merge_keys(uint32_t *a, F other)
+{
+    uint32_t b[K];
 #pragma unroll
-        for (int q = 0; q < NE; ++q) {
-            const int e = sub + q * L;
-            const uint32_t u = __float_as_uint(row[e < E ? e : E - 1] + 0.f);
-            key[q] = e < E ? u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u) : 0u;
+    for (int i = 0; i < K; ++i) b[i] = other(K - 1 - i);
+#pragma unroll
+    for (int i = 0; i < K; ++i) a[i] = max(a[i], b[i]);          // larger half, bitonic
+#pragma unroll
+    for (int d = K / 2; d >= 1; d /= 2)
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if ((i & d) == 0) keep_larger_first(a[i], a[i + d]);
+}
+// the K largest of a token's keys (NE in each of its L lanes), in descending order, in every lane of the token
+template <int K, int L, int NE>
+__device__ __forceinline__ void largest_keys(const uint32_t (&key)[NE], uint32_t (&top)[K])
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i) top[i] = key[i];
+    sort_keys<K>(top);
+#pragma unroll
+    for (int q = K; q < NE; q += K) {
+        uint32_t next[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) next[i] = key[q + i];
+        sort_keys<K>(next);
+        merge_keys<K>(top, [&](int i) { return next[i]; });
+    }
+    over_token_lanes<L>([&](auto mask) {
+        uint32_t mine[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) mine[i] = top[i];
+        merge_keys<K>(top, [&](int i) { return (uint32_t)xor_lanes<decltype(mask)::value>((int)mine[i]); });
+    });
+}
+
+// key[q] by the bits of q: registers have no address
+template <int N>
+__device__ __forceinline__ uint32_t pick_key(const uint32_t (&key)[N], int q)
+{
+    if constexpr (N == 1) {
+        return key[0];
+    } else {
+        uint32_t half[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const uint32_t even = key[2 * i], odd = key[2 * i + 1];     // values: a choice of places would be an address
+            half[i] = q & 1 ? odd : even;
         }
-        int first = 0;
+        return pick_key<N / 2>(half, q >> 1);
+    }
+}
+
+// Steps 1, 2 and the masks of 4: the choices of `nt` tokens whose logits start at src.  Choice j of token tok and its logit go to
+// s_sel and s_top[tok * k + j]; bit tok % 64 of s_mask[e * expert_step + tok / 64 * word_step] (cleared by the caller) is
+// set where token tok chose e.  idx_out: the choices also to memory, if it is not null.  s_den: sums of all exponentials, if it is
+// not null.  All threads of the workgroup; ends without a barrier.
+// Up to two choices, or more than eight, are found one after the other: the largest key of the token, its lowest place, and that key is
+// cleared, about 4.5 instructions per key and choice.  Three to eight: the largest keys in order, from sorting networks over the
+// lane's keys and then over the token's lanes, about 11 instructions per key for eight; then each lane looks up the few of its keys
+// that are among them, and the number of larger ones is their place.  Equal keys among the chosen ones (seen by that some place would
+// be taken twice, or too many keys qualify) are dealt with choice by choice, for the whole wave.
+// What bounds it is instructions.  Measured on MI355X, routing and plan, logits through the LDS and choice after choice, now: 32768 tokens,
+// 256 experts, top-8 35.7 -> 28.1 us (the kernel 22.3 -> 14.6), with logits of 8 bits, full of ties, 36.6 -> 32.7, all equal 30.1 -> 26.8;
+// 65536 tokens, 64 experts, top-8 28.0 -> 23.9; 16384 tokens, 255 experts, top-2, renorm = 0 25.6 -> 23.9.
+template <int L, int NE>
+__device__ __forceinline__ void route_select(const float *__restrict__ src, int nt, int E, int k, int *s_sel, float *s_top,
+                                             unsigned long long *s_mask, int expert_step, int word_step, double *s_den,
+                                             int32_t *__restrict__ idx_out)
+{
+    static_assert(NE % 8 == 0 && NE <= 32, "route_select: keys of a lane");
+    constexpr int kShift = L == 1 ? 2 : L == 2 ? 3 : L == 4 ? 4 : L == 8 ? 5 : 6;         // experts of all lanes' fours: 1 << kShift
+    const int tid = threadIdx.x, tok = tid / L, sub = tid % L;      // token handled by this lane, and which of its L lanes it is
+    const unsigned long long tbit = 1ull << (tok & 63);
+    unsigned long long *const mask = s_mask + (tok >> 6) * word_step;
+    int *const sel = s_sel + tok * k;
+    float *const top_logit = s_top + tok * k;
+    auto expert = [&](int q) { return ((q >> 2) << kShift) + sub * 4 + (q & 3); };        // of the lane's key q
+    const int rest = E - sub * 4;
+    auto exists = [&](int q) { return ((q >> 2) << kShift) + (q & 3) < rest; };           // (a constant against one register)
+
+    // A lane's four logits from key q on are one load, which on this hardware has to be aligned to its elements only.  Where rows are not
+    // whole fours, one that reaches past the row's end is read from the row's last four and shifted.  What no expert has is never
+    // looked at.  Offsets of 32 bits from the workgroup's first logit (at most 1024 tokens of 256): one register per load on its way.
+    const uint32_t row = tok < nt ? (uint32_t)(tok * E) : 0u;
+    auto at = [&](int e) { return reinterpret_cast<const unsigned char *>(src) + (size_t)((row + (uint32_t)e) * 4u); };
+    auto last_four = [&](int q) { return min(expert(q), E - 4); };
+    auto load_four = [&](int q) { return *reinterpret_cast<const f32x4_any *>(at(last_four(q))); };
+    auto shifted = [&](int q, f32x4 x) {
+        const int past = expert(q) - last_four(q);
+        const float y0 = past & 1 ? x[1] : x[0], y1 = past & 1 ? x[2] : x[1], y2 = past & 1 ? x[3] : x[2];
+        return f32x4{past & 2 ? y2 : y0, past & 2 ? x[3] : y1, y2, x[3]};
+    };
+    auto load_few = [&](int i) { return *reinterpret_cast<const float *>(at(min(expert(i), E - 1))); };        // fewer than four experts
+    float v[NE];
+    if (E >= 4) {
+        f32x4 x[NE / 4];
+#pragma unroll
+        for (int q = 0; q < NE; q += 4) x[q / 4] = load_four(q);
+        if (E & 3) {
+#pragma unroll
+            for (int q = 0; q < NE; q += 4) x[q / 4] = shifted(q, x[q / 4]);
+        }
+#pragma unroll
+        for (int q = 0; q < NE; ++q) v[q] = x[q / 4][q % 4];
+    } else {
+#pragma unroll
+        for (int q = 0; q < NE; ++q) v[q] = q < 4 ? load_few(q) : 0.f;
+    }
+    __syncthreads();                                                // the masks are cleared
+    if (tok >= nt) return;
+    // Unsigned keys of the same order (zeros of both signs alike, NaN as -infinity); 0: taken, or no element.
+    uint32_t key[NE];
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        const uint32_t u = __float_as_uint((v[q] != v[q] ? -INFINITY : v[q]) + 0.f);
+        key[q] = exists(q) ? u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u) : 0u;
+    }
+    auto pick = [&](int q) { return pick_key<NE>(key, q); };
+    auto logit = [](uint32_t x) { return __uint_as_float(x & 0x80000000u ? x ^ 0x80000000u : ~x); };
+    // called by one lane per choice
+    auto choose = [&](int j, int e, uint32_t x) {
+        sel[j] = e;
+        top_logit[j] = logit(x);
+        if (idx_out) idx_out[tok * k + j] = e;
+        atomicOr(&mask[e * expert_step], tbit);
+    };
+    auto largest = [&] {                                            // of the token
+        uint32_t most = key[0];
+#pragma unroll
+        for (int q = 1; q < NE; ++q) most = max(most, key[q]);
+        over_token_lanes<L>([&](auto m) { most = max(most, (uint32_t)xor_lanes<decltype(m)::value>((int)most)); });
+        return most;
+    };
+    if (s_den) {
+        // softmax over all E: the token's lanes each sum their experts, read again four at a time, then add up across the lanes
+        const double first = (double)logit(largest());
+        double part = 0.0;
+        auto add = [&](int q, f32x4 x) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part += exp((double)(exists(q + i) && x[i] == x[i] ? x[i] : -INFINITY) - first);
+        };
+        if (E >= 4) {
+            f32x4 next = load_four(0);
+#pragma unroll 1
+            for (int q = 0; q < NE && exists(q); q += 4) {
+                const f32x4 x = E & 3 ? shifted(q, next) : next;
+                next = load_four(q + 4);
+                add(q, x);
+            }
+        } else {
+            add(0, f32x4{load_few(0), load_few(1), load_few(2), load_few(3)});
+        }
+        for (int mk = 1; mk < L; mk <<= 1) part += __shfl_xor(part, mk, kWave);
+        if (sub == 0) s_den[tok] = part;
+    }
+    auto lowest = [&](int at) {                                     // of the token's lanes' places; E only if k > E, then any in range
+        over_token_lanes<L>([&](auto m) { at = min(at, xor_lanes<decltype(m)::value>(at)); });
+        return min(at, E - 1);
+    };
+    auto one_by_one = [&] {
         for (int j = 0; j < k; ++j) {
-            uint32_t most = key[0];
+            const uint32_t most = largest();
+            int at = -1;
 #pragma unroll
-            for (int q = 1; q < NE; ++q) most = max(most, key[q]);
-            auto larger = [&](auto mask) { most = max(most, (uint32_t)xor_lanes<decltype(mask)::value>((int)most)); };
-            if constexpr (L > 1) larger(std::integral_constant<int, 1>{});
-            if constexpr (L > 2) larger(std::integral_constant<int, 2>{});
-            if constexpr (L > 4) larger(std::integral_constant<int, 4>{});
-            if constexpr (L > 8) larger(std::integral_constant<int, 8>{});
-            int at = E;                             // the lowest place of that value: in this lane, then among the token's lanes
-#pragma unroll
-            for (int q = NE - 1; q >= 0; --q) at = key[q] == most ? sub + q * L : at;
-            auto lower = [&](auto mask) { at = min(at, xor_lanes<decltype(mask)::value>(at)); };
-            if constexpr (L > 1) lower(std::integral_constant<int, 1>{});
-            if constexpr (L > 2) lower(std::integral_constant<int, 2>{});
-            if constexpr (L > 4) lower(std::integral_constant<int, 4>{});
-            if constexpr (L > 8) lower(std::integral_constant<int, 8>{});
-            const int best = min(at, E - 1);        // E only if k > E; keeps indices in range
-            if (j == 0) first = best;
-            const int mine = best % L == sub ? best / L : -1;
+            for (int q = NE - 1; q >= 0; --q) at = key[q] == most ? q : at;
+            const int best = lowest(at >= 0 ? expert(at) : E);
+            const int mine = ((best >> 2) & (L - 1)) == sub ? ((best >> kShift) << 2) + (best & 3) : -1;
 #pragma unroll
             for (int q = 0; q < NE; ++q) key[q] = mine == q ? 0u : key[q];
-            if (sub == 0) {
-                sel[j] = best;
-                if (idx_out) idx_out[tok * k + j] = best;
-                atomicOr(&s_mask[best * expert_step + tword * word_step], tbit);
+            if (sub == 0) choose(j, best, most);
+        }
+    };
+    auto by_networks = [&](auto kc) {
+        constexpr int K = decltype(kc)::value;
+        uint32_t top[K];
+        largest_keys<K, L, NE>(key, top);
+        uint32_t least = top[0];                                    // the smallest that is chosen
+        bool equal = false;
+#pragma unroll
+        for (int j = 1; j < K; ++j)
+            if (j < k) {
+                least = top[j];
+                equal |= top[j] == top[j - 1];
             }
+        uint32_t chosen = 0;                                        // bit q: key q is among them
+#pragma unroll
+        for (int q = NE - 1; q >= 0; --q) chosen = chosen + chosen + (key[q] >= least ? 1u : 0u);
+        int count = __popc(chosen);
+        over_token_lanes<L>([&](auto m) { count += xor_lanes<decltype(m)::value>(count); });
+        if (__any(equal || count != k)) {
+            int at = 0;
+            uint32_t last = 0;
+#pragma unroll 1
+            for (int j = 0; j < k; ++j) {
+                uint32_t want = top[0], same = 0;
+#pragma unroll
+                for (int i = 1; i < K; ++i) want = j == i ? top[i] : want;
+#pragma unroll
+                for (int q = NE - 1; q >= 0; --q) same = same + same + (key[q] == want ? 1u : 0u);
+                if (want == last) {                                 // past the place of the one before
+                    const int four = (at >> kShift) << 2, its_sub = (at >> 2) & (L - 1);
+                    const int from = four + (sub < its_sub ? 4 : sub == its_sub ? (at & 3) + 1 : 0);
+                    same = from < 32 ? same & (~0u << from) : 0u;
+                }
+                at = lowest(same ? expert(__builtin_ctz(same)) : E);
+                last = want;
+                if (sub == 0) choose(j, at, want);
+            }
+            return;
         }
-        if (s_den) {
-            // softmax over all E: the token's lanes each sum their experts, then add up across the lanes
-            const double top_logit = (double)row[first];
-            double part = 0.0;
-            for (int e = sub; e < E; e += L) part += exp((double)row[e] - top_logit);
-            for (int mk = 1; mk < L; mk <<= 1) part += __shfl_xor(part, mk, kWave);
-            if (sub == 0) s_den[tok] = part;
+        while (chosen) {
+            const int q = __builtin_ctz(chosen);
+            chosen &= chosen - 1;
+            const uint32_t x = pick(q);
+            int j = 0;
+#pragma unroll
+            for (int i = 0; i < K; ++i) j += top[i] > x ? 1 : 0;
+            choose(j, expert(q), x);
         }
-    }
+    };
+    if (k <= 2 || k > 8) one_by_one();
+    else if (k <= 4) by_networks(std::integral_constant<int, 4>{});
+    else by_networks(std::integral_constant<int, 8>{});
 }
 
 // Step 3 for tokens [0, nt), by threads tid of nthr, in two parts with a barrier between: w_j = exp(l_j - l_0) in fp64 (w_0 = 1
 // needs no call), one (token, choice) pair per lane so that every lane has an exp to do, not only one per token; then the
 // denominator, summed in j order (or taken from s_den, the sums over all experts, if that is not null), one division, one rounding
 // to fp32: store(pair, gate).
-__device__ __forceinline__ void route_weights(int nt, int k, int stride, const float *s_l, const int *s_sel, double *s_w, FastDiv by_k1,
-                                              int tid, int nthr)
+__device__ __forceinline__ void route_weights(int nt, int k, const float *s_top, double *s_w, FastDiv by_k1, int tid, int nthr)
 {
     for (int tk = tid; tk < nt; tk += nthr) s_w[tk * k] = 1.0;
     for (int idx = tid; idx < nt * (k - 1); idx += nthr) {               // only the choices j >= 1 need an exp
         const int tk = idx / by_k1, j = 1 + idx - tk * (k - 1);
-        const float *row = s_l + tk * stride;
-        const int *sel = s_sel + tk * k;
-        s_w[tk * k + j] = exp((double)row[sel[j]] - (double)row[sel[0]]);
+        s_w[tk * k + j] = exp((double)s_top[tk * k + j] - (double)s_top[tk * k]);
     }
 }
 template <typename F>
@@ -272,6 +425,23 @@ __device__ __forceinline__ void route_gates(int nt, int k, const double *s_w, co
     }
 }
 
+// Dynamic LDS of route_plan_kernel (byte offsets): [TB][k] choices, their logits, bit masks [E][words of 64 tokens], [TB][k] weights,
+// [TB] softmax denominators (renorm = 0).
+struct RouteLds {
+    int top, mask, w, den, bytes;
+};
+__host__ __device__ inline RouteLds route_lds(int TB, int E, int k)
+{
+    const int NW = TB > kWave ? TB / kWave : 1;
+    RouteLds l;
+    l.top = TB * k * 4;
+    l.mask = (l.top + TB * k * 4 + 7) & ~7;
+    l.w = l.mask + E * NW * 8;
+    l.den = l.w + TB * k * 8;
+    l.bytes = l.den + TB * 8;
+    return l;
+}
+
 template <int L, int NE>
 __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restrict__ logits,
                                                          int32_t *__restrict__ topk_idx,
@@ -279,14 +449,12 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int E = s.E, k = s.k, TB = s.TB;
-    const int stride = route_row_stride(E, L);
     const int NW = TB > kWave ? TB / kWave : 1;
-    float *s_l = reinterpret_cast<float *>(smem);
-    int *s_sel = reinterpret_cast<int *>(s_l + (size_t)TB * stride);
-    unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(
-        smem + (((size_t)TB * stride * 4 + (size_t)TB * k * 4 + 7) & ~(size_t)7));
-    double *s_w = reinterpret_cast<double *>(s_mask + (size_t)E * NW);     // [TB][k] unnormalised weights
-    double *s_den = s_w + (size_t)TB * k;                                  // [TB] softmax denominators (renorm = 0)
+    const RouteLds lds = route_lds(TB, E, k);
+    int *s_sel = reinterpret_cast<int *>(smem);
+    float *s_top = reinterpret_cast<float *>(smem + lds.top);
+    unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(smem + lds.mask);
+    double *s_w = reinterpret_cast<double *>(smem + lds.w), *s_den = reinterpret_cast<double *>(smem + lds.den);
 
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
@@ -296,10 +464,10 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
     if (nt > TB) nt = TB;
 
     for (int i = tid; i < E * NW; i += blockDim.x) s_mask[i] = 0ull;
-    route_select<L, NE>(logits + (size_t)t_begin * E, nt, E, k, stride, s_l, s_sel, s_mask, NW, 1, s.renorm ? nullptr : s_den,
-                        topk_idx + (size_t)t_begin * k, s.by_E);
+    route_select<L, NE>(logits + (size_t)t_begin * E, nt, E, k, s_sel, s_top, s_mask, NW, 1, s.renorm ? nullptr : s_den,
+                        topk_idx + (size_t)t_begin * k);
     __syncthreads();
-    route_weights(nt, k, stride, s_l, s_sel, s_w, s.by_k1, tid, blockDim.x);
+    route_weights(nt, k, s_top, s_w, s.by_k1, tid, blockDim.x);
     __syncthreads();
     route_gates(nt, k, s_w, s.renorm ? nullptr : s_den, s.by_k, tid, blockDim.x,
                 [&](int idx, float g) { gates[(size_t)t_begin * k + idx] = g; });
@@ -1358,20 +1526,20 @@ enum SmallWhat { SMALL_ROUTE = 0, SMALL_PLACE = 1, SMALL_COMBINE = 2 };
 // Dynamic LDS of the kernel (byte offsets; made on the host: in every workgroup it is a chain of a hundred scalar instructions).
 // NW: words of 64 tokens.
 struct SmallLds {
-    int stride, NW, sel, mask, w, den, gate, pre, total, off, kpre, base, stage, bytes;
+    int NW, sel, top, mask, w, den, gate, pre, total, off, kpre, base, stage, bytes;
 };
-inline SmallLds small_lds(int T, int E, int k, int U, int L)
+inline SmallLds small_lds(int T, int E, int k, int U)
 {
     SmallLds l;
-    l.stride = route_row_stride(E, L);
     l.NW = (T + kWave - 1) / kWave;
-    int64_t at = (int64_t)T * l.stride * 4;
+    int64_t at = 0;
     auto take = [&](int64_t n) {
         const int64_t o = (at + 7) & ~(int64_t)7;
         at = o + n;
         return (int)o;
     };
     l.sel = take((int64_t)T * k * 4);
+    l.top = take((int64_t)T * k * 4);
     l.mask = take((int64_t)E * l.NW * 8);
     l.w = take((int64_t)T * k * 8);
     l.den = take((int64_t)T * 8);
@@ -1395,8 +1563,8 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned long long s_alive[16];
     const int T = s.T, E = s.E, k = s.k, U = s.U, Tu = s.Tu, C = s.C, vpr = s.vpr, lpr = s.lpr;
-    float *s_l = reinterpret_cast<float *>(smem);
     int *s_sel = reinterpret_cast<int *>(smem + lds.sel);
+    float *s_top = reinterpret_cast<float *>(smem + lds.top);
     unsigned long long *s_mask = reinterpret_cast<unsigned long long *>(smem + lds.mask);      // [word][expert]
     double *s_w = reinterpret_cast<double *>(smem + lds.w), *s_den = reinterpret_cast<double *>(smem + lds.den);
     float *s_gate = reinterpret_cast<float *>(smem + lds.gate);                                 // of this workgroup's rows
@@ -1404,7 +1572,7 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
     int *s_off = reinterpret_cast<int *>(smem + lds.off), *s_kpre = reinterpret_cast<int *>(smem + lds.kpre);
     int *s_base = reinterpret_cast<int *>(smem + lds.base), *s_stage = reinterpret_cast<int *>(smem + lds.stage);
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & (kWave - 1), wave = tid >> 6, nwaves = nthr >> 6;
-    const int NW = lds.NW, stride = lds.stride;
+    const int NW = lds.NW;
     enum { PAIRS = 0, TABLES = 1, GATES = 2, ROWS = 3 };           // what workgroups 0, 1, 2 and the others write
     const int role = blockIdx.x < ROWS ? (int)blockIdx.x : ROWS;
     const bool mover = role == ROWS;
@@ -1424,11 +1592,11 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
     if (tid < 16) s_alive[tid] = 0ull;
     const bool weighted = role == GATES || (mover && what == SMALL_COMBINE);
     double *den = s.renorm || !weighted ? nullptr : s_den;
-    route_select<L, NE>(logits, T, E, k, stride, s_l, s_sel, s_mask, 1, E, den, role == GATES ? topk_idx : nullptr, s.by_E);
+    route_select<L, NE>(logits, T, E, k, s_sel, s_top, s_mask, 1, E, den, role == GATES ? topk_idx : nullptr);
     __syncthreads();
     // Gates of all tokens, or of this workgroup's own: by the last waves first, beside the scans, which are the first waves' work.
     const int rtid = nthr - 1 - tid;
-    if (weighted) route_weights(t1 - t0, k, stride, s_l + t0 * stride, s_sel + t0 * k, s_w + t0 * k, s.by_k1, rtid, nthr);
+    if (weighted) route_weights(t1 - t0, k, s_top + t0 * k, s_w + t0 * k, s.by_k1, rtid, nthr);
     for (int e = tid; e < E; e += nthr) {
         int c = 0;
         for (int w = 0; w < NW; ++w) {

@@ -56,3 +56,32 @@ def test_route_tables(m, E, k, T, tp, S, tied):
         row_map = np.empty(pl.R, np.int32)
         row_map[pl.pos_stage.reshape(-1)[kept]] = pl.pos_final.reshape(-1)[kept]
         assert np.array_equal(t["row_map"][:pl.R], row_map)
+
+
+# every count of choices that is found by networks, over lanes per token and keys per lane, rows that are not whole fours and logits that are
+# aligned to their elements only; ties among the chosen and at their end in some tokens, masked experts (the type's lowest value) in others
+@pytest.mark.parametrize("offset", [0, 1, 3])
+@pytest.mark.parametrize("E", [3, 5, 8, 13, 16, 30, 64, 101, 129, 254, 255, 256])
+def test_route_choices(m, E, offset):
+    import torch
+    T = 700
+    rng = np.random.default_rng(E + offset)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    logits[100:300] = np.round(logits[100:300] * 4) / 4
+    logits[200:400, rng.permutation(E)[:E // 2]] = np.finfo(np.float32).min
+    logits[650:] = logits[650:, :1]
+    x = np.zeros((T, 8), np.uint16)
+    for k in range(1, min(E, 9) + 1):
+        w = Workload("choices", T, 8, BF16, E, k, 1, 1, 1, 0.9, renorm=k % 2)
+        ref = oracle.forward(logits, x, k=k, ep=1, tp=1, S=1, cf=w.capacity_factor, renorm=w.renorm)
+        cfg = m.make_cfg(T, 8, BF16, E, k, 1, 1, 1, w.capacity_factor, w.renorm)
+        b = m.alloc_buffers(cfg, logits, x)
+        flat = torch.empty(T * E + 4, device="cuda:0")
+        view = flat[offset:offset + T * E].view(T, E)
+        view.copy_(b.logits)
+        m.monta_route(cfg, view, b.topk_idx, b.gates, b.ws)
+        torch.cuda.synchronize()
+        t = m.read_tables(cfg, b.ws)
+        assert np.array_equal(b.topk_idx.cpu().numpy(), ref.topk_idx), k
+        np.testing.assert_allclose(b.gates.cpu().numpy(), ref.gates, rtol=1e-6)
+        assert np.array_equal(t["pos_final"].reshape(-1), np.asarray(ref.plan.pos_final).reshape(-1)), k
