@@ -1719,23 +1719,26 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
         return;
     }
 
-    // One 16-byte vector of the output: the gate-weighted sum over the kept choices, in order, of copies of the row's vector
-    auto combined_as = [&](auto bf, u32x4 v, auto each_gate) {
+    // One 16-byte vector of the output: the gate-weighted sum over the kept choices, in order, of copies of the row's vector.
+    // each(add): add(gate) for every kept choice
+    auto combined_as = [&](auto bf, u32x4 v, auto each) {
         constexpr bool BF16 = decltype(bf)::value;
         constexpr int NF = BF16 ? 8 : 4;
-        double acc[NF];
+        double val[NF], acc[NF];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if constexpr (BF16) {
+                val[2 * c] = bf16_lo(v[c]);
+                val[2 * c + 1] = bf16_hi(v[c]);
+            } else {
+                val[c] = (double)__uint_as_float(v[c]);
+            }
+        }
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[f] = 0.0;
-        each_gate([&](double g) {
+        each([&](double g) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if constexpr (BF16) {
-                    acc[2 * c] = __builtin_fma(g, bf16_lo(v[c]), acc[2 * c]);
-                    acc[2 * c + 1] = __builtin_fma(g, bf16_hi(v[c]), acc[2 * c + 1]);
-                } else {
-                    acc[c] = __builtin_fma(g, (double)__uint_as_float(v[c]), acc[c]);
-                }
-            }
+            for (int f = 0; f < NF; ++f) acc[f] = __builtin_fma(g, val[f], acc[f]);
         });
         u32x4 o;
 #pragma unroll
@@ -1745,8 +1748,8 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
         }
         return o;
     };
-    auto combined = [&](u32x4 v, auto each_gate) {
-        return bf16 ? combined_as(std::true_type{}, v, each_gate) : combined_as(std::false_type{}, v, each_gate);
+    auto combined = [&](u32x4 v, auto each) {
+        return bf16 ? combined_as(std::true_type{}, v, each) : combined_as(std::false_type{}, v, each);
     };
     const int gbase = lpr >= kWave ? 0 : (lane & ~(lpr - 1)), gl = lane - gbase;
     u32x4 *dst = out + (size_t)(have ? t : 0) * vpr;
@@ -1757,33 +1760,58 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
         if (ok && what == SMALL_COMBINE) my_g = s_gate[sub * k + gl];
         const unsigned int kmask = k >= 32 ? 0xffffffffu : ((1u << k) - 1u);
         const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
-        for (int vbase = 0; vbase < vpr; vbase += lpr * kVecInFlight) {
-            const int v0 = vbase + rl;
-            if (vbase != 0) {
-#pragma unroll
-                for (int q = 0; q < kVecInFlight; ++q)
-                    if (have && v0 + q * lpr < vpr) val[q] = src[v0 + q * lpr];
-            }
-            for (unsigned int rem = kept; rem; rem &= rem - 1) {
-                const int j = __builtin_ctz(rem);
-                u32x4 *ds = stage + (size_t)__shfl(ps, gbase + j, kWave) * vpr, *df = fin + (size_t)__shfl(pf, gbase + j, kWave) * vpr;
-#pragma unroll
-                for (int q = 0; q < kVecInFlight; ++q)
-                    if (v0 + q * lpr < vpr) {
-                        st16<true>(ds + v0 + q * lpr, val[q]);
-                        df[v0 + q * lpr] = val[q];
-                    }
-            }
-            if (what == SMALL_COMBINE && have) {
-#pragma unroll
-                for (int q = 0; q < kVecInFlight; ++q) {
-                    const u32x4 o = combined(val[q], [&](auto add) {
-                        for (unsigned int rem = kept; rem; rem &= rem - 1) add((double)__shfl(my_g, gbase + __builtin_ctz(rem), kWave));
-                    });
-                    if (v0 + q * lpr < vpr) st16<true>(dst + v0 + q * lpr, o);
+        // All rows being copies of one, the sum of products is the product with the sum of the gates: the same to the last bit of 64 where
+        // that sum is exact, which it is unless gates are 2^29 apart.  Not for three or more choices in fp32, whose chain rounds in
+        // between, and not with a gate of zero, which an infinite activation would tell from no choice.  Rows that whole waves
+        // share have their destinations in scalar registers.
+        auto move = [&](auto whole_waves) {
+            constexpr bool WAVE = decltype(whole_waves)::value;
+            const unsigned int mine = WAVE ? (unsigned int)__builtin_amdgcn_readfirstlane((int)kept) : kept;
+            auto of = [&](int v, int j) { return WAVE ? __builtin_amdgcn_readlane(v, j) : __shfl(v, gbase + j, kWave); };
+            double gate_sum = 0.0;
+            bool summed = bf16 || k <= 2;
+            if (what == SMALL_COMBINE && summed) {
+                for (unsigned int rem = mine; rem; rem &= rem - 1) {
+                    const float g = __int_as_float(of(__float_as_int(my_g), __builtin_ctz(rem)));
+                    summed &= g != 0.f;
+                    gate_sum += (double)g;
                 }
             }
-        }
+            for (int vbase = 0; vbase < vpr; vbase += lpr * kVecInFlight) {
+                const int v0 = vbase + rl;
+                if (vbase != 0) {
+#pragma unroll
+                    for (int q = 0; q < kVecInFlight; ++q)
+                        if (have && v0 + q * lpr < vpr) val[q] = src[v0 + q * lpr];
+                }
+                for (unsigned int rem = mine; rem; rem &= rem - 1) {
+                    const int j = __builtin_ctz(rem);
+                    u32x4 *ds = stage + (size_t)of(ps, j) * vpr, *df = fin + (size_t)of(pf, j) * vpr;
+#pragma unroll
+                    for (int q = 0; q < kVecInFlight; ++q)
+                        if (v0 + q * lpr < vpr) {
+                            st16<true>(ds + v0 + q * lpr, val[q]);
+                            df[v0 + q * lpr] = val[q];
+                        }
+                }
+                if (what == SMALL_COMBINE) {
+#pragma unroll
+                    for (int q = 0; q < kVecInFlight; ++q) {
+                        if (vbase + q * lpr >= vpr) break;
+                        const u32x4 o = combined(val[q], [&](auto add) {
+                            if (summed) {
+                                if (mine) add(gate_sum);
+                            } else {
+                                for (unsigned int rem = mine; rem; rem &= rem - 1) add((double)__int_as_float(of(__float_as_int(my_g), __builtin_ctz(rem))));
+                            }
+                        });
+                        if (have && v0 + q * lpr < vpr) st16<true>(dst + v0 + q * lpr, o);
+                    }
+                }
+            }
+        };
+        if (lpr >= kWave) move(std::true_type{});
+        else move(std::false_type{});
     } else if (have) {
         // fewer lanes per row than choices: rows of at most 256 bytes, one vector per lane
         for (int j = 0; j < k; ++j) {
