@@ -1225,6 +1225,61 @@ int route_dispatch_regather_impl(const Geometry &g, const float *logits, const v
     return pipeline_impl(g, pp, x, stage, final_, ws, true, st);
 }
 
+int64_t combine_unit_count(const Shape &s)
+{
+    const int tokens = s.vpr >= kWave ? 1 : kWave / s.lpr;          // of a wave
+    return s.vpr >= kWave ? (int64_t)s.T * ((s.vpr + kWave - 1) / kWave) : (s.T + tokens - 1) / tokens;
+}
+// How many choices combine_units_t has on their way, 0 where the forms of 256 lanes per row are the better ones.  Measured on MI355X, the
+// combine alone (three sets in turn, us, 256 lanes and a wave per 64 vectors; bf16 unless said):
+//  - rows of up to 4 KiB: 7500 x 1632, top-2 20.4 and 16.5; 30000 x 1024, top-2 39.2 and 32.5; 8000 x 512, top-8 17.4 and 13.8;
+//    60000 x 2048, top-1 100 and 96;
+//  - longer ones that leave more than three tenths of the lanes' vectors unused: 30595 x 5120, top-3 226 and 204; 8407 x 5008, top-3 64 and
+//    57; but 4876 x 5120, fp32, top-2, half of it dropped 29.4 and 32.1, and with full lanes 30000 x 4096, top-2 120 and 123, 65536 x 7168,
+//    top-8, half dropped 712 and 735;
+//  - few tokens, whose chain of row after row is what takes the time: 492 x 4096, top-8 9.0 and 5.6; 285 x 3200, top-6 7.2 and 4.5; 675 x
+//    8192, top-8 19.0 and 18.2; but top-1, 1123 x 7168 7.0 and 7.7.
+// Eight rows on their way pay where waves are few (500 x 512, top-8, two 4.9, eight 4.0; 8000 x 512 13.8 and 14.3).  Over 150 shapes 1.08
+// times as fast.  The return path, which also stores the rows, gains less (13347 x 1024, top-3 13.7 and 12.0; 3658 x 132, fp32, top-6 6.1 and 5.2)
+// and loses with one or two choices on rows of 4 KiB (39259 x 1024, fp32, top-2 141 and 146; 335 x 4096, fp32 5.4 and 5.8).
+int combine_units(const Shape &s, bool bf16, bool returned)
+{
+    if (s.k > s.lpr) return 0;
+    const bool few = combine_unit_count(s) <= 4096;
+    if (s.vpr <= kMoverThreads) {
+        if (returned && s.k <= 2 && s.vpr > 192 && !few) return 0;
+    } else if (s.k < 2) {
+        return 0;
+    } else if (s.T <= 1024) {
+        if (returned && s.k == 2 && !few) return 0;
+    } else {
+        const int pass = kMoverThreads * (s.vpr > 2 * kMoverThreads ? 4 : 2);
+        if (s.vpr * 10ll > (s.vpr + pass - 1) / pass * pass * 7ll) return 0;
+        if (!bf16 && (returned || (s.C < s.T && (int64_t)s.C * s.E < 2ll * s.T * s.k))) return 0;
+    }
+    return s.k > 2 && (few || s.T <= 1024) ? 8 : 2;
+}
+dim3 combine_units_grid(const Shape &s)
+{
+    constexpr int kPerWg = kMoverThreads / kWave;
+    return dim3((unsigned)std::min<int64_t>((combine_unit_count(s) + kPerWg - 1) / kPerWg, 1 << 20));
+}
+// launch(is bf16, choices on their way at a time, rows of whole waves)
+template <typename F>
+void with_units(int dtype, const Shape &s, int K, F launch)
+{
+    auto by_k = [&](auto bf, auto wave) {
+        if (K == 8) launch(bf, std::integral_constant<int, 8>{}, wave);
+        else launch(bf, std::integral_constant<int, 2>{}, wave);
+    };
+    auto by_rows = [&](auto bf) {
+        if (s.vpr >= kWave) by_k(bf, std::true_type{});
+        else by_k(bf, std::false_type{});
+    };
+    if (dtype == MONTA_BF16) by_rows(std::true_type{});
+    else by_rows(std::false_type{});
+}
+
 int combine_impl(const Geometry &g, int dtype, const void *y, const float *gates, void *out, const void *ws, hipStream_t st)
 {
     const Shape &s = g.s;
@@ -1234,7 +1289,16 @@ int combine_impl(const Geometry &g, int dtype, const void *y, const float *gates
     const bool wide = s.vpr > 2 * s.lpr;   // more than two vectors per lane: 4 per pass
     const u32x4 *yv = static_cast<const u32x4 *>(y);
     u32x4 *ov = static_cast<u32x4 *>(out);
-    // With three or more choices per token the software-pipelined form wins (measured on MI355X, 65536 tokens of
+    if (const int K = combine_units(s, dtype == MONTA_BF16, false)) {
+        const dim3 ugrid = combine_units_grid(s);
+        with_units(dtype, s, K, [&](auto bf, auto kc, auto wave) {
+            hipLaunchKernelGGL((combine_units_kernel<decltype(bf)::value, decltype(kc)::value, decltype(wave)::value>), ugrid, block, 0, st, yv, gates,
+                               ov, p, s);
+        });
+        HIP_TRY(hipGetLastError());
+        return MONTA_OK;
+    }
+    // Otherwise, with three or more choices per token, the software-pipelined form wins (measured on MI355X, 65536 tokens of
     // 14 KiB, top-8 with drops: 802 -> 707 us); with one or two there is nothing to pipeline and its extra
     // registers cost 2-4 %.  It needs the token's k positions to fit the lanes that share its row.
     if (s.k >= 3 && s.k <= s.lpr) {
@@ -1687,6 +1751,15 @@ int launch_return(const Geometry &g, const PlanPtrs &p, int dtype, const void *y
     u32x4 *sv = static_cast<u32x4 *>(y_stage), *ov = static_cast<u32x4 *>(out);
     const dim3 grid(mover_grid(s, s.T)), block(kMoverThreads);
     ProfScope ps(MONTA_K_RETURN, st);
+    if (const int K = combine_units(s, dtype == MONTA_BF16, true)) {
+        const dim3 ugrid = combine_units_grid(s);
+        with_units(dtype, s, K, [&](auto bf, auto kc, auto wave) {
+            hipLaunchKernelGGL((return_units_kernel<decltype(bf)::value, decltype(kc)::value, decltype(wave)::value>), ugrid, block, 0, st, yv, sv, gates,
+                               ov, p, s);
+        });
+        HIP_TRY(hipGetLastError());
+        return MONTA_OK;
+    }
     auto launch = [&](auto bf, auto nv, auto pfc) {
         hipLaunchKernelGGL((return_kernel<decltype(bf)::value, decltype(nv)::value, decltype(pfc)::value>), grid, block, 0, st,
                            yv, sv, gates, ov, p, s);

@@ -1486,6 +1486,85 @@ __device__ __forceinline__ void combine_rows_pf_t(const u32x4 *__restrict__ y, c
     }
 }
 
+// The same scale-add in smaller pieces: a wave takes 64 vectors of one token's output (WAVE; with rows of fewer vectors several tokens), one
+// per lane, and has the rows of up to K choices on their way at a time.  No lane is without work but in a row's last piece, where 256 lanes
+// of 2 or 4 vectors leave up to half of themselves idle, and few registers per lane leave room for many waves.  Same order of additions, same
+// result.  What bounds it is memory, and for few tokens the chain position, row, output.  Where it is used and what it gives stands at combine_units.
+template <bool BF16, int K, bool WAVE, bool NTL, bool NTS, bool KEEP, bool NTK>
+__device__ __forceinline__ void combine_units_t(const u32x4 *__restrict__ y, const float *__restrict__ gates, u32x4 *__restrict__ out,
+                                                const int32_t *__restrict__ pos_table, const Shape &s, u32x4 *__restrict__ keep,
+                                                const int32_t *__restrict__ keep_table)
+{
+    constexpr int NF = BF16 ? 8 : 4;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int vpr = s.vpr, k = s.k, lpr = WAVE ? kWave : s.lpr;
+    const int gbase = WAVE ? 0 : lane & ~(lpr - 1), gl = lane - gbase;
+    const uint32_t parts = WAVE ? (uint32_t)((vpr + kWave - 1) / kWave) : 1u;
+    const int per = WAVE ? 1 : kWave / lpr;                        // tokens of a wave
+    const int64_t units = WAVE ? (int64_t)s.T * parts : (s.T + per - 1) / per;
+    for (int64_t unit = (int64_t)blockIdx.x * (kMoverThreads / kWave) + wave; unit < units; unit += (int64_t)gridDim.x * (kMoverThreads / kWave)) {
+        const int i = !WAVE ? (int)unit * per + (lane / lpr) : units >> 32 ? (int)(unit / parts) : (int)((uint32_t)unit / parts);
+        const int v = (WAVE ? (int)(unit - (int64_t)i * parts) * kWave : 0) + gl, t = s.T - 1 - i;
+        const bool have = t >= 0, in = have && v < vpr;
+        int my_pos = -1, my_keep = -1;
+        float my_g = 0.f;
+        if (have && gl < k) {
+            my_pos = pos_table[(size_t)t * k + gl];
+            my_g = gates[(size_t)t * k + gl];
+            if (KEEP) my_keep = keep_table[(size_t)t * k + gl];
+        }
+        const unsigned int kmask = k >= 32 ? 0xffffffffu : ((1u << k) - 1u);
+        unsigned int kept = (unsigned int)(__ballot((unsigned)my_pos < (unsigned)s.max_rows) >> gbase) & kmask;
+        if (WAVE) kept = (unsigned int)__builtin_amdgcn_readfirstlane((int)kept);
+        auto of = [&](int x, int j) { return WAVE ? __builtin_amdgcn_readlane(x, j) : __shfl(x, gbase + j, kWave); };
+        double acc[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[f] = 0.0;
+        for (int j0 = 0; j0 < k; j0 += K) {
+            u32x4 val[K];
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                const int pf = of(my_pos, j0 + q < k ? j0 + q : 0);
+                if ((kept >> (j0 + q) & 1u) && j0 + q < k && in) val[q] = ld16<NTL>(y + (size_t)pf * vpr + v);
+            }
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                const int j = j0 + q < k ? j0 + q : 0;
+                const double g = (double)__int_as_float(of(__float_as_int(my_g), j));
+                const int pk = KEEP ? of(my_keep, j) : -1;
+                if ((kept >> (j0 + q) & 1u) && j0 + q < k) {
+                    if (KEEP && in && (unsigned)pk < (unsigned)s.max_rows) st16<NTK>(keep + (size_t)pk * vpr + v, val[q]);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        if (BF16) {
+                            acc[2 * c] = __builtin_fma(g, bf16_lo(val[q][c]), acc[2 * c]);
+                            acc[2 * c + 1] = __builtin_fma(g, bf16_hi(val[q][c]), acc[2 * c + 1]);
+                        } else {
+                            acc[c] = __builtin_fma(g, (double)__uint_as_float(val[q][c]), acc[c]);
+                        }
+                    }
+                }
+            }
+        }
+        u32x4 o;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (BF16) o[c] = f64_to_bf16_rne(acc[2 * c]) | (f64_to_bf16_rne(acc[2 * c + 1]) << 16);
+            else o[c] = __float_as_uint((float)acc[c]);
+        }
+        if (in) st16<NTS>(out + (size_t)t * vpr + v, o);
+    }
+}
+
+template <bool BF16, int K, bool WAVE>
+__global__ __launch_bounds__(kMoverThreads) void combine_units_kernel(const u32x4 *__restrict__ y, const float *__restrict__ gates,
+                                                                      u32x4 *__restrict__ out, PlanPtrs p, Shape s)
+{
+    with_policy(s.cache & NT_COMB_LD, s.cache & NT_COMB_ST, [&](auto l, auto st) {
+        combine_units_t<BF16, K, WAVE, decltype(l)::value, decltype(st)::value, false, false>(y, gates, out, p.pos_final, s, nullptr, nullptr);
+    });
+}
+
 template <bool BF16, int NV>
 __global__ __launch_bounds__(kMoverThreads) void combine_pf_kernel(const u32x4 *__restrict__ y,
                                                                    const float *__restrict__ gates,
@@ -1956,6 +2035,17 @@ __global__ __launch_bounds__(kMoverThreads) void return_kernel(const u32x4 *__re
         else
             combine_rows_t<BF16, NV, NTL, NTS, true, NTK>(y, gates, out, p.pos_final, s, 0, s.T, blockIdx.x, gridDim.x,
                                                           y_stage, p.pos_stage);
+    });
+}
+
+template <bool BF16, int K, bool WAVE>
+__global__ __launch_bounds__(kMoverThreads) void return_units_kernel(const u32x4 *__restrict__ y, u32x4 *__restrict__ y_stage,
+                                                                     const float *__restrict__ gates, u32x4 *__restrict__ out, PlanPtrs p,
+                                                                     Shape s)
+{
+    with_policy3(s.cache & NT_REG_LD, s.cache & NT_COMB_ST, s.cache & NT_REG_ST, [&](auto l, auto st, auto kp) {
+        combine_units_t<BF16, K, WAVE, decltype(l)::value, decltype(st)::value, true, decltype(kp)::value>(y, gates, out, p.pos_final, s, y_stage,
+                                                                                                          p.pos_stage);
     });
 }
 
