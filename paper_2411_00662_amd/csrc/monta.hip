@@ -601,6 +601,9 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, ExpertArg
     // 164; but 32 experts, 4096 x 4096, where the ragged tile runs beside it, 391 and 433, and 1024 x 1024, whose walk is short,
     // 84 and 85).
     const bool deep_w = rows_per_expert <= kBigBM || (ragged_last && a.H >= 4096 && rows_per_expert <= kBigBM * 3 / 2);
+    // Spread starts (walk_start), by expert, with the third stage of weights: us, in step and spread, 64 experts of 4096 x 2048, 120 rows 263 and
+    // 212, 190 rows 285 and 238; 128 of 2048 x 2048, 190 rows 308 and 259; 256 of 2048 x 1024, 70 rows 264 and 221.
+    a.spread = (int64_t)a.H * 2 % 4096 == 0;
     if (ragged_last) return deep_w ? launch_expert_big_t<true, true>(x_final, w_exp, y, a, grid_last, st)
                                    : launch_expert_big_t<true, false>(x_final, w_exp, y, a, grid_last, st);
     return deep_w ? launch_expert_big_t<false, true>(x_final, w_exp, y, a, grid, st)

@@ -3254,7 +3254,6 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const ExpertTileHit hit = RAGGED_LAST ? find_expert_tile<BM, true>(a, nct, L, lane, &whole)
                                           : find_expert_tile<BM, false>(a, nct, L, lane);
     constexpr int WST = DEEP_W ? 3 : 2;                            // stages of w
-    constexpr int kWaitStage = DEEP_W ? 0x0078 : 0x0072, kWaitFirst = DEEP_W ? 0x4f78 : 0x4f70;       // vmcnt(24), vmcnt(16)
     int e = hit.e, row0 = 0, row_end = 0, ct = 0;
     int sharers = 1, share = 0;                                    // row tiles side by side on one weight tile; which of them
     int alone = 0;                                                 // 1: the tile holds all rows of its expert
@@ -3330,6 +3329,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const bool stream = kMayStream && (int64_t)e * a.N + col0 >= a.stream_from && __builtin_amdgcn_readfirstlane(alone);
     const uint32_t rowb = (uint32_t)cpr * 16;
     const int wr = min(a.N - col0, cols);
+    const int start = DEEP_W && !TAIL && a.spread ? walk_start(e, nsteps) : 0;
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= kShortRows) {                                        // tiles with little arithmetic
@@ -3340,18 +3340,17 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         return;
     }
 
-    // A step's tile is 32 + 32 chunks of 8 rows (1 KiB); this wave fetches chunks 8 wave .. 8 wave + 7 of x and of w.
+    // A step's tile is chunks of 8 rows (1 KiB), 32 of w and, as far as there are rows, of x; a wave fetches 8 neighbouring chunks of w and
+    // an equal share of those of x.
     const int lr = lane >> 3;
-    uint32_t off2[2];                                             // chunks 16 rows apart have the same swizzle
+    auto first_offset = [&](int chunk) { return (uint32_t)(chunk * 8 + lr) * rowb + (((lane & 7) ^ ((chunk * 4 + (lr >> 1)) & 7)) * 16); };
+    uint32_t off_w[2], off_x[2];                                  // chunks 16 rows apart have the same swizzle
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int trow = (wave * 8 + q) * 8 + lr;
-        off2[q] = (uint32_t)trow * rowb + (((lane & 7) ^ ((trow >> 1) & 7)) * 16);
-    }
-    auto off = [&](int q) {
+    for (int q = 0; q < 2; ++q) off_w[q] = first_offset(wave * 8 + q);
+    auto off = [&](const uint32_t(&first)[2], int q) {
         uint32_t rows = (uint32_t)(q >> 1) * (16 * rowb);
         asm volatile("" : "+s"(rows));                             // added at each use: eight offsets kept would be spilled
-        return off2[q & 1] + rows;
+        return first[q & 1] + rows;
     };
     // Before the first loads of step `step`, at whatever is the last step: the lane offsets of the pieces past the end of a row go
     // out of range, for good (what is loaded after them is the last step again, into buffers that are not read any more).
@@ -3362,51 +3361,34 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
             asm volatile("" : "+v"(l));                            // found again each time: kept, the pieces would be spilled
 #pragma unroll
             for (int q = 0; q < 2; ++q)                            // rows 8 apart: pieces 4 apart, the wave's 64 rows make no difference
-                off2[q] |= ((l & 7) ^ ((4 * q + (l >> 4)) & 7)) >= left ? kOutOfRange : 0u;
+                off_w[q] |= ((l & 7) ^ ((4 * q + (l >> 4)) & 7)) >= left ? kOutOfRange : 0u;
         }
     };
     unsigned char *const w_lds = big_lds + 2 * kBigXBytes;
-    auto issue_x = [&](int q, int step, int at) {                 // `at`: byte offset of the stage among those of x, of w
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(big_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, 0);
+    auto issue_w = [&](int q, uint32_t so, int at) {              // `at`: byte offset of the stage among those of w (of x)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(off_w, q), so, 0, 0);
     };
-    auto issue_w = [&](int q, int step, int at) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, 0);
-    };
-    auto stream_w = [&](int q, int step, int at) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(q), step * 128, 0, kStreamLoad);
+    auto stream_w = [&](int q, uint32_t so, int at) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(w_lds + at + (wave * 8 + q) * 1024), 16, off(off_w, q), so, 0, kStreamLoad);
     };
 
     // the early touches (not with the third stage of w)
     const uint32_t touch_w = lane * sharers / 64 == share ? (uint32_t)(wave * 64 + lane) * rowb : kOutOfRange;
     const uint32_t touch_x = lane < 16 ? (uint32_t)((ct & 3) * 64 + wave * 16 + lane) * rowb : kOutOfRange;
-    auto touch = [&](int step) {
-        if constexpr (!DEEP_W) {
-            const int so = min(step, nsteps - 1) * 128;
-            lds_void *sink = (lds_void *)(w_lds + 2 * kBigWBytes + wave * 512);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sink, 4, touch_w, so, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, sink, 4, touch_x, so, 0, 0);
-        }
-    };
 
     // The waves form a 2 x 2 grid.  In a ragged tile the rows are split evenly between the two row halves: nb 16-row
-    // blocks each.
+    // blocks each, at least 4.  The loop is compiled for each count: only rows in use are requested, read and multiplied, all spread evenly
+    // under the MFMAs (64 experts of 7168 x 2048, 160 and 224 rows: 384 and 548 us with one loop for all counts, 376 and 534).
     const int m = lane & 15, g = lane >> 4, wm = wave >> 1, wn = wave & 1;
-    const int nb = (xr + 31) / 32;
-    const int wrow = wm * nb * 16;
+    const int nb = max((xr + 31) / 32, 4);
     f32x4 acc[8][8];                                               // [16-row block of x][16 output features]
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int n = 0; n < 8; ++n) acc[i][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const unsigned char *px = big_lds + (wrow + m) * 128, *pw = w_lds + (wn * 128 + m) * 128;
+    const unsigned char *pw = w_lds + (wn * 128 + m) * 128;
     const int k0 = (g ^ ((m >> 1) & 7)) * 16, k1 = ((4 + g) ^ ((m >> 1) & 7)) * 16;      // this lane's piece, slice 0 and 1
     bf16x8 fx[2][8], fw[2][8];
-    auto read_w = [&](int set, int i, int at, int ko) {
-        fw[set][i] = *reinterpret_cast<const bf16x8 *>(pw + at + ko + i * 2048);
-    };
-    auto read_x = [&](int set, int i, int at, int ko) {
-        fx[set][i] = *reinterpret_cast<const bf16x8 *>(px + at + ko + i * 2048);
-    };
     // no instruction near it reads the accumulator: the next MFMA on the same one is a whole slice away, and the epilogue
     // waits first
     auto mma = [&](int set, int i, int n) {
@@ -3417,96 +3399,110 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // One slice: 64 MFMAs on fragment set `set`; between them the 16 reads of the other set (stages at xat and wat, piece
-    // offset ko) and, if LOADS, the 8 loads of x for step sx and then the 8 of w for step sw, into the stages at xto and wto.
-    auto slice = [&](auto load_w, int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
+    // All steps of a tile of NB row blocks per half
+    auto run = [&](auto nbc, auto load_w) {
+        constexpr int NB = decltype(nbc)::value;
+        constexpr int XL = TAIL ? 8 : NB;                          // loads of x per wave and step (TAIL: of all 256 rows, one trim for both)
+        constexpr int kYoungerStage = DEEP_W ? 8 : 2, kYoungerFirst = XL + 8 + (DEEP_W ? 8 : 0);
+        constexpr int kWaitStage = 0x0070 | kYoungerStage, kWaitFirst = 0x0f70 | (kYoungerFirst & 15) | (kYoungerFirst >> 4 << 14);
+        const unsigned char *px = big_lds + (wm * NB * 16 + m) * 128;
+        if constexpr (XL < 8) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            if (q < 8) read_w(set ^ 1, q, wat, ko);
-            else read_x(set ^ 1, q - 8, xat, ko);
-            mma(set, q / 2, (q & 1) * 4 + 0);
-            mma(set, q / 2, (q & 1) * 4 + 1);
-            if (loads) {
-                if (q == 0 && !DEEP_W) trim(sx);
-                if (q == 8 && DEEP_W) trim(sw);
-                if (q < 8) issue_x(q, sx, xto);
-                else load_w(q - 8, sw, wto);
-            }
-            mma(set, q / 2, (q & 1) * 4 + 2);
-            mma(set, q / 2, (q & 1) * 4 + 3);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int q = 0; q < 2; ++q) off_x[q] = first_offset(wave * XL + q);
         }
-    };
-    // the same for a ragged tile: only the wave's nb blocks with rows are multiplied
-    auto slice_ragged = [&](auto load_w, int set, int xat, int wat, int ko, bool loads, int sx, int xto, int sw, int wto) {
+        auto issue_x = [&](int q, uint32_t so, int at) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(big_lds + at + (wave * XL + q) * 1024), 16, off(XL == 8 ? off_w : off_x, q), so, 0, 0);
+        };
+        auto touch = [&](uint32_t so) {
+            if constexpr (!DEEP_W) {
+                lds_void *sink = (lds_void *)(w_lds + 2 * kBigWBytes + wave * 512);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, sink, 4, touch_w, so, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, sink, 4, touch_x, so, 0, 0);
+            }
+        };
+        auto read = [&](int set, int r, int xat, int wat, int ko) {
+            if (r < 8) fw[set][r] = *reinterpret_cast<const bf16x8 *>(pw + wat + ko + r * 2048);
+            else fx[set][r - 8] = *reinterpret_cast<const bf16x8 *>(px + xat + ko + (r - 8) * 2048);
+        };
+        // One slice: 8 NB MFMAs on fragment set `set`; spread between them the 8 + NB reads of the other set (stages at xat and wat, piece
+        // offset ko) and, if LOADS, the loads of x at column `xso` and then the 8 of w at `wso`, into the stages at xto and wto.
+        auto slice = [&](int set, int xat, int wat, int ko, bool loads, uint32_t xso, int xto, uint32_t wso, int wto, int trim_x, int trim_w) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            read_w(set ^ 1, i, wat, ko);
-            read_x(set ^ 1, i, xat, ko);
-            if (loads) {
-                if (i == 0 && !DEEP_W) trim(sx);
-                if (i == 4 && DEEP_W) trim(sw);
-                if (i < 4) {
-                    issue_x(2 * i, sx, xto);
-                    issue_x(2 * i + 1, sx, xto);
-                } else {
-                    load_w(2 * i - 8, sw, wto);
-                    load_w(2 * i - 7, sw, wto);
+            for (int q = 0; q < 2 * NB; ++q) {
+#pragma unroll
+                for (int r = q * (8 + NB) / (2 * NB); r < (q + 1) * (8 + NB) / (2 * NB); ++r) read(set ^ 1, r, xat, wat, ko);
+                mma(set, q / 2, (q & 1) * 4 + 0);
+                mma(set, q / 2, (q & 1) * 4 + 1);
+                if (loads) {
+#pragma unroll
+                    for (int l = q * (XL + 8) / (2 * NB); l < (q + 1) * (XL + 8) / (2 * NB); ++l) {
+                        if (l == 0 && !DEEP_W) trim(trim_x);
+                        if (l == XL && DEEP_W) trim(trim_w);
+                        if (l < XL) issue_x(l, xso, xto);
+                        else load_w(l - XL, wso, wto);
+                    }
                 }
+                mma(set, q / 2, (q & 1) * 4 + 2);
+                mma(set, q / 2, (q & 1) * 4 + 3);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            if (i < nb) {
+        };
+        // the columns of the steps that are requested next: from `start` round, past the end the last one again
+        const uint32_t turn = (uint32_t)nsteps * 128u;
+        auto column = [&](int step) {
+            const uint32_t at = (uint32_t)(min(step, nsteps - 1) + start) * 128u;
+            if constexpr (!DEEP_W || TAIL) return at;
+            return at >= turn ? at - turn : at;
+        };
+        trim(0);
 #pragma unroll
-                for (int n = 0; n < 8; ++n) mma(set, i, n);
-            }
+        for (int q = 0; q < XL + 8; ++q) {                        // x and w in turn, then the rest of w
+            if (q < 2 * XL && !(q & 1)) issue_x(q / 2, column(0), 0);
+            else load_w(q < 2 * XL ? q / 2 : q - XL, column(0), 0);
         }
-    };
-    auto run = [&](auto slice_fn, auto load_w) {
+        trim(1);
+#pragma unroll
+        for (int q = 0; q < XL + 8; ++q) {
+            if (q < 2 * XL && !(q & 1)) issue_x(q / 2, column(1), kBigXBytes);
+            else load_w(q < 2 * XL ? q / 2 : q - XL, column(1), kBigWBytes);
+        }
+        if constexpr (DEEP_W) {
+            trim(2);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) load_w(q, column(2), 2 * kBigWBytes);
+        }
+        __builtin_amdgcn_s_waitcnt(kWaitFirst);                    // stage 0
+        touch(column(2));
+        barrier();
+#pragma unroll
+        for (int r = 0; r < 8 + NB; ++r) read(0, r, 0, 0, k0);
         int xat = 0, wat = 0;                                      // where stage s is
         for (int s = 0; s < nsteps; ++s) {
-            slice_fn(load_w, 0, xat, wat, k1, false, 0, 0, 0, 0);
-            // lgkmcnt(0): this wave has read all of stage s; vmcnt(8 or 2): stage s+1 is in LDS, younger are only the 8 loads
-            // of w for stage s+2, or the two early touches
+            slice(0, xat, wat, k1, false, 0, 0, 0, 0, 0, 0);
+            // lgkmcnt(0): this wave has read all of stage s; vmcnt: stage s+1 is in LDS, younger are only the 8 loads of w for stage
+            // s+2 or the early touches
             __builtin_amdgcn_s_waitcnt(kWaitStage);
             barrier();
             // past the end the last stage is fetched again, into buffers that are not read any more
             const int wnext = wat == (WST - 1) * kBigWBytes ? 0 : wat + kBigWBytes;
-            slice_fn(load_w, 1, xat ^ kBigXBytes, wnext, k0, true, min(s + 2, nsteps - 1), xat, min(s + WST, nsteps - 1), wat);
-            touch(s + 3);
+            slice(1, xat ^ kBigXBytes, wnext, k0, true, column(s + 2), xat, column(s + WST), wat, min(s + 2, nsteps - 1), min(s + WST, nsteps - 1));
+            touch(column(s + 3));
             xat ^= kBigXBytes;
             wat = wnext;
         }
     };
-    trim(0);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) q & 1 ? issue_w(q / 2, 0, 0) : issue_x(q / 2, 0, 0);
-    trim(1);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) q & 1 ? issue_w(q / 2, min(1, nsteps - 1), kBigWBytes) : issue_x(q / 2, min(1, nsteps - 1), kBigXBytes);
-    if constexpr (DEEP_W) {
-        trim(2);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) issue_w(q, min(2, nsteps - 1), 2 * kBigWBytes);
-    }
-    __builtin_amdgcn_s_waitcnt(kWaitFirst);                        // stage 0
-    touch(2);
-    barrier();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        read_w(0, i, 0, k0);
-        read_x(0, i, 0, k0);
-    }
+    auto run_nb = [&](auto load_w) {
+        if (nb == 8) run(std::integral_constant<int, 8>{}, load_w);
+        else if (nb == 7) run(std::integral_constant<int, 7>{}, load_w);
+        else if (nb == 6) run(std::integral_constant<int, 6>{}, load_w);
+        else if (nb == 5) run(std::integral_constant<int, 5>{}, load_w);
+        else run(std::integral_constant<int, 4>{}, load_w);
+    };
     if constexpr (kMayStream) {
-        if (stream) {
-            if (nb == 8) run(slice, stream_w);
-            else run(slice_ragged, stream_w);
-        } else {
-            if (nb == 8) run(slice, issue_w);
-            else run(slice_ragged, issue_w);
-        }
+        if (stream) run_nb(stream_w);
+        else run_nb(issue_w);
     } else {
-        if (nb == 8) run(slice, issue_w);
-        else run(slice_ragged, issue_w);
+        run_nb(issue_w);
     }
     asm volatile("s_nop 15\n\ts_nop 15");                          // the last MFMAs' results
     __builtin_amdgcn_sched_barrier(0);
@@ -3516,7 +3512,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const int l2 = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int r = row0 + wrow + i * 16 + (l2 & 15);
+        const int r = row0 + (wm * nb + i) * 16 + (l2 & 15);
         if (i < nb && r < row_end) {
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
