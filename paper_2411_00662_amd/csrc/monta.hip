@@ -666,6 +666,9 @@ int launch_expert_split(const void *x_final, const void *w_exp, void *y, const E
 //    per CU (fp32, 8 of 8192 x 136: four waves 18.7, eight 14.1);
 //  - 16 x 32, then 32 x 32, up to one tile per CU, where rows are more: 3 of 6176 x 336, 83 rows 21.9, 14.6, 12.5, 15.2; 4 of 8192 x 688,
 //    47 rows 28.5, 19.7, 19.7, 14.5; but 2 of 5120 x 1984, 130 rows, 564 tiles of 32 x 32 25.1, 35.6, 31.5, 29.9;
+//  - fp32, whose MFMAs take four times as long, in 16 x 32 to about three tiles of 32 x 32 per CU if rows are more than one such tile (us in 32
+//    x 64, 16 x 32: 8 of 1224 x 688, 81 rows 26.0, 21.7; 2 of 4096 x 2840, 125 rows 78, 71; 32 of 4096 x 320, 47 rows 79, 71; but 4 of 1348 x
+//    484, 546 rows, 1124 tiles 39, 48, and 8 of 2172 x 1380, 20 rows 29, 39);
 //  - not on short walks (4 of 208 x 232, 467 rows 4.2, 9.0, 6.9, 6.7), up to 23 steps only where the tiles are fewest (32 of 1024 x 112,
 //    4 rows, 168 tiles 5.9, 3.9; 2 of 512 x 4752, 3 rows, 408 tiles 5.2, 5.0, 4.8, 6.9, in blocks of 8 4.5).
 template <bool F32>
@@ -677,7 +680,7 @@ int launch_expert_few(const void *x_final, const void *w_exp, void *y, const Exp
     if (steps < 8 || (steps < 24 && small > 256)) return 1;
     if (steps >= 128 && small <= 128) return launch_expert_split<1, 1, 8, 4, F32>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 32 && small <= 400) return launch_expert_split<1, 1, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
-    if (tiles(16, 32) <= 256) return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if (tiles(16, 32) <= 256 || (F32 && r > 40 && tiles(32, 32) <= 800)) return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     if (tiles(32, 32) <= 256) return launch_expert_split<2, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     return 1;
 }
@@ -710,11 +713,11 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
 // So a tile is taken where most experts fit one of its rows' tiles, or where its tiles number at most 2.5 per CU; on short rows,
 // where a large tile's first loads and its stores weigh most, at most 5 per CU (64 experts, 1024 x 1024, r = 96: 45, 35, 38, 48;
 // 128 experts, 512 x 512, r = 96: 33, 24, 37, 33).  The register-staged tile, which has no such rule of its own, is taken
-//  - on rows of 4096 elements and more where each of at most 64 experts fits one row of its tiles and these come in nearly full
-//    rounds of two per CU (64 experts, 4096 x 4096, r = 48: 471, 415, 432, 369   80: 621, 480, 475, 379; 32 experts 80: 312, 246,
-//    250, 188; 64 experts, 4096 x 1536, three quarters of a round, 80: 241, 192, 211, 174; but 5120 x 1536, 40: 241, 177, 207, 210).  With
-//    more experts a skewed load leaves many without rows, and there it is the worst form (256 experts, 4096 x 512, r = 64: even
-//    293, 251, 257, 208; skewed 117, 106, 115, 159);
+//  - on rows of 4096 to 5120 elements where at most 64 experts have 57 to 76 rows in the mean, some more than 64 and some less, and its
+//    tiles come in nearly full rounds of two per CU (register-staged and the large tile with its short ragged ones: 64 experts of 4096 x
+//    2048, r = 64: 193, 209   80: 196, 196   100: 235, 203; 5120 x 2048, 64: 251, 238; 7168 x 2048, 64: 345, 319   100: 423, 340; in 64 x
+//    128 tiles 4096 x 2048, 40: 187, 177).  With more experts a skewed load leaves many without rows, and there it is the worst form
+//    (256 experts, 4096 x 512, r = 64: even 293, 251, 257, 208; skewed 117, 106, 115, 159);
 //  - on rows of at most 512 (128 experts, 512 x 512, r = 192: 56, 39, 43, 29; 256 experts: 120, 74, 57, 55, skewed 60, 35, 40, 32);
 //  - on rows that are not whole steps, whose lines the large tile fetches twice, where an expert's second large tile would be
 //    half empty (16 experts, 8184 x 2048, r = 300: 614, 378, 363, 326; 64 experts, 3000 x 1024: 472, 279, 285, 265; r = 1000: 1537,
@@ -734,7 +737,7 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
     auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
     constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kRound = 512, kOddShortRow = 448, kOddNarrowRow = 1104;
     const int64_t one_row = active * ((a.N + 255) / 256), rounds = (one_row + kRound - 1) / kRound;
-    const bool full_rounds = one_row * 10 >= rounds * kRound * (r < 64 ? 9 : 7);
+    const bool full_rounds = one_row * 10 >= rounds * kRound * 9;
     if (const int rc = launch_expert_few<false>(x_final, w_exp, y, a, rows_bound, active, r, st); rc <= 0) return rc;
     if (a.H % 64 && a.H <= kOddShortRow) {
         if (tiles(32, 64) <= (r <= 16 ? kFewTilesShortRows : kFewTiles)) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
@@ -743,7 +746,7 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
         return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     }
     if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
-    if (a.H >= 4096 && a.E <= 64 && r <= 100 && full_rounds) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
+    if (a.H >= 4096 && a.H < 5120 && a.E <= 64 && r > 56 && r <= 76 && full_rounds) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 56 || tiles(64, 128) <= (a.H <= 1024 ? kFewTilesShortRows : kFewTiles))
         return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, r, st);
     if (a.H <= 512 && a.E <= 128 && r <= 384) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);

@@ -81,6 +81,17 @@ def test_long_rows_full_rounds(m):
     check_on_gpu(m, [40, 1, 0, 100, 33, 64, 65, 17], 4096, 57 * 256 + 8, BF16)
 
 
+# the register-staged tiles on long rows: 57 to 76 rows in the mean, tiles in full rounds; and fp32 in 16 x 32 tiles up to three per CU
+@pytest.mark.parametrize("H", [4096, 4104])
+def test_long_rows_staged(m, H):
+    check_on_gpu(m, [70, 64, 65, 100, 33, 129, 40, 60], H, 63 * 256 + 8, BF16)
+
+
+@pytest.mark.parametrize("H", [800, 1300])
+def test_fp32_many_split_tiles(m, H):
+    check_on_gpu(m, [50, 1, 130, 64, 0, 47, 33, 80], H, 1028, FP32)
+
+
 # weights of 128 MiB, which are not streamed, and of 256 MiB and more, all but 96 MiB of which are where an expert's rows fit one tile
 # and not where they take two: the line lies inside an expert, on a column tile's edge or beside it
 @pytest.mark.parametrize("sizes,H,N,dtype", [
