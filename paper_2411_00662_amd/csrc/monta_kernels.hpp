@@ -488,7 +488,7 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
         p.local_rank[(size_t)t_begin * k + idx] = r;    // rank inside the workgroup; the positions kernels finish it
     }
 
-    if (b == 0 && tid == 0) p.meta[META_ALIVE] = 0;   // counted by the kernel that finishes the positions
+    if (b == 0 && tid == 0) p.meta[META_ALIVE] = s.T;  // the kernel that finishes the positions takes the tokens without a kept pair off
 }
 
 // Exclusive scans of the route workgroups' histograms, per expert, in workgroup (= token) order, for tables that are too
@@ -554,8 +554,10 @@ struct BlockPlan {
     int kpre[256];     // exclusive scan of the kept counts (= off when the layout is compact)
     int stage[256];    // stage_off[u][e]: first STAGE row of block (u, e)
     int alive[256];    // per token of the workgroup: has a kept pair (plan_positions_block)
+    int sums[256 / kWave][3];      // of each wave's experts: kept counts, the unit's rows, the rows of the units before
     int R, unit_row0;
 };
+static_assert(kMoverThreads == 256, "block_plan: four waves scan 256 experts");
 
 // One lane's share of the histogram-table reduction of block_plan: the counters of expert e in blocks bl, bl + bstep,
 // ..., LD loads requested before any is added up.
@@ -647,37 +649,42 @@ __device__ __forceinline__ void block_plan(BlockPlan &bp, int b, const PlanPtrs 
         }
     }
     __syncthreads();
-    if (wave == 0) {
-        int carry_off = 0, carry_stage = 0;
-        int base_u = 0;     // sum over experts of min(P[u][e], C): first STAGE row of the unit
-        for (int e0 = 0; e0 < E; e0 += kWave) {
-            const int e = e0 + lane;
-            const int v = e < E ? (bp.before[e] < C ? bp.before[e] : C) : 0;
-            const int incl = wave_inclusive_scan(v);
-            base_u += wave_total(incl);
+    // A wave scans 64 experts, the sums of the others' experts come through LDS: all four scan at a time (one after the other, by one
+    // wave, 256 experts took eight scans in a row).
+    const int e = wave * kWave + lane;
+    int kp = 0, nu = 0, lo = 0, incl_off = 0, incl_st = 0;
+    if (wave < 256 / kWave) {
+        if (e < E) {
+            kp = min(bp.total[e], C);
+            lo = min(bp.before[e], C);
+            nu = min(bp.before[e] + bp.unit[e], C) - lo;
         }
-        for (int e0 = 0; e0 < E; e0 += kWave) {
-            const int e = e0 + lane;
-            int kp = 0, nu = 0;
-            if (e < E) {
-                const int cnt = bp.total[e];
-                kp = cnt < C ? cnt : C;
-                const int lo = bp.before[e] < C ? bp.before[e] : C;
-                const int nxt = bp.before[e] + bp.unit[e];
-                nu = (nxt < C ? nxt : C) - lo;
-            }
-            const int incl_off = wave_inclusive_scan(kp);
-            const int incl_st = wave_inclusive_scan(nu);
-            if (e < E) {
-                bp.kpre[e] = carry_off + incl_off - kp;
-                bp.off[e] = s.padded ? e * C : carry_off + incl_off - kp;
-                bp.stage[e] = base_u + carry_stage + incl_st - nu;
-            }
-            carry_off += wave_total(incl_off);
-            carry_stage += wave_total(incl_st);
+        incl_off = wave_inclusive_scan(kp);
+        incl_st = wave_inclusive_scan(nu);
+        const int incl_lo = wave_inclusive_scan(lo);
+        if (lane == kWave - 1) {
+            bp.sums[wave][0] = incl_off;
+            bp.sums[wave][1] = incl_st;
+            bp.sums[wave][2] = incl_lo;
         }
-        if (lane == 0) {
-            bp.R = carry_off;
+    }
+    __syncthreads();
+    if (wave < 256 / kWave) {
+        int before_off = 0, before_st = 0, base_u = 0, R = 0;     // base_u: sum over experts of min(P[u][e], C), first STAGE row of the unit
+#pragma unroll
+        for (int w = 0; w < 256 / kWave; ++w) {
+            before_off += w < wave ? bp.sums[w][0] : 0;
+            before_st += w < wave ? bp.sums[w][1] : 0;
+            R += bp.sums[w][0];
+            base_u += bp.sums[w][2];
+        }
+        if (e < E) {
+            bp.kpre[e] = before_off + incl_off - kp;
+            bp.off[e] = s.padded ? e * C : before_off + incl_off - kp;
+            bp.stage[e] = base_u + before_st + incl_st - nu;
+        }
+        if (threadIdx.x == 0) {
+            bp.R = R;
             bp.unit_row0 = base_u;
         }
     }
@@ -791,17 +798,19 @@ __device__ __forceinline__ void plan_positions_block(BlockPlan &bp, int b, const
         if (idx < npairs) place(idx, e_pre[q], r_pre[q]);
     }
     for (int idx = tid + PRE * nthr; idx < npairs; idx += nthr) place(idx, topk_idx[pair0 + idx], p.local_rank[pair0 + idx]);
+    // The tokens without a kept pair are taken off the shared counter, which holds all of them: an addition per workgroup makes a queue at
+    // the memory, 10 ns each (32768 tokens in 512 workgroups: 28.2 us for routing and plan, none 22.9), and most have nothing to take.
+    if (C >= s.T) return;
     __syncthreads();
-    // tokens with a kept pair: one addition to the shared counter per workgroup (one per wave makes a queue at the L2)
     int mine = 0;
-    for (int i = tid; i < nt; i += nthr) mine += bp.alive[i];
-    if (tid < kWave) bp.total[tid] = 0;                          // the plan's sums are no longer needed
+    for (int i = tid; i < nt; i += nthr) mine += bp.alive[i] ? 0 : 1;
+    mine = wave_total(wave_inclusive_scan(mine));
+    if (lane == 0) bp.sums[tid >> 6][0] = mine;                  // the plan's sums are no longer needed
     __syncthreads();
-    if (mine) atomicAdd(&bp.total[lane], mine);
-    __syncthreads();
-    if (tid < kWave) {
-        const int sum = wave_total(wave_inclusive_scan(bp.total[lane]));
-        if (lane == 0 && sum) atomicAdd(&p.meta[META_ALIVE], sum);
+    if (tid == 0) {
+        int dead = 0;
+        for (int w = 0; w < nthr / kWave; ++w) dead += bp.sums[w][0];
+        if (dead) atomicSub(&p.meta[META_ALIVE], dead);
     }
 }
 
