@@ -548,6 +548,38 @@ int launch_gate_split(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     return MONTA_OK;
 }
 
+template <int XB, int CB, int W, int NST>
+int launch_gate_ring(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
+{
+    using G = SplitTile<XB, CB, W, NST>;
+    static LdsOptIn lds_opt_in;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_ring_kernel<XB, CB, W, NST>), G::kLdsBytes, lds_opt_in)) return rc;
+    const int64_t grid = (T + 16 * XB - 1) / (16 * XB) * ((E + 16 * CB - 1) / (16 * CB));
+    if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((gate_ring_kernel<XB, CB, W, NST>), dim3((unsigned)grid), dim3(G::kThreads), G::kLdsBytes, st, x, w, logits, T, H / 8, E);
+    return MONTA_OK;
+}
+
+// bf16, few tiles: with the hidden axis split (gate_ring_kernel), 1 if they are not few.  About one tile per CU: 16 x 16, 16 x 32, 32 x 32 and,
+// on rows of 2048 elements and more, 32 x 64, whichever is the first to be few enough; eight waves for the longest rows and half a tile per
+// CU.  Measured on MI355X, three sets in turn, us, the forms before (split tiles straight into registers, 32 x 64 tiles, whole rows for up to 8
+// experts) and these: 1 x 5264, 128 experts 6.8 and 5.2; 64 x 7168, 256 experts 15.8 and 6.9; 376 x 4096, 256 experts 14.2 and 6.9;
+// 4559 x 5120, 16 experts 23.0 and 10.3; 1513 x 2048, 256 experts 10.8 and 9.5; 8192 x 4096, 8 experts 13.1 and 12.1; 2000 x 8192, 8 experts 10.4 and
+// 7.3; 1003 x 792, 256 experts, 256 tiles of 32 x 32 on 13 steps 5.6 and 5.7; 8000 x 8192, 8 experts, 125 MiB of activations 27.4 and 29.6.
+// Over 60 shapes of up to 300 tiles of 32 x 64 1.44 times as fast.  Error against 64 bits nowhere larger (at split_tile).
+int launch_gate_few(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
+{
+    auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
+    const int64_t steps = ((int64_t)H * 2 + 127) / 128, small = tiles(16, 16);
+    if (H > kBigMaxHidden || steps < 8 || T * H * 2 > (96ll << 20)) return 1;
+    if (steps >= 128 && small <= 128) return launch_gate_ring<1, 1, 8, 4>(x, w, logits, T, H, E, st);
+    if (small <= 200) return launch_gate_ring<1, 1, 4, 3>(x, w, logits, T, H, E, st);
+    if (tiles(16, 32) <= 256) return launch_gate_ring<1, 2, 4, 3>(x, w, logits, T, H, E, st);
+    if (tiles(32, 32) <= (steps >= 16 ? 256 : 160)) return launch_gate_ring<2, 2, 4, 3>(x, w, logits, T, H, E, st);
+    if (tiles(32, 64) <= 256 && steps >= 32) return launch_gate_ring<2, 4, 4, 3>(x, w, logits, T, H, E, st);
+    return 1;
+}
+
 int launch_gate_f32_few(const float4 *x, const float4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
 {
     const dim3 grid((unsigned)((T + 3) / 4)), block(256);
@@ -1382,6 +1414,7 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
     ProfScope ps(MONTA_K_GATE, st);
     if (cfg->dtype == MONTA_BF16) {
         // validate() guarantees H % 8 == 0 (rows are whole 16-byte vectors) and E <= 256 (at most 8 tiles).
+        //  - Few tiles: launch_gate_few.  What it leaves, up to 8 experts on whole rows: launch_gate_small_any.  The rest, as follows.
         //  - Few tiles of 16 tokens x 16 experts (or 32, where that makes them one round): the hidden axis is split, too.  More than a
         //    round of them only for up to 16 experts and rows over 2 KiB (8192 x 4096, 9 experts: 14 us, in 32 x 64 20; but 6144 x 512,
         //    16 experts: 9.2 and 5.1).  One round with 32 experts a tile, too, but not on rows that the tiles below read faster and add as
@@ -1407,7 +1440,8 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
         // several in turn, this takes 1.02 of the best tile's time.
         const int64_t tiles32 = (T + 31) / 32;
         const u32x4 *xv = static_cast<const u32x4 *>(x), *wv = static_cast<const u32x4 *>(w_gate);
-        rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
+        rc = launch_gate_few(xv, wv, logits, T, H, E, st);
+        if (rc > 0) rc = launch_gate_small_any(xv, wv, logits, T, H, E, st);
         auto tiles = [&](int64_t R, int64_t C) { return (T + R - 1) / R * ((E + C - 1) / C); };
         const int64_t tiles16 = tiles(16, 16), round = 256, n64 = tiles(32, 64), n128 = tiles(32, 128);
         const bool stream_x = T * H * 2 >= (300ll << 20);

@@ -3114,31 +3114,14 @@ struct SplitTile {
     static_assert(XB * CB * 1024 <= kRingBytes, "split tile: the waves' sums lie in the rings");
 };
 
-template <int XB, int CB, int W, int NST, bool F32>
-__global__ __launch_bounds__(64 * W) void expert_split_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w, void *__restrict__ y,
-                                                              ExpertArgs a)
+// T: unsigned short, y is rounded to bf16; float, the sums themselves are stored, rows of whole 16-byte vectors (VEC) or of any N columns.
+template <int XB, int CB, int W, int NST, bool F32, bool VEC, typename T>
+__device__ __forceinline__ void split_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr, int N, int64_t row0,
+                                           int64_t row_end, int col0, unsigned char *split_lds)
 {
     using G = SplitTile<XB, CB, W, NST>;
-    using T = std::conditional_t<F32, float, unsigned short>;
-    constexpr int XR = 16 * XB, WR = 16 * CB;
-    extern __shared__ __align__(16) unsigned char split_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), m = lane & 15, g = lane >> 4, lr = lane >> 3;
-    const int cpr = F32 ? a.H / 4 : a.H / 8, nct = (a.N + WR - 1) / WR;
-    // tile numbers in blocks of 8 per XCD: so few of them, in blocks of 32, would leave XCDs without any
-    const int64_t j = blockIdx.x / kXcds;
-    const int64_t L = (j / 8) * (8 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 8 + j % 8;
-    const ExpertTileHit hit = find_expert_tile<XR>(a, nct, L, lane);
-    const int e = __builtin_amdgcn_readfirstlane(hit.e);
-    if (e >= a.E) return;                                          // surplus workgroup
-    const int ct = __builtin_amdgcn_readfirstlane((int)(hit.L / (uint32_t)hit.tiles));
-    const int row0 = __builtin_amdgcn_readfirstlane(hit.lo + (int)(hit.L % (uint32_t)hit.tiles) * XR);
-    const int seg_end = __builtin_amdgcn_readfirstlane(hit.hi < a.max_rows ? hit.hi : a.max_rows);
-    if (row0 < 0 || row0 >= seg_end) return;
-    const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
     const uint32_t rowb = (uint32_t)cpr * 16;
-    const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb);
-    const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb);
-
     // Rows in LDS and their swizzle as in the short tiles.  Every wave issues the same loads per step, also past the end of its share
     // (out of range, at scalar offset 0: no traffic), because the wait for a stage counts the younger ones.
     const int nsteps = (cpr + 7) / 8, first = nsteps * wave / W, last = nsteps * (wave + 1) / W;
@@ -3161,7 +3144,10 @@ __global__ __launch_bounds__(64 * W) void expert_split_kernel(const u32x4 *__res
         for (int q = 0; q < 2 * XB; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(base + q * 1024), 16, o[q & 1] + (uint32_t)(q >> 1) * 16 * rowb, so, 0, 0);
     };
-    // two chains per result, by half of the step, and two levels, 8 steps at a time
+    // Two chains per result, by half of the step, and two levels, 8 steps at a time; of logits 2 or 1, whose error must not be above that of
+    // eight shares with one level (gate_split_kernel and now, against 64 bits: 1024 elements 6.9e-8, 6.9e-8, 2048 8.1e-8, 7.5e-8, 8192
+    // 1.4e-7, 9.9e-8; with 8 steps at a time 2048 9.7e-8, with 2 at 512 6.3e-8 in place of 6.1e-8).
+    const int span = !(std::is_same<T, float>::value && !VEC) ? 8 : nsteps <= 16 ? 1 : 2;
     f32x4 acc[2][XB][CB], total[XB][CB];
 #pragma unroll
     for (int i = 0; i < XB; ++i)
@@ -3170,8 +3156,8 @@ __global__ __launch_bounds__(64 * W) void expert_split_kernel(const u32x4 *__res
 #pragma unroll
     for (int q = 0; q < NST - 1; ++q) issue(first + q, q);
     int slot = 0;
-    for (int from = first; from < last; from += 8) {
-        const int to = min(from + 8, last);
+    for (int from = first; from < last; from += span) {
+        const int to = min(from + span, last);
         for (int step = from; step < to; ++step) {
             __builtin_amdgcn_s_waitcnt(G::kWait);                  // stage `step` has landed (loads finish in order)
             asm volatile("" ::: "memory");
@@ -3228,11 +3214,45 @@ __global__ __launch_bounds__(64 * W) void expert_split_kernel(const u32x4 *__res
             for (int v = 0; v < d; ++v) sum[v] += sum[v + d];
         const int64_t r = row0 + (b / CB) * 16 + m;
         const int n = col0 + (b % CB) * 16 + 4 * g;
-        if (r < row_end && n < a.N) {
-            if constexpr (F32) *reinterpret_cast<f32x4 *>(static_cast<T *>(y) + r * a.N + n) = sum[0];
-            else *reinterpret_cast<uint2 *>(static_cast<T *>(y) + r * a.N + n) = pack_bf16x4(sum[0]);
+        if (r < row_end && n < N) {
+            if constexpr (!std::is_same<T, float>::value) {
+                *reinterpret_cast<uint2 *>(y + r * N + n) = pack_bf16x4(sum[0]);
+            } else if constexpr (VEC) {
+                *reinterpret_cast<f32x4 *>(y + r * N + n) = sum[0];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (n + v < N) y[r * N + n + v] = sum[0][v];
+            }
         }
     }
+}
+
+template <int XB, int CB, int W, int NST, bool F32>
+__global__ __launch_bounds__(64 * W) void expert_split_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w, void *__restrict__ y,
+                                                              ExpertArgs a)
+{
+    constexpr int XR = 16 * XB, WR = 16 * CB;
+    extern __shared__ __align__(16) unsigned char split_lds[];
+    const int lane = threadIdx.x & 63;
+    const int cpr = F32 ? a.H / 4 : a.H / 8, nct = (a.N + WR - 1) / WR;
+    // tile numbers in blocks of 8 per XCD: so few of them, in blocks of 32, would leave XCDs without any
+    const int64_t j = blockIdx.x / kXcds;
+    const int64_t L = (j / 8) * (8 * kXcds) + (int64_t)(blockIdx.x % kXcds) * 8 + j % 8;
+    const ExpertTileHit hit = find_expert_tile<XR>(a, nct, L, lane);
+    const int e = __builtin_amdgcn_readfirstlane(hit.e);
+    if (e >= a.E) return;                                          // surplus workgroup
+    const int ct = __builtin_amdgcn_readfirstlane((int)(hit.L / (uint32_t)hit.tiles));
+    const int row0 = __builtin_amdgcn_readfirstlane(hit.lo + (int)(hit.L % (uint32_t)hit.tiles) * XR);
+    const int seg_end = __builtin_amdgcn_readfirstlane(hit.hi < a.max_rows ? hit.hi : a.max_rows);
+    if (row0 < 0 || row0 >= seg_end) return;
+    const int row_end = min(seg_end, row0 + XR), col0 = ct * WR;
+    const uint32_t rowb = (uint32_t)cpr * 16;
+    const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)(row_end - row0) * rowb);
+    const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)min(a.N - col0, WR) * rowb);
+
+    using T = std::conditional_t<F32, float, unsigned short>;
+    split_tile<XB, CB, W, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, split_lds);
 }
 
 // TAIL: rows are not whole steps; the last step's pieces past the end of a row are out of range.
@@ -3557,6 +3577,22 @@ __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restr
     expert_short_tile<XR, WR, NST, F32, false>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
                                                make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, cpr, E, t0,
                                                t1, e0, gshort_lds, spread ? walk_start((int)(blockIdx.x / nct), cpr / 8) : 0);
+}
+
+// Gate projection of few tiles, bf16: the expert layer's split tiles, tokens x experts.  Against waves that stream their shares straight into
+// registers, 64 bytes of 16 rows a load (gate_split_kernel), and against 32 x 64 tiles: 16 x 7168, 64 experts 15.5 -> 5.6 us, 300 x 7168, 256
+// experts 21.8 -> 9.9, 512 x 7168, 64 experts 15.9 -> 7.8, 1024 x 8192, 256 experts 28.6 -> 20.1.
+template <int XB, int CB, int W, int NST>
+__global__ __launch_bounds__(64 * W) void gate_ring_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w, float *__restrict__ logits,
+                                                           int64_t T, int cpr, int E)
+{
+    extern __shared__ __align__(16) unsigned char ring_lds[];
+    const int nct = (E + 16 * CB - 1) / (16 * CB);
+    const int64_t t0 = (int64_t)(blockIdx.x / nct) * (16 * XB), t1 = t0 + 16 * XB < T ? t0 + 16 * XB : T;
+    const int e0 = (int)(blockIdx.x % nct) * (16 * CB);
+    const uint32_t rowb = (uint32_t)cpr * 16;
+    split_tile<XB, CB, W, NST, false, false>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb), make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, 16 * CB) * rowb),
+                                             logits, cpr, E, t0, t1, e0, ring_lds);
 }
 
 // Gate projection with the hidden axis split over the 8 waves of a workgroup: 16 tokens x 16 NB experts each.  For fp32

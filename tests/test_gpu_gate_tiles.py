@@ -54,6 +54,18 @@ def test_gate_bf16(T, H, E):
     check(T, H, E, BF16)
 
 
+# few tiles, their steps dealt to four or eight waves: one token, one step less than the least and just enough, steps that do not divide,
+# pieces past a row's end, both sides of the lines between 16 x 16 (200 tiles, eight waves up to 128), 16 x 32, 32 x 32 and 32 x 64 (256 tiles)
+FEW_BF16 = [(1, 504, 9), (1, 512, 9), (17, 520, 33), (16, 1032, 16), (3199, 512, 5), (3200, 520, 16), (3201, 512, 16), (2048, 8192, 16),
+            (2049, 8200, 16), (4096, 600, 32), (4097, 1024, 32), (8192, 1024, 32), (8193, 1024, 32), (5120, 1000, 30), (5121, 1000, 30),
+            (8192, 2048, 64), (8193, 2048, 64), (8192, 2040, 33), (2000, 2056, 250), (100, 4104, 256)]
+
+
+@pytest.mark.parametrize("T,H,E", FEW_BF16)
+def test_gate_few_tiles(T, H, E):
+    check(T, H, E, BF16)
+
+
 # bf16: rows that are not whole steps in the direct-to-LDS tiles of each shape, and the lines drawn for them; short rows on up to 8
 # experts; two persistent workgroups per CU; and activations of 256 MiB, which are not streamed yet, and of 300 MiB, which are
 RAGGED = [(4100, 520, 33), (8161, 72, 9), (9000, 2056, 64), (12000, 1096, 200), (16353, 2056, 24), (16352, 2056, 24), (6000, 8, 100),
