@@ -855,9 +855,9 @@ bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
 }
 
 // Lanes per token of small_step_kernel, 0 if the problem is not a small one: all tokens have to be covered by one pass of a
-// workgroup's threads, their logits and the plan by its LDS.  And routing them all in every workgroup must not take longer than
+// workgroup's threads, their choices and the plan by its LDS.  And routing them all in every workgroup must not take longer than
 // routing a share of them and waiting for the others, which grows with tokens x experts and, where each row's workgroup does it, with
-// the choices.  Measured on MI355X, GPU time in us, several launches and one: routing 64 x 8, top-2 7.8 and 4.9; 128 x 64, top-8 10.5
+// the choices.  Measured on MI355X, when both took the logits through the LDS, GPU time in us, several launches and one: routing 64 x 8, top-2 7.8 and 4.9; 128 x 64, top-8 10.5
 // and 9.1, 256 x 64 10.6 and 14.4; 512 x 16, top-2 8.2 and 6.8, 512 x 32, top-4 8.8 and 11.4; 64 x 256, top-8 17.5 and 13.2.  With the
 // rows (4096 elements): 64 x 8, top-2 8.4 and 5.5, 512 x 8 10.6 and 8.3, 1024 x 8 13.3 and 15.5; 256 x 32, top-4 11.3 and 10.9, 128 x
 // 64, top-8 12.8 and 14.1.  The whole step 64 x 8 12.8 and 7.7, 512 x 8 18.2 and 10.8.

@@ -1606,9 +1606,9 @@ __global__ __launch_bounds__(kMoverThreads) void combine_kernel(const u32x4 *__r
 // positions, the other plan tables, and the choices with the gates, the others each move threads / lanes-per-row rows.
 // WHAT: tables and gates alone (three workgroups), the rows as well, or the whole step with identity experts, in which a token's output is
 // added up from its row while that is in registers (the rows of its choices are copies of it) instead of being read back from FINAL.
-// What bounds it: a chain of latencies of about 8000 clocks (kernel arguments, logits, the choices one after the other, scans,
-// positions).  Measured on MI355X: 64 tokens, 8 experts, top-2, 4096 elements 12.8 us of GPU time in three launches, 7.7 in one;
-// where the lines lie stands at small_lanes.
+// What bounds it: a chain of latencies (kernel arguments, logits, choices, scans, positions, stores; of 15000 clocks the sums of the
+// outputs took 7000 when each choice was a product of its own).  Measured on MI355X: 64 tokens, 8 experts, top-2, 4096 elements 12.8 us
+// of GPU time in three launches, 7.7 in one, now 6.5; where the lines lie stands at small_lanes.
 enum SmallWhat { SMALL_ROUTE = 0, SMALL_PLACE = 1, SMALL_COMBINE = 2 };
 
 // Dynamic LDS of the kernel (byte offsets; made on the host: in every workgroup it is a chain of a hundred scalar instructions).
@@ -3597,13 +3597,12 @@ __global__ __launch_bounds__(64 * W) void gate_ring_kernel(const u32x4 *__restri
 
 // Gate projection with the hidden axis split over the 8 waves of a workgroup: 16 tokens x 16 NB experts each.  For fp32
 // activations (16x16x4 fp32 MFMA) and for so few bf16 tokens that a tile's walk along the whole hidden axis is what takes the
-// time.  A wave streams its share straight into registers, D steps of 128 bytes per row ahead; lane l holds 16 bytes of row
+// time, on rows that gate_ring_kernel does not take (below 512 elements, beyond 2^20).  A wave streams its share straight into registers, D steps of 128 bytes per row ahead; lane l holds 16 bytes of row
 // l % 16, at the same place of x and of w, so which element of the hidden axis meets which MFMA does not matter.  The waves'
 // sums are added through LDS in a fixed order.  Rows past the end repeat the last one and are not stored.  Steps past a
 // wave's share multiply zeros: an MFMA takes no notice of a lane mask, so it may not stand under a condition that the
 // compiler cannot prove uniform.
-// Measured, bf16, workgroups that walk the whole hidden axis before: 64 x 7168, 64 experts 27 -> 16 us; 256 x 4096, 256
-// experts 57 -> 10.  fp32, a wave per token and eight experts at a time before: 8192 x 4096, 8 / 64 experts 48 / 325 -> 26 / 75.
+// Measured, fp32, a wave per token and eight experts at a time before: 8192 x 4096, 8 / 64 experts 48 / 325 -> 26 / 75.
 template <bool BF16, int NB>
 __global__ __launch_bounds__(512) void gate_split_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                          float *__restrict__ logits, int64_t T, int64_t cpr, int E)
