@@ -3358,14 +3358,15 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
     const bool stream = kMayStream && (int64_t)e * a.N + col0 >= a.stream_from && __builtin_amdgcn_readfirstlane(alone);
     const uint32_t rowb = (uint32_t)cpr * 16;
     const int wr = min(a.N - col0, cols);
+    // by the expert, in tiles of every kind: a row may be in a large tile of one launch and in a short one of another
     const int start = DEEP_W && !TAIL && a.spread ? walk_start(e, nsteps) : 0;
     const auto rx = make_rsrc(x + (int64_t)row0 * cpr, (uint32_t)xr * rowb);
     const auto rw = make_rsrc(w + ((int64_t)e * a.N + col0) * cpr, (uint32_t)wr * rowb);
     if (xr <= kShortRows) {                                        // tiles with little arithmetic
         if (kMayStream && stream)
-            expert_short_tile<64, kShortCols, kStages, false, false, kMayStream ? kStreamLoad : 0>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds, 0);
+            expert_short_tile<64, kShortCols, kStages, false, false, kMayStream ? kStreamLoad : 0>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds, start);
         else
-            expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds, 0);
+            expert_short_tile<64, kShortCols, kStages, false, false>(rx, rw, y, cpr, a.N, row0, row_end, col0, big_lds, start);
         return;
     }
 

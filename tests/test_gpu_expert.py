@@ -286,6 +286,49 @@ def test_overlapped_pipeline_gives_the_same_buffers(m, case):
         np.testing.assert_array_equal(bufs.to_host_act(cfg, y), want)
 
 
+# All forms whose walk along the hidden axis may start at another step, rows 4096 bytes or a multiple of it apart: 256 x 256 tiles with
+# their ragged ones last, in place, and two of them per expert, each with segments and slices that end in tiles of up to 64 rows, in
+# which a row of a slice lies where the whole segment has it in a large tile; 64 x 128, 32 x 64, fp32
+@pytest.mark.parametrize("sizes,H,N,dtype", [
+    ([300, 128, 64, 65, 320, 0, 3, 200] * 3, 2048, 2056, BF16),
+    ([300, 128, 64, 65, 320, 0, 3, 200] * 3, 2048, 4104, BF16),
+    ([300, 520, 257, 320, 400, 100, 260, 411], 4096, 4104, BF16),
+    ([44, 40, 64, 65, 1, 0, 33, 61] * 4, 2048, 2056, BF16),
+    ([16, 1, 0, 33, 17, 5, 32, 40] * 3, 4096, 2056, BF16),
+    ([16, 1, 0, 33, 17, 5, 32, 40] * 3, 1024, 2052, FP32),
+], ids=["last", "inplace", "two", "64x128", "32x64", "fp32"])
+def test_rows_do_not_depend_on_the_launch(m, sizes, H, N, dtype):
+    """Normal inputs, whose sums tell one order of additions from another: all rows in one launch, slice by slice, and in the
+    pipeline with and without overlap give y bit for bit."""
+    import torch
+    T, E, S = sum(sizes), len(sizes), 4
+    t = torch.float32 if dtype == FP32 else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+    x = torch.randn((T, H), generator=g, device="cuda").to(t)
+    wd = torch.randn((E * N, H), generator=g, device="cuda", dtype=t) * H ** -0.5
+    expert = torch.repeat_interleave(torch.arange(E, device="cuda"), torch.tensor(sizes, device="cuda"))
+    logits = torch.zeros((T, E), device="cuda")
+    logits[torch.arange(T, device="cuda"), expert[torch.randperm(T, generator=g, device="cuda")]] = 4.0
+    cfg = m.make_cfg(T, H, dtype, E, 1, 1, 1, S, 0.0)
+    b = m.alloc_buffers(cfg, logits.cpu().numpy())
+
+    def buffer():
+        return torch.full((T, N), float("nan"), dtype=t, device="cuda")
+
+    got = {}
+    for overlap in (0, 1):
+        y = got[f"overlap {overlap}"] = buffer()
+        m.monta_route_dispatch_expert(cfg, b.logits, x, b.topk_idx, b.gates, b.stage, b.final, wd, N, y, b.ws, overlap)
+    y = got["slices"] = buffer()
+    for j in range(S):
+        m.monta_expert_linear(cfg, b.final, wd, N, y, b.ws, j)
+    whole = buffer()
+    m.monta_expert_linear(cfg, b.final, wd, N, whole, b.ws, -1)
+    assert not bool(torch.isnan(whole).any())
+    for name, y in got.items():
+        assert torch.equal(y, whole), f"{name}: {int((y != whole).sum())} of {y.numel()}"
+
+
 @pytest.mark.parametrize("overlap", [0, 1])
 def test_gate_expert_step_in_a_hip_graph(m, overlap):
     """gate -> route/dispatch/expert (with and without the second stream) -> combine, captured in a HIP graph and replayed
