@@ -1848,10 +1848,12 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
         if (ok && what == SMALL_COMBINE) my_g = s_gate[sub * k + gl];
         const unsigned int kmask = k >= 32 ? 0xffffffffu : ((1u << k) - 1u);
         const unsigned int kept = (unsigned int)(__ballot(ok) >> gbase) & kmask;
-        // All rows being copies of one, the sum of products is the product with the sum of the gates: the same to the last bit of 64 where
-        // that sum is exact, which it is unless gates are 2^29 apart.  Not for three or more choices in fp32, whose chain rounds in
-        // between, and not with a gate of zero, which an infinite activation would tell from no choice.  Rows that whole waves
-        // share have their destinations in scalar registers.
+        // All rows being copies of one, the sum of products is the product with the sum of the gates, and to the last bit of 64 where no
+        // addition of the combine's chain but its last one can round.  A product of a gate and a bf16 element has 32 bits, so that sums of
+        // up to 32 of them are exact in 53 bits if the gates' exponents are at most 16 apart, and then so is the sum of the gates.  Of
+        // two products, in fp32, too, only the last addition rounds, and their gates' sum is exact with exponents up to 28 apart.
+        // Otherwise, and with a gate of zero, which an infinite activation would tell from no choice, product after product.  Rows that
+        // whole waves share have their destinations in scalar registers.
         auto move = [&](auto whole_waves) {
             constexpr bool WAVE = decltype(whole_waves)::value;
             const unsigned int mine = WAVE ? (unsigned int)__builtin_amdgcn_readfirstlane((int)kept) : kept;
@@ -1859,11 +1861,14 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
             double gate_sum = 0.0;
             bool summed = bf16 || k <= 2;
             if (what == SMALL_COMBINE && summed) {
+                uint32_t most = 0, least = ~0u;                    // gates are positive: their bits are in their order
                 for (unsigned int rem = mine; rem; rem &= rem - 1) {
-                    const float g = __int_as_float(of(__float_as_int(my_g), __builtin_ctz(rem)));
-                    summed &= g != 0.f;
-                    gate_sum += (double)g;
+                    const int bits = of(__float_as_int(my_g), __builtin_ctz(rem));
+                    most = max(most, (uint32_t)bits);
+                    least = min(least, (uint32_t)bits);
+                    gate_sum += (double)__int_as_float(bits);
                 }
+                summed = least != 0 && (int)(most >> 23) - (int)(least >> 23) <= (k <= 2 ? 28 : 16);
             }
             for (int vbase = 0; vbase < vpr; vbase += lpr * kVecInFlight) {
                 const int v0 = vbase + rl;

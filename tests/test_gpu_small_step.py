@@ -205,6 +205,43 @@ def test_routing_in_the_logits_memory(m, T, E, k, tp, what, at, call):
         np.testing.assert_array_equal(shared[name], apart[name], err_msg=name)
 
 
+# Four tokens whose strongest choice is dropped and whose three kept gates are 2^24 to 2^28 apart: (bf16 value of the row, logits of the
+# kept choices; that of the dropped one is 0).  The sum of the three products lies within 2^-53 of the middle between two bf16
+# numbers: added one after the other in 64 bits it falls on the middle or on one side, the value times the sum of the gates on another.
+FAR_GATES = [(246 / 128, (-0.9775711894035339, -17.92718505859375, -18.063194274902344)),
+             (151 / 128, (-1.1030322313308716, -18.03681182861328, -18.30622100830078)),
+             (225 / 128, (-1.1926922798156738, -18.10735511779785, -18.39781951904297)),
+             (210 / 128, (-0.2344007045030594, -19.29912567138672, -19.637168884277344))]
+
+
+def test_gates_far_apart(m):
+    """The one-launch step adds the products of a token's choices as the combine does, where the order of the roundings shows."""
+    import torch
+    n, E, k, H = len(FAR_GATES), 8, 4, 512
+    logits = np.full((2 * n, E), -60.0, np.float32)
+    logits[:n, [0, 4, 5, 6]] = np.float32([0.0, -1.0, -2.0, -3.0])      # these fill expert 0
+    logits[n:, 0] = 0.0
+    logits[n:, 1:4] = np.float32([far for _, far in FAR_GATES])
+    x = np.ones((2 * n, H), np.float32)
+    x[n:] = np.float32([v for v, _ in FAR_GATES])[:, None]
+    cfg = m.make_cfg(2 * n, H, m.BF16, E, k, 1, 1, 1, 1.0)              # four rows per expert
+    got = []
+    for static in (True, False):
+        b = m.alloc_buffers(cfg, logits, workloads.f32_to_bf16_bits(x), canary=0xA5)
+        if static:
+            m.monta_route_dispatch_combine_static(cfg, b.logits, b.x, b.topk_idx, b.gates, b.stage, b.final, b.out)
+        else:
+            m.monta_route_dispatch_regather(cfg, b.logits, b.x, b.topk_idx, b.gates, b.stage, b.final, b.ws)
+            m.monta_combine(cfg, b.final, b.gates, b.out, b.ws)
+        torch.cuda.synchronize()
+        got.append(b.out.view(torch.int16).cpu().numpy())
+    g = b.gates.cpu().numpy().astype(np.float64)[n:, 1:]
+    v = x[n:, 0].astype(np.float64)
+    chain = (g[:, 0] * v + g[:, 1] * v) + g[:, 2] * v                   # products are exact in 64 bits
+    assert np.all(chain != ((g[:, 0] + g[:, 1]) + g[:, 2]) * v)         # the case is what it is meant to be
+    np.testing.assert_array_equal(got[0], got[1])
+
+
 def test_replayed_from_a_hip_graph(m):
     import torch
     w = Workload("graph", 256, 1024, BF16, 8, 2, 4, 2, 2, 0.8, zipf_s=0.6)
