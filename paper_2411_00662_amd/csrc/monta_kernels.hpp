@@ -226,8 +226,9 @@ __device__ __forceinline__ uint32_t pick_key(const uint32_t (&key)[N], int q)
 
 // Steps 1, 2 and the masks of 4: the choices of `nt` tokens whose logits start at src.  Choice j of token tok and its logit go to
 // s_sel and s_top[tok * k + j]; bit tok % 64 of s_mask[e * expert_step + tok / 64 * word_step] (cleared by the caller) is
-// set where token tok chose e.  idx_out: the choices also to memory, if it is not null.  s_den: sums of all exponentials, if it is
-// not null.  All threads of the workgroup; ends without a barrier.
+// set where token tok chose e.  s_den: sums of all exponentials, if it is not null.  All threads of the workgroup; ends without a
+// barrier.  Nothing goes to memory here: choices and gates may be stored in the logits' own memory, and until the caller's barrier
+// waves still read theirs, those of the sums a second time.
 // Up to two choices, or more than eight, are found one after the other: the largest key of the token, its lowest place, and that key is
 // cleared, about 4.5 instructions per key and choice.  Three to eight: the largest keys in order, from sorting networks over the
 // lane's keys and then over the token's lanes, about 11 instructions per key for eight; then each lane looks up the few of its keys
@@ -238,8 +239,7 @@ __device__ __forceinline__ uint32_t pick_key(const uint32_t (&key)[N], int q)
 // 65536 tokens, 64 experts, top-8 28.0 -> 23.9; 16384 tokens, 255 experts, top-2, renorm = 0 25.6 -> 23.9.
 template <int L, int NE>
 __device__ __forceinline__ void route_select(const float *__restrict__ src, int nt, int E, int k, int *s_sel, float *s_top,
-                                             unsigned long long *s_mask, int expert_step, int word_step, double *s_den,
-                                             int32_t *__restrict__ idx_out)
+                                             unsigned long long *s_mask, int expert_step, int word_step, double *s_den)
 {
     static_assert(NE % 8 == 0 && NE <= 32, "route_select: keys of a lane");
     constexpr int kShift = L == 1 ? 2 : L == 2 ? 3 : L == 4 ? 4 : L == 8 ? 5 : 6;         // experts of all lanes' fours: 1 << kShift
@@ -295,7 +295,6 @@ __device__ __forceinline__ void route_select(const float *__restrict__ src, int 
     auto choose = [&](int j, int e, uint32_t x) {
         sel[j] = e;
         top_logit[j] = logit(x);
-        if (idx_out) idx_out[tok * k + j] = e;
         atomicOr(&mask[e * expert_step], tbit);
     };
     auto largest = [&] {                                            // of the token
@@ -464,9 +463,8 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
     if (nt > TB) nt = TB;
 
     for (int i = tid; i < E * NW; i += blockDim.x) s_mask[i] = 0ull;
-    route_select<L, NE>(logits + (size_t)t_begin * E, nt, E, k, s_sel, s_top, s_mask, NW, 1, s.renorm ? nullptr : s_den,
-                        topk_idx + (size_t)t_begin * k);
-    __syncthreads();
+    route_select<L, NE>(logits + (size_t)t_begin * E, nt, E, k, s_sel, s_top, s_mask, NW, 1, s.renorm ? nullptr : s_den);
+    __syncthreads();                                               // no logit is read any more: their memory may be stored to
     route_weights(nt, k, s_top, s_w, s.by_k1, tid, blockDim.x);
     __syncthreads();
     route_gates(nt, k, s_w, s.renorm ? nullptr : s_den, s.by_k, tid, blockDim.x,
@@ -481,6 +479,7 @@ __global__ __launch_bounds__(1024) void route_plan_kernel(const float *__restric
     for (int idx = tid; idx < npairs; idx += blockDim.x) {      // one pair per lane again
         const int tk = idx / s.by_k;
         const int e = s_sel[idx];
+        topk_idx[(size_t)t_begin * k + idx] = e;
         const int word = tk >> 6;
         int r = 0;
         for (int w = 0; w < word; ++w) r += __popcll(s_mask[e * NW + w]);
@@ -1680,7 +1679,7 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
     if (tid < 16) s_alive[tid] = 0ull;
     const bool weighted = role == GATES || (mover && what == SMALL_COMBINE);
     double *den = s.renorm || !weighted ? nullptr : s_den;
-    route_select<L, NE>(logits, T, E, k, s_sel, s_top, s_mask, 1, E, den, role == GATES ? topk_idx : nullptr);
+    route_select<L, NE>(logits, T, E, k, s_sel, s_top, s_mask, 1, E, den);
     __syncthreads();
     // Gates of all tokens, or of this workgroup's own: by the last waves first, beside the scans, which are the first waves' work.
     const int rtid = nthr - 1 - tid;
@@ -1696,8 +1695,12 @@ __global__ __launch_bounds__(1024) void small_step_kernel(const float *__restric
     __syncthreads();
     if (weighted) {
         route_gates(t1 - t0, k, s_w + t0 * k, den ? den + t0 : nullptr, s.by_k, rtid, nthr, [&](int idx, float g) {
-            if (mover) s_gate[idx] = g;
-            else gates[idx] = g;
+            if (mover) {
+                s_gate[idx] = g;
+            } else {
+                gates[idx] = g;
+                topk_idx[idx] = s_sel[idx];
+            }
         });
         if (role == GATES) return;
     }

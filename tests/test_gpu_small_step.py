@@ -169,8 +169,22 @@ def test_shared_memory_takes_several_launches(m, shared):
 @pytest.mark.parametrize("T,E,k,tp,what,at", [(64, 8, 2, 1, "gates", 0), (64, 8, 2, 1, "gates", 37), (64, 8, 2, 1, "idx", 0),
                                              (64, 8, 2, 1, "idx", 384), (62, 4, 4, 2, "gates", 0)])
 def test_routing_in_the_logits_memory(m, T, E, k, tp, what, at, call):
+    in_the_logits_memory(m, T, E, k, tp, what, at, call, 1)
+
+
+# the same where several waves route together (two, four and eight lanes a token), and where the logits are read again for the sums
+# of their exponentials: choices in front of the first logits, in the middle and behind
+@pytest.mark.parametrize("renorm", [0, 1])
+@pytest.mark.parametrize("call", ["route", "dispatch"])
+@pytest.mark.parametrize("T,E,k,what,at", [(64, 64, 2, "idx", 0), (64, 64, 2, "idx", 1999), (64, 64, 2, "gates", 0), (64, 16, 1, "idx", 0),
+                                          (63, 33, 8, "idx", 512), (64, 256, 4, "idx", 0), (50, 256, 6, "idx", 12500), (64, 128, 9, "idx", 3)])
+def test_routing_of_several_waves_in_the_logits_memory(m, T, E, k, what, at, call, renorm):
+    in_the_logits_memory(m, T, E, k, 1, what, at, call, renorm)
+
+
+def in_the_logits_memory(m, T, E, k, tp, what, at, call, renorm):
     import torch
-    cfg = m.make_cfg(T, 512, m.BF16, E, k, 1, tp, 1, 0.5)
+    cfg = m.make_cfg(T, 512, m.BF16, E, k, 1, tp, 1, 0.5, renorm)
     rng = np.random.default_rng(T + at)
     logits = rng.normal(size=(T, E)).astype(np.float32)
     x = workloads.f32_to_bf16_bits(rng.normal(size=(T, 512)).astype(np.float32))
