@@ -500,22 +500,30 @@ int launch_gate_small(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, 
     return MONTA_OK;
 }
 
-template <int XR, int WR, int NST, bool F32 = false>
-int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
+template <int XR, int WR, int NST, bool F32, bool SPREAD>
+int launch_gate_short_t(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
 {
     using G = ShortTile<XR, WR, NST>;
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(gate_short_kernel<XR, WR, NST, F32, SPREAD>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t grid = (T + XR - 1) / XR * ((E + WR - 1) / WR);
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    // Spread starts (walk_start) where the weights, which the tiles then read at different places, stay in every L2.  Three sets of
-    // activations in turn, in step and spread, us: 8192 x 4096, 64 experts 21.0 and 16.5; 16384 x 8192, 64 experts 71.3 and 61.5; 4096 x 8192,
-    // 128 experts 36.6 and 29.6; 16384 x 2048, 64 experts 15.4 and 14.0; but 1024 x 8192, 256 experts, 4 MiB of weights 31.9 and 33.0.
-    // In fp32 the matrix rate decides (16384 x 4096, 64 experts: 95.9 and 96.3).
-    const int64_t row = (int64_t)H * 2;
-    const int spread = !F32 && row % 4096 == 0 && E * row <= (2 << 20);
-    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E, spread);
+    hipLaunchKernelGGL((gate_short_kernel<XR, WR, NST, F32, SPREAD>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st, x, w, logits, T, H, E);
     return MONTA_OK;
+}
+
+// Spread starts (walk_start) up to 2 MiB of weights, half an L2: the tiles then read them at different places.  Three sets of activations in
+// turn, in step and spread, us: 9000 x 4096, 20 experts 22.7 and 16.5; 16384 x 2048, 64 experts 15.0 and 13.8; 16384 x 8192 70.3 and 61.1;
+// 10000 x 4096, 256 experts 64.8 and 58.8; 30000 x 2048, 128 experts 41.9 and 41.4.  The line is a cautious one: 12000 x 8192, 160 experts,
+// 2.5 MiB, 116.8 and 93.7, 10000 x 8192, 256 experts, 4 MiB, 114 and 107.  In fp32 the matrix rate decides (16384 x 4096, 64 experts:
+// 95.9 and 96.3).
+template <int XR, int WR, int NST, bool F32 = false>
+int launch_gate_short(const u32x4 *x, const u32x4 *w, float *logits, int64_t T, int H, int E, hipStream_t st)
+{
+    const int64_t row = (int64_t)H * 2;
+    if constexpr (!F32)
+        if (row % 4096 == 0 && E * row <= (2 << 20)) return launch_gate_short_t<XR, WR, NST, false, true>(x, w, logits, T, H, E, st);
+    return launch_gate_short_t<XR, WR, NST, F32, false>(x, w, logits, T, H, E, st);
 }
 
 // The whole-row kernel for at most 8 experts; returns 1 if the shape does not fit it.  Measured on MI355X: tiles

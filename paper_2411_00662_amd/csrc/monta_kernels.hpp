@@ -2825,8 +2825,9 @@ struct ShortTile {
 // per element of a piece), so that neither short rows nor long ones cost precision; the middle one, on bf16 rows of up to 16 steps,
 // in a chain per even and odd step of each half of the row.  Error against 64 bits with one chain and two levels, and now: 512
 // elements 1.2e-7, 6.1e-8; 1536 1.3e-7, 7.4e-8; 8192 1.5e-7, 1.05e-7; fp32, 1000 2.9e-7, 9.6e-8, 8192 3.1e-7, 1.4e-7.
+// ANY_START, of bf16 logits whose walk begins at an even step: added so that where it begins does not show (run_any_start).
 // AUX_W: cache bits of the weights' loads.
-template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, typename T>
+template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, bool ANY_START = false, typename T>
 __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
                                                   int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds, int start)
 {
@@ -2869,6 +2870,7 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     constexpr bool kLevels = std::is_same<T, float>::value;
     constexpr bool kLogits = kLevels && !VEC;
     constexpr int kChains = !kLogits ? 1 : F32 ? 4 : 2;
+    static_assert(!ANY_START || (kLogits && !F32), "short tile: a start that does not show is one of bf16 logits");
     f32x4 acc[kChains][RB][CB];
 #pragma unroll
     for (int c = 0; c < kChains; ++c)
@@ -3004,11 +3006,59 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
                 }
         }
     };
+    // All steps of logits whose tiles begin at different even steps: equal tokens have to have equal logits wherever they stand.  The sums of
+    // two neighbouring steps, always the same two, are added up in 64 bits: 24-bit numbers, up to 64 of them (rows of 8192
+    // elements) without any rounding where they are at most 2^23 apart, and what rounds beyond that is 2^-53 of the sum, to be seen in
+    // the logit only beside the middle of two 32-bit numbers.  It takes fewer registers than three levels, no more time, and is more
+    // exact: 2048 elements 7.6e-8 off 64 bits, now 5.6e-8, 4096 9.1e-8 and 5.6e-8, 8192 1.05e-7 and 5.6e-8.
+    auto run_any_start = [&](auto blocks, int whole_to) {
+        constexpr int BLOCKS = decltype(blocks)::value;
+        double sums[BLOCKS][CB][4];
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sums[i][j][v] = 0.0;
+        auto two_steps = [&](auto whole, int step) {
+            f32x4 half[2][BLOCKS][CB];
+#pragma unroll
+            for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+                for (int j = 0; j < CB; ++j) half[0][i][j] = half[1][i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            auto add = [&](const auto &fw, const auto &fx) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int i = 0; i < BLOCKS; ++i) multiply(fw[ks], fx[ks][i], half[ks][i], 0);
+            };
+            advance(blocks, whole, step, add);
+            advance(blocks, whole, step + 1, add);
+#pragma unroll
+            for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+                for (int j = 0; j < CB; ++j) {
+                    const f32x4 both = half[0][i][j] + half[1][i][j];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sums[i][j][v] += (double)both[v];
+                }
+        };
+        int step = 0;
+        for (; step + 1 < whole_to; step += 2) two_steps(std::true_type{}, step);
+        for (; step < nsteps; step += 2) two_steps(std::false_type{}, step);
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+            for (int j = 0; j < CB; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) total[i][j][v] = (float)sums[i][j][v];
+    };
     // With at most half of the row blocks in use only those are multiplied.  One choice before the loop, as for the steps that are
     // not whole: with a condition per block inside it a step waits for one read after the other (2 rows each of 16 experts of 5120 x
     // 152, 48 workgroups: 21.8 us, now 16.4; 2 experts of 8192 x 64, 60 rows: 38 and 25).
     auto run = [&](auto blocks) {
         const int whole_to = cpr / 8 - (NST - 1);                      // up to here the step NST - 1 ahead is a whole one
+        if constexpr (ANY_START) return run_any_start(blocks, whole_to);
         if constexpr (kLogits && !F32)
             if (nsteps <= 16) return run_each(blocks, whole_to);
         const int span = kLevels ? 8 : nsteps, sub = !kLogits || F32 ? span : nsteps <= 32 ? 2 : 4;
@@ -3573,9 +3623,10 @@ __global__ __launch_bounds__(kBigThreads, 1) void expert_big_kernel(const u32x4 
 // 256 experts 61 -> 37, 1024 x 7168, 256 experts 92 -> 35; rows that are not whole steps: 1024 x 8184, 256 experts 109 -> 29, 12000 x
 // 520, 9 experts 12.5 -> 5.8.  Against persistent workgroups of whole rows: 65536 x 512, 8 experts 49 -> 13.  fp32 against tiles of
 // 16 tokens x 64 experts with a split hidden axis: 8192 x 4096, 128 experts 171 -> 99, 32000 x 8192, 64 experts 694 -> 333.
-template <int XR, int WR, int NST, bool F32>
+// SPREAD: the row tiles' walks begin at different even steps; rows of whole pairs of steps.
+template <int XR, int WR, int NST, bool F32, bool SPREAD>
 __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
-                                                            float *__restrict__ logits, int64_t T, int H, int E, int spread)
+                                                            float *__restrict__ logits, int64_t T, int H, int E)
 {
     extern __shared__ __align__(16) unsigned char gshort_lds[];
     const int nct = (E + WR - 1) / WR, cpr = F32 ? H / 4 : H / 8;
@@ -3583,9 +3634,9 @@ __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restr
     const int e0 = (int)(blockIdx.x % nct) * WR;
     const int64_t t1 = t0 + XR < T ? t0 + XR : T;
     const uint32_t rowb = (uint32_t)cpr * 16;
-    expert_short_tile<XR, WR, NST, F32, false>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
-                                               make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, cpr, E, t0,
-                                               t1, e0, gshort_lds, spread ? walk_start((int)(blockIdx.x / nct), cpr / 8) : 0);
+    expert_short_tile<XR, WR, NST, F32, false, 0, SPREAD>(make_rsrc(x + t0 * cpr, (uint32_t)(t1 - t0) * rowb),
+                                                          make_rsrc(w + (int64_t)e0 * cpr, (uint32_t)min(E - e0, WR) * rowb), logits, cpr, E, t0,
+                                                          t1, e0, gshort_lds, SPREAD ? walk_start((int)(blockIdx.x / nct), cpr / 8) & ~1 : 0);
 }
 
 // Gate projection of few tiles, bf16: the expert layer's split tiles, tokens x experts.  Against waves that stream their shares straight into

@@ -110,3 +110,19 @@ def test_gate_longest_rows(T, E, H, dtype):
     m.monta_gate(m.make_cfg(T, H, dtype, E, 1, 1, 1, 1, 0.0), x, w, out[:T])
     assert bool(torch.isnan(out[T]).all())
     assert torch.equal(out[:T], x.float() @ w.float().t())
+
+
+# rows 4096 bytes or a multiple of it apart in the direct-to-LDS tiles of each shape, and in the forms around them
+@pytest.mark.parametrize("T,H,E", [(16384, 2048, 64), (12000, 8192, 64), (12001, 4096, 128), (9001, 6144, 100), (4097, 2048, 9), (33, 4096, 40),
+                                   (40000, 2048, 20)])
+def test_equal_tokens_have_equal_logits(T, H, E):
+    """Bit for bit, wherever in the batch they stand."""
+    import paper_2411_00662_amd as m
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((1, H), generator=g, device="cuda").to(torch.bfloat16).repeat(T, 1)
+    w = torch.randn((E, H), generator=g, device="cuda", dtype=torch.bfloat16) * H ** -0.5
+    out = torch.empty((T, E), device="cuda")
+    m.monta_gate(m.make_cfg(T, H, BF16, E, 1, 1, 1, 1, 0.0), x, w, out)
+    assert bool((out == out[0]).all())
