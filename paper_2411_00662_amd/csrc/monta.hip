@@ -1423,12 +1423,10 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
     if (cfg->dtype == MONTA_BF16) {
         // validate() guarantees H % 8 == 0 (rows are whole 16-byte vectors) and E <= 256 (at most 8 tiles).
         //  - Few tiles: launch_gate_few.  What it leaves, up to 8 experts on whole rows: launch_gate_small_any.  The rest, as follows.
-        //  - Few tiles of 16 tokens x 16 experts (or 32, where that makes them one round): the hidden axis is split, too.  More than a
-        //    round of them only for up to 16 experts and rows over 2 KiB (8192 x 4096, 9 experts: 14 us, in 32 x 64 20; but 6144 x 512,
-        //    16 experts: 9.2 and 5.1).  One round with 32 experts a tile, too, but not on rows that the tiles below read faster and add as
-        //    exactly: 576 to 1024 elements (4096 x 576, 32 experts: 7.1 us and 5.3, error against 64 bits 6.35e-8 and 6.34e-8; 2048 x 1024,
-        //    64 experts: 7.1 and 6.9, 6.9e-8 and 6.8e-8; but 4096 x 1024, 17 experts: 6.0 and 6.4) and up to 512 (2048 x 512, 40 experts:
-        //    7.0 and 5.1; but 4096 x 520, 17 experts: 4.8 and 5.1, 6.1e-8 and 6.3e-8).
+        //  - Up to a round of tiles of 16 tokens x 16 experts, two rounds for up to 16 experts on rows over 2 KiB, or a round of 16 x 32 on such
+        //    rows: the hidden axis is split, too.  launch_gate_few leaves these only rows below 456 elements, activations of more than
+        //    96 MiB and rows beyond 2^20 (three sets in turn, us, split and in 32 x 64: 6500 x 8192, 9 experts 29 and 31; 4096 x 16384, 16 / 24
+        //    experts 39 / 48 and 58; 2048 x 28672, 32 experts 59 and 101; but 8192 x 8192, 16 experts 37 and 32).
         //  - Up to 32736 tokens, and short rows on up to 32 experts beyond: direct-to-LDS tiles.  32 x 64 come three per CU, the
         //    others two; the larger, the fewer bytes, and the longer a workgroup's walk.
         //    Up to 64 experts one tile of 32 x 64 holds them all: those up to three rounds' worth of tiles and, on short rows, always
@@ -1471,7 +1469,7 @@ int monta_gate(const monta_cfg *cfg, const void *x, const void *w_gate, float *l
         }
         else if (tiles16 <= (E <= 16 && !short_rows ? 2 * round : round) || (!k_split && H > kBigMaxHidden))
             rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 1, st);
-        else if (E > 16 && tiles(16, 32) <= round && (!short_rows || (H > 512 && H < 576) || (H >= 960 && E <= 24)))
+        else if (E > 16 && tiles(16, 32) <= round && !short_rows)
             rc = launch_gate_split<true>(xv, wv, logits, T, H / 8, E, 2, st);
         else if (!k_split && use_32x64()) rc = launch_gate_short<32, 64, 4>(xv, wv, logits, T, H, E, st);
         else if (!k_split && use_32x128()) rc = launch_gate_short<32, 128, 4>(xv, wv, logits, T, H, E, st);

@@ -54,11 +54,13 @@ def test_gate_bf16(T, H, E):
     check(T, H, E, BF16)
 
 
-# few tiles, their steps dealt to four or eight waves: one token, one step less than the least and just enough, steps that do not divide,
-# pieces past a row's end, both sides of the lines between 16 x 16 (200 tiles, eight waves up to 128), 16 x 32, 32 x 32 and 32 x 64 (256 tiles)
-FEW_BF16 = [(1, 504, 9), (1, 512, 9), (17, 520, 33), (16, 1032, 16), (3199, 512, 5), (3200, 520, 16), (3201, 512, 16), (2048, 8192, 16),
-            (2049, 8200, 16), (4096, 600, 32), (4097, 1024, 32), (8192, 1024, 32), (8193, 1024, 32), (5120, 1000, 30), (5121, 1000, 30),
-            (8192, 2048, 64), (8193, 2048, 64), (8192, 2040, 33), (2000, 2056, 250), (100, 4104, 256)]
+# few tiles, their steps dealt to four or eight waves: one token, seven steps (other forms) and eight, the last of them one piece and whole, steps
+# that do not divide, pieces past a row's end, both sides of the lines between 16 x 16 (200 tiles, eight waves up to 128), 16 x 32, 32 x 32
+# and 32 x 64 (256 tiles); activations of 96 MiB and of more, which split tiles in registers take in 16 x 16 and 16 x 32
+FEW_BF16 = [(1, 448, 9), (1, 456, 9), (1, 504, 9), (1, 512, 9), (17, 520, 33), (16, 1032, 16), (3199, 512, 5), (3200, 520, 16), (3201, 512, 16),
+            (2048, 8192, 16), (2049, 8200, 16), (4096, 600, 32), (4097, 1024, 32), (8192, 1024, 32), (8193, 1024, 32), (5120, 1000, 30),
+            (5121, 1000, 30), (8192, 2048, 64), (8193, 2048, 64), (8192, 2040, 33), (2000, 2056, 250), (100, 4104, 256), (6144, 8192, 16),
+            (6145, 8192, 16), (8193, 8184, 9), (4095, 12296, 17), (4096, 12296, 17)]
 
 
 @pytest.mark.parametrize("T,H,E", FEW_BF16)
