@@ -752,12 +752,9 @@ int launch_expert(const void *x_final, const void *w_exp, void *y, ExpertArgs a,
 //   64 experts, 7168 x 2048:  r = 16: 310, 311, 309, 312   64: 511, 389, 333, 333   96: 630, 431, 341, 343   192: -, 671, 408, 590
 // So a tile is taken where most experts fit one of its rows' tiles, or where its tiles number at most 2.5 per CU; on short rows,
 // where a large tile's first loads and its stores weigh most, at most 5 per CU (64 experts, 1024 x 1024, r = 96: 45, 35, 38, 48;
-// 128 experts, 512 x 512, r = 96: 33, 24, 37, 33).  The register-staged tile, which has no such rule of its own, is taken
-//  - on rows of 4096 to 5120 elements where at most 64 experts have 57 to 76 rows in the mean, some more than 64 and some less, and its
-//    tiles come in nearly full rounds of two per CU (register-staged and the large tile with its short ragged ones: 64 experts of 4096 x
-//    2048, r = 64: 193, 209   80: 196, 196   100: 235, 203; 5120 x 2048, 64: 251, 238; 7168 x 2048, 64: 345, 319   100: 423, 340; in 64 x
-//    128 tiles 4096 x 2048, 40: 187, 177).  With more experts a skewed load leaves many without rows, and there it is the worst form
-//    (256 experts, 4096 x 512, r = 64: even 293, 251, 257, 208; skewed 117, 106, 115, 159);
+// 128 experts, 512 x 512, r = 96: 33, 24, 37, 33).  The register-staged tile, which has no such rule of its own, is not taken on long
+// rows (64 experts of 4096 x 2048, large tiles with their short ragged ones and it, three sets of weights in turn: r = 57 189 and 191, 76
+// 195 and 197, with a skewed load 182 and 281, 217 and 287; 4992 x 2040, r = 66: 228 and 239), but
 //  - on rows of at most 512 (128 experts, 512 x 512, r = 192: 56, 39, 43, 29; 256 experts: 120, 74, 57, 55, skewed 60, 35, 40, 32);
 //  - on rows that are not whole steps, whose lines the large tile fetches twice, where an expert's second large tile would be
 //    half empty (16 experts, 8184 x 2048, r = 300: 614, 378, 363, 326; 64 experts, 3000 x 1024: 472, 279, 285, 265; r = 1000: 1537,
@@ -775,9 +772,7 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
 {
     const int64_t active = std::min<int64_t>(a.E, kept_bound), r = kept_bound / active;
     auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
-    constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kRound = 512, kOddShortRow = 448, kOddNarrowRow = 1104;
-    const int64_t one_row = active * ((a.N + 255) / 256), rounds = (one_row + kRound - 1) / kRound;
-    const bool full_rounds = one_row * 10 >= rounds * kRound * 9;
+    constexpr int64_t kFewTiles = 640, kFewTilesShortRows = 1300, kOddShortRow = 448, kOddNarrowRow = 1104;
     if (const int rc = launch_expert_few<false>(x_final, w_exp, y, a, rows_bound, active, r, st); rc <= 0) return rc;
     if (a.H % 64 && a.H <= kOddShortRow) {
         if (tiles(32, 64) <= (r <= 16 ? kFewTilesShortRows : kFewTiles)) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
@@ -786,7 +781,6 @@ int launch_expert_tiled(const void *x_final, const void *w_exp, void *y, const E
         return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     }
     if (r <= 24 || tiles(32, 64) <= kFewTiles) return launch_expert_short_t<32, 64, 4>(x_final, w_exp, y, a, rows_bound, r, st);
-    if (a.H >= 4096 && a.H < 5120 && a.E <= 64 && r > 56 && r <= 76 && full_rounds) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 56 || tiles(64, 128) <= (a.H <= 1024 ? kFewTilesShortRows : kFewTiles))
         return launch_expert_short_t<64, 128, 3>(x_final, w_exp, y, a, rows_bound, r, st);
     if (a.H <= 512 && a.E <= 128 && r <= 384) return launch_expert<128, 256, 2, 2>(x_final, w_exp, y, a, rows_bound, st);

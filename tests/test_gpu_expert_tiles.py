@@ -47,7 +47,7 @@ def check(m, sizes, H, N, dtype):
     assert np.all(got[T].view(np.uint8) == 0x5A)
 
 
-# many experts on short rows, and few rows per expert on long ones, in nearly full rounds: the register-staged tiles
+# many experts on short rows: the register-staged tiles
 def test_short_rows_many_experts(m):
     check(m, [120 + (37 * e) % 33 for e in range(64)], 128, 1032, BF16)
 
@@ -81,9 +81,9 @@ def test_long_rows_full_rounds(m):
     check_on_gpu(m, [40, 1, 0, 100, 33, 64, 65, 17], 4096, 57 * 256 + 8, BF16)
 
 
-# the register-staged tiles on long rows: 57 to 76 rows in the mean, tiles in full rounds; and fp32 in 16 x 32 tiles up to three per CU
+# 57 to 76 rows in the mean on long rows, large tiles beside ragged ones of up to 64 rows; and fp32 in 16 x 32 tiles up to three per CU
 @pytest.mark.parametrize("H", [4096, 4104])
-def test_long_rows_staged(m, H):
+def test_long_rows(m, H):
     check_on_gpu(m, [70, 64, 65, 100, 33, 129, 40, 60], H, 63 * 256 + 8, BF16)
 
 
@@ -217,16 +217,18 @@ def test_longest_rows(m, sizes, H, dtype):
     check_on_gpu(m, sizes, H, 72, dtype)
 
 
-# rows a multiple of 4096 bytes apart, whose tiles start their walk at different steps: fewer steps than stages hold and more, a start in
-# every step, an expert without rows, experts of one tile and of two; the line at seven eighths of a tile's rows on average
+# rows a multiple of 4096 bytes apart, whose tiles start their walk at different steps: a start in every step, an expert without rows, experts
+# of one tile and of two; both sides of the lines at seven eighths of a tile's rows on average, 28 of 32 and 56 of 64
 @pytest.mark.parametrize("sizes,H,N,dtype", [
     ([28, 1, 0, 33, 16, 40, 27, 32] * 3, 2048, 2056, BF16),
     ([28, 1, 0, 33, 16, 40, 27, 32] * 3, 6144, 2056, BF16),
     ([56, 1, 0, 65, 48, 64, 33, 40] * 4, 2048, 2056, BF16),
-    ([28, 29, 28, 28] * 6, 2048, 2056, BF16),
-    ([29, 30, 28, 29] * 6, 2048, 2056, BF16),
+    ([28, 29, 28, 28] * 2, 2048, 2056, BF16),
+    ([29, 30, 28, 29] * 2, 2048, 2056, BF16),
+    ([56, 57, 55, 56] * 6, 2048, 2056, BF16),
+    ([57, 58, 56, 57] * 6, 2048, 2056, BF16),
     ([28, 1, 0, 33, 16, 40, 27, 32] * 3, 1024, 2052, FP32),
-], ids=["32x64", "32x64-long", "64x128", "28", "29", "fp32"])
+], ids=["32x64", "32x64-long", "64x128", "28", "29", "56", "57", "fp32"])
 def test_spread_starts(m, sizes, H, N, dtype):
     check_on_gpu(m, sizes, H, N, dtype)
 
