@@ -705,7 +705,11 @@ int launch_expert_split(const void *x_final, const void *w_exp, void *y, const E
 //    8.9, 7.4; 2 of 4096 x 4504, 20 rows, 987 tiles 15.8 in blocks of 8, 17.2, 17.9, 19.4); eight waves for long rows and half a tile
 //    per CU (fp32, 8 of 8192 x 136: four waves 18.7, eight 14.1);
 //  - 16 x 32, then 32 x 32, up to one tile per CU, where rows are more: 3 of 6176 x 336, 83 rows 21.9, 14.6, 12.5, 15.2; 4 of 8192 x 688,
-//    47 rows 28.5, 19.7, 19.7, 14.5; but 2 of 5120 x 1984, 130 rows, 564 tiles of 32 x 32 25.1, 35.6, 31.5, 29.9;
+//    47 rows 28.5, 19.7, 19.7, 14.5; but 2 of 5120 x 1984, 130 rows, 564 tiles of 32 x 32 25.1, 35.6, 31.5, 29.9.  An expert with rows has one
+//    row tile at the least, which the estimate of its tiles falls short of where rows are less than half a tile's: a second round of few
+//    tiles costs a whole walk (in 32 x 64 and 32 x 32: 8 of 2504 x 1352, 6 rows, 344 tiles 11.7, 15.6, 64 of 4096 x 152, 8 rows, 320
+//    tiles 15.0, 18.8; fp32, 16 of 5788 x 784, 4 rows, 400 tiles 59.6, 73.5; in 32 x 64 and 16 x 32: 6 of 2504 x 1600, 5 rows 11.1, 12.9;
+//    fp32, whose 32 x 64 tiles take longer, 19.2, 14.9 for 64 of 2000 x 192, one row, 384 tiles);
 //  - fp32, whose MFMAs take four times as long, in 16 x 32 to about three tiles of 32 x 32 per CU if rows are more than one such tile (us in 32
 //    x 64, 16 x 32: 8 of 1224 x 688, 81 rows 26.0, 21.7; 2 of 4096 x 2840, 125 rows 78, 71; 32 of 4096 x 320, 47 rows 79, 71; but 4 of 1348 x
 //    484, 546 rows, 1124 tiles 39, 48, and 8 of 2172 x 1380, 20 rows 29, 39);
@@ -716,12 +720,14 @@ int launch_expert_few(const void *x_final, const void *w_exp, void *y, const Exp
                       hipStream_t st)
 {
     auto tiles = [&](int64_t R, int64_t C) { return active * ((a.N + C - 1) / C) * (2 * r + R) / (2 * R); };
+    auto whole_tiles = [&](int64_t R, int64_t C) { return std::max(tiles(R, C), active * ((a.N + C - 1) / C)); };
     const int64_t steps = ((int64_t)a.H * (F32 ? 4 : 2) + 127) / 128, small = tiles(16, 16);
     if (steps < 8 || (steps < 24 && small > 256)) return 1;
     if (steps >= 128 && small <= 128) return launch_expert_split<1, 1, 8, 4, F32>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 32 && small <= 400) return launch_expert_split<1, 1, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
-    if (tiles(16, 32) <= 256 || (F32 && r > 40 && tiles(32, 32) <= 800)) return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
-    if (tiles(32, 32) <= 256) return launch_expert_split<2, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if ((F32 ? tiles(16, 32) : whole_tiles(16, 32)) <= 256 || (F32 && r > 40 && tiles(32, 32) <= 800))
+        return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if (whole_tiles(32, 32) <= 256) return launch_expert_split<2, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     return 1;
 }
 

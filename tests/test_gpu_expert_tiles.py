@@ -248,3 +248,11 @@ def test_split_tiles(m, sizes, N, H):
                          ids=["one", "few", "32", "16x32", "32x32"])
 def test_split_tiles_fp32(m, sizes, N, H):
     check_on_gpu(m, sizes, H, N, FP32)
+
+
+# fewer rows than half a tile's: both sides of the line at one column tile per CU, 256, counted by experts, and both forms on the near side
+@pytest.mark.parametrize("dtype", [BF16, FP32])
+@pytest.mark.parametrize("sizes,N", [([5, 4, 6, 5], 2048), ([5, 4, 6, 5], 2056), ([12, 10, 14, 0, 12], 2048), ([12, 11, 13, 12], 2056),
+                                     ([1] * 16, 640)], ids=["16x32", "16x32-more", "32x32", "32x32-more", "one"])
+def test_split_tiles_of_few_rows(m, sizes, N, dtype):
+    check_on_gpu(m, sizes, 1544, N, dtype)
