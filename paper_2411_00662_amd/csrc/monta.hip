@@ -710,9 +710,12 @@ int launch_expert_split(const void *x_final, const void *w_exp, void *y, const E
 //    tiles costs a whole walk (in 32 x 64 and 32 x 32: 8 of 2504 x 1352, 6 rows, 344 tiles 11.7, 15.6, 64 of 4096 x 152, 8 rows, 320
 //    tiles 15.0, 18.8; fp32, 16 of 5788 x 784, 4 rows, 400 tiles 59.6, 73.5; in 32 x 64 and 16 x 32: 6 of 2504 x 1600, 5 rows 11.1, 12.9;
 //    fp32, whose 32 x 64 tiles take longer, 19.2, 14.9 for 64 of 2000 x 192, one row, 384 tiles);
-//  - fp32, whose MFMAs take four times as long, in 16 x 32 to about three tiles of 32 x 32 per CU if rows are more than one such tile (us in 32
-//    x 64, 16 x 32: 8 of 1224 x 688, 81 rows 26.0, 21.7; 2 of 4096 x 2840, 125 rows 78, 71; 32 of 4096 x 320, 47 rows 79, 71; but 4 of 1348 x
-//    484, 546 rows, 1124 tiles 39, 48, and 8 of 2172 x 1380, 20 rows 29, 39);
+//  - fp32, whose MFMAs take four times as long, in 16 x 32 up to less than four tiles per CU if rows are more than one of 32 x 32, and up to
+//    1200 where 32 x 64 tiles are past one per CU and take two walks' time (us in 32 x 64, 16 x 32: 3 of 4096 x 664, 121 rows, 507 tiles
+//    50.9, 23.3; 2 of 2048 x 1836, 116 rows, 899 tiles 34.0, 24.8; 16 of 2048 x 340, 73 rows, 891 tiles 40.1, 27.5; beyond 4 of 2500 x
+//    1020, 114 rows, 976 tiles 33.1, 37.9, 8 of 5788 x 1048, 75 rows, 1369 tiles 119, 152; with 317 tiles of 32 x 64 3 of 4096 x 2416, 73
+//    rows, 1154 tiles 77.4, 56.2, with 345 2 of 2500 x 1320, 247 rows, 1338 tiles 49.8, 52.8; and 8 of 2172 x 1380, 20 rows 29, 39).  Over 38
+//    such shapes 1.02 of the better form's time, 1.16 at the worst (32 of 5788 x 160, 58 rows 72, 84);
 //  - not on short walks (4 of 208 x 232, 467 rows 4.2, 9.0, 6.9, 6.7), up to 23 steps only where the tiles are fewest (32 of 1024 x 112,
 //    4 rows, 168 tiles 5.9, 3.9; 2 of 512 x 4752, 3 rows, 408 tiles 5.2, 5.0, 4.8, 6.9, in blocks of 8 4.5).
 template <bool F32>
@@ -725,9 +728,10 @@ int launch_expert_few(const void *x_final, const void *w_exp, void *y, const Exp
     if (steps < 8 || (steps < 24 && small > 256)) return 1;
     if (steps >= 128 && small <= 128) return launch_expert_split<1, 1, 8, 4, F32>(x_final, w_exp, y, a, rows_bound, st);
     if (r <= 32 && small <= 400) return launch_expert_split<1, 1, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
-    if ((F32 ? tiles(16, 32) : whole_tiles(16, 32)) <= 256 || (F32 && r > 40 && tiles(32, 32) <= 800))
-        return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if ((F32 ? tiles(16, 32) : whole_tiles(16, 32)) <= 256) return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     if (whole_tiles(32, 32) <= 256) return launch_expert_split<2, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if (F32 && r > 40 && (tiles(16, 32) <= 950 || (tiles(32, 64) > 272 && tiles(16, 32) <= 1200)))
+        return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     return 1;
 }
 
