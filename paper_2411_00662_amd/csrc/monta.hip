@@ -67,7 +67,7 @@ struct Geometry {
     int64_t row_bytes;
     size_t route_lds;
     int route_threads;   // workgroup size of the route kernel: TB * lanes per token
-    int64_t blocks_by_lds;   // route workgroups if only the LDS limited their tokens
+    int64_t blocks_by_tile;  // route workgroups if only route_tile_bytes limited their tokens
 };
 
 // Per-expert capacity: C = min(T, ceil(cf*T*k/E)), cf = 0 meaning "no drop".
@@ -87,8 +87,9 @@ int route_lanes_per_token(int TB, int E)
     return rl;
 }
 
-// What decides how many tokens a route workgroup takes, and with it the layout of the workspace: about the bytes of its logits, its bit
-// masks, and three words per choice.
+// What decides how many tokens a route workgroup takes, and with it the layout of the workspace and the limit of the static entry point: the
+// bytes of its logits, its bit masks, and three words per choice.  The workgroup's LDS (route_lds) is smaller by the logits, which are in
+// registers: 11 KiB for 64 tokens on 256 experts, top-8, which is all that fit this budget.
 size_t route_tile_bytes(int TB, int E, int k)
 {
     const int NW = TB > kWave ? TB / kWave : 1, L = route_lanes_per_token(TB, E);
@@ -136,15 +137,14 @@ int validate(const monta_cfg *c, Geometry *g)
     s.vpr = (int32_t)(row / 16);
     const int lpr_max = kMoverThreads;
     s.lpr = pow2ceil(s.vpr) < lpr_max ? pow2ceil(s.vpr) : lpr_max;
-    // route workgroup: as many tokens as fit the LDS budget (gfx950 gives a workgroup up to 160 KiB),
-    // at most 256, no more than a unit needs
+    // route workgroup: as many tokens as fit route_tile_bytes' budget, at most 256, no more than a unit needs
     int TB = 256;
     while (TB > 32 && (route_tile_bytes(TB, s.E, s.k) > kRouteTileBudget || TB / 2 >= s.Tu)) TB >>= 1;
     if (route_tile_bytes(TB, s.E, s.k) > kRouteTileBudget) return MONTA_ERR_UNSUPPORTED;
     // ... and no more than leaves every second CU a workgroup (down to one wave of tokens): 8192 tokens, 64 experts, top-8:
     // 28.5 us for routing and plan in workgroups of 256 tokens, 24.2 in 64; 16384 tokens, 32 experts: 19.1 and 18.2
     auto blocks = [&](int tb) { return (int64_t)((s.Tu + tb - 1) / tb) * U; };
-    g->blocks_by_lds = blocks(TB);
+    g->blocks_by_tile = blocks(TB);
     while (TB > kWave && blocks(TB) < kFewRouteBlocks) TB >>= 1;
     s.TB = TB;
     s.bpu = (s.Tu + TB - 1) / TB;
@@ -869,10 +869,12 @@ bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
 // Lanes per token of small_step_kernel, 0 if the problem is not a small one: all tokens have to be covered by one pass of a
 // workgroup's threads, their choices and the plan by its LDS.  And routing them all in every workgroup must not take longer than
 // routing a share of them and waiting for the others, which grows with tokens x experts and, where each row's workgroup does it, with
-// the choices.  Measured on MI355X, when both took the logits through the LDS, GPU time in us, several launches and one: routing 64 x 8, top-2 7.8 and 4.9; 128 x 64, top-8 10.5
-// and 9.1, 256 x 64 10.6 and 14.4; 512 x 16, top-2 8.2 and 6.8, 512 x 32, top-4 8.8 and 11.4; 64 x 256, top-8 17.5 and 13.2.  With the
-// rows (4096 elements): 64 x 8, top-2 8.4 and 5.5, 512 x 8 10.6 and 8.3, 1024 x 8 13.3 and 15.5; 256 x 32, top-4 11.3 and 10.9, 128 x
-// 64, top-8 12.8 and 14.1.  The whole step 64 x 8 12.8 and 7.7, 512 x 8 18.2 and 10.8.
+// the choices.  Measured on MI355X, GPU time in us, several launches and one: routing 64 x 8, top-2 8.2 and 4.3; 128 x 64, top-8 9.2 and 7.8,
+// 256 x 64 9.5 and 11.0; 512 x 16, top-2 8.4 and 6.2, top-8 10.6 and 11.7, 512 x 32, top-4 8.7 and 9.5; 64 x 256, top-8 12.0 and 9.0;
+// 1024 x 8 8.3 and 7.1.  With the rows (4096 elements): 64 x 8, top-2 8.8 and 5.2, 512 x 8 10.7 and 7.7, 1024 x 8 12.5 and 13.2; 256 x 32, top-4
+// 11.2 and 10.1, 512 x 32 12.9 and 13.1; 128 x 64, top-8 11.9 and 12.7, 256 x 64 13.5 and 15.7; 512 x 16, top-8 19.4 and 17.2.  The
+// whole step, which takes the same line, could take one launch further: 64 x 8 12.0 and 6.4, 512 x 8 15.8 and 9.0, 128 x 64, top-8 17.2 and
+// 14.6, 512 x 32, top-4 18.7 and 14.8, 1024 x 8 19.3 and 15.5.
 constexpr int kSmallTokens = 512, kSmallUnits = 4096, kSmallPerLogits = 8192, kSmallPerChoices = 32768, kSmallAnyway = 64;
 int small_lanes(const Geometry &g, bool rows)
 {
@@ -1943,7 +1945,7 @@ int monta_route_dispatch_combine_static(const monta_cfg *cfg, const float *logit
     fill_layout(g, &L);
     // the limit is on the tables as they are with as few route workgroups as fit: what the finer histograms of small
     // problems add does not count against it
-    const int64_t finer = 2 * (align_up((int64_t)g.s.num_blocks * g.s.E * 4, 256) - align_up(g.blocks_by_lds * g.s.E * 4, 256));
+    const int64_t finer = 2 * (align_up((int64_t)g.s.num_blocks * g.s.E * 4, 256) - align_up(g.blocks_by_tile * g.s.E * 4, 256));
     if ((size_t)(L.ws_bytes - finer) > kStaticScratchBytes || finer > (int64_t)kStaticFinerBytes) return MONTA_ERR_TOO_LARGE;
     // event profiling creates events per launch and the two-stream pipeline creates a stream: neither belongs
     // in a call that must not allocate

@@ -1612,7 +1612,7 @@ __global__ __launch_bounds__(kMoverThreads) void combine_kernel(const u32x4 *__r
 // added up from its row while that is in registers (the rows of its choices are copies of it) instead of being read back from FINAL.
 // What bounds it: a chain of latencies (kernel arguments, logits, choices, scans, positions, stores; of 15000 clocks the sums of the
 // outputs took 7000 when each choice was a product of its own).  Measured on MI355X: 64 tokens, 8 experts, top-2, 4096 elements 12.8 us
-// of GPU time in three launches, 7.7 in one, now 6.5; where the lines lie stands at small_lanes.
+// of GPU time in three launches, 7.7 in one, now 6.4; where the lines lie stands at small_lanes.
 enum SmallWhat { SMALL_ROUTE = 0, SMALL_PLACE = 1, SMALL_COMBINE = 2 };
 
 // Dynamic LDS of the kernel (byte offsets; made on the host: in every workgroup it is a chain of a hundred scalar instructions).
@@ -3644,9 +3644,9 @@ __global__ __launch_bounds__(256, 2) void gate_short_kernel(const u32x4 *__restr
                                                           t1, e0, gshort_lds, SPREAD ? walk_start((int)(blockIdx.x / nct), cpr / 8) & ~1 : 0);
 }
 
-// Gate projection of few tiles, bf16: the expert layer's split tiles, tokens x experts.  Against waves that stream their shares straight into
-// registers, 64 bytes of 16 rows a load (gate_split_kernel), and against 32 x 64 tiles: 16 x 7168, 64 experts 15.5 -> 5.6 us, 300 x 7168, 256
-// experts 21.8 -> 9.9, 512 x 7168, 64 experts 15.9 -> 7.8, 1024 x 8192, 256 experts 28.6 -> 20.1.
+// Gate projection of few tiles, bf16, rows of 456 elements (eight steps) and more: the expert layer's split tiles, tokens x experts.  Against
+// waves that stream their shares straight into registers, 64 bytes of 16 rows a load (gate_split_kernel), and against 32 x 64 tiles: 16 x
+// 7168, 64 experts 15.5 -> 5.6 us, 300 x 7168, 256 experts 21.8 -> 9.9, 512 x 7168, 64 experts 15.9 -> 7.8, 1024 x 8192, 256 experts 28.6 -> 20.1.
 template <int XB, int CB, int W, int NST>
 __global__ __launch_bounds__(64 * W) void gate_ring_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w, float *__restrict__ logits,
                                                            int64_t T, int cpr, int E)
@@ -3662,8 +3662,9 @@ __global__ __launch_bounds__(64 * W) void gate_ring_kernel(const u32x4 *__restri
 
 // Gate projection with the hidden axis split over the 8 waves of a workgroup: 16 tokens x 16 NB experts each.  For fp32
 // activations (16x16x4 fp32 MFMA) and for so few bf16 tokens that a tile's walk along the whole hidden axis is what takes the
-// time, on rows that gate_ring_kernel does not take (below 512 elements, beyond 2^20).  A wave streams its share straight into registers, D steps of 128 bytes per row ahead; lane l holds 16 bytes of row
-// l % 16, at the same place of x and of w, so which element of the hidden axis meets which MFMA does not matter.  The waves'
+// time, where gate_ring_kernel is not taken (rows below 456 elements or beyond 2^20, activations of more than 96 MiB).  A wave streams its
+// share straight into registers, D steps of 128 bytes per row ahead; lane l holds 16 bytes of row l % 16, at the same place of x and of
+// w, so which element of the hidden axis meets which MFMA does not matter.  The waves'
 // sums are added through LDS in a fixed order.  Rows past the end repeat the last one and are not stored.  Steps past a
 // wave's share multiply zeros: an MFMA takes no notice of a lane mask, so it may not stand under a condition that the
 // compiler cannot prove uniform.
