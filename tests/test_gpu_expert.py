@@ -288,7 +288,7 @@ def test_overlapped_pipeline_gives_the_same_buffers(m, case):
 
 # All forms whose walk along the hidden axis may start at another step, rows 4096 bytes or a multiple of it apart: 256 x 256 tiles with
 # their ragged ones last, in place, and two of them per expert, each with segments and slices that end in tiles of up to 64 rows, in
-# which a row of a slice lies where the whole segment has it in a large tile; 64 x 128, 32 x 64, fp32
+# which a row of a slice lies where the whole segment has it in a large tile; 64 x 128, 32 x 64, fp32; and the split tiles, which deal it to waves
 @pytest.mark.parametrize("sizes,H,N,dtype", [
     ([300, 128, 64, 65, 320, 0, 3, 200] * 3, 2048, 2056, BF16),
     ([300, 128, 64, 65, 320, 0, 3, 200] * 3, 2048, 4104, BF16),
@@ -296,7 +296,10 @@ def test_overlapped_pipeline_gives_the_same_buffers(m, case):
     ([44, 40, 64, 65, 1, 0, 33, 61] * 4, 2048, 2056, BF16),
     ([16, 1, 0, 33, 17, 5, 32, 40] * 3, 4096, 2056, BF16),
     ([16, 1, 0, 33, 17, 5, 32, 40] * 3, 1024, 2052, FP32),
-], ids=["last", "inplace", "two", "64x128", "32x64", "fp32"])
+    ([16, 1, 0, 33, 17, 5, 32, 40], 2048, 136, BF16),
+    ([16, 1, 0, 33, 17, 5, 32, 40], 4096, 136, FP32),
+    ([70, 0, 90, 64, 65, 129, 1, 81], 2052, 260, FP32),
+], ids=["last", "inplace", "two", "64x128", "32x64", "fp32", "split", "split-fp32", "split-fp32-many"])
 def test_rows_do_not_depend_on_the_launch(m, sizes, H, N, dtype):
     """Normal inputs, whose sums tell one order of additions from another: all rows in one launch, slice by slice, and in the
     pipeline with and without overlap give y bit for bit."""

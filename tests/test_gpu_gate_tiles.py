@@ -116,7 +116,7 @@ def test_gate_longest_rows(T, E, H, dtype):
 
 # rows 4096 bytes or a multiple of it apart in the direct-to-LDS tiles of each shape, and in the forms around them
 @pytest.mark.parametrize("T,H,E", [(16384, 2048, 64), (12000, 8192, 64), (12001, 4096, 128), (9001, 6144, 100), (4097, 2048, 9), (33, 4096, 40),
-                                   (40000, 2048, 20)])
+                                   (40000, 2048, 20), (40000, 2048, 100), (9001, 2048, 8), (6145, 8192, 16), (300, 7168, 256)])
 def test_equal_tokens_have_equal_logits(T, H, E):
     """Bit for bit, wherever in the batch they stand."""
     import paper_2411_00662_amd as m
