@@ -650,7 +650,7 @@ int launch_expert_big(const void *x_final, const void *w_exp, void *y, ExpertArg
                   : launch_expert_big_t<false, false>(x_final, w_exp, y, a, grid, st);
 }
 
-template <int XR, int WR, int NST, bool F32 = false>
+template <int XR, int WR, int NST, bool F32 = false, bool FINE = false>
 int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, ExpertArgs a, int64_t rows_bound, int64_t rows_per_expert,
                           hipStream_t st)
 {
@@ -673,12 +673,12 @@ int launch_expert_short_t(const void *x_final, const void *w_exp, void *y, Exper
     // tiles, 4 of 4096 x 2048, 100 rows, 20.0 and 20.7, one by one 38).
     a.deal = rows_per_expert <= XR && std::min<int64_t>(a.E, rows_bound) * ((a.N + WR - 1) / WR) < 512 ? 3 : 5;
     static LdsOptIn lds_opt_in;
-    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST, F32>), G::kLdsBytes, lds_opt_in)) return rc;
+    if (int rc = opt_in_lds(reinterpret_cast<const void *>(expert_short_kernel<XR, WR, NST, F32, FINE>), G::kLdsBytes, lds_opt_in)) return rc;
     const int64_t row_tiles = rows_bound / XR + std::min<int64_t>(a.E, rows_bound);
     const int64_t nct = (a.N + WR - 1) / WR;
     const int64_t grid = (row_tiles * nct + 32 * kXcds - 1) / (32 * kXcds) * (32 * kXcds);
     if (grid > 0x7fffffff) return MONTA_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((expert_short_kernel<XR, WR, NST, F32>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st,
+    hipLaunchKernelGGL((expert_short_kernel<XR, WR, NST, F32, FINE>), dim3((unsigned)grid), dim3(256), G::kLdsBytes, st,
                        static_cast<const u32x4 *>(x_final), static_cast<const u32x4 *>(w_exp), y, a);
     return MONTA_OK;
 }
@@ -711,11 +711,13 @@ int launch_expert_split(const void *x_final, const void *w_exp, void *y, const E
 //    tiles 15.0, 18.8; fp32, 16 of 5788 x 784, 4 rows, 400 tiles 59.6, 73.5; in 32 x 64 and 16 x 32: 6 of 2504 x 1600, 5 rows 11.1, 12.9;
 //    fp32, whose 32 x 64 tiles take longer, 19.2, 14.9 for 64 of 2000 x 192, one row, 384 tiles);
 //  - fp32, whose MFMAs take four times as long, in 16 x 32 up to less than four tiles per CU if rows are more than one of 32 x 32, and up to
-//    1200 where 32 x 64 tiles are past one per CU and take two walks' time (us in 32 x 64, 16 x 32: 3 of 4096 x 664, 121 rows, 507 tiles
+//    1300 where 32 x 64 tiles are past one per CU and take two walks' time (us in 32 x 64, 16 x 32: 3 of 4096 x 664, 121 rows, 507 tiles
 //    50.9, 23.3; 2 of 2048 x 1836, 116 rows, 899 tiles 34.0, 24.8; 16 of 2048 x 340, 73 rows, 891 tiles 40.1, 27.5; beyond 4 of 2500 x
 //    1020, 114 rows, 976 tiles 33.1, 37.9, 8 of 5788 x 1048, 75 rows, 1369 tiles 119, 152; with 317 tiles of 32 x 64 3 of 4096 x 2416, 73
-//    rows, 1154 tiles 77.4, 56.2, with 345 2 of 2500 x 1320, 247 rows, 1338 tiles 49.8, 52.8; and 8 of 2172 x 1380, 20 rows 29, 39).  Over 38
-//    such shapes 1.02 of the better form's time, 1.16 at the worst (32 of 5788 x 160, 58 rows 72, 84);
+//    rows, 1154 tiles 77.4, 56.2, with 400 32 of 8192 x 208, 84 rows, 1288 tiles 157, 142, with 345 2 of 2500 x 1320, 247 rows, 1338 tiles
+//    51.5, 52.8; and 8 of 2172 x 1380, 20 rows 29, 39).  At the worst 1.16 of the better form's time (32 of 5788 x 160, 58 rows 72, 84);
+//  - fp32 beyond these lines, up to about three tiles of 32 x 32 per CU: 32 x 64 with sums as exact as the split tiles' (FINE, error against 64
+//    bits 2.1e-7 at 1024 to 8192 elements in split tiles);
 //  - not on short walks (4 of 208 x 232, 467 rows 4.2, 9.0, 6.9, 6.7), up to 23 steps only where the tiles are fewest (32 of 1024 x 112,
 //    4 rows, 168 tiles 5.9, 3.9; 2 of 512 x 4752, 3 rows, 408 tiles 5.2, 5.0, 4.8, 6.9, in blocks of 8 4.5).
 template <bool F32>
@@ -730,8 +732,12 @@ int launch_expert_few(const void *x_final, const void *w_exp, void *y, const Exp
     if (r <= 32 && small <= 400) return launch_expert_split<1, 1, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     if ((F32 ? tiles(16, 32) : whole_tiles(16, 32)) <= 256) return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
     if (whole_tiles(32, 32) <= 256) return launch_expert_split<2, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
-    if (F32 && r > 40 && (tiles(16, 32) <= 950 || (tiles(32, 64) > 272 && tiles(16, 32) <= 1200)))
+    if (F32 && r > 40 && (tiles(16, 32) <= 950 || (tiles(32, 64) > 272 && tiles(16, 32) <= 1300)))
         return launch_expert_split<1, 2, 4, 3, F32>(x_final, w_exp, y, a, rows_bound, st);
+    if constexpr (F32)
+        if (tiles(32, 32) <= (r > 40 ? 800 : 256))
+            return r <= 24 ? launch_expert_short_t<32, 64, 4, true, true>(x_final, w_exp, y, a, rows_bound, r, st)
+                           : launch_expert_short_t<32, 64, 3, true, true>(x_final, w_exp, y, a, rows_bound, r, st);
     return 1;
 }
 

@@ -2831,8 +2831,10 @@ struct ShortTile {
 // in a chain per even and odd step of each half of the row.  Error against 64 bits with one chain and two levels, and now: 512
 // elements 1.2e-7, 6.1e-8; 1536 1.3e-7, 7.4e-8; 8192 1.5e-7, 1.05e-7; fp32, 1000 2.9e-7, 9.6e-8, 8192 3.1e-7, 1.4e-7.
 // ANY_START, of bf16 logits whose walk begins at an even step: added so that where it begins does not show (run_any_start).
+// FINE, of fp32 sums: a chain per half of a step and levels of 4 steps, 1 to 3 % of the time; error against 64 bits at 1024 elements 2.9e-7,
+// 1.6e-7, at 5788 3.0e-7, 1.9e-7.
 // AUX_W: cache bits of the weights' loads.
-template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, bool ANY_START = false, typename T>
+template <int XR, int WR, int NST, bool F32, bool VEC, int AUX_W = 0, bool ANY_START = false, bool FINE = false, typename T>
 __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __amdgpu_buffer_rsrc_t rw, T *__restrict__ y, int cpr,
                                                   int N, int64_t row0, int64_t row_end, int col0, unsigned char *lds, int start)
 {
@@ -2874,8 +2876,9 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
     };
     constexpr bool kLevels = std::is_same<T, float>::value;
     constexpr bool kLogits = kLevels && !VEC;
-    constexpr int kChains = !kLogits ? 1 : F32 ? 4 : 2;
+    constexpr int kChains = kLogits && F32 ? 4 : kLogits || FINE ? 2 : 1;
     static_assert(!ANY_START || (kLogits && !F32), "short tile: a start that does not show is one of bf16 logits");
+    static_assert(!FINE || (kLevels && !kLogits), "short tile: finer levels are those of fp32 sums");
     f32x4 acc[kChains][RB][CB];
 #pragma unroll
     for (int c = 0; c < kChains; ++c)
@@ -2955,7 +2958,7 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
                     for (int v = 0; v < (F32 ? 4 : 1); ++v)
 #pragma unroll
                         for (int i = 0; i < decltype(blocks)::value; ++i)
-                            multiply(fw[ks], fx[ks][i], acc[!kLogits ? 0 : F32 ? v : ks][i], v);
+                            multiply(fw[ks], fx[ks][i], acc[kChains == 1 ? 0 : kChains == 2 ? ks : v][i], v);
                 if constexpr (kLogits && F32) {
 #pragma unroll
                     for (int i = 0; i < decltype(blocks)::value; ++i)
@@ -3066,7 +3069,7 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
         if constexpr (ANY_START) return run_any_start(blocks, whole_to);
         if constexpr (kLogits && !F32)
             if (nsteps <= 16) return run_each(blocks, whole_to);
-        const int span = kLevels ? 8 : nsteps, sub = !kLogits || F32 ? span : nsteps <= 32 ? 2 : 4;
+        const int span = FINE ? 4 : kLevels ? 8 : nsteps, sub = !kLogits || F32 ? span : nsteps <= 32 ? 2 : 4;
         for (int from = 0; from < nsteps; from += span) {
             const int end = min(from + span, nsteps);
             for (int first = from; first < end; first += sub) {
@@ -3131,7 +3134,7 @@ __device__ __forceinline__ void expert_short_tile(__amdgpu_buffer_rsrc_t rx, __a
 // each for a wave of the 32 x 64 tile).  A 64 x 64 tile with one step in flight through registers before, now: 2 experts of 4096 x
 // 4096, 8 rows each 108 -> 49 us (21), 10 of 516 x 516, about 240 rows 30 -> 19 us, 8 of 1024 x 1024, 600 rows 113 -> 100 us
 // (70 at the 143 TFLOP/s of a library GEMM); error against 64 bits at 8192 elements 1.6e-6 -> 3.1e-7 (two levels of sums).
-template <int XR, int WR, int NST, bool F32>
+template <int XR, int WR, int NST, bool F32, bool FINE>
 __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__restrict__ x, const u32x4 *__restrict__ w,
                                                               void *__restrict__ y, ExpertArgs a)
 {
@@ -3156,9 +3159,9 @@ __global__ __launch_bounds__(256, 2) void expert_short_kernel(const u32x4 *__res
     // by the column tile, whichever the rows: a row's result does not depend on the launch that computes it
     const int start = a.spread ? walk_start(e * nct + ct, cpr / 8) : 0;
     if ((int64_t)e * a.N + col0 >= a.stream_from && __builtin_amdgcn_readfirstlane(hit.tiles) == 1)
-        expert_short_tile<XR, WR, NST, F32, F32, kStreamLoad>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
+        expert_short_tile<XR, WR, NST, F32, F32, kStreamLoad, false, FINE>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
     else
-        expert_short_tile<XR, WR, NST, F32, F32>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
+        expert_short_tile<XR, WR, NST, F32, F32, 0, false, FINE>(rx, rw, static_cast<T *>(y), cpr, a.N, row0, row_end, col0, short_lds, start);
 }
 
 // Layers of so few tiles that one tile's walk along the hidden axis is what takes the time, not the bytes: a tile of 16 XB rows x 16 CB

@@ -89,7 +89,7 @@ def test_long_rows(m, H):
 
 
 @pytest.mark.parametrize("H", [800, 1300])
-@pytest.mark.parametrize("N", [836, 1028, 1284])
+@pytest.mark.parametrize("N", [836, 1028, 1412])
 def test_fp32_many_split_tiles(m, H, N):
     check_on_gpu(m, [50, 1, 130, 64, 0, 47, 33, 80], H, N, FP32)
 
